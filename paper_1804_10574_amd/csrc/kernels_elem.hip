@@ -348,12 +348,34 @@ __global__ __launch_bounds__(256) void bn_bwd_reduce_kernel(const T* __restrict_
       }
     }
   }
-  // threads with equal (threadIdx.x*V) % C hold the same channels; combine in thread order
+  // Threads with equal (threadIdx.x*V) % C hold the same channels. Up to 64 channel vectors: the
+  // lanes of a wave that share one are added by a butterfly, the four waves through LDS (a chain of
+  // 6 + 4 sums; the loop below, 128 sums long for 16 channels in two threads, was most of this
+  // kernel: 11.3 -> 5.2 us at 37 x 32 x 32 x 16). More: at most two threads hold the same channels.
+  const int per = C / V < 256 ? C / V : 256;  // distinct channel vectors among the block's threads
+  if (per <= 64) {
+    __shared__ float wred[4][2][64 * V];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int o = per; o < 64; o <<= 1) {
+#pragma unroll
+      for (int j = 0; j < V; ++j) { s1[j] += __shfl_xor(s1[j], o, 64); s2[j] += __shfl_xor(s2[j], o, 64); }
+    }
+    if (lane < per) {
+#pragma unroll
+      for (int j = 0; j < V; ++j) { wred[wave][0][lane * V + j] = s1[j]; wred[wave][1][lane * V + j] = s2[j]; }
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < 2 * C; e += 256) {
+      const int which = e / C, c = e - which * C;
+      partial[((size_t)blockIdx.x * 2 + which) * C + c] =
+          (wred[0][which][c] + wred[1][which][c]) + (wred[2][which][c] + wred[3][which][c]);
+    }
+    return;
+  }
   __shared__ float red[2][256][V + 1];
 #pragma unroll
   for (int j = 0; j < V; ++j) { red[0][threadIdx.x][j] = s1[j]; red[1][threadIdx.x][j] = s2[j]; }
   __syncthreads();
-  const int per = C / V < 256 ? C / V : 256;  // distinct channel vectors among the block's threads
   if ((int)threadIdx.x < per) {
     float t1[V], t2[V];
 #pragma unroll
@@ -623,21 +645,50 @@ hipError_t eval_vectors_launch(const RunDesc* dev_descs, int n, int max_c, hipSt
   return hipGetLastError();
 }
 
-// mean of the per-sample losses, added in order (evaluation; training gets it from head_wgrad_kernel)
-__global__ void loss_mean_kernel(const float* __restrict__ loss_n, int N, float* __restrict__ out) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    float l = 0.f;
-    for (int n = 0; n < N; ++n) l += loss_n[n];
-    *out = l / (float)N;
-  }
+// Sum / maximum over a workgroup of NW waves in a fixed order; every thread gets the result. sh: NW
+// floats of LDS that no other step uses between two barriers.
+template <int NW>
+__device__ __forceinline__ float block_sum(float v, float* sh) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  float t = sh[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) t += sh[w];
+  return t;
+}
+template <int NW>
+__device__ __forceinline__ float block_max(float v, float* sh) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  float t = sh[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) t = fmaxf(t, sh[w]);
+  return t;
+}
+
+// mean of the per-sample losses (evaluation; training gets it from head_wgrad_kernel)
+__global__ __launch_bounds__(256) void loss_mean_kernel(const float* __restrict__ loss_n, int N, float* __restrict__ out) {
+  __shared__ float sh[4];
+  float l = 0.f;
+  for (int n = threadIdx.x; n < N; n += 256) l += loss_n[n];
+  l = block_sum<4>(l, sh);
+  if (threadIdx.x == 0) *out = l / (float)N;
 }
 
 // ---------------------------------------------------------------------------------
-// Head. Small: N x C x classes is a few hundred thousand operations.
+// Head. Small: N x C x classes is a few hundred thousand operations, so what it costs is the length
+// of its chains of loads and sums. Every sum is spread over the workgroup with as many loads in
+// flight as there are terms per thread (16 at most), and runs in a fixed order.
 // ---------------------------------------------------------------------------------
 // Per sample (one workgroup of 256 threads): global average pool, logits, stable softmax, loss,
-// dlogits = (p - onehot)/N, and dh = dlogits * fcw / HW broadcast over the pixels. Every sum
-// runs in a fixed order. Dynamic LDS: 2*C + 2*classes + 256 floats.
+// dlogits = (p - onehot)/N, and dh = dlogits * fcw / HW broadcast over the pixels.
+// Dynamic LDS: 2*C + 2*classes + 256 floats.
 template <typename T>
 __global__ __launch_bounds__(256) void head_sample_kernel(const T* __restrict__ h, const float* __restrict__ fcw,
                                                           const float* __restrict__ fcb,
@@ -646,6 +697,7 @@ __global__ __launch_bounds__(256) void head_sample_kernel(const T* __restrict__ 
                                                           float* __restrict__ loss_n, T* __restrict__ dh, int N,
                                                           int HW, int C, int classes, float* __restrict__ logits_out) {
   extern __shared__ float sm[];
+  __shared__ float s_w[4];
   float* s_pool = sm;               // [C]
   float* s_dh = sm + C;             // [C]
   float* s_lg = sm + 2 * C;         // [classes]
@@ -660,7 +712,7 @@ __global__ __launch_bounds__(256) void head_sample_kernel(const T* __restrict__ 
     float a = 0.f;
     if (g < groups && c < C) {
       const T* p = h + (size_t)n * HW * C + c;
-#pragma unroll 8
+#pragma unroll 16
       for (int i = g; i < HW; i += groups) a += Store<T>::load1(p + (size_t)i * C);
     }
     s_red[tid] = a;
@@ -674,27 +726,29 @@ __global__ __launch_bounds__(256) void head_sample_kernel(const T* __restrict__ 
     }
     __syncthreads();
   }
-  // logits
+  // logits (C is a multiple of 4 and so is every offset in the parameter vector: 16-byte loads)
   for (int j = tid; j < classes; j += 256) {
     float a = fcb[j];
-    const float* w = fcw + (size_t)j * C;
-#pragma unroll 8
-    for (int c = 0; c < C; ++c) a += w[c] * s_pool[c];
+    const float4* w = reinterpret_cast<const float4*>(fcw + (size_t)j * C);
+#pragma unroll 16
+    for (int c = 0; c < C / 4; ++c) {
+      const float4 q = w[c];
+      a += q.x * s_pool[c * 4]; a += q.y * s_pool[c * 4 + 1]; a += q.z * s_pool[c * 4 + 2]; a += q.w * s_pool[c * 4 + 3];
+    }
     s_lg[j] = a;
     if (logits_out) logits_out[(size_t)n * classes + j] = a;
   }
   __syncthreads();
   float mx = s_lg[0];
-  for (int j = 1; j < classes; ++j) mx = s_lg[j] > mx ? s_lg[j] : mx;
-  for (int j = tid; j < classes; j += 256) s_dl[j] = expf(s_lg[j] - mx);
-  __syncthreads();
+  for (int j = tid; j < classes; j += 256) mx = fmaxf(mx, s_lg[j]);
+  mx = block_max<4>(mx, s_w);
   float den = 0.f;
-  for (int j = 0; j < classes; ++j) den += s_dl[j];
+  for (int j = tid; j < classes; j += 256) { const float e = expf(s_lg[j] - mx); s_dl[j] = e; den += e; }
+  den = block_sum<4>(den, s_w);
   // a label outside [0, classes) has no class to point at: that sample's loss (and with it the
   // mean loss) is NaN, so the caller sees it, and nothing outside the logits is read
   const int y = labels[n];
   const bool y_ok = (unsigned)y < (unsigned)classes;
-  __syncthreads();
   for (int j = tid; j < classes; j += 256) {
     const float d = (s_dl[j] / den - (j == y ? 1.f : 0.f)) / (float)N;
     s_dl[j] = d;
@@ -703,13 +757,23 @@ __global__ __launch_bounds__(256) void head_sample_kernel(const T* __restrict__ 
   if (tid == 0) loss_n[n] = y_ok ? -(s_lg[y] - mx - logf(den)) : __builtin_nanf("");
   if (!dh) return;
   __syncthreads();
-  for (int c = tid; c < C; c += 256) {
+  // thread (channel lane cl, class of classes g), as the pool above
+  for (int c0 = 0; c0 < C; c0 += cpt) {
+    const int c = c0 + cl;
     float a = 0.f;
-#pragma unroll 4
-    for (int j = 0; j < classes; ++j) a += s_dl[j] * fcw[(size_t)j * C + c];
-    s_dh[c] = Store<T>::round(a / (float)HW);
+    if (g < groups && c < C) {
+#pragma unroll 16
+      for (int j = g; j < classes; j += groups) a += s_dl[j] * fcw[(size_t)j * C + c];
+    }
+    s_red[tid] = a;
+    __syncthreads();
+    if (g == 0 && c < C) {
+      float t = 0.f;
+      for (int q = 0; q < groups; ++q) t += s_red[q * cpt + cl];
+      s_dh[c] = Store<T>::round(t / (float)HW);
+    }
+    __syncthreads();
   }
-  __syncthreads();
   // broadcast over the pixels, 4 channels per store
   const int c4n = C / 4;
   for (int e = tid; e < HW * c4n; e += 256) {
@@ -718,56 +782,48 @@ __global__ __launch_bounds__(256) void head_sample_kernel(const T* __restrict__ 
   }
 }
 
-// One workgroup per class j: dfcw[j][:] = sum_n dlogits[n][j] * pooled[n][:], dfcb[j]; thread
-// (channel lane, sample class g) adds samples g, g+groups, ... in order, then the classes are
-// added in order. Workgroup 0 also writes the mean loss.
-__global__ __launch_bounds__(256) void head_wgrad_kernel(const float* __restrict__ pooled,
-                                                         const float* __restrict__ dlogits,
-                                                         const float* __restrict__ loss_n, float* __restrict__ dfcw,
-                                                         float* __restrict__ dfcb, float* loss_out, int N, int C,
-                                                         int classes) {
-  __shared__ float s_red[256];
+// One workgroup of 1024 threads per class j: dfcw[j][:] = sum_n dlogits[n][j] * pooled[n][:],
+// dfcb[j]; thread (channel lane, sample class g) adds samples g, g+groups, ... in order (16 loads
+// in flight: one round trip at batch 256 and 64 channels), then the classes are added in order.
+// Workgroup 0 also writes the mean loss.
+__global__ __launch_bounds__(1024) void head_wgrad_kernel(const float* __restrict__ pooled,
+                                                          const float* __restrict__ dlogits,
+                                                          const float* __restrict__ loss_n, float* __restrict__ dfcw,
+                                                          float* __restrict__ dfcb, float* loss_out, int N, int C,
+                                                          int classes) {
+  __shared__ float s_red[1024];
+  __shared__ float s_w[16];
   const int j = blockIdx.x, tid = threadIdx.x;
-  const int cpt = C < 256 ? C : 256, groups = 256 / cpt;
+  const int cpt = C < 1024 ? C : 1024, groups = 1024 / cpt;
   const int cl = tid % cpt, g = tid / cpt;
   for (int c0 = 0; c0 < C; c0 += cpt) {
     const int c = c0 + cl;
     float a = 0.f;
     if (g < groups && c < C) {
-#pragma unroll 8
+#pragma unroll 16
       for (int n = g; n < N; n += groups) a += dlogits[(size_t)n * classes + j] * pooled[(size_t)n * C + c];
     }
     s_red[tid] = a;
     __syncthreads();
     if (g == 0 && c < C) {
       float t = 0.f;
+#pragma unroll 16
       for (int q = 0; q < groups; ++q) t += s_red[q * cpt + cl];
       dfcw[(size_t)j * C + c] = t;
     }
     __syncthreads();
   }
-  // bias gradient (and the mean loss): 256 partial sums over samples, added in order
+  // bias gradient (and the mean loss)
   float a = 0.f, l = 0.f;
-  for (int n = tid; n < N; n += 256) {
+  for (int n = tid; n < N; n += 1024) {
     a += dlogits[(size_t)n * classes + j];
     if (j == 0) l += loss_n[n];
   }
-  s_red[tid] = a;
-  __syncthreads();
-  if (tid == 0) {
-    float t = 0.f;
-    for (int q = 0; q < 256; ++q) t += s_red[q];
-    dfcb[j] = t;
-  }
+  a = block_sum<16>(a, s_w);
+  if (tid == 0) dfcb[j] = a;
   if (j == 0 && loss_out) {
-    __syncthreads();
-    s_red[tid] = l;
-    __syncthreads();
-    if (tid == 0) {
-      float t = 0.f;
-      for (int q = 0; q < 256; ++q) t += s_red[q];
-      *loss_out = t / (float)N;
-    }
+    l = block_sum<16>(l, s_w);
+    if (tid == 0) *loss_out = l / (float)N;
   }
 }
 
@@ -781,10 +837,10 @@ hipError_t head_launch(const HeadArgs& a, hipStream_t s) {
     DDG_LAUNCH(head_sample_kernel<float>, dim3(a.N), dim3(256), lds, s, (const float*)a.h, a.fcw, a.fcb, a.labels,
                a.pooled, a.dlogits, a.loss_n, (float*)a.dh, a.N, a.HW, a.C, a.classes, a.logits_out);
   if (!a.dfcw) {   // evaluation: no gradients; the mean loss if asked for
-    if (a.loss_out) DDG_LAUNCH(loss_mean_kernel, dim3(1), dim3(64), 0, s, a.loss_n, a.N, a.loss_out);
+    if (a.loss_out) DDG_LAUNCH(loss_mean_kernel, dim3(1), dim3(256), 0, s, a.loss_n, a.N, a.loss_out);
     return hipGetLastError();
   }
-  DDG_LAUNCH(head_wgrad_kernel, dim3(a.classes), dim3(256), 0, s, a.pooled, a.dlogits, a.loss_n, a.dfcw, a.dfcb,
+  DDG_LAUNCH(head_wgrad_kernel, dim3(a.classes), dim3(1024), 0, s, a.pooled, a.dlogits, a.loss_n, a.dfcw, a.dfcb,
              a.loss_out, a.N, a.C, a.classes);
   return hipGetLastError();
 }
