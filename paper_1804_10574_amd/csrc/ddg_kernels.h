@@ -32,12 +32,12 @@ inline int mma_kv(int dt) { return dt == BF16 ? 8 : 4; }
 // (partial == nullptr: the per-channel vectors are already final).
 struct BnRows {        // forward: rows [rows][2][C] of (sum, sum of squares)
   const float* partial; int rows;
-  const float* gamma; const float* beta; float count, eps;
+  const float* gamma; const float* beta; double inv_count; float eps;
   float* mean; float* invstd; float* scale; float* shift;   // written by workgroup 0
 };
 struct BnBwdRows {     // backward: rows of (sum g, sum g*xhat)
   const float* partial; int rows;
-  const float* gamma; const float* mean; const float* invstd; float count;
+  const float* gamma; const float* mean; const float* invstd; double inv_count;   // 1 / pixels per channel
   float* dgamma; float* dbeta;                              // written by workgroup 0
 };
 

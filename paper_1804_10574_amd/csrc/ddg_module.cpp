@@ -564,7 +564,7 @@ BnRows fwd_rows(ddg_module* m, Unit& u, int g = 0) {
   BnRows r{};
   r.partial = u.fstat + (size_t)g * u.fcap * 2 * u.cout; r.rows = u.frows;
   r.gamma = m->theta + u.og; r.beta = m->theta + u.ob;
-  r.count = (float)((size_t)u.N * u.P * u.Q); r.eps = m->d.bn_eps;
+  r.inv_count = 1.0 / (double)((size_t)u.N * u.P * u.Q); r.eps = m->d.bn_eps;
   const int vo = g * u.vec_stride();
   r.mean = u.mean + vo; r.invstd = u.invstd + vo; r.scale = u.scale + vo; r.shift = u.shift + vo;
   return r;
@@ -919,7 +919,7 @@ ddg_status unit_backward(ddg_module* m, Unit& u, const void* dy, const void* mas
   }
   BnBwdRows br{};
   br.partial = u.bstat; br.rows = stats_rows; br.gamma = m->theta_bwd + u.og; br.mean = u.mean; br.invstd = u.invstd;
-  br.count = (float)((size_t)u.N * u.P * u.Q); br.dgamma = m->grad + u.og; br.dbeta = m->grad + u.ob;
+  br.inv_count = 1.0 / (double)((size_t)u.N * u.P * u.Q); br.dgamma = m->grad + u.og; br.dbeta = m->grad + u.ob;
   if (m->defer_wgrad && u.wg_tiled_rows > 0 && u.tiled_grid > 0 && dx && dx != dy) {   // (a halo kernel cannot work in place)
     // The input-gradient kernel forms dz = BN-backward(dy) while staging (coefficients from the
     // rows), stores it, convolves it, and forms the sums of the unit below in its epilogue. The

@@ -13,31 +13,39 @@ namespace ddg {
 constexpr int STATS_CMAX = 64;
 
 // 256 threads, C a compile-time constant in {16, 32, 64}. f(c, t1, t2) runs once per channel (in
-// one thread) with the two column sums. A row is 2*C floats; a thread owns one 16-byte column
-// group and every NSL-th row, keeps 16 loads in flight and adds its rows in order (fp32, like
-// the rows themselves). The NSL row slices of a column are then combined in a fixed order in
+// thread c) with the two column sums. A row is 2*C floats; a thread owns one 16-byte column
+// group and every NSL-th row, keeps its loads in flight together (unconditional: a row past the end
+// repeats the last one and counts as zero) and adds its rows in order (fp32, like the rows
+// themselves). The NSL row slices of a column are then combined in a fixed order in
 // fp64 in two short steps (four values per thread, then 256/(2C) per column), all unrolled.
+// This sits in the prologue of nearly every training kernel, where latency is all that counts: the
+// per-channel parameters are requested before the rows (by the callers below), and the fp64 part
+// multiplies by 1/count and takes one rsqrt instead of two divisions, a square root and a division.
 template <int C, typename F>
 __device__ __forceinline__ void reduce_stat_rows(const float* __restrict__ partial, int rows, F f) {
   static_assert(C == 16 || C == 32 || C == 64, "channel count");
   constexpr int NCOL4 = C / 2;            // float4 groups per row (2*C/4)
   constexpr int NSL = 256 / NCOL4;        // row slices: 32, 16, 8
   constexpr int G = 256 / (2 * C);        // second-step groups per column: 8, 4, 2 (NSL == 4*G)
+  constexpr int U = C == 64 ? 12 : 8;     // loads in flight: all rows of the usual launches (256, 128, 96)
   __shared__ float4 sh[256];
   __shared__ double sh2[256];
   const int tid = threadIdx.x;
   const int c4 = tid % NCOL4, slice = tid / NCOL4;
   const float4* __restrict__ p4 = reinterpret_cast<const float4*>(partial);
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int r0 = slice; r0 < rows; r0 += NSL * 16) {
-    float4 v[16];
+  for (int r0 = slice; r0 < rows; r0 += NSL * U) {
+    float4 v[U];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
+    for (int u = 0; u < U; ++u) {
       const int rr = r0 + u * NSL;
-      v[u] = rr < rows ? p4[(size_t)rr * NCOL4 + c4] : make_float4(0.f, 0.f, 0.f, 0.f);
+      v[u] = p4[(rr < rows ? rr : rows - 1) * NCOL4 + c4];
     }
 #pragma unroll
-    for (int u = 0; u < 16; ++u) { acc.x += v[u].x; acc.y += v[u].y; acc.z += v[u].z; acc.w += v[u].w; }
+    for (int u = 0; u < U; ++u) {
+      const float k = r0 + u * NSL < rows ? 1.f : 0.f;
+      acc.x += k * v[u].x; acc.y += k * v[u].y; acc.z += k * v[u].z; acc.w += k * v[u].w;
+    }
   }
   sh[tid] = acc;
   __syncthreads();
@@ -64,13 +72,15 @@ __device__ __forceinline__ void reduce_stat_rows(const float* __restrict__ parti
 // workgroup 0 (write != 0) also stores mean, invstd, scale, shift.
 template <int C>
 __device__ __forceinline__ void bn_fwd_from_rows(const BnRows& p, float* s_scale, float* s_shift, bool write) {
+  const int tc = threadIdx.x < C ? threadIdx.x : 0;
+  const float gamma = p.gamma[tc], beta = p.beta[tc];
   reduce_stat_rows<C>(p.partial, p.rows, [&](int c, double t1, double t2) {
-    const double mu = t1 / (double)p.count;
-    double var = t2 / (double)p.count - mu * mu;
+    const double mu = t1 * p.inv_count;
+    double var = t2 * p.inv_count - mu * mu;
     if (var < 0.0) var = 0.0;
-    const float is = (float)(1.0 / sqrt(var + (double)p.eps));
-    const float sc = p.gamma[c] * is;
-    const float sh = p.beta[c] - (float)mu * sc;
+    const float is = (float)rsqrt(var + (double)p.eps);
+    const float sc = gamma * is;
+    const float sh = beta - (float)mu * sc;
     s_scale[c] = sc; s_shift[c] = sh;
     if (write) { p.mean[c] = (float)mu; p.invstd[c] = is; p.scale[c] = sc; p.shift[c] = sh; }
   });
@@ -80,9 +90,10 @@ __device__ __forceinline__ void bn_fwd_from_rows(const BnRows& p, float* s_scale
 // workgroup 0 also stores dgamma, dbeta.
 template <int C>
 __device__ __forceinline__ void bn_bwd_from_rows(const BnBwdRows& p, float* s_coef, bool write) {
+  const int tc = threadIdx.x < C ? threadIdx.x : 0;
+  const double g = p.gamma[tc], is = p.invstd[tc], mu = p.mean[tc];
   reduce_stat_rows<C>(p.partial, p.rows, [&](int c, double db, double dg) {
-    const double g = p.gamma[c], is = p.invstd[c], mu = p.mean[c], m = p.count;
-    const double A = g * is, B = -g * is * is * dg / m, C0 = -g * is * db / m - B * mu;
+    const double A = g * is, B = -A * is * (dg * p.inv_count), C0 = -A * (db * p.inv_count) - B * mu;
     s_coef[c] = (float)A; s_coef[C + c] = (float)B; s_coef[2 * C + c] = (float)C0;
     if (write) { p.dgamma[c] = (float)dg; p.dbeta[c] = (float)db; }
   });
