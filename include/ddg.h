@@ -35,6 +35,8 @@
  *                    ReLU mask load the mask tensor and apply it again (same values)
  *   DDG_NO_LDS32=1   fp32 3x3 stride-1 layers run the gather kernels and separate batch-norm
  *                    passes instead of the LDS-tiled kernels
+ *   DDG_NO_FUSED_EVAL=1  the evaluation forward of stem / basic-block modules runs the per-layer
+ *                    kernels instead of the one that keeps activations in LDS across layers
  *   DDG_CHECK_ORDER=1  ddg_pipeline_step also runs its host-side model of the stream ordering
  *                    (always on in dry-run pipelines) and fails with DDG_ERR_STATE, naming the
  *                    tensor, if the events it issues leave two accesses of a tensor unordered

@@ -11,6 +11,8 @@ void ddg_internal_skip_launches(ddg_module* m, bool skip);
 // The update reads its step size from this device float instead of the call argument.
 void ddg_internal_lr_from(ddg_module* m, const float* lr_dev);
 bool ddg_internal_profiling(const ddg_module* m);
+// Evaluation passes of the module go to stream s (on) or to its own stream again (off).
+void ddg_internal_eval_stream(ddg_module* m, bool on, hipStream_t s);
 // A pipeline orders the module's two streams itself (events around graph launches); the module
 // then records and waits on nothing.
 void ddg_internal_external_sync(ddg_module* m, bool on);

@@ -5,6 +5,7 @@
 #include <hip/hip_ext.h>
 #include <stddef.h>
 #include <stdint.h>
+#include <vector>
 
 namespace ddg {
 
@@ -261,6 +262,24 @@ struct RunDesc {
 };
 hipError_t running_update_launch(const RunDesc* dev_descs, int n, int max_c, float rho, hipStream_t s);
 hipError_t eval_vectors_launch(const RunDesc* dev_descs, int n, int max_c, hipStream_t s);
+
+// Evaluation forward of stem / basic blocks with 16, 32 or 64 channels, many layers per launch
+// (kernels_eval.hip). A module's convolutions lie in a device table in parameter order: the packed
+// forward operand and the batch norm whose running estimates the pass normalises with; toff: where
+// the layer's scale and shift go in the pass's LDS table (floats, counted over the module).
+enum { EVAL_STEM = 0, EVAL_IDENTITY = 1, EVAL_DOWN = 2 };   // DOWN: stride 2, channels doubled, projection
+struct EvalConvDesc { const void* w; const float *gamma, *beta, *rmean, *rvar; float eps; int cout, toff; };
+struct EvalBlockDesc { int kind, stride, conv0; };          // conv0: index of the block's first convolution
+struct EvalBlockShape { int kind, c, stride; };             // c: input channels
+struct EvalLaunch {        // blocks [first, first + count) of a module on H x W inputs
+  int first, count, conv0, nconv, H, W, TH, strips;
+  unsigned off1, off2, red_off, tab_off, dump_off; size_t lds;
+};
+struct EvalPlan { std::vector<EvalLaunch> launches; };
+bool eval_block_ok(int kind, int c);
+bool eval_plan(const EvalBlockShape* b, int nb, int N, int H, int W, int dtype, EvalPlan* out);   // false: not covered
+hipError_t eval_blocks_launch(const EvalBlockDesc* dev_blocks, const EvalConvDesc* dev_convs, const EvalLaunch& l, const void* in,
+                              void* out, int N, int C, int dtype, hipStream_t s);
 
 // lr_dev != nullptr: the step size is read from device memory (lets a captured graph be replayed
 // with a different step size).

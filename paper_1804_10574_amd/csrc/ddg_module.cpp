@@ -42,7 +42,7 @@ enum ProfKind {
   PK_CONV_FPROP_WIDE = PK_BWD_PAIR_T64 + 1, PK_CONV_DGRAD_WIDE, PK_CONV_WGRAD_WIDE,
   PK_CONV_WGRAD_S2,   // the LDS-tiled weight gradient of the stride-2 layers between stages
   PK_WGRAD_REDUCE, PK_BN_FINALIZE, PK_BN_APPLY,
-  PK_BN_BWD_REDUCE, PK_BN_BWD_FINALIZE, PK_BN_BWD_APPLY, PK_HEAD, PK_SGD, PK_PACK, PK_COPY, PK_ADAM, PK_BN_RUNNING, PK_COUNT
+  PK_BN_BWD_REDUCE, PK_BN_BWD_FINALIZE, PK_BN_BWD_APPLY, PK_HEAD, PK_SGD, PK_PACK, PK_COPY, PK_ADAM, PK_BN_RUNNING, PK_EVAL, PK_COUNT
 };
 static const char* kProfNames[PK_COUNT] = {
   "conv_fprop.generic", "conv_fprop.tiled_c16_w32", "conv_fprop.tiled_c32_w16", "conv_fprop.tiled_c64_w8",
@@ -51,7 +51,7 @@ static const char* kProfNames[PK_COUNT] = {
   "conv_bwd_pair.tiled_c16_w32", "conv_bwd_pair.tiled_c32_w16", "conv_bwd_pair.tiled_c64_w8",
   "conv_fprop.wide", "conv_dgrad.wide", "conv_wgrad.wide", "conv_wgrad.tiled_stride2",
   "wgrad_reduce", "bn_finalize", "bn_apply",
-  "bn_bwd_reduce", "bn_bwd_finalize", "bn_bwd_apply", "head", "sgd", "pack_weights", "copy", "adam", "bn_running"};
+  "bn_bwd_reduce", "bn_bwd_finalize", "bn_bwd_apply", "head", "sgd", "pack_weights", "copy", "adam", "bn_running", "eval_blocks"};
 
 struct Unit {  // convolution + batch normalisation
   int cin = 0, cout = 0, R = 0, stride = 1, pad = 0;
@@ -159,6 +159,10 @@ struct ddg_module {
   float bn_rho = 0.1f;
   std::vector<RunDesc*> run_descs; RunDesc* run_descs_f = nullptr; int n_run = 0, run_max_c = 0;
   int32_t* zero_labels = nullptr;  // head modules: labels for an evaluation without labels
+  EvalPlan eval;                   // launches of the many-layer evaluation kernel; empty: the per-layer kernels
+  EvalBlockDesc* eval_descs = nullptr;
+  EvalConvDesc* eval_convs = nullptr;
+  bool eval_elsewhere = false; hipStream_t estream = nullptr;   // the pipeline runs every module's evaluation on one stream
   bool eval_mode = false;          // the forward helpers normalise with the evaluation vectors
   float* ws_stat = nullptr; size_t ws_stat_elems = 0;
   PackDesc* pack_descs = nullptr; int n_pack = 0;     // device tables for the whole-module kernels
@@ -1233,6 +1237,55 @@ ddg_status build_running_tables(ddg_module* m) {
   return DDG_OK;
 }
 
+// Launches of the evaluation forward for modules made of stem and basic blocks only, and the device
+// table of their convolutions (see kernels_eval.hip). Other modules keep the per-layer kernels.
+ddg_status build_eval_plan(ddg_module* m) {
+  const char* e = getenv("DDG_NO_FUSED_EVAL");
+  if (e && e[0] == '1') return DDG_OK;
+  std::vector<EvalBlockShape> shp;
+  std::vector<EvalBlockDesc> tab;
+  std::vector<EvalConvDesc> convs;
+  int toff = 0;
+  for (const Blk& b : m->blocks) {
+    if (b.kind == DDG_BLOCK_HEAD) break;
+    const Unit& u = b.u[0];
+    EvalBlockDesc t{};
+    t.stride = u.stride; t.conv0 = (int)convs.size();
+    if (b.kind == DDG_BLOCK_STEM) {
+      if (u.cout != 16) return DDG_OK;
+      t.kind = EVAL_STEM;
+    } else if (b.kind == DDG_BLOCK_BASIC && !b.proj) {
+      t.kind = EVAL_IDENTITY;
+    } else if (b.kind == DDG_BLOCK_BASIC && u.stride == 2 && u.cout == 2 * u.cin) {
+      t.kind = EVAL_DOWN;
+    } else {
+      return DDG_OK;
+    }
+    for (const Unit& q : b.u) {
+      EvalConvDesc c{};
+      c.w = q.wpack_f; c.gamma = m->theta + q.og; c.beta = m->theta + q.ob; c.rmean = q.rmean; c.rvar = q.rvar;
+      c.eps = m->d.bn_eps; c.cout = q.cout; c.toff = toff;
+      toff += 2 * q.cout;
+      convs.push_back(c);
+    }
+    tab.push_back(t);
+    shp.push_back({t.kind, u.cin, t.stride});
+  }
+  EvalPlan plan;
+  if (tab.empty() || !eval_plan(shp.data(), (int)shp.size(), m->d.batch, m->d.in_h, m->d.in_w, m->d.compute, &plan)) return DDG_OK;
+  if (m->d.dry_run) return DDG_OK;
+  void *p = nullptr, *q = nullptr;
+  DDG_OKAY(dev_alloc(m, &p, tab.size() * sizeof(EvalBlockDesc)));
+  DDG_OKAY(dev_alloc(m, &q, convs.size() * sizeof(EvalConvDesc)));
+  if (hipMemcpy(p, tab.data(), tab.size() * sizeof(EvalBlockDesc), hipMemcpyHostToDevice) != hipSuccess ||
+      hipMemcpy(q, convs.data(), convs.size() * sizeof(EvalConvDesc), hipMemcpyHostToDevice) != hipSuccess)
+    return fail(DDG_ERR_DEVICE, "copying the layer tables failed");
+  m->eval_descs = (EvalBlockDesc*)p;
+  m->eval_convs = (EvalConvDesc*)q;
+  m->eval = plan;
+  return DDG_OK;
+}
+
 ddg_status sync_streams(ddg_module* m) {
   DDG_TRY(hipStreamSynchronize(m->bstream));
   if (m->two_streams) DDG_TRY(hipStreamSynchronize(m->fstream));
@@ -1271,6 +1324,7 @@ ddg_status ddg_module_create(const ddg_module_desc* desc, ddg_module** out) {
   ddg_status st = build_plan(m);
   if (st == DDG_OK && m->two_streams) st = build_forward_shadow(m);
   if (st == DDG_OK) st = build_running_tables(m);
+  if (st == DDG_OK) st = build_eval_plan(m);
   if (st != DDG_OK) {
     for (void* p : m->allocs) (void)hipFree(p);
     delete m;
@@ -1540,14 +1594,26 @@ struct HeadScratch { float* pooled; float* dlogits; float* loss_n; };
 static ddg_status eval_forward(ddg_module* m, std::vector<Blk>& blocks, const HeadScratch& hs, const void* h_in,
                                void* h_out, const int32_t* labels, float* loss_out, float* logits_out) {
   const bool head = m->d.num_classes > 0;
-  m->stream = m->bstream;
-  if (m->n_run) DDG_TRY(eval_vectors_launch(m->run_descs[0], m->n_run, m->run_max_c, m->stream));
+  m->stream = m->eval_elsewhere ? m->estream : m->bstream;
+  if (m->n_run && m->eval.launches.empty()) DDG_TRY(eval_vectors_launch(m->run_descs[0], m->n_run, m->run_max_c, m->stream));
   const int nres = (int)blocks.size() - (head ? 1 : 0);
-  m->eval_mode = true;
-  ddg_status st = DDG_OK;
-  if (nres > 0) st = run_forward(m, blocks, h_in, head ? nullptr : h_out);
-  m->eval_mode = false;
-  DDG_OKAY(st);
+  if (!m->eval.launches.empty()) {
+    const void* in = h_in;
+    for (const EvalLaunch& l : m->eval.launches) {
+      const int last = l.first + l.count - 1;
+      void* out = last == nres - 1 && !head ? h_out : blocks[last].y;
+      double flops = 0.0, bytes = ((double)blocks[l.first].u[0].in_elems() + blocks[last].y_elems) * m->esz;
+      for (int i = l.first; i <= last; ++i) for (const Unit& u : blocks[i].u) { flops += conv_flops(u); bytes += wbytes(m, u); }
+      Launch L(m, PK_EVAL, bytes, flops);
+      DDG_TRY(eval_blocks_launch(m->eval_descs, m->eval_convs, l, in, out, m->d.batch, blocks[l.first].u[0].cin, m->d.compute, m->stream));
+      in = out;
+    }
+  } else if (nres > 0) {
+    m->eval_mode = true;
+    const ddg_status st = run_forward(m, blocks, h_in, head ? nullptr : h_out);
+    m->eval_mode = false;
+    DDG_OKAY(st);
+  }
   if (head) {
     Blk& hb = blocks.back();
     HeadArgs a{};
@@ -1720,6 +1786,7 @@ ddg_status ddg_module_sync(ddg_module* m) {
 }
 
 void ddg_internal_skip_launches(ddg_module* m, bool skip) { m->skip = skip; }
+void ddg_internal_eval_stream(ddg_module* m, bool on, hipStream_t s) { m->eval_elsewhere = on; m->estream = s; }
 void ddg_internal_external_sync(ddg_module* m, bool on) { m->external_sync = on; }
 void ddg_internal_streams(ddg_module* m, hipStream_t* fwd, hipStream_t* bwd) { *fwd = m->fstream; *bwd = m->bstream; }
 void ddg_internal_lr_from(ddg_module* m, const float* lr_dev) { m->lr_dev = lr_dev; }

@@ -84,7 +84,6 @@ struct ddg_pipeline {
   std::vector<int> dtype;
   std::vector<hipEvent_t> fwd_done[2];  // [t%2][k] recorded after module k's forward
   std::vector<hipEvent_t> bwd_done[2];  // [t%2][k] recorded after module k's backward+update
-  hipEvent_t input_free = nullptr;
   long t = 0;
   bool dry = false;
   float* scratch_f32 = nullptr; size_t scratch_elems = 0;
@@ -292,8 +291,9 @@ ddg_status ddg_pipeline_set_bn_momentum(ddg_pipeline* p, float rho) {
 }
 
 // Evaluation of the whole network between iterations. Module k writes into the buffer that
-// iteration p->t will overwrite anyway (the one ddg_pipeline_get_h does not read); modules run
-// one after the other, each waited for.
+// iteration p->t will overwrite anyway (the one ddg_pipeline_get_h does not read). Everything
+// before it has been waited for, so the modules run one after the other on the last module's stream:
+// no wait on another stream (5-10 us each) and one for the host.
 ddg_status ddg_pipeline_forward_eval(ddg_pipeline* p, const void* x, const int32_t* labels, float* loss_out,
                                      float* logits_out) {
   if (!p || !x) return DDG_ERR_INVALID_ARG;
@@ -303,14 +303,14 @@ ddg_status ddg_pipeline_forward_eval(ddg_pipeline* p, const void* x, const int32
   const void* in = x;
   for (int k = 1; k <= p->K; ++k) {
     void* out = (k < p->K) ? ((p->t & 1) ? p->h_odd[k] : p->h[k]) : nullptr;
+    ddg_internal_eval_stream(p->mods[k], true, p->streams[p->K]);
     st = ddg_forward_eval(p->mods[k], in, out, k == p->K ? labels : nullptr, k == p->K ? loss_out : nullptr,
                           k == p->K ? logits_out : nullptr);
-    if (st != DDG_OK) return st;
-    st = ddg_module_sync(p->mods[k]);
+    ddg_internal_eval_stream(p->mods[k], false, nullptr);
     if (st != DDG_OK) return st;
     in = out;
   }
-  return DDG_OK;
+  return hipStreamSynchronize(p->streams[p->K]) == hipSuccess ? DDG_OK : DDG_ERR_DEVICE;
 }
 
 ddg_status ddg_pipeline_step(ddg_pipeline* p, const void* x, const int32_t* labels, float lr, float* loss_out) {

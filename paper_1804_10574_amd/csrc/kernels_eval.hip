@@ -1,0 +1,691 @@
+// Evaluation forward of the CIFAR-shaped networks. With running estimates a batch norm is a fixed
+// affine map, so nothing has to be known about the whole minibatch between two layers, and one
+// workgroup can take an image (or a strip of its rows) through many layers without leaving its
+// compute unit: activations stay in LDS, weights come from L2 in fragment order, and memory sees
+// the network's input and output only.
+//
+// What bounds it: a layer of one image is 4.7 MFLOP on one compute unit, about 1 us of matrix and
+// LDS time in bf16, against 10-13 us for the per-layer launch of a whole minibatch of 256 and 6-7
+// us for the smallest one (the launch, its weights and its halo loads are then all there is).
+// Measured, whole call: ResNet-110, batch 256, bf16 1290 -> 282 us (2.4 us per layer); the 32-channel group of
+// ResNet-56, batch 100, bf16 133 -> 42 us; ResNet-20, one image, fp32 222 -> 118 us.
+//
+// Two ways of cutting the work, chosen by eval_plan() below:
+//   whole images: all blocks of a module in one launch, one image per workgroup (bf16);
+//   strips: one residual block per launch, TH output rows per workgroup, the rows of the halo
+//           recomputed (fp32, whose matrix rate makes an image 10-18 us per layer on one unit, so
+//           that one image has to be spread over several; and images too large for LDS).
+//
+// Buffers: three LDS regions of NHWC pixels with a zero border (row and column -1 and H / W); a
+// pixel is padded by 16 bytes, so that the 16 pixels of a fragment read start in 16 different bank
+// groups. An identity block reads x, writes o = relu(bn1(conv1 x)), then adds relu(bn2(conv2 o) + x)
+// back into x in place (an output pixel needs x at that pixel only). A block between stages writes
+// its output to the third region, and the regions change roles.
+//
+// Eight waves; a wave holds the weight fragments of one layer in registers (two sets: the next
+// layer's are requested before the current one is contracted) and walks over 16-pixel blocks:
+//   16 channels: every wave all channels, 8 pixel groups;  32 channels: bf16 the same with two
+//   channel blocks per wave (halves the LDS reads per matrix instruction), fp32 one block each;
+//   64 channels: 4 channel blocks x 2 halves of the contraction (a layer's weights, 73 KB in bf16,
+//   then enter the compute unit once; the halves meet in LDS).
+// Rounding points are those of the per-layer kernels: the conv output and the activations are
+// rounded to the storage type, sums are fp32.
+#include "ddg_device.h"
+#include "ddg_kernels.h"
+
+namespace ddg {
+
+namespace ev {
+
+constexpr int NT = 512;
+constexpr size_t LDS_MAX = 160 * 1024;
+constexpr int RED_BYTES = 2 * 8 * 2 * 64 * 16;   // exchange of the contraction halves, double-buffered
+constexpr int DUMP_BYTES = 64 * 16;               // where lanes without a pixel write
+
+// The layer table is in memory, so the compiler cannot see that the pointers in it are global ones, and
+// the LDS regions change roles at run time: without help it makes flat accesses of both kinds, which
+// wait for both memories. Pointers from the table are cast to the global address space, LDS is
+// addressed by byte offsets from its start.
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+#define EV_GLOBAL __attribute__((address_space(1)))
+template <typename V> __device__ __forceinline__ V load16(const void* p) {
+  static_assert(sizeof(V) == 16, "16-byte vectors");
+  return __builtin_bit_cast(V, *(const EV_GLOBAL u32x4_t*)(uintptr_t)p);
+}
+__device__ __forceinline__ float load_f(const float* p) { return *(const EV_GLOBAL float*)(uintptr_t)p; }
+__device__ __forceinline__ unsigned char* lds() {
+  extern __shared__ __align__(16) unsigned char smem[];
+  return smem;
+}
+
+template <typename T> constexpr int pix_bytes(int ch) { return ch == Mma<T>::KV ? 16 : ch * (int)sizeof(T) + 16; }
+
+struct Args {
+  const EvalBlockDesc* blocks; int nb;   // the blocks this launch runs
+  const EvalConvDesc* convs; int nconv;  // and their convolutions
+  const void* in; void* out;
+  int N, H, W, C;          // input of the first block (C: real channels)
+  int TH, strips;          // output rows per workgroup; strips > 1 only with nb == 1
+  unsigned off1, off2, red_off, tab_off, dump_off;   // LDS offsets: second and third region, exchange area, scale / shift table
+};
+
+// One convolution layer shape: CIN -> COUT, R x R, stride S, NCB channel blocks and 1/KS of the
+// contraction per wave, U pixel blocks in flight.
+template <typename T, int CIN, int COUT, int R, int S, int NCB, int KS, int U>
+struct Conv {
+  typedef typename Mma<T>::frag_t frag_t;
+  static constexpr int KV = Mma<T>::KV, KSTEP = Mma<T>::KSTEP, PIX = pix_bytes<T>(CIN);
+  static constexpr int KSTEPS = (R * R * CIN + KSTEP - 1) / KSTEP, KPW = KSTEPS / KS;
+  static constexpr int NCB_ = NCB, KS_ = KS, U_ = U, OCB = COUT / 16, CBG = OCB / NCB, PG = 8 / (CBG * KS), PAD = R / 2;
+  static_assert(KSTEPS % KS == 0 && OCB % NCB == 0 && 8 % (CBG * KS) == 0 && (KS == 1 || (PG == 1 && NCB == 1 && U % 2 == 0)), "wave layout");
+
+  struct Wts { frag_t w[NCB][KPW]; float4 sc[NCB], sh[NCB]; };
+
+  // this wave's place: channel-block group, half of the contraction, pixel group
+  __device__ static __forceinline__ int cbg(int wave) { return wave % CBG; }
+  __device__ static __forceinline__ int kh(int wave) { return KS == 1 ? 0 : (wave / CBG) % KS; }
+  __device__ static __forceinline__ int pg(int wave) { return wave / (CBG * KS); }
+
+  // weights from memory, scale and shift ([COUT] each) from the LDS table
+  __device__ static __forceinline__ void load(const EvalConvDesc& d, int tab, Wts& r, int wave, int lane) {
+    const T* w = reinterpret_cast<const T*>(d.w);
+    const float* sc = reinterpret_cast<const float*>(lds() + tab) + d.toff;
+#pragma unroll
+    for (int b = 0; b < NCB; ++b) {
+      const int cb = cbg(wave) * NCB + b;
+#pragma unroll
+      for (int ks = 0; ks < KPW; ++ks)
+        r.w[b][ks] = load16<frag_t>(w + ((size_t)((kh(wave) * KPW + ks) * OCB + cb) * 64 + lane) * KV);
+      const int c = cb * 16 + (lane >> 4) * 4;
+      r.sc[b] = *reinterpret_cast<const float4*>(sc + c);
+      r.sh[b] = *reinterpret_cast<const float4*>(sc + COUT + c);
+    }
+  }
+  // per-lane LDS offset of k-step ks relative to the top left tap of an output pixel (WC: columns
+  // of the source buffer); lanes past the last tap read tap 0 (their weights are zero)
+  __device__ static __forceinline__ void addresses(int (&ka)[KPW], int wave, int lane, int WC) {
+#pragma unroll
+    for (int ks = 0; ks < KPW; ++ks) {
+      const int k = ((kh(wave) * KPW + ks) * 4 + (lane >> 4)) * KV;
+      int tap = k / CIN;
+      const int c0 = k % CIN;
+      if (tap >= R * R) tap = 0;
+      ka[ks] = ((tap / R) * WC + tap % R) * PIX + c0 * (int)sizeof(T);
+    }
+  }
+  template <int V>
+  __device__ static __forceinline__ void contract(int src, const int (&pa)[U], const int (&ka)[KPW], const Wts& wt, f32x4_t (&acc)[NCB][U]) {
+#pragma unroll
+    for (int ks = 0; ks < KPW; ++ks) {
+      frag_t x[V];
+#pragma unroll
+      for (int u = 0; u < V; ++u) x[u] = *reinterpret_cast<const frag_t*>(lds() + src + pa[u] + ka[ks]);
+#pragma unroll
+      for (int b = 0; b < NCB; ++b)
+#pragma unroll
+        for (int u = 0; u < V; ++u) acc[b][u] = Mma<T>::mma(wt.w[b][ks], x[u], acc[b][u]);
+    }
+  }
+  // The halves of the contraction meet: each wave hands U/2 pixel blocks over and finishes the others,
+  // which end up in acc[0 .. U/2) (blocks 0 .. U/2-1 in the first half's waves, the rest in the second's).
+  __device__ static __forceinline__ void exchange(f32x4_t (&acc)[U], int red, int& flip, int wave, int lane) {
+    constexpr int E = U / 2 > 0 ? U / 2 : 1;
+    f32x4_t* ex = reinterpret_cast<f32x4_t*>(lds() + red) + flip * (8 * E * 64);
+    flip ^= 1;
+    const int h = kh(wave), cb = cbg(wave);
+#pragma unroll
+    for (int i = 0; i < U / 2; ++i) ex[((cb * 2 + h) * E + i) * 64 + lane] = h == 0 ? acc[U / 2 + i] : acc[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < U / 2; ++i) acc[i] = (h == 0 ? acc[i] : acc[U / 2 + i]) + ex[((cb * 2 + (1 - h)) * E + i) * 64 + lane];
+  }
+  // Output rows [lo, hi) of W columns from the source buffer (its first row is image row srow0, WC
+  // columns). f(acc, channel block index, row, col, valid) once per 16-pixel block and channel block.
+  template <typename F>
+  __device__ static __forceinline__ void pass(int src, int srow0, int WC, int lo, int hi, int W,
+                                              const int (&ka)[KPW], const Wts& wt, int red, int& flip,
+                                              int wave, int lane, F f) {
+    const int npx = (hi - lo) * W, npb = (npx + 15) >> 4;
+    const float invW = 1.0f / (float)W;
+    for (int g0 = pg(wave); g0 < npb; g0 += PG * U) {
+      int row[U], col[U], pa[U];
+      bool ok[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int p = (g0 + u * PG) * 16 + (lane & 15);
+        ok[u] = p < npx;
+        const int pc = ok[u] ? p : npx - 1;
+        const int q = (int)(((float)pc + 0.5f) * invW);     // exact: pc < 2^16
+        row[u] = lo + q; col[u] = pc - q * W;
+        pa[u] = ((row[u] * S - PAD - srow0) * WC + col[u] * S - PAD + 1) * PIX;
+      }
+      f32x4_t acc[NCB][U];
+#pragma unroll
+      for (int b = 0; b < NCB; ++b)
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc[b][u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      // (fp32 matrix instructions are worth a branch that leaves out a second block that does not exist)
+      const bool all = sizeof(T) == 2 || U == 1 || g0 + (U - 1) * PG < npb;
+      if (all) contract<U>(src, pa, ka, wt, acc);
+      else contract<U == 1 ? 1 : U - 1>(src, pa, ka, wt, acc);
+      if (KS == 1) {
+#pragma unroll
+        for (int b = 0; b < NCB; ++b)
+#pragma unroll
+          for (int u = 0; u < U; ++u) f(acc[b][u], b, row[u], col[u], ok[u]);
+      } else {
+        // the halves of the contraction meet: each wave hands two pixel blocks over and finishes two
+        exchange(acc[0], red, flip, wave, lane);
+        const int h = kh(wave);
+#pragma unroll
+        for (int i = 0; i < U / 2; ++i)
+          f(acc[0][i], 0, h == 0 ? row[i] : row[U / 2 + i], h == 0 ? col[i] : col[U / 2 + i], h == 0 ? ok[i] : ok[U / 2 + i]);
+      }
+    }
+  }
+};
+
+template <typename T, int C> struct Same;       // 3x3, stride 1, C -> C
+template <> struct Same<bf16_t, 16> { typedef Conv<bf16_t, 16, 16, 3, 1, 1, 1, 4> type; };
+template <> struct Same<bf16_t, 32> { typedef Conv<bf16_t, 32, 32, 3, 1, 2, 1, 2> type; };
+template <> struct Same<bf16_t, 64> { typedef Conv<bf16_t, 64, 64, 3, 1, 1, 2, 4> type; };
+template <> struct Same<float, 16> { typedef Conv<float, 16, 16, 3, 1, 1, 1, 1> type; };
+template <> struct Same<float, 32> { typedef Conv<float, 32, 32, 3, 1, 1, 1, 1> type; };
+template <> struct Same<float, 64> { typedef Conv<float, 64, 64, 3, 1, 1, 2, 2> type; };
+template <typename T, int C> struct Down;       // 3x3, stride 2, C -> 2C
+template <> struct Down<bf16_t, 16> { typedef Conv<bf16_t, 16, 32, 3, 2, 2, 1, 2> type; };
+template <> struct Down<bf16_t, 32> { typedef Conv<bf16_t, 32, 64, 3, 2, 1, 1, 2> type; };
+template <> struct Down<float, 16> { typedef Conv<float, 16, 32, 3, 2, 1, 1, 1> type; };
+template <> struct Down<float, 32> { typedef Conv<float, 32, 64, 3, 2, 1, 1, 1> type; };
+
+// what a workgroup holds between blocks
+struct Bufs {
+  int x, o, y;     // LDS offsets
+  int row0;        // image row of buffer row 0 of x
+  int H, W;        // of x
+};
+
+template <typename T>
+__device__ __forceinline__ void zero(int p, int bytes) {
+  for (int i = threadIdx.x * 16; i < bytes; i += NT * 16) *reinterpret_cast<uint4*>(lds() + p + i) = make_uint4(0, 0, 0, 0);
+}
+
+// z (as stored) * scale + shift of four channels
+__device__ __forceinline__ void as_stored(const f32x4_t& a, float (&v)[4], bf16_t) {
+  const uint32_t p = Store<bf16_t>::pack2(a[0], a[1]), q = Store<bf16_t>::pack2(a[2], a[3]);
+  v[0] = __uint_as_float(p << 16); v[1] = __uint_as_float(p & 0xffff0000u);
+  v[2] = __uint_as_float(q << 16); v[3] = __uint_as_float(q & 0xffff0000u);
+}
+__device__ __forceinline__ void as_stored(const f32x4_t& a, float (&v)[4], float) { v[0] = a[0]; v[1] = a[1]; v[2] = a[2]; v[3] = a[3]; }
+template <typename T>
+__device__ __forceinline__ void affine(const f32x4_t& a, const float4& sc, const float4& sh, float (&v)[4]) {
+  as_stored(a, v, T{});
+  v[0] = v[0] * sc.x + sh.x; v[1] = v[1] * sc.y + sh.y; v[2] = v[2] * sc.z + sh.z; v[3] = v[3] * sc.w + sh.w;
+}
+template <typename T>
+__device__ __forceinline__ void store_relu(int p, const float (&v)[4]) {
+  Store<T>::store4(reinterpret_cast<T*>(lds() + p), fmaxf(v[0], 0.f), fmaxf(v[1], 0.f), fmaxf(v[2], 0.f), fmaxf(v[3], 0.f));
+}
+
+// Identity blocks on whole images whose pixel blocks fit G groups per wave: every address of a layer
+// is the same for all layers of the run (both buffers start at image row -1), so a lane computes its
+// pixels' offsets once. Lanes past the last pixel write to `dump`.
+template <typename T, int C, int G>
+__device__ __forceinline__ void identity_images(const EvalConvDesc* cv, int tab, int count, Bufs& B, int red, int dump, int& flip) {
+  typedef typename Same<T, C>::type K;
+  constexpr int PIX = K::PIX, U = K::U_, NCB = K::NCB_, F = K::KS_ == 1 ? U : U / 2;   // F: pixel blocks a wave finishes per group
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int W = B.W, WC = W + 2, npx = B.H * W;
+  int ka[K::KPW];
+  K::addresses(ka, wave, lane, WC);
+  const int centre = (WC + 1) * PIX + (K::cbg(wave) * NCB * 16 + (lane >> 4) * 4) * (int)sizeof(T);
+  int pa[G][U], da[G][F];
+  const float invW = 1.0f / (float)W;
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    int ok[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int p = ((g * U + u) * K::PG + K::pg(wave)) * 16 + (lane & 15), pc = p < npx ? p : npx - 1;
+      const int q = (int)(((float)pc + 0.5f) * invW);
+      pa[g][u] = (q * WC + pc - q * W) * PIX;
+      ok[u] = p < npx ? pa[g][u] + centre : -1;
+    }
+#pragma unroll
+    for (int i = 0; i < F; ++i) da[g][i] = (K::KS_ == 1 || K::kh(wave) == 0) ? ok[i] : ok[U - F + i];
+  }
+  typename K::Wts w1, w2;
+  K::load(cv[0], tab, w1, wave, lane);
+  auto layer = [&](int src, const typename K::Wts& wt, int g, f32x4_t (&acc)[NCB][U]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int b = 0; b < NCB; ++b)
+#pragma unroll
+      for (int u = 0; u < U; ++u) acc[b][u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    K::template contract<U>(src, pa[g], ka, wt, acc);
+    if (K::KS_ == 2) K::exchange(acc[0], red, flip, wave, lane);
+  };
+  for (int i = 0; i < count; ++i) {
+    K::load(cv[2 * i + 1], tab, w2, wave, lane);
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      f32x4_t acc[NCB][U];
+      layer(B.x, w1, g, acc);
+#pragma unroll
+      for (int b = 0; b < NCB; ++b)
+#pragma unroll
+        for (int u = 0; u < F; ++u) {
+          float v[4];
+          affine<T>(acc[b][u], w1.sc[b], w1.sh[b], v);
+          store_relu<T>(da[g][u] >= 0 ? B.o + da[g][u] + b * 16 * (int)sizeof(T) : dump + lane * 16, v);
+        }
+    }
+    __syncthreads();
+    if (i + 1 < count) K::load(cv[2 * i + 2], tab, w1, wave, lane);
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      f32x4_t acc[NCB][U];
+      layer(B.o, w2, g, acc);
+#pragma unroll
+      for (int b = 0; b < NCB; ++b)
+#pragma unroll
+        for (int u = 0; u < F; ++u) {
+          float v[4], r[4];
+          const int p = da[g][u] >= 0 ? B.x + da[g][u] + b * 16 * (int)sizeof(T) : dump + lane * 16;
+          affine<T>(acc[b][u], w2.sc[b], w2.sh[b], v);
+          Store<T>::load4(reinterpret_cast<const T*>(lds() + p), r);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] += r[e];
+          store_relu<T>(p, v);
+        }
+    }
+    __syncthreads();
+  }
+}
+
+// `count` identity blocks of C channels, output rows [lo, hi) (all rows when count > 1)
+template <typename T, int C>
+__device__ __forceinline__ void identity_run(const EvalConvDesc* cv, int tab, int count, Bufs& B, int lo, int hi, int red, int& flip) {
+  typedef typename Same<T, C>::type K;
+  constexpr int PIX = K::PIX;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int W = B.W, WC = W + 2;
+  const int olo = lo > 0 ? lo - 1 : 0, ohi = hi < B.H ? hi + 1 : B.H;
+  const int orow0 = lo - 1;
+  const int cq = K::cbg(wave) * K::NCB_ * 16 + (lane >> 4) * 4;
+  int ka[K::KPW];
+  K::addresses(ka, wave, lane, WC);
+  typename K::Wts w1, w2;
+  K::load(cv[0], tab, w1, wave, lane);
+  for (int i = 0; i < count; ++i) {
+    K::load(cv[2 * i + 1], tab, w2, wave, lane);
+    K::pass(B.x, B.row0, WC, olo, ohi, W, ka, w1, red, flip, wave, lane,
+            [&](const f32x4_t& acc, int b, int row, int col, bool ok) __attribute__((always_inline)) {
+              float v[4];
+              affine<T>(acc, w1.sc[b], w1.sh[b], v);
+              if (ok) store_relu<T>(B.o + ((row - orow0) * WC + col + 1) * PIX + (cq + b * 16) * (int)sizeof(T), v);
+            });
+    __syncthreads();
+    if (i + 1 < count) K::load(cv[2 * i + 2], tab, w1, wave, lane);
+    K::pass(B.o, orow0, WC, lo, hi, W, ka, w2, red, flip, wave, lane,
+            [&](const f32x4_t& acc, int b, int row, int col, bool ok) __attribute__((always_inline)) {
+              float v[4], r[4];
+              affine<T>(acc, w2.sc[b], w2.sh[b], v);
+              const int p = B.x + ((row - B.row0) * WC + col + 1) * PIX + (cq + b * 16) * (int)sizeof(T);
+              Store<T>::load4(reinterpret_cast<const T*>(lds() + p), r);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) v[e] += r[e];
+              if (ok) store_relu<T>(p, v);
+            });
+    __syncthreads();
+  }
+}
+
+// A block between stages: C -> 2C channels, stride 2, 1x1 projection on the shortcut
+template <typename T, int C>
+__device__ __forceinline__ void down_block(const EvalConvDesc* cv, int tab, Bufs& B, int lo, int hi, int Ho, int Wo, int red, int& flip) {
+  typedef typename Down<T, C>::type K1;
+  typedef typename Same<T, 2 * C>::type K2;
+  typedef Conv<T, C, 2 * C, 1, 2, K2::NCB_, 1, 1> KP;    // (only its weight layout: same channel blocks as K2)
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int WC = B.W + 2, WCo = Wo + 2;
+  const int olo = lo > 0 ? lo - 1 : 0, ohi = hi < Ho ? hi + 1 : Ho;
+  const int orow0 = lo - 1;
+  zero<T>(B.o, (hi - lo + 2) * WCo * K2::PIX);
+  zero<T>(B.y, (hi - lo + 2) * WCo * K2::PIX);
+  typename K1::Wts w1;
+  typename K2::Wts w2;
+  K1::load(cv[0], tab, w1, wave, lane);
+  __syncthreads();
+  {
+    int ka[K1::KPW];
+    K1::addresses(ka, wave, lane, WC);
+    const int cq = K1::cbg(wave) * K1::NCB_ * 16 + (lane >> 4) * 4;
+    K2::load(cv[1], tab, w2, wave, lane);
+    K1::pass(B.x, B.row0, WC, olo, ohi, Wo, ka, w1, red, flip, wave, lane,
+             [&](const f32x4_t& acc, int b, int row, int col, bool ok) __attribute__((always_inline)) {
+               float v[4];
+               affine<T>(acc, w1.sc[b], w1.sh[b], v);
+               if (ok) store_relu<T>(B.o + ((row - orow0) * WCo + col + 1) * K2::PIX + (cq + b * 16) * (int)sizeof(T), v);
+             });
+  }
+  __syncthreads();
+  {
+    int ka[K2::KPW], kp[KP::KPW];
+    K2::addresses(ka, wave, lane, WCo);
+    const int cg = K2::cbg(wave), cq = cg * K2::NCB_ * 16 + (lane >> 4) * 4;
+    // the projection: every wave the channel blocks it finishes, the whole contraction
+    typename KP::frag_t wp[K2::NCB_][KP::KPW];
+    float4 psc[K2::NCB_], psh[K2::NCB_];
+#pragma unroll
+    for (int b = 0; b < K2::NCB_; ++b) {
+#pragma unroll
+      for (int ks = 0; ks < KP::KPW; ++ks)
+        wp[b][ks] = load16<typename KP::frag_t>(reinterpret_cast<const T*>(cv[2].w) +
+                                                ((size_t)(ks * KP::OCB + cg * K2::NCB_ + b) * 64 + lane) * KP::KV);
+      psc[b] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(lds() + tab) + cv[2].toff + cq + b * 16);
+      psh[b] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(lds() + tab) + cv[2].toff + 2 * C + cq + b * 16);
+    }
+#pragma unroll
+    for (int ks = 0; ks < KP::KPW; ++ks) {
+      const int k = (ks * 4 + (lane >> 4)) * KP::KV;
+      kp[ks] = (k < C ? k : 0) * (int)sizeof(T);         // (channels past the last have zero weights)
+    }
+    K2::pass(B.o, orow0, WCo, lo, hi, Wo, ka, w2, red, flip, wave, lane,
+             [&](const f32x4_t& acc, int b, int row, int col, bool ok) __attribute__((always_inline)) {
+               const int xp = B.x + ((row * 2 - B.row0) * WC + col * 2 + 1) * K1::PIX;
+               f32x4_t pa = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+               for (int ks = 0; ks < KP::KPW; ++ks)
+                 pa = Mma<T>::mma(wp[b][ks], *reinterpret_cast<const typename KP::frag_t*>(lds() + xp + kp[ks]), pa);
+               float v[4], r[4];
+               affine<T>(acc, w2.sc[b], w2.sh[b], v);
+               affine<T>(pa, psc[b], psh[b], r);
+#pragma unroll
+               for (int e = 0; e < 4; ++e) v[e] += r[e];
+               if (ok) store_relu<T>(B.y + ((row - orow0) * WCo + col + 1) * K2::PIX + (cq + b * 16) * (int)sizeof(T), v);
+             });
+  }
+  __syncthreads();
+  const int t = B.x; B.x = B.y; B.y = t;
+  B.row0 = orow0; B.H = Ho; B.W = Wo;
+}
+
+// rows [row0, row0 + rows) of an image with C channels into a buffer with a zero border
+template <typename T>
+__device__ __forceinline__ void load_rows(int buf, const T* img, int row0, int rows, int H, int W, int C, int pix) {
+  constexpr int V = Store<T>::VEC;
+  const int cpp = pix / 16, per_row = (W + 2) * cpp, total = rows * per_row;   // 16-byte chunks, the pixel's padding included
+  const int ch = C / V;
+  for (int i = threadIdx.x; i < total; i += NT) {
+    const int r = i / per_row, e = i - r * per_row, px = e / cpp, k = e - px * cpp;
+    const int h = row0 + r, w = px - 1;
+    uint4 q = make_uint4(0, 0, 0, 0);
+    if (k < ch && h >= 0 && h < H && w >= 0 && w < W)
+      q = *reinterpret_cast<const uint4*>(img + ((size_t)h * W + w) * C + k * V);
+    *reinterpret_cast<uint4*>(lds() + buf + i * 16) = q;
+  }
+}
+// the network input: up to KV channels per pixel, one 16-byte chunk each
+template <typename T>
+__device__ __forceinline__ void load_rows_stem(int buf, const T* img, int row0, int rows, int H, int W, int C) {
+  constexpr int V = Store<T>::VEC;
+  const int total = rows * (W + 2);
+  for (int i = threadIdx.x; i < total; i += NT) {
+    const int r = i / (W + 2), w = i - r * (W + 2) - 1, h = row0 + r;
+    float f[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) f[e] = 0.f;
+    if (h >= 0 && h < H && w >= 0 && w < W)
+#pragma unroll
+      for (int e = 0; e < V; ++e) if (e < C) f[e] = Store<T>::load1(img + ((size_t)h * W + w) * C + e);
+    Store<T>::store_vec(reinterpret_cast<T*>(lds() + buf + i * 16), f);
+  }
+}
+
+// (the fp32 kernel runs strips; whole images only where an image is one strip)
+template <typename T, bool WHOLE>
+__global__ __launch_bounds__(NT) void eval_blocks_kernel(Args a) {
+  const int n = blockIdx.x / a.strips, st = blockIdx.x - n * a.strips;
+  const int tid = threadIdx.x;
+  const int red = (int)a.red_off;
+  int flip = 0;
+  Bufs B;
+  B.x = 0; B.o = (int)a.off1; B.y = (int)a.off2;
+  B.H = a.H; B.W = a.W;
+  int C = a.C;
+  const T* img = reinterpret_cast<const T*>(a.in) + (size_t)n * a.H * a.W * a.C;
+  // output rows of the (first) block, and the input rows they need
+  const EvalBlockDesc& b0 = a.blocks[0];
+  const int st0 = b0.kind == EVAL_DOWN ? 2 : b0.stride;
+  const int Ho0 = (a.H - 1) / st0 + 1;
+  int lo = a.strips > 1 ? st * a.TH : 0, hi = a.strips > 1 ? (lo + a.TH < Ho0 ? lo + a.TH : Ho0) : Ho0;
+  {
+    const int olo = b0.kind == EVAL_STEM ? lo : (lo > 0 ? lo - 1 : 0), ohi = b0.kind == EVAL_STEM ? hi : (hi < Ho0 ? hi + 1 : Ho0);
+    B.row0 = olo * st0 - 1;
+    const int rows = (ohi - 1) * st0 + 2 - B.row0;
+    if (b0.kind == EVAL_STEM) {
+      load_rows_stem<T>(B.o, img, B.row0, rows, a.H, a.W, a.C);
+    } else {
+      load_rows<T>(B.x, img, B.row0, rows, a.H, a.W, a.C, pix_bytes<T>(a.C));
+      if (b0.kind == EVAL_IDENTITY) zero<T>(B.o, (hi - lo + 2) * (a.W + 2) * pix_bytes<T>(a.C));
+    }
+  }
+  // scale and shift of every batch norm of the launch, a wave per layer and four layers at a time
+  float* const tab0 = reinterpret_cast<float*>(lds() + a.tab_off);
+  const int tab = (int)a.tab_off - 4 * a.convs[0].toff;
+  {
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int c0 = wave; c0 < a.nconv; c0 += 32) {
+      float g[4], be[4], rm[4], rv[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int ci = c0 + k * 8 < a.nconv ? c0 + k * 8 : c0;
+        const EvalConvDesc& d = a.convs[ci];
+        const int c = lane < d.cout ? lane : 0;
+        g[k] = load_f(d.gamma + c); be[k] = load_f(d.beta + c); rm[k] = load_f(d.rmean + c); rv[k] = load_f(d.rvar + c);
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (c0 + k * 8 >= a.nconv) break;
+        const EvalConvDesc& d = a.convs[c0 + k * 8];
+        const float sc = g[k] / sqrtf(rv[k] + d.eps);
+        if (lane < d.cout) {
+          tab0[d.toff - a.convs[0].toff + lane] = sc;
+          tab0[d.toff - a.convs[0].toff + d.cout + lane] = be[k] - rm[k] * sc;
+        }
+      }
+    }
+  }
+  int bi = 0;
+  if (b0.kind == EVAL_STEM) {
+    typedef Conv<T, Mma<T>::KV, 16, 3, 1, 1, 1, 2> K1;
+    typedef Conv<T, Mma<T>::KV, 16, 3, 2, 1, 1, 2> K2;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int Wo = (a.W - 1) / b0.stride + 1, srow0 = B.row0;
+    constexpr int PIX = pix_bytes<T>(16);
+    B.row0 = lo - 1;
+    zero<T>(B.x, (hi - lo + 2) * (Wo + 2) * PIX);
+    typename K1::Wts w;
+    __syncthreads();
+    K1::load(a.convs[0], tab, w, wave, lane);
+    int ka[K1::KPW];
+    K1::addresses(ka, wave, lane, a.W + 2);
+    __syncthreads();
+    auto put = [&](const f32x4_t& acc, int b, int row, int col, bool ok) __attribute__((always_inline)) {
+      float v[4];
+      affine<T>(acc, w.sc[b], w.sh[b], v);
+      if (ok) store_relu<T>(B.x + ((row - B.row0) * (Wo + 2) + col + 1) * PIX + (lane >> 4) * 4 * (int)sizeof(T), v);
+    };
+    if (b0.stride == 1) {
+      K1::pass(B.o, srow0, a.W + 2, lo, hi, Wo, ka, w, red, flip, wave, lane, put);
+    } else {
+      typename K2::Wts v2;
+#pragma unroll
+      for (int k = 0; k < K2::KPW; ++k) v2.w[0][k] = w.w[0][k];
+      K2::pass(B.o, srow0, a.W + 2, lo, hi, Wo, ka, v2, red, flip, wave, lane, put);
+    }
+    B.H = Ho0; B.W = Wo; C = 16;
+    __syncthreads();
+    bi = 1;
+    if (bi < a.nb) zero<T>(B.o, (B.H + 2) * (B.W + 2) * PIX);   // (the input image was there)
+  }
+  __syncthreads();
+  while (bi < a.nb) {
+    const int kind = a.blocks[bi].kind;
+    if (bi > 0) { lo = 0; hi = kind == EVAL_DOWN ? (B.H - 1) / 2 + 1 : B.H; }
+    if (kind == EVAL_IDENTITY) {
+      int cnt = 1;
+      while (bi + cnt < a.nb && a.blocks[bi + cnt].kind == EVAL_IDENTITY) ++cnt;
+      const int npx = B.H * B.W;
+      const EvalConvDesc* cv0 = a.convs + (a.blocks[bi].conv0 - a.blocks[0].conv0);
+      const bool whole = a.strips == 1 && WHOLE;
+      if (C == 16) {
+        if (whole && npx <= 1024) identity_images<T, 16, WHOLE ? 2 : 1>(cv0, tab, cnt, B, red, (int)a.dump_off, flip);
+        else identity_run<T, 16>(cv0, tab, cnt, B, lo, hi, red, flip);
+      } else if (C == 32) {
+        if (whole && npx <= 256) identity_images<T, 32, 1>(cv0, tab, cnt, B, red, (int)a.dump_off, flip);
+        else identity_run<T, 32>(cv0, tab, cnt, B, lo, hi, red, flip);
+      } else {
+        if (whole && npx <= 64) identity_images<T, 64, 1>(cv0, tab, cnt, B, red, (int)a.dump_off, flip);
+        else identity_run<T, 64>(cv0, tab, cnt, B, lo, hi, red, flip);
+      }
+      bi += cnt;
+    } else {
+      const int Ho = (B.H - 1) / 2 + 1, Wo = (B.W - 1) / 2 + 1;
+      const EvalConvDesc* cv = a.convs + (a.blocks[bi].conv0 - a.blocks[0].conv0);
+      if (C == 16) down_block<T, 16>(cv, tab, B, lo, hi, Ho, Wo, red, flip);
+      else down_block<T, 32>(cv, tab, B, lo, hi, Ho, Wo, red, flip);
+      C *= 2;
+      ++bi;
+    }
+  }
+  // the output rows of this workgroup
+  constexpr int V = Store<T>::VEC;
+  const int ch = C / V, pix = pix_bytes<T>(C), per_row = B.W * ch, total = (hi - lo) * per_row;
+  T* out = reinterpret_cast<T*>(a.out) + ((size_t)n * B.H + lo) * B.W * C;
+  for (int i = tid; i < total; i += NT) {
+    const int r = i / per_row, e = i - r * per_row, px = e / ch, k = e - px * ch;
+    *reinterpret_cast<uint4*>(out + (size_t)i * V) =
+        *reinterpret_cast<const uint4*>(lds() + B.x + ((lo + r - B.row0) * (B.W + 2) + px + 1) * pix + k * 16);
+  }
+}
+
+}  // namespace ev
+
+// LDS of a launch over `kinds`/`chans` (nb blocks) on H x W images with TH output rows per workgroup.
+static void eval_lds(const EvalBlockShape* b, int nb, int H, int W, int TH, int strips, int dtype, EvalLaunch* l) {
+  const size_t esz = dtype_size(dtype);
+  auto pix = [&](int c) -> size_t { return c * esz + 16; };
+  size_t need[3] = {0, 0, 0};     // regions A, B, C
+  int xi = 0, yi = 2;             // which region holds x, which is free
+  auto want = [&](int region, size_t bytes) { if (bytes > need[region]) need[region] = bytes; };
+  auto rows = [&](int r, int h) -> size_t { return strips > 1 && r < h + 2 ? r : h + 2; };
+  bool exch = false;
+  size_t tab = 0;                 // scale and shift of every convolution
+  int h = H, w = W;
+  for (int i = 0; i < nb; ++i) {
+    if (b[i].kind == EVAL_STEM) {
+      want(1, rows((TH - 1) * b[i].stride + 3, h) * (w + 2) * 16);
+      h = (h - 1) / b[i].stride + 1; w = (w - 1) / b[i].stride + 1;
+      want(0, rows(TH + 2, h) * (w + 2) * pix(16));
+      if (nb > 1) want(1, (size_t)(h + 2) * (w + 2) * pix(16));
+    } else if (b[i].kind == EVAL_IDENTITY) {
+      want(xi, rows(TH + 4, h) * (w + 2) * pix(b[i].c));
+      want(1, rows(TH + 2, h) * (w + 2) * pix(b[i].c));
+      if (b[i].c == 64) exch = true;
+    } else {
+      want(xi, rows((TH + 1) * 2 + 3, h) * (w + 2) * pix(b[i].c));
+      h = (h - 1) / 2 + 1; w = (w - 1) / 2 + 1;
+      want(1, rows(TH + 2, h) * (w + 2) * pix(2 * b[i].c));
+      want(yi, rows(TH + 2, h) * (w + 2) * pix(2 * b[i].c));
+      int t = xi; xi = yi; yi = t;
+      if (2 * b[i].c == 64) exch = true;
+    }
+  }
+  for (int i = 0; i < nb; ++i)
+    tab += 8 * (size_t)(b[i].kind == EVAL_STEM ? 16 : b[i].kind == EVAL_IDENTITY ? 2 * b[i].c : 6 * b[i].c);
+  l->off1 = (unsigned)need[0];
+  l->off2 = (unsigned)(need[0] + need[1]);
+  l->red_off = (unsigned)(need[0] + need[1] + need[2]);
+  l->tab_off = l->red_off + (exch ? ev::RED_BYTES : 0);
+  l->dump_off = l->tab_off + (unsigned)tab;
+  l->lds = l->dump_off + ev::DUMP_BYTES;
+}
+
+bool eval_block_ok(int kind, int c) {
+  if (kind == EVAL_STEM) return c >= 1 && c <= 4;
+  if (kind == EVAL_IDENTITY) return c == 16 || c == 32 || c == 64;
+  return kind == EVAL_DOWN && (c == 16 || c == 32);
+}
+
+// How a module's blocks are cut into launches. bf16: whole images, all blocks at once, if the
+// buffers fit LDS. Otherwise one block per launch in strips of the height that minimises
+//   rounds over 256 compute units x (2 us + the strip's matrix time, halo rows included)
+// (2 us: loads, barriers and epilogues of a block, measured on one image).
+bool eval_plan(const EvalBlockShape* b, int nb, int N, int H, int W, int dtype, EvalPlan* out) {
+  for (int i = 0; i < nb; ++i)
+    if (!eval_block_ok(b[i].kind, b[i].c) || (i > 0 && b[i].kind == EVAL_STEM)) return false;
+  if (nb < 1 || H * W >= 65536) return false;
+  out->launches.clear();
+  auto convs = [&](int lo, int hi) { int c = 0; for (int i = lo; i < hi; ++i) c += b[i].kind == EVAL_STEM ? 1 : b[i].kind == EVAL_IDENTITY ? 2 : 3; return c; };
+  if (dtype == BF16) {
+    EvalLaunch l{};
+    l.first = 0; l.count = nb; l.H = H; l.W = W; l.TH = H; l.strips = 1;
+    eval_lds(b, nb, H, W, H, 1, dtype, &l);
+    l.conv0 = 0; l.nconv = convs(0, nb);
+    if (l.lds <= ev::LDS_MAX) { out->launches.push_back(l); return true; }
+  }
+  // matrix-core FLOP per second of one compute unit
+  const double rate = dtype == BF16 ? 4.0e12 : 0.5e12;
+  int h = H, w = W;
+  for (int i = 0; i < nb; ++i) {
+    const int s = b[i].kind == EVAL_DOWN ? 2 : (b[i].kind == EVAL_STEM ? b[i].stride : 1);
+    const int ho = (h - 1) / s + 1, wo = (w - 1) / s + 1;
+    const int co = b[i].kind == EVAL_STEM ? 16 : (b[i].kind == EVAL_DOWN ? 2 * b[i].c : b[i].c);
+    const double f2 = 2.0 * 9 * co * co, f1 = b[i].kind == EVAL_STEM ? 0.0 : 2.0 * 9 * co * b[i].c;
+    EvalLaunch best{};
+    double best_t = 1e30;
+    for (int th = 1; th <= ho; ++th) {
+      if (th > 8 && th < ho && th % 4 != 0) continue;
+      EvalLaunch l{};
+      l.first = i; l.count = 1; l.H = h; l.W = w; l.TH = th; l.strips = (ho + th - 1) / th;
+      eval_lds(b + i, 1, h, w, th, l.strips, dtype, &l);
+      if (l.lds > ev::LDS_MAX) continue;
+      // 16-pixel blocks, walked in groups of a workgroup's 8 waves (64 channels: 4 blocks together)
+      auto blocks = [&](int r) { const int pb = (r * wo + 15) / 16, g = co == 16 ? 8 : co == 32 ? 4 : dtype == BF16 ? 4 : 1; return (pb + g - 1) / g * g; };
+      const int r1 = th + 2 < ho ? th + 2 : ho;
+      const double flop = 16.0 * (blocks(r1) * f1 + blocks(th) * f2);   // whole groups of pixel blocks
+      const double rounds = ((size_t)N * l.strips + 255) / 256;   // (registers: one workgroup per compute unit)
+      const double t = rounds * (2e-6 + flop / rate);
+      if (t < best_t) { best_t = t; best = l; }
+    }
+    if (best_t >= 1e30) return false;
+    best.conv0 = convs(0, i); best.nconv = convs(i, i + 1);
+    out->launches.push_back(best);
+    h = ho; w = wo;
+  }
+  return true;
+}
+
+hipError_t eval_blocks_launch(const EvalBlockDesc* dev_blocks, const EvalConvDesc* dev_convs, const EvalLaunch& l, const void* in, void* out, int N, int C,
+                              int dtype, hipStream_t s) {
+  if (!dev_blocks || !dev_convs || l.nconv < 1 || N < 1 || l.count < 1 || l.lds > ev::LDS_MAX || (l.strips > 1 && l.count != 1)) return hipErrorInvalidValue;
+  ev::Args a{};
+  a.blocks = dev_blocks + l.first; a.nb = l.count; a.in = in; a.out = out; a.N = N; a.H = l.H; a.W = l.W; a.C = C;
+  a.TH = l.TH; a.strips = l.strips; a.off1 = l.off1; a.off2 = l.off2; a.red_off = l.red_off;
+  a.convs = dev_convs + l.conv0; a.nconv = l.nconv; a.tab_off = l.tab_off; a.dump_off = l.dump_off;
+  const void* f = dtype == BF16 ? reinterpret_cast<const void*>(&ev::eval_blocks_kernel<bf16_t, true>)
+                                : reinterpret_cast<const void*>(&ev::eval_blocks_kernel<float, false>);
+  static bool attr_set[2] = {false, false};
+  if (!attr_set[dtype == BF16]) {
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ev::LDS_MAX);
+    if (e != hipSuccess) return e;
+    attr_set[dtype == BF16] = true;
+  }
+  const dim3 grid((unsigned)(N * l.strips));
+  if (dtype == BF16) DDG_LAUNCH((ev::eval_blocks_kernel<bf16_t, true>), grid, dim3(ev::NT), l.lds, s, a);
+  else DDG_LAUNCH((ev::eval_blocks_kernel<float, false>), grid, dim3(ev::NT), l.lds, s, a);
+  return hipGetLastError();
+}
+
+}  // namespace ddg
