@@ -225,6 +225,14 @@ struct BnApplySet {
 };
 bool bn_apply_pair_launch(const BnApplySet& a, const BnApplySet& b, size_t elems, int C, int relu, int dtype,
                           hipStream_t s, hipError_t* err);
+// Layers with more than 64 channels and few partial rows (kernels_bn_wide.hip): the elementwise
+// kernel derives its channels' values from the rows itself, as the narrow layers' consumers do, and
+// stores the vectors (forward) or dgamma, dbeta (backward). M pixels of C channels; b (optional): the
+// second minibatch. The sets' scale / shift are outputs of zrows / rrows here.
+bool bn_rows_wide_ok(int rows, int C);
+hipError_t bn_apply_wide_launch(const BnApplySet& a, const BnApplySet* b, int M, int C, int relu, int dtype, hipStream_t s);
+hipError_t bn_bwd_apply_wide_launch(const void* dy, const void* mask, const float* mscale, const float* mshift, const void* z,
+                                    const BnBwdRows& rows, void* dz, int M, int C, int dtype, hipStream_t s);
 // g = dy where the ReLU that follows was active, else 0: active means mask > 0, or
 // mask*mscale+mshift > 0 when mscale is given (the mask tensor is then the conv output the
 // activation derives from); mask == nullptr: g = dy. partial[grid][2][C] = (sum g, sum g*xhat)

@@ -82,6 +82,7 @@ struct Unit {  // convolution + batch normalisation
   bool wide_f = false, wide_d = false;   // the GEMM-class kernel runs the forward conv / the input gradient
   int wide_splits = 0;                   // > 0: the GEMM-class weight-gradient kernel, this many pixel slices
   bool small_c() const { return cout == 16 || cout == 32 || cout == 64; }
+  bool fin_in_apply = false;   // more channels, few rows: the normalise-add-ReLU kernel finalises the statistics
   int tiled_instance() const { return cin == 16 ? 1 : cin == 32 ? 2 : 3; }   // offset of a tiled kernel's profile kind
   size_t out_elems() const { return (size_t)N * P * Q * cout; }
   size_t in_elems() const { return (size_t)N * H * W * cin; }
@@ -431,6 +432,13 @@ ddg_status build_plan(ddg_module* m) {
       if (!on_load) DDG_OKAY(dev_alloc(m, &a, m->groups * b.u[ui].out_elems() * m->esz));
       b.act.push_back(a);
     }
+    // units whose batch norm an elementwise kernel applies: the block's last, its projection, and those
+    // with a materialised activation; the two that meet in one kernel go the same way
+    auto rows_ok = [](const Unit& u) { return bn_rows_wide_ok(u.fcap, u.cout); };
+    for (int ui = 0; ui + 1 < b.nmain; ++ui) b.u[ui].fin_in_apply = b.act[ui] != nullptr && rows_ok(b.u[ui]);
+    Unit& bl = b.u[b.nmain - 1];
+    bl.fin_in_apply = rows_ok(bl) && (!b.proj || rows_ok(b.u[b.nmain]));
+    if (b.proj) b.u[b.nmain].fin_in_apply = bl.fin_in_apply;
     b.y_elems = b.u[b.nmain - 1].out_elems();
     DDG_OKAY(dev_alloc(m, &b.y, m->groups * b.y_elems * m->esz));
     c = bd.cout; h = out_dim(h, bd.stride); w = out_dim(w, bd.stride);
@@ -622,13 +630,23 @@ ddg_status unit_forward(ddg_module* m, Unit& u, const void* in, Unit* src, const
       DDG_TRY(conv_launch(a, m->stream));
     }
   }
-  if (!u.small_c() && !m->eval_mode) {   // (evaluation normalises with the running estimates)
+  if (!u.small_c() && !u.fin_in_apply && !m->eval_mode) {   // (evaluation normalises with the running estimates)
     Launch L(m, PK_BN_FINALIZE);
     DDG_TRY(bn_finalize_launch(fstat, u.frows, u.cout, m->theta + u.og, m->theta + u.ob,
                                (float)((size_t)u.N * u.P * u.Q), m->d.bn_eps, u.mean + vo, u.invstd + vo, u.scale + vo,
                                u.shift + vo, m->stream));
   }
   return DDG_OK;
+}
+
+// What bn_apply_wide_launch needs for group g of a unit whose statistics that kernel finalises.
+BnApplySet wide_apply_set(ddg_module* m, Unit& u, const void* res, Unit* ru, void* y, int g) {
+  BnApplySet q{};
+  q.z = grp(u.z, u.out_elems() * m->esz, g); q.zrows = fwd_rows(m, u, g);
+  q.res = ru ? grp(ru->z, ru->out_elems() * m->esz, g) : res;
+  if (ru) q.rrows = fwd_rows(m, *ru, g);
+  q.y = y;
+  return q;
 }
 
 // y = relu(bn(u.z) [+ shortcut]) for group g; the shortcut is `res` itself or, with ru, bn(ru->z)
@@ -640,6 +658,11 @@ ddg_status apply_bn(ddg_module* m, Unit& u, const void* res, Unit* ru, void* y, 
   if (rrows) rr = fwd_rows(m, *ru, g);
   const int vo = g * u.vec_stride(), rvo = ru ? g * ru->vec_stride() : 0;
   Launch L(m, PK_BN_APPLY, ((res || ru) ? 3.0 : 2.0) * u.out_elems() * m->esz);
+  if (u.fin_in_apply && !m->eval_mode) {
+    const BnApplySet q = wide_apply_set(m, u, res, ru, y, g);
+    DDG_TRY(bn_apply_wide_launch(q, nullptr, u.N * u.P * u.Q, u.cout, 1, m->d.compute, m->stream));
+    return DDG_OK;
+  }
   const bool ev = m->eval_mode;
   DDG_TRY(bn_apply_launch(grp(u.z, u.out_elems() * m->esz, g), ev ? u.escale : u.scale + vo, ev ? u.eshift : u.shift + vo,
                           zrows ? &zr : nullptr,
@@ -706,7 +729,7 @@ ddg_status unit_forward_two(ddg_module* m, Unit& u, const void* in0, const void*
     Launch L(m, PK_CONV_FPROP, bytes, 2.0 * conv_flops(u));
     DDG_TRY(conv_launch(a, m->stream));
   }
-  if (!u.small_c()) {
+  if (!u.small_c() && !u.fin_in_apply) {
     Launch L(m, PK_BN_FINALIZE);
     DDG_TRY(bn_finalize_launch(u.fstat, u.frows, u.cout, m->theta + u.og, m->theta + u.ob,
                                (float)((size_t)u.N * u.P * u.Q), m->d.bn_eps, u.mean, u.invstd, u.scale, u.shift, m->stream,
@@ -717,6 +740,12 @@ ddg_status unit_forward_two(ddg_module* m, Unit& u, const void* in0, const void*
 
 // y = relu(bn(u.z) [+ shortcut]) for both groups in one launch (see apply_bn).
 ddg_status apply_bn_two(ddg_module* m, Unit& u, const void* res0, const void* res1, Unit* ru, void* y0, void* y1) {
+  if (u.fin_in_apply) {
+    const BnApplySet q0 = wide_apply_set(m, u, res0, ru, y0, 0), q1 = wide_apply_set(m, u, res1, ru, y1, 1);
+    Launch L(m, PK_BN_APPLY, 2.0 * ((res0 || ru) ? 3.0 : 2.0) * u.out_elems() * m->esz);
+    DDG_TRY(bn_apply_wide_launch(q0, &q1, u.N * u.P * u.Q, u.cout, 1, m->d.compute, m->stream));
+    return DDG_OK;
+  }
   const int V = m->d.compute == DDG_BF16 ? 8 : 4;
   if ((256 * V) % u.cout != 0) {   // not covered by the two-set kernel
     DDG_OKAY(apply_bn(m, u, res0, ru, y0, 0));
@@ -985,6 +1014,9 @@ ddg_status unit_backward(ddg_module* m, Unit& u, const void* dy, const void* mas
       // the apply kernel derives dgamma, dbeta and its coefficients from the rows
       Launch L(m, PK_BN_BWD_APPLY, (mask && mask != u.z ? 4.0 : 3.0) * E * m->esz);
       DDG_TRY(bn_bwd_apply_launch(dy, mask, mscale, mshift, u.z, nullptr, &br, dz_buf, E, u.cout, dt, m->stream));
+    } else if (bn_rows_wide_ok(stats_rows, u.cout)) {
+      Launch L(m, PK_BN_BWD_APPLY, (mask && mask != u.z ? 4.0 : 3.0) * E * m->esz);
+      DDG_TRY(bn_bwd_apply_wide_launch(dy, mask, mscale, mshift, u.z, br, dz_buf, u.N * u.P * u.Q, u.cout, dt, m->stream));
     } else {
       { Launch L(m, PK_BN_BWD_FINALIZE);
         DDG_TRY(bn_bwd_finalize_launch(u.bstat, stats_rows, u.cout, m->theta_bwd + u.og, u.mean, u.invstd,

@@ -1,4 +1,4 @@
-// Bandwidth-bound kernels: batch-norm finalise / apply / backward, the head
+// Bandwidth-bound kernels: batch-norm apply / backward, the head
 // (global average pool, linear, softmax cross-entropy), momentum SGD, copies.
 //
 // Tensors are NHWC, so a thread that walks the tensor with a stride that is a
@@ -11,63 +11,6 @@
 #include "ddg_stats.h"
 
 namespace ddg {
-
-// ---------------------------------------------------------------------------------
-// Finalise per-channel statistics. partial is [rows][2][C] (sum, sum of squares).
-// One workgroup per 16 channels; 16 row-slices per channel are combined in order.
-// ---------------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void bn_finalize_kernel(const float* __restrict__ partial, int rows,
-                                                          int C, const float* __restrict__ gamma,
-                                                          const float* __restrict__ beta, float count,
-                                                          float eps, float* mean, float* invstd,
-                                                          float* scale, float* shift,
-                                                          const float* __restrict__ partial_b, float* mean_b) {
-  if (blockIdx.y) {   // the second set of rows and vectors
-    partial = partial_b; mean = mean_b; invstd = mean_b + C; scale = mean_b + 2 * C; shift = mean_b + 3 * C;
-  }
-  __shared__ double r1[64][17], r2[64][17];
-  const int cl = threadIdx.x & 15, slice = threadIdx.x >> 4;
-  const int c = blockIdx.x * 16 + cl;
-  double s1 = 0.0, s2 = 0.0;
-  if (c < C)
-    for (int r = slice; r < rows; r += 64) {
-      s1 += (double)partial[((size_t)r * 2 + 0) * C + c];
-      s2 += (double)partial[((size_t)r * 2 + 1) * C + c];
-    }
-  r1[slice][cl] = s1; r2[slice][cl] = s2;
-  __syncthreads();
-  // the 64 slices in two short steps (8 x 8, each in a fixed order) instead of one chain of 64
-  double p1 = 0.0, p2 = 0.0;
-  if (slice < 8) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) { p1 += r1[slice * 8 + i][cl]; p2 += r2[slice * 8 + i][cl]; }
-  }
-  __syncthreads();
-  if (slice < 8) { r1[slice][cl] = p1; r2[slice][cl] = p2; }
-  __syncthreads();
-  if (slice == 0 && c < C) {
-    double t1 = 0.0, t2 = 0.0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) { t1 += r1[i][cl]; t2 += r2[i][cl]; }
-    const double mu = t1 / (double)count;
-    double var = t2 / (double)count - mu * mu;
-    if (var < 0.0) var = 0.0;
-    const float is = (float)(1.0 / sqrt(var + (double)eps));
-    const float sc = gamma[c] * is;
-    mean[c] = (float)mu;
-    invstd[c] = is;
-    scale[c] = sc;
-    shift[c] = beta[c] - (float)mu * sc;
-  }
-}
-
-hipError_t bn_finalize_launch(const float* partial, int rows, int C, const float* gamma,
-                              const float* beta, float count, float eps, float* mean, float* invstd,
-                              float* scale, float* shift, hipStream_t s, const float* partial_b, float* mean_b) {
-  DDG_LAUNCH(bn_finalize_kernel, dim3((C + 15) / 16, partial_b ? 2 : 1), dim3(1024), 0, s, partial, rows, C, gamma,
-                     beta, count, eps, mean, invstd, scale, shift, partial_b, mean_b);
-  return hipGetLastError();
-}
 
 // ---------------------------------------------------------------------------------
 // y = [relu](z*scale + shift + shortcut), shortcut = res*rscale+rshift, res, or nothing
@@ -128,8 +71,10 @@ static int elem_grid(size_t nvec, int C, int V, int max_blocks) {
 // its vectors). A workgroup owns 256*U consecutive vectors; every thread issues all its loads
 // first, the per-channel vectors are derived from the partial rows while those are in flight,
 // and nothing loops: with U = 4 a thread keeps 128 bytes in flight, which is what it takes to
-// approach the memory system's bandwidth with two workgroups per compute unit.
-template <typename T, int U>
+// approach the memory system's bandwidth with two workgroups per compute unit. ROWS: some vectors come
+// from partial rows; without (wider layers) the kernel carries neither that code's LDS nor its
+// registers (two 6272 x 1024 bf16 minibatches: 23.6 us with them, 20 us without).
+template <typename T, int U, bool ROWS>
 __global__ __launch_bounds__(256) void bn_apply_chunk_kernel(const T* __restrict__ z, const float* __restrict__ scale,
                                                              const float* __restrict__ shift, BnRows zrows,
                                                              const T* __restrict__ res,
@@ -149,9 +94,11 @@ __global__ __launch_bounds__(256) void bn_apply_chunk_kernel(const T* __restrict
       if (res) rq[j] = *reinterpret_cast<const vec_t*>(res + i * V);
     }
   }
-  __shared__ float s_sc[STATS_CMAX], s_sh[STATS_CMAX], s_rs[STATS_CMAX], s_rh[STATS_CMAX];
-  if (zrows.partial) { bn_fwd_from_rows_rt(zrows, C, s_sc, s_sh, blockIdx.x == 0); scale = s_sc; shift = s_sh; }
-  if (rrows.partial) { bn_fwd_from_rows_rt(rrows, C, s_rs, s_rh, blockIdx.x == 0); rscale = s_rs; rshift = s_rh; }
+  if constexpr (ROWS) {
+    __shared__ float s_sc[STATS_CMAX], s_sh[STATS_CMAX], s_rs[STATS_CMAX], s_rh[STATS_CMAX];
+    if (zrows.partial) { bn_fwd_from_rows_rt(zrows, C, s_sc, s_sh, blockIdx.x == 0); scale = s_sc; shift = s_sh; }
+    if (rrows.partial) { bn_fwd_from_rows_rt(rrows, C, s_rs, s_rh, blockIdx.x == 0); rscale = s_rs; rshift = s_rh; }
+  }
   float sc[V], sh[V], rs[V], rh[V];
 #pragma unroll
   for (int j = 0; j < V; ++j) {
@@ -182,7 +129,7 @@ __global__ __launch_bounds__(256) void bn_apply_chunk_kernel(const T* __restrict
 }
 
 // Two minibatches of one layer per launch: blockIdx.y selects the set of pointers.
-template <typename T, int U>
+template <typename T, int U, bool ROWS>
 __global__ __launch_bounds__(256) void bn_apply_pair_kernel(BnApplySet s0, BnApplySet s1, size_t nvec, int C, int relu) {
   constexpr int V = Store<T>::VEC;
   typedef typename Store<T>::vec_t vec_t;
@@ -202,9 +149,11 @@ __global__ __launch_bounds__(256) void bn_apply_pair_kernel(BnApplySet s0, BnApp
       if (res) rq[j] = *reinterpret_cast<const vec_t*>(res + i * V);
     }
   }
-  __shared__ float s_sc[STATS_CMAX], s_sh[STATS_CMAX], s_rs[STATS_CMAX], s_rh[STATS_CMAX];
-  if (q.zrows.partial) { bn_fwd_from_rows_rt(q.zrows, C, s_sc, s_sh, blockIdx.x == 0); scale = s_sc; shift = s_sh; }
-  if (q.rrows.partial) { bn_fwd_from_rows_rt(q.rrows, C, s_rs, s_rh, blockIdx.x == 0); rscale = s_rs; rshift = s_rh; }
+  if constexpr (ROWS) {
+    __shared__ float s_sc[STATS_CMAX], s_sh[STATS_CMAX], s_rs[STATS_CMAX], s_rh[STATS_CMAX];
+    if (q.zrows.partial) { bn_fwd_from_rows_rt(q.zrows, C, s_sc, s_sh, blockIdx.x == 0); scale = s_sc; shift = s_sh; }
+    if (q.rrows.partial) { bn_fwd_from_rows_rt(q.rrows, C, s_rs, s_rh, blockIdx.x == 0); rscale = s_rs; rshift = s_rh; }
+  }
   float sc[V], sh[V], rs[V], rh[V];
 #pragma unroll
   for (int j = 0; j < V; ++j) {
@@ -234,14 +183,14 @@ __global__ __launch_bounds__(256) void bn_apply_pair_kernel(BnApplySet s0, BnApp
   }
 }
 
-template <typename T>
+template <typename T, bool ROWS>
 static void bn_apply_pair_dispatch(const BnApplySet& a, const BnApplySet& b, size_t nvec, int C, int relu, hipStream_t s) {
   if (nvec >= (size_t)512 * 1024)
-    DDG_LAUNCH((bn_apply_pair_kernel<T, 4>), dim3((unsigned)((nvec + 1023) / 1024), 2), dim3(256), 0, s, a, b, nvec, C, relu);
+    DDG_LAUNCH((bn_apply_pair_kernel<T, 4, ROWS>), dim3((unsigned)((nvec + 1023) / 1024), 2), dim3(256), 0, s, a, b, nvec, C, relu);
   else if (nvec >= (size_t)512 * 512)
-    DDG_LAUNCH((bn_apply_pair_kernel<T, 2>), dim3((unsigned)((nvec + 511) / 512), 2), dim3(256), 0, s, a, b, nvec, C, relu);
+    DDG_LAUNCH((bn_apply_pair_kernel<T, 2, ROWS>), dim3((unsigned)((nvec + 511) / 512), 2), dim3(256), 0, s, a, b, nvec, C, relu);
   else
-    DDG_LAUNCH((bn_apply_pair_kernel<T, 1>), dim3((unsigned)((nvec + 255) / 256), 2), dim3(256), 0, s, a, b, nvec, C, relu);
+    DDG_LAUNCH((bn_apply_pair_kernel<T, 1, ROWS>), dim3((unsigned)((nvec + 255) / 256), 2), dim3(256), 0, s, a, b, nvec, C, relu);
 }
 
 bool bn_apply_pair_launch(const BnApplySet& a, const BnApplySet& b, size_t elems, int C, int relu, int dtype,
@@ -249,10 +198,33 @@ bool bn_apply_pair_launch(const BnApplySet& a, const BnApplySet& b, size_t elems
   const int V = dtype == BF16 ? 8 : 4;
   if ((256 * V) % C != 0) return false;
   // the same kind of work in both sets (the kernel decides per set, the shapes must agree)
-  if (dtype == BF16) bn_apply_pair_dispatch<bf16_t>(a, b, elems / 8, C, relu, s);
-  else bn_apply_pair_dispatch<float>(a, b, elems / 4, C, relu, s);
+  const bool rows = a.zrows.partial || a.rrows.partial;
+  if (dtype == BF16) {
+    if (rows) bn_apply_pair_dispatch<bf16_t, true>(a, b, elems / 8, C, relu, s);
+    else bn_apply_pair_dispatch<bf16_t, false>(a, b, elems / 8, C, relu, s);
+  } else {
+    if (rows) bn_apply_pair_dispatch<float, true>(a, b, elems / 4, C, relu, s);
+    else bn_apply_pair_dispatch<float, false>(a, b, elems / 4, C, relu, s);
+  }
   *err = hipGetLastError();
   return true;
+}
+
+template <typename T, bool ROWS>
+static void bn_apply_chunk_dispatch(const T* z, const float* scale, const float* shift, const BnRows& zr, const T* res,
+                                    const float* rscale, const float* rshift, const BnRows& rr, T* y, size_t nvec, int C,
+                                    int relu, hipStream_t s) {
+  // 4 vectors per thread once that still leaves two workgroups per compute unit
+  if (nvec >= (size_t)512 * 1024) {
+    DDG_LAUNCH((bn_apply_chunk_kernel<T, 4, ROWS>), dim3((unsigned)((nvec + 1023) / 1024)), dim3(256), 0, s, z, scale, shift, zr,
+               res, rscale, rshift, rr, y, nvec, C, relu);
+  } else if (nvec >= (size_t)512 * 512) {
+    DDG_LAUNCH((bn_apply_chunk_kernel<T, 2, ROWS>), dim3((unsigned)((nvec + 511) / 512)), dim3(256), 0, s, z, scale, shift, zr,
+               res, rscale, rshift, rr, y, nvec, C, relu);
+  } else {
+    DDG_LAUNCH((bn_apply_chunk_kernel<T, 1, ROWS>), dim3((unsigned)((nvec + 255) / 256)), dim3(256), 0, s, z, scale, shift, zr,
+               res, rscale, rshift, rr, y, nvec, C, relu);
+  }
 }
 
 template <typename T>
@@ -267,17 +239,8 @@ static void bn_apply_dispatch(const T* z, const float* scale, const float* shift
                rshift, rr, y, nvec, C, relu);
     return;
   }
-  // 4 vectors per thread once that still leaves two workgroups per compute unit
-  if (nvec >= (size_t)512 * 1024) {
-    DDG_LAUNCH((bn_apply_chunk_kernel<T, 4>), dim3((unsigned)((nvec + 1023) / 1024)), dim3(256), 0, s, z, scale, shift, zr,
-               res, rscale, rshift, rr, y, nvec, C, relu);
-  } else if (nvec >= (size_t)512 * 512) {
-    DDG_LAUNCH((bn_apply_chunk_kernel<T, 2>), dim3((unsigned)((nvec + 511) / 512)), dim3(256), 0, s, z, scale, shift, zr,
-               res, rscale, rshift, rr, y, nvec, C, relu);
-  } else {
-    DDG_LAUNCH((bn_apply_chunk_kernel<T, 1>), dim3((unsigned)((nvec + 255) / 256)), dim3(256), 0, s, z, scale, shift, zr,
-               res, rscale, rshift, rr, y, nvec, C, relu);
-  }
+  if (rows) bn_apply_chunk_dispatch<T, true>(z, scale, shift, zr, res, rscale, rshift, rr, y, nvec, C, relu, s);
+  else bn_apply_chunk_dispatch<T, false>(z, scale, shift, zr, res, rscale, rshift, rr, y, nvec, C, relu, s);
 }
 
 hipError_t bn_apply_launch(const void* z, const float* scale, const float* shift, const BnRows* zrows,
@@ -425,56 +388,7 @@ hipError_t bn_bwd_reduce_launch(const void* dy, const void* mask, const float* m
   return hipGetLastError();
 }
 
-// dbeta = sum g, dgamma = sum g*xhat; dz = A*g + B*z + C0 with
-//   A = gamma*invstd, B = -gamma*invstd^2*dgamma/m, C0 = -gamma*invstd*dbeta/m - B*mean
-__global__ __launch_bounds__(1024) void bn_bwd_finalize_kernel(const float* __restrict__ partial, int rows, int C,
-                                                              const float* __restrict__ gamma,
-                                                              const float* __restrict__ mean,
-                                                              const float* __restrict__ invstd, float count,
-                                                              float* dgamma, float* dbeta, float* coef) {
-  __shared__ double r1[64][17], r2[64][17];
-  const int cl = threadIdx.x & 15, slice = threadIdx.x >> 4;
-  const int c = blockIdx.x * 16 + cl;
-  double s1 = 0.0, s2 = 0.0;
-  if (c < C)
-    for (int r = slice; r < rows; r += 64) {
-      s1 += (double)partial[((size_t)r * 2 + 0) * C + c];
-      s2 += (double)partial[((size_t)r * 2 + 1) * C + c];
-    }
-  r1[slice][cl] = s1; r2[slice][cl] = s2;
-  __syncthreads();
-  double p1 = 0.0, p2 = 0.0;   // two short steps, as in bn_finalize_kernel
-  if (slice < 8) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) { p1 += r1[slice * 8 + i][cl]; p2 += r2[slice * 8 + i][cl]; }
-  }
-  __syncthreads();
-  if (slice < 8) { r1[slice][cl] = p1; r2[slice][cl] = p2; }
-  __syncthreads();
-  if (slice == 0 && c < C) {
-    double db = 0.0, dg = 0.0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) { db += r1[i][cl]; dg += r2[i][cl]; }
-    dbeta[c] = (float)db;
-    dgamma[c] = (float)dg;
-    const double g = gamma[c], is = invstd[c], mu = mean[c], m = count;
-    const double A = g * is;
-    const double B = -g * is * is * dg / m;
-    const double C0 = -g * is * db / m - B * mu;
-    coef[c] = (float)A;
-    coef[C + c] = (float)B;
-    coef[2 * C + c] = (float)C0;
-  }
-}
-
-hipError_t bn_bwd_finalize_launch(const float* partial, int rows, int C, const float* gamma,
-                                  const float* mean, const float* invstd, float count, float* dgamma,
-                                  float* dbeta, float* coef, hipStream_t s) {
-  DDG_LAUNCH(bn_bwd_finalize_kernel, dim3((C + 15) / 16), dim3(1024), 0, s, partial, rows, C, gamma,
-                     mean, invstd, count, dgamma, dbeta, coef);
-  return hipGetLastError();
-}
-
+// dz = A*g + B*z + C0 (coefficients from bn_bwd_finalize_launch, or derived from the rows)
 template <typename T>
 __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(const T* __restrict__ dy, const T* __restrict__ mask,
                                                            const float* __restrict__ mscale,

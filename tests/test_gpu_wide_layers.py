@@ -1,0 +1,75 @@
+"""Layers with more than 64 channels at the sizes where their kernels can go wrong, one bottleneck block
+as module 2 of 3 (delay 1) against the oracle: pixel counts below one tile, ragged, exactly at
+and just above the line up to which the elementwise kernels finalise the statistics, rows that wrap inside
+a tile, one channel group and several, a projection (two sets of statistics meet in one kernel)."""
+import numpy as np
+import pytest
+
+import workloads as wk
+
+pytestmark = pytest.mark.gpu
+
+# (dtype, batch, height = width, cin, cmid, cout, projection): what the size is there for
+CASES = [("bf16", 1, 5, 128, 128, 128, 0),       # 25 pixels: less than one tile
+         ("bf16", 3, 15, 512, 128, 512, 0),      # 675 pixels: ragged tiles that span image rows and images
+         ("bf16", 8, 32, 128, 128, 128, 0),      # 8192 pixels = 128 statistics rows: the last size finalised by the consumers
+         ("bf16", 129, 8, 128, 128, 128, 0),     # 8256 pixels = 129 rows: finalise launches
+         ("bf16", 2, 12, 256, 256, 512, 1),      # projection, several channel groups everywhere
+         ("bf16", 2, 40, 128, 256, 128, 0),      # rows longer than a tile's halo of a 14 x 14 image
+         ("f32", 3, 9, 128, 128, 256, 1)]
+
+
+@pytest.mark.parametrize("dtype,batch,hw,cin,cmid,cout,proj", CASES)
+def test_one_wide_block_matches_the_oracle(dtype, batch, hw, cin, cmid, cout, proj):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    import paper_1804_10574_amd as ddg
+    from paper_1804_10574_amd.ddg import make_desc
+    from oracle import ddg_oracle as orc
+    from tests import gpu_harness as H
+    print(f"case wide block {dtype} batch={batch} hw={hw} {cin}-{cmid}-{cout} proj={proj}", flush=True)
+    blocks = [(wk.BLOCK_BOTTLENECK, cin, cmid, cout, 1, proj)]
+    shape = (batch, cin, hw, hw)
+    mod = ddg.Module(make_desc(3, 2, batch, (cin, hw, hw), blocks, 0, ddg.DDG_BF16 if dtype == "bf16" else ddg.DDG_F32,
+                               0.9, 0.0, 1e-5))
+    oracle = orc.OracleNet(3, [blocks], batch, (cin, hw, hw), 0, 0.9, 0.0, 1e-5, "f64", k_first=2,
+                           store_bf16=(dtype == "bf16"))
+    n = oracle.param_count(2)
+    theta = (wk.normal(11, 1, n) * 0.05 + 0.02).astype(np.float32)
+    oracle.set_params(2, theta.astype(np.float64))
+    mod.set_params(theta)
+
+    class WL:
+        pass
+    wl = WL(); wl.dtype = dtype
+    # fp32: sums of up to 2304 products and 8256 pixels in another order. bf16: the two sides round at
+    # the same points; where a sum falls on the other side of a rounding boundary a value differs by 2^-9
+    # and a ReLU decision near zero flips (two ReLU layers between the error gradient and dx: a
+    # fraction f of flipped decisions moves the gradient by about sqrt(f), f < 1e-3 here)
+    tol_h, tol_g = (1e-4, 1e-3) if dtype == "f32" else (2e-2, 4e-2)
+    for t in range(3):
+        h_in = wk.normal(13, t, int(np.prod(shape))).reshape(shape)
+        delta = wk.normal(17, t, batch * cout * hw * hw).reshape(batch, cout, hw, hw)
+        hd, dd = H.to_dev_nhwc(h_in, wl), H.to_dev_nhwc(delta, wl)
+        if dtype == "bf16":
+            h_in, delta = H.from_dev_nhwc(hd), H.from_dev_nhwc(dd)
+        h_out = torch.empty((batch, hw, hw, cout), dtype=H.tdtype(wl), device="cuda")
+        d_out = torch.zeros_like(hd)
+        torch.cuda.synchronize()
+        mod.forward(t, hd, h_out)
+        did = mod.backward_delayed(t, delta_in=dd, delta_out=d_out)
+        mod.sync()
+        ref_h = oracle.forward(2, t, h_in)
+        ref_did, ref_dout, _ = oracle.backward_delayed(2, t, delta, None, in_shape=shape)
+        assert did == bool(ref_did) == (t >= 1)
+        e_h = H.rel_err(H.from_dev_nhwc(h_out), ref_h)
+        print(f"  t={t} h {e_h:.2e}", flush=True)
+        assert e_h <= tol_h
+        if did:
+            e_d, e_g = H.rel_err(H.from_dev_nhwc(d_out), ref_dout), H.rel_err(mod.get_grad(), oracle.get_grad(2))
+            print(f"  t={t} dx {e_d:.2e} grad {e_g:.2e}", flush=True)
+            assert e_d <= tol_g and e_g <= tol_g
+        mod.update(t, 0.0)
+        oracle.update(2, 0.0)
+    mod.close()
