@@ -180,15 +180,15 @@ int wgrad_tiled_f32_rows(int N, int H, int W, int Cin, int Cout, int R, int stri
 // GEMM-class kernel for wide bf16 layers (1x1 / 3x3, stride 1, contraction channels a power of
 // two >= 64, output channels a multiple of 128): forward, or input gradient with an operand
 // packed with mirrored taps. in [N*H*W][IC], out [N*H*W][OC], wpack as for conv_launch;
-// stat_partial (optional): [conv_wide_rows(M)][2][OC] sums / sums of squares of the stored
+// stat_partial (optional): [conv_wide_rows()][2][OC] sums / sums of squares of the stored
 // values; add_g / add_mask as in ConvArgs.
 bool conv_wide_ok(int IC, int OC, int R, int stride, int dtype);
-int conv_wide_rows(int M);
+int conv_wide_rows(int M, int W, int IC, int R);   // statistics rows of a launch (one per pixel tile)
 // scale/shift (optional, forward only): the conv input is relu(in*scale + shift) per input
 // channel, applied while staging.
 // second (optional, forward only): a second minibatch in the same launch, same weights.
 // below (optional, input gradient only; mode 2): the epilogue forms the BN-backward sums of the
-// layer below into below->partial, conv_wide_rows(M) rows (see ConvStat).
+// layer below into below->partial, conv_wide_rows() rows (see ConvStat).
 struct ConvWideSecond { const void* in; void* out; float* stat_partial; const float* scale; const float* shift; };
 hipError_t conv_wide_launch(const void* in, const void* wpack, void* out, float* stat_partial, const void* add_g,
                             const void* add_mask, int N, int H, int W, int IC, int OC, int R, hipStream_t s,

@@ -24,32 +24,10 @@
 // meet in an fp32 LDS tile, from which stores (and the optional masked shortcut-gradient term)
 // are 16-byte accesses along the channels; the batch-norm statistics of the stored values go
 // to one partial row per 64-pixel tile.
-#include "ddg_device.h"
-#include "ddg_kernels.h"
+#include "ddg_conv_wide.h"
 #include <cstdlib>
 
 namespace ddg {
-
-struct ConvWideArgs {
-  const bf16_t* in;        // [M][IC]
-  const bf16_t* wpack;     // [k-step][OC/16][64][8], k = tap*IC + channel
-  bf16_t* out;             // [M][OC]
-  float* stat_partial;     // [gridDim.x][2][OC] or null
-  const bf16_t* add_g;     // optional: out += add_g (where add_mask > 0, if given)
-  const bf16_t* add_mask;
-  const float* scale;      // optional (XFORM kernels): the conv input is relu(in*scale + shift), per input channel
-  const float* shift;
-  // STATS = 2 (input gradient): the outputs are an error gradient v; with the ReLU mask of the
-  // layer below applied, g = (bmask*bmscale + bmshift > 0) ? v : 0 (bmask null: g = v), the rows
-  // hold sum g and sum g*xhat of that layer's BN (xhat = (bz - bmean)*binvstd): its
-  // bn_bwd_reduce pass comes for free. stat_partial receives the rows, and the stored output is
-  // g (the mask is applied here, once; readers take the gradient as already masked).
-  const bf16_t* bmask; const float* bmscale; const float* bmshift;
-  const bf16_t* bz; const float* bmean; const float* binvstd;
-  // optional second minibatch (blockIdx.z = 1; forward only): same weights, its own tensors
-  const bf16_t* in_b; bf16_t* out_b; float* stat_partial_b; const float* scale_b; const float* shift_b;
-  int M, H, W, HW, IC, OC, R;
-};
 
 namespace wide {
 constexpr int BM = 64, BN = 128;
@@ -390,7 +368,7 @@ bool conv_wide_ok(int IC, int OC, int R, int stride, int dtype) {
   if (IC < 64 || (IC & (IC - 1)) != 0) return false;      // power of two: k = tap*IC + channel in the packed operand
   return OC % wide::BN == 0;
 }
-int conv_wide_rows(int M) { return (M + wide::BM - 1) / wide::BM; }
+int conv_wide_rows(int M, int W, int IC, int R) { return conv_halo_ok(IC, W, R) ? conv_halo_rows(M) : (M + wide::BM - 1) / wide::BM; }
 
 hipError_t conv_wide_launch(const void* in, const void* wpack, void* out, float* stat_partial, const void* add_g,
                             const void* add_mask, int N, int H, int W, int IC, int OC, int R, hipStream_t s,
@@ -416,9 +394,10 @@ hipError_t conv_wide_launch(const void* in, const void* wpack, void* out, float*
     stats = 2;
   }
   a.M = (int)M; a.H = H; a.W = W; a.HW = H * W; a.IC = IC; a.OC = OC; a.R = R;
-  const dim3 grid(conv_wide_rows((int)M), OC / wide::BN, second ? 2 : 1);
   const bool xf = scale != nullptr;
   if (xf && (add_g || IC > 2048)) return hipErrorInvalidValue;   // forward only; the table lives in LDS
+  if (conv_halo_ok(IC, W, R)) return conv_halo_launch(a, second ? 2 : 1, stats, xf, s);
+  const dim3 grid(conv_wide_rows((int)M, W, IC, R), OC / wide::BN, second ? 2 : 1);
   // few tiles (one workgroup per compute unit at most): the long chunk; else two workgroups per unit
   const bool long_chunk = IC >= 128 && grid.x * grid.y * grid.z <= 256;
   if (R == 3)
