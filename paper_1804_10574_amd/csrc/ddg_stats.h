@@ -43,8 +43,8 @@ __device__ __forceinline__ void reduce_stat_rows(const float* __restrict__ parti
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const float k = r0 + u * NSL < rows ? 1.f : 0.f;
-      acc.x += k * v[u].x; acc.y += k * v[u].y; acc.z += k * v[u].z; acc.w += k * v[u].w;
+      const bool in = r0 + u * NSL < rows;
+      acc.x += in ? v[u].x : 0.f; acc.y += in ? v[u].y : 0.f; acc.z += in ? v[u].z : 0.f; acc.w += in ? v[u].w : 0.f;
     }
   }
   sh[tid] = acc;

@@ -311,49 +311,24 @@ __global__ __launch_bounds__(256) void bn_bwd_reduce_kernel(const T* __restrict_
       }
     }
   }
-  // Threads with equal (threadIdx.x*V) % C hold the same channels. Up to 64 channel vectors: the
-  // lanes of a wave that share one are added by a butterfly, the four waves through LDS (a chain of
-  // 6 + 4 sums; the loop below, 128 sums long for 16 channels in two threads, was most of this
-  // kernel: 11.3 -> 5.2 us at 37 x 32 x 32 x 16). More: at most two threads hold the same channels.
+  // Threads with equal (threadIdx.x*V) % C hold the same channels; their sums are added in thread
+  // order, one thread per sum. (Two threads that added all sums of 128 rows were most of this kernel for
+  // 16 channels: 11.3 -> 7.2 us at 37 x 32 x 32 x 16 in a running
+  // pipeline.)
   const int per = C / V < 256 ? C / V : 256;  // distinct channel vectors among the block's threads
-  if (per <= 64) {
-    __shared__ float wred[4][2][64 * V];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int o = per; o < 64; o <<= 1) {
-#pragma unroll
-      for (int j = 0; j < V; ++j) { s1[j] += __shfl_xor(s1[j], o, 64); s2[j] += __shfl_xor(s2[j], o, 64); }
-    }
-    if (lane < per) {
-#pragma unroll
-      for (int j = 0; j < V; ++j) { wred[wave][0][lane * V + j] = s1[j]; wred[wave][1][lane * V + j] = s2[j]; }
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < 2 * C; e += 256) {
-      const int which = e / C, c = e - which * C;
-      partial[((size_t)blockIdx.x * 2 + which) * C + c] =
-          (wred[0][which][c] + wred[1][which][c]) + (wred[2][which][c] + wred[3][which][c]);
-    }
-    return;
-  }
   __shared__ float red[2][256][V + 1];
 #pragma unroll
   for (int j = 0; j < V; ++j) { red[0][threadIdx.x][j] = s1[j]; red[1][threadIdx.x][j] = s2[j]; }
   __syncthreads();
-  if ((int)threadIdx.x < per) {
-    float t1[V], t2[V];
-#pragma unroll
-    for (int j = 0; j < V; ++j) { t1[j] = 0.f; t2[j] = 0.f; }
-    for (int t = threadIdx.x; t < 256; t += per) {
-#pragma unroll
-      for (int j = 0; j < V; ++j) { t1[j] += red[0][t][j]; t2[j] += red[1][t][j]; }
-    }
-    // block b, thread t covers channels ((b*256+t)*V) % C
-    const int cb = (int)((((size_t)blockIdx.x * 256 + threadIdx.x) * V) % C);
-#pragma unroll
-    for (int j = 0; j < V; ++j) {
-      partial[((size_t)blockIdx.x * 2 + 0) * C + cb + j] = t1[j];
-      partial[((size_t)blockIdx.x * 2 + 1) * C + cb + j] = t2[j];
-    }
+  // sum e of 2 * per * V: (which, channel vector, element); block b, thread t covers channels ((b*256+t)*V) % C
+  const int nper = per * V, rows = 256 / per;
+  for (int e = threadIdx.x; e < 2 * nper; e += 256) {
+    const int which = e / nper, k = e - which * nper, t0 = k / V, j = k - t0 * V;
+    float t = 0.f;
+#pragma unroll 16
+    for (int r = 0; r < rows; ++r) t += red[which][r * per + t0][j];
+    const int cb = (int)((((size_t)blockIdx.x * 256 + t0) * V) % C);
+    partial[((size_t)blockIdx.x * 2 + which) * C + cb + j] = t;
   }
 }
 
@@ -559,31 +534,23 @@ hipError_t eval_vectors_launch(const RunDesc* dev_descs, int n, int max_c, hipSt
   return hipGetLastError();
 }
 
-// Sum / maximum over a workgroup of NW waves in a fixed order; every thread gets the result. sh: NW
+// Sum / maximum over a workgroup of four waves in a fixed order; every thread gets the result. sh: 4
 // floats of LDS that no other step uses between two barriers.
-template <int NW>
 __device__ __forceinline__ float block_sum(float v, float* sh) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   __syncthreads();
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
-  float t = sh[0];
-#pragma unroll
-  for (int w = 1; w < NW; ++w) t += sh[w];
-  return t;
+  return ((sh[0] + sh[1]) + sh[2]) + sh[3];
 }
-template <int NW>
 __device__ __forceinline__ float block_max(float v, float* sh) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
   __syncthreads();
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
-  float t = sh[0];
-#pragma unroll
-  for (int w = 1; w < NW; ++w) t = fmaxf(t, sh[w]);
-  return t;
+  return fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]));
 }
 
 // mean of the per-sample losses (evaluation; training gets it from head_wgrad_kernel)
@@ -591,19 +558,21 @@ __global__ __launch_bounds__(256) void loss_mean_kernel(const float* __restrict_
   __shared__ float sh[4];
   float l = 0.f;
   for (int n = threadIdx.x; n < N; n += 256) l += loss_n[n];
-  l = block_sum<4>(l, sh);
+  l = block_sum(l, sh);
   if (threadIdx.x == 0) *out = l / (float)N;
 }
 
 // ---------------------------------------------------------------------------------
 // Head. Small: N x C x classes is a few hundred thousand operations, so what it costs is the length
-// of its chains of loads and sums. Every sum is spread over the workgroup with as many loads in
-// flight as there are terms per thread (16 at most), and runs in a fixed order.
+// of its chains of loads and sums. Operands are brought to LDS in one round trip (STAGED: wherever they fit),
+// and the sums run there in plain ascending order.
 // ---------------------------------------------------------------------------------
+constexpr size_t HEAD_LDS_MAX = (size_t)96 << 10;
+
 // Per sample (one workgroup of 256 threads): global average pool, logits, stable softmax, loss,
 // dlogits = (p - onehot)/N, and dh = dlogits * fcw / HW broadcast over the pixels.
-// Dynamic LDS: 2*C + 2*classes + 256 floats.
-template <typename T>
+// Dynamic LDS: 2*C + 2*classes + 256 floats, and with STAGED the classifier, rows of C + 1 floats.
+template <typename T, bool STAGED>
 __global__ __launch_bounds__(256) void head_sample_kernel(const T* __restrict__ h, const float* __restrict__ fcw,
                                                           const float* __restrict__ fcb,
                                                           const int32_t* __restrict__ labels,
@@ -617,7 +586,14 @@ __global__ __launch_bounds__(256) void head_sample_kernel(const T* __restrict__ 
   float* s_lg = sm + 2 * C;         // [classes]
   float* s_dl = s_lg + classes;     // [classes]
   float* s_red = s_dl + classes;    // [256]
+  float* s_fc = s_red + 256;        // STAGED: [classes][C + 1]
   const int n = blockIdx.x, tid = threadIdx.x;
+  if (STAGED) {
+    const int total = classes * C;
+#pragma unroll 8
+    for (int e = tid; e < total; e += 256) s_fc[e + e / C] = fcw[e];
+  }
+  auto weight = [&](int j, int c) __attribute__((always_inline)) { return STAGED ? s_fc[j * (C + 1) + c] : fcw[(size_t)j * C + c]; };
   // pool: thread (channel lane cl, pixel class g); pixel classes are added in order afterwards
   const int cpt = C < 256 ? C : 256, groups = 256 / cpt;
   const int cl = tid % cpt, g = tid / cpt;
@@ -640,29 +616,28 @@ __global__ __launch_bounds__(256) void head_sample_kernel(const T* __restrict__ 
     }
     __syncthreads();
   }
-  // logits (C is a multiple of 4 and so is every offset in the parameter vector: 16-byte loads)
+  // logits
   for (int j = tid; j < classes; j += 256) {
     float a = fcb[j];
-    const float4* w = reinterpret_cast<const float4*>(fcw + (size_t)j * C);
 #pragma unroll 16
-    for (int c = 0; c < C / 4; ++c) {
-      const float4 q = w[c];
-      a += q.x * s_pool[c * 4]; a += q.y * s_pool[c * 4 + 1]; a += q.z * s_pool[c * 4 + 2]; a += q.w * s_pool[c * 4 + 3];
-    }
+    for (int c = 0; c < C; ++c) a += weight(j, c) * s_pool[c];
     s_lg[j] = a;
     if (logits_out) logits_out[(size_t)n * classes + j] = a;
   }
   __syncthreads();
   float mx = s_lg[0];
   for (int j = tid; j < classes; j += 256) mx = fmaxf(mx, s_lg[j]);
-  mx = block_max<4>(mx, s_w);
+  mx = block_max(mx, s_w);
+  for (int j = tid; j < classes; j += 256) s_dl[j] = expf(s_lg[j] - mx);
+  __syncthreads();
   float den = 0.f;
-  for (int j = tid; j < classes; j += 256) { const float e = expf(s_lg[j] - mx); s_dl[j] = e; den += e; }
-  den = block_sum<4>(den, s_w);
+#pragma unroll 16
+  for (int j = 0; j < classes; ++j) den += s_dl[j];
   // a label outside [0, classes) has no class to point at: that sample's loss (and with it the
   // mean loss) is NaN, so the caller sees it, and nothing outside the logits is read
   const int y = labels[n];
   const bool y_ok = (unsigned)y < (unsigned)classes;
+  __syncthreads();
   for (int j = tid; j < classes; j += 256) {
     const float d = (s_dl[j] / den - (j == y ? 1.f : 0.f)) / (float)N;
     s_dl[j] = d;
@@ -671,23 +646,13 @@ __global__ __launch_bounds__(256) void head_sample_kernel(const T* __restrict__ 
   if (tid == 0) loss_n[n] = y_ok ? -(s_lg[y] - mx - logf(den)) : __builtin_nanf("");
   if (!dh) return;
   __syncthreads();
-  // thread (channel lane cl, class of classes g), as the pool above
-  for (int c0 = 0; c0 < C; c0 += cpt) {
-    const int c = c0 + cl;
+  for (int c = tid; c < C; c += 256) {
     float a = 0.f;
-    if (g < groups && c < C) {
 #pragma unroll 16
-      for (int j = g; j < classes; j += groups) a += s_dl[j] * fcw[(size_t)j * C + c];
-    }
-    s_red[tid] = a;
-    __syncthreads();
-    if (g == 0 && c < C) {
-      float t = 0.f;
-      for (int q = 0; q < groups; ++q) t += s_red[q * cpt + cl];
-      s_dh[c] = Store<T>::round(t / (float)HW);
-    }
-    __syncthreads();
+    for (int j = 0; j < classes; ++j) a += s_dl[j] * weight(j, c);
+    s_dh[c] = Store<T>::round(a / (float)HW);
   }
+  __syncthreads();
   // broadcast over the pixels, 4 channels per store
   const int c4n = C / 4;
   for (int e = tid; e < HW * c4n; e += 256) {
@@ -697,66 +662,108 @@ __global__ __launch_bounds__(256) void head_sample_kernel(const T* __restrict__ 
 }
 
 // One workgroup of 1024 threads per class j: dfcw[j][:] = sum_n dlogits[n][j] * pooled[n][:],
-// dfcb[j]; thread (channel lane, sample class g) adds samples g, g+groups, ... in order (16 loads
-// in flight: one round trip at batch 256 and 64 channels), then the classes are added in order.
-// Workgroup 0 also writes the mean loss.
+// dfcb[j]; thread (channel lane, sample class g) of the first 256 adds samples g, g+groups, ... in order,
+// then the classes are added in order. Workgroup 0 also writes the mean loss. STAGED: dynamic LDS
+// holds [N][C] of pooled and [N] of dlogits.
+template <bool STAGED>
 __global__ __launch_bounds__(1024) void head_wgrad_kernel(const float* __restrict__ pooled,
                                                           const float* __restrict__ dlogits,
                                                           const float* __restrict__ loss_n, float* __restrict__ dfcw,
                                                           float* __restrict__ dfcb, float* loss_out, int N, int C,
                                                           int classes) {
-  __shared__ float s_red[1024];
-  __shared__ float s_w[16];
+  extern __shared__ float sm[];
+  __shared__ float s_red[256], s_b[256], s_l[256];
   const int j = blockIdx.x, tid = threadIdx.x;
-  const int cpt = C < 1024 ? C : 1024, groups = 1024 / cpt;
+  float* s_pool = sm;
+  float* s_dl = sm + (size_t)N * C;
+  if (STAGED) {
+    for (int n = tid; n < N; n += 1024) s_dl[n] = dlogits[(size_t)n * classes + j];
+    const float4* p4 = reinterpret_cast<const float4*>(pooled);
+#pragma unroll 8
+    for (int e = tid; e < N * C / 4; e += 1024) reinterpret_cast<float4*>(s_pool)[e] = p4[e];
+  }
+  // 256 partial sums over samples of the bias gradient (and the mean loss)
+  if (tid < 256) {
+    float a = 0.f, l = 0.f;
+    for (int n = tid; n < N; n += 256) {
+      a += dlogits[(size_t)n * classes + j];
+      if (j == 0) l += loss_n[n];
+    }
+    s_b[tid] = a; s_l[tid] = l;
+  }
+  __syncthreads();
+  const int cpt = C < 256 ? C : 256, groups = 256 / cpt;
   const int cl = tid % cpt, g = tid / cpt;
   for (int c0 = 0; c0 < C; c0 += cpt) {
     const int c = c0 + cl;
     float a = 0.f;
-    if (g < groups && c < C) {
+    if (tid < 256 && g < groups && c < C) {
 #pragma unroll 16
-      for (int n = g; n < N; n += groups) a += dlogits[(size_t)n * classes + j] * pooled[(size_t)n * C + c];
+      for (int n = g; n < N; n += groups)
+        a += (STAGED ? s_dl[n] : dlogits[(size_t)n * classes + j]) * (STAGED ? s_pool[n * C + c] : pooled[(size_t)n * C + c]);
     }
-    s_red[tid] = a;
+    if (tid < 256) s_red[tid] = a;
     __syncthreads();
-    if (g == 0 && c < C) {
+    if (tid < 256 && g == 0 && c < C) {
       float t = 0.f;
-#pragma unroll 16
       for (int q = 0; q < groups; ++q) t += s_red[q * cpt + cl];
       dfcw[(size_t)j * C + c] = t;
     }
     __syncthreads();
   }
-  // bias gradient (and the mean loss)
-  float a = 0.f, l = 0.f;
-  for (int n = tid; n < N; n += 1024) {
-    a += dlogits[(size_t)n * classes + j];
-    if (j == 0) l += loss_n[n];
+  // added in order by one thread each, beside the sums above's last stores
+  const int terms = N < 256 ? N : 256;
+  if (tid == 256) {
+    float t = 0.f;
+#pragma unroll 16
+    for (int q = 0; q < terms; ++q) t += s_b[q];
+    dfcb[j] = t;
   }
-  a = block_sum<16>(a, s_w);
-  if (tid == 0) dfcb[j] = a;
-  if (j == 0 && loss_out) {
-    l = block_sum<16>(l, s_w);
-    if (tid == 0) *loss_out = l / (float)N;
+  if (tid == 320 && j == 0 && loss_out) {
+    float t = 0.f;
+#pragma unroll 16
+    for (int q = 0; q < terms; ++q) t += s_l[q];
+    *loss_out = t / (float)N;
   }
+}
+
+template <bool STAGED>
+static hipError_t head_wgrad_run(const HeadArgs& a, size_t lds, hipStream_t s) {
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&head_wgrad_kernel<STAGED>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)HEAD_LDS_MAX);
+  if (attr != hipSuccess) return attr;
+  DDG_LAUNCH(head_wgrad_kernel<STAGED>, dim3(a.classes), dim3(1024), lds, s, a.pooled, a.dlogits, a.loss_n, a.dfcw, a.dfcb,
+             a.loss_out, a.N, a.C, a.classes);
+  return hipGetLastError();
+}
+
+template <typename T, bool STAGED>
+static hipError_t head_sample_run(const HeadArgs& a, size_t lds, hipStream_t s) {
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&head_sample_kernel<T, STAGED>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)HEAD_LDS_MAX);
+  if (attr != hipSuccess) return attr;
+  DDG_LAUNCH((head_sample_kernel<T, STAGED>), dim3(a.N), dim3(256), lds, s, (const T*)a.h, a.fcw, a.fcb, a.labels,
+             a.pooled, a.dlogits, a.loss_n, (T*)a.dh, a.N, a.HW, a.C, a.classes, a.logits_out);
+  return hipGetLastError();
+}
+
+template <typename T>
+static hipError_t head_sample_any(const HeadArgs& a, hipStream_t s) {
+  const size_t lds = (size_t)(2 * a.C + 2 * a.classes + 256) * sizeof(float);
+  const size_t with_fc = lds + (size_t)a.classes * (a.C + 1) * sizeof(float);
+  return with_fc <= HEAD_LDS_MAX ? head_sample_run<T, true>(a, with_fc, s) : head_sample_run<T, false>(a, lds, s);
 }
 
 hipError_t head_launch(const HeadArgs& a, hipStream_t s) {
   if (a.C % 4 != 0) return hipErrorInvalidValue;
-  const size_t lds = (size_t)(2 * a.C + 2 * a.classes + 256) * sizeof(float);
-  if (a.dtype == BF16)
-    DDG_LAUNCH(head_sample_kernel<bf16_t>, dim3(a.N), dim3(256), lds, s, (const bf16_t*)a.h, a.fcw, a.fcb, a.labels,
-               a.pooled, a.dlogits, a.loss_n, (bf16_t*)a.dh, a.N, a.HW, a.C, a.classes, a.logits_out);
-  else
-    DDG_LAUNCH(head_sample_kernel<float>, dim3(a.N), dim3(256), lds, s, (const float*)a.h, a.fcw, a.fcb, a.labels,
-               a.pooled, a.dlogits, a.loss_n, (float*)a.dh, a.N, a.HW, a.C, a.classes, a.logits_out);
+  hipError_t e = a.dtype == BF16 ? head_sample_any<bf16_t>(a, s) : head_sample_any<float>(a, s);
+  if (e != hipSuccess) return e;
   if (!a.dfcw) {   // evaluation: no gradients; the mean loss if asked for
     if (a.loss_out) DDG_LAUNCH(loss_mean_kernel, dim3(1), dim3(256), 0, s, a.loss_n, a.N, a.loss_out);
     return hipGetLastError();
   }
-  DDG_LAUNCH(head_wgrad_kernel, dim3(a.classes), dim3(1024), 0, s, a.pooled, a.dlogits, a.loss_n, a.dfcw, a.dfcb,
-             a.loss_out, a.N, a.C, a.classes);
-  return hipGetLastError();
+  const size_t lds = (size_t)a.N * (a.C + 1) * sizeof(float);
+  return lds + 3 * 256 * sizeof(float) <= HEAD_LDS_MAX ? head_wgrad_run<true>(a, lds, s) : head_wgrad_run<false>(a, 0, s);
 }
 
 // ---------------------------------------------------------------------------------
