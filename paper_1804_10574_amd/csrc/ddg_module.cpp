@@ -5,6 +5,7 @@
 #include "../../include/ddg.h"
 #include "ddg_kernels.h"
 #include "ddg_internal.h"
+#include "ddg_readback.h"
 
 #include <hip/hip_runtime_api.h>
 
@@ -117,6 +118,7 @@ struct ddg_module {
   hipStream_t bstream = nullptr;   // backward / update stream (desc.stream)
   hipStream_t fstream = nullptr;   // forward stream (== bstream unless two_streams)
   bool two_streams = false;
+  Readback readback;               // device -> host copies of weights, optimizer state, stored inputs
   bool external_sync = false;      // a pipeline orders the two streams; the module records/waits nothing
   hipEvent_t ev_fwd[2] = {nullptr, nullptr};   // forward(t) done, by parity of t
   hipEvent_t ev_upd = nullptr;                 // last update (or parameter load) done
@@ -1375,6 +1377,7 @@ ddg_status ddg_module_destroy(ddg_module* m) {
     if (m->ev_upd) (void)hipEventDestroy(m->ev_upd);
     for (auto& e : m->evs) { (void)hipEventDestroy(e.a); (void)hipEventDestroy(e.b); }
     for (void* p : m->allocs) (void)hipFree(p);
+    m->readback.release();
   }
   delete m;
   return DDG_OK;
@@ -1477,7 +1480,7 @@ static ddg_status get_vec(ddg_module* m, const float* dev, float* host_dst) {
   if (!host_dst) return fail(DDG_ERR_INVALID_ARG, "host_dst is null");
   if (m->d.dry_run) { memset(host_dst, 0, m->nparams * sizeof(float)); return DDG_OK; }
   DDG_OKAY(sync_streams(m));
-  DDG_TRY(hipMemcpy(host_dst, dev, m->nparams * sizeof(float), hipMemcpyDeviceToHost));
+  DDG_TRY(m->readback.copy(host_dst, dev, m->nparams * sizeof(float), m->bstream));
   return DDG_OK;
 }
 ddg_status ddg_get_params(ddg_module* m, float* host_dst) { return get_vec(m, m ? m->theta : nullptr, host_dst); }
@@ -1574,7 +1577,7 @@ ddg_status ddg_get_ring_slot(ddg_module* m, int slot, void* host_dst) {
   DDG_OKAY(ring_slot_ok(m, slot, host_dst));
   if (m->d.dry_run) return DDG_OK;
   DDG_OKAY(sync_streams(m));
-  DDG_TRY(hipMemcpy(host_dst, m->ring[slot], m->in_elems * m->esz, hipMemcpyDeviceToHost));
+  DDG_TRY(m->readback.copy(host_dst, m->ring[slot], m->in_elems * m->esz, m->bstream));
   return DDG_OK;
 }
 

@@ -1,0 +1,114 @@
+// Device -> host copies of a module's state (weights, velocity, gradients, stored inputs).
+//
+// A large copy into fresh pageable memory moves about 10 GB/s here: the runtime stages it in 1 MiB pieces, and its
+// one thread takes the page faults of the destination between two pieces. From RING_MIN on the pieces land in a
+// small ring of pinned slots instead while threads of this process copy earlier pieces out: 102 MB (23
+// bottleneck blocks) 9.8 -> 3.6 ms, 27 MB 1.6 -> 1.0 ms; at 1.7 MB the two are even (0.10 ms), below the
+// runtime's way is shorter (0.04 MB: 22 against 38 us), and it needs no pinned memory.
+#include "ddg_readback.h"
+
+#include <algorithm>
+#include <atomic>
+#include <cstring>
+#include <system_error>
+#include <thread>
+#include <vector>
+
+namespace ddg {
+
+namespace {
+
+constexpr size_t PIECE = (size_t)1 << 20, RING_MIN = (size_t)8 << 20;
+constexpr int SLOTS = Readback::SLOTS;
+constexpr int WORKERS = 7;            // beside the calling thread
+
+struct Job {
+  char* dst; const char* ring; size_t bytes, pieces;
+  std::atomic<size_t> landed{0}, ticket{0}, copied{0};
+  std::atomic<bool> stop{false};
+  std::vector<std::atomic<char>> done;
+  Job(char* d, const char* r, size_t b, size_t n) : dst(d), ring(r), bytes(b), pieces(n), done(n) {
+    for (auto& x : done) x.store(0, std::memory_order_relaxed);
+  }
+  size_t len(size_t i) const { return std::min(PIECE, bytes - i * PIECE); }
+  void copy_out(size_t i) {
+    memcpy(dst + i * PIECE, ring + (i % SLOTS) * PIECE, len(i));
+    done[i].store(1, std::memory_order_release);
+    copied.fetch_add(1, std::memory_order_release);
+  }
+  void work() {   // until every piece has an owner, or stop
+    for (;;) {
+      const size_t i = ticket.fetch_add(1, std::memory_order_relaxed);
+      if (i >= pieces) return;
+      while (landed.load(std::memory_order_acquire) <= i) {
+        if (stop.load(std::memory_order_relaxed)) return;
+        std::this_thread::yield();
+      }
+      copy_out(i);
+    }
+  }
+};
+
+// The copy through the ring. With workers, they copy every piece out and the caller only feeds them.
+hipError_t through_ring(Readback& rb, char* dst, const char* src, size_t bytes, hipStream_t s) {
+  const size_t pieces = (bytes + PIECE - 1) / PIECE;
+  Job job(dst, (const char*)rb.ring, bytes, pieces);
+  std::vector<std::thread> team;
+  const unsigned hw = std::thread::hardware_concurrency();
+  const size_t want = std::min<size_t>(WORKERS, hw > 1 ? hw - 1 : 0);
+  team.reserve(want);
+  try {
+    for (size_t i = 0; i < want; ++i) team.emplace_back([&job] { job.work(); });
+  } catch (const std::system_error&) {}   // fewer threads, or none: the caller copies
+  hipError_t err = hipSuccess;
+  size_t sent = 0, landed = 0;
+  while (landed < pieces && err == hipSuccess) {
+    while (sent < pieces && err == hipSuccess &&
+           (sent < (size_t)SLOTS || job.done[sent - SLOTS].load(std::memory_order_acquire))) {
+      err = hipMemcpyAsync((char*)rb.ring + (sent % SLOTS) * PIECE, src + sent * PIECE, job.len(sent), hipMemcpyDeviceToHost, s);
+      if (err == hipSuccess) err = hipEventRecord(rb.ev[sent % SLOTS], s);
+      if (err == hipSuccess) ++sent;
+    }
+    if (err != hipSuccess) break;
+    if (landed == sent) { std::this_thread::yield(); continue; }   // the ring is full of pieces being copied out
+    err = hipEventSynchronize(rb.ev[landed % SLOTS]);
+    if (err != hipSuccess) break;
+    if (team.empty()) job.copy_out(landed);
+    job.landed.store(++landed, std::memory_order_release);
+  }
+  if (err != hipSuccess) { job.stop.store(true); (void)hipStreamSynchronize(s); }
+  for (auto& t : team) t.join();
+  return err;
+}
+
+}  // namespace
+
+hipError_t Readback::copy(void* host, const void* dev, size_t bytes, hipStream_t s) {
+  if (bytes < RING_MIN) return hipMemcpy(host, dev, bytes, hipMemcpyDeviceToHost);
+  std::lock_guard<std::mutex> hold(mu);
+  if (!ring) {
+    void* p = nullptr;
+    if (hipHostMalloc(&p, SLOTS * PIECE, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      return hipMemcpy(host, dev, bytes, hipMemcpyDeviceToHost);
+    }
+    for (int i = 0; i < SLOTS; ++i) {
+      const hipError_t e = hipEventCreateWithFlags(&ev[i], hipEventDisableTiming);
+      if (e == hipSuccess) continue;
+      while (i-- > 0) (void)hipEventDestroy(ev[i]);
+      (void)hipHostFree(p);
+      return e;
+    }
+    ring = p;
+  }
+  return through_ring(*this, (char*)host, (const char*)dev, bytes, s);
+}
+
+void Readback::release() {
+  if (!ring) return;
+  for (int i = 0; i < SLOTS; ++i) (void)hipEventDestroy(ev[i]);
+  (void)hipHostFree(ring);
+  ring = nullptr;
+}
+
+}  // namespace ddg
