@@ -193,6 +193,157 @@ __global__ __launch_bounds__(256) void conv_mfma_kernel(ConvArgs a) {
   }
 }
 
+// Input gradient of a stride-2 convolution (the first block of a stage and its projection). A pixel of the
+// input meets only the taps of its parity: 1, 2, 2 or 4 of the nine (1 or none of a 1x1 kernel's one),
+// and the kernel above multiplied zeros for the rest and waited for a gather per tap. Here a wave owns
+// 16*MB pixels of ONE parity class: its taps are known at compile time, its source pixels are
+// neighbours in memory, and a tap's fragments are requested while the tap before is multiplied. The sums
+// keep their order (a skipped tap added zero), so results are bit-identical.
+// Bound by memory and latency. 3x3 and 1x1 launch together, in a running pipeline: fp32 batch 128, 32 -> 16 channels
+// 56 -> 26 us, 64 -> 32 channels 36 -> 18 us.
+// CPT: k-steps per tap (contraction channels / KSTEP). PR, PC: parity of the pixel's row and column.
+template <typename T, int MB, int NB, int CPT, int R, int PR, int PC>
+__device__ __forceinline__ void dgrad_s2_tile(const ConvArgs& a, int tile, int cb0) {
+  using M_ = Mma<T>;
+  using S_ = Store<T>;
+  typedef typename M_::frag_t frag_t;
+  constexpr int KV = M_::KV;
+  constexpr int NR = R == 3 ? 1 + PR : 1 - PR, NS = R == 3 ? 1 + PC : 1 - PC, NT = NR * NS;   // taps of this class
+  const int lane = threadIdx.x & 63, l16 = lane & 15, lg = lane >> 4;
+  const int OCB = a.OC >> 4;
+  const T* __restrict__ in = reinterpret_cast<const T*>(a.in);
+  const T* __restrict__ wp = reinterpret_cast<const T*>(a.wpack);
+  T* __restrict__ out = reinterpret_cast<T*>(a.out);
+  const T* __restrict__ addg = reinterpret_cast<const T*>(a.add_g);
+  const T* __restrict__ addm = reinterpret_cast<const T*>(a.add_mask);
+  const int hc = (a.OH + 1 - PR) >> 1, wc = (a.OW + 1 - PC) >> 1, hwc = hc * wc, mc = a.N * hwc;
+
+  int pn[MB], pi[MB], pj[MB];
+  bool pv[MB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i) {
+    const int p = (tile * MB + i) * 16 + l16;
+    pv[i] = p < mc;
+    const int pp = pv[i] ? p : 0;
+    pn[i] = pp / hwc;
+    const int rem = pp - pn[i] * hwc;
+    pi[i] = rem / wc; pj[i] = rem - pi[i] * wc;
+  }
+  f32x4_t acc[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[i][nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  frag_t wf[2][CPT][NB], xf[2][CPT][MB];
+  bool ok[2][MB];
+  // tap t of the class: kernel row r, column s; source pixel (pi + dh, pj + dw)
+#define DDG_S2_TAP(t, set)                                                                         \
+  {                                                                                                \
+    constexpr int NS1 = NS > 0 ? NS : 1;                                                           \
+    const int tr = (t) / NS1, ts = (t) % NS1;                                                      \
+    const int r = R == 3 ? (PR ? 2 * tr : 1) : 0, sc = R == 3 ? (PC ? 2 * ts : 1) : 0;             \
+    const int dh = R == 3 && PR ? 1 - tr : 0, dw = R == 3 && PC ? 1 - ts : 0;                      \
+    _Pragma("unroll") for (int i = 0; i < MB; ++i) {                                               \
+      const int ih = pi[i] + dh, iw = pj[i] + dw;                                                  \
+      ok[set][i] = pv[i] && ih < a.IH && iw < a.IW;                                                \
+      const unsigned off = ok[set][i] ? (unsigned)((pn[i] * a.IH + ih) * a.IW + iw) * (unsigned)a.IC : 0u; \
+      _Pragma("unroll") for (int c = 0; c < CPT; ++c)                                              \
+        xf[set][c][i] = M_::load(in + (off + (unsigned)((c * 4 + lg) * KV)));                      \
+    }                                                                                              \
+    _Pragma("unroll") for (int c = 0; c < CPT; ++c)                                                \
+      _Pragma("unroll") for (int nb = 0; nb < NB; ++nb)                                            \
+        wf[set][c][nb] = M_::load(wp + ((size_t)(((r * R + sc) * CPT + c) * OCB + cb0 + nb) * 64 + lane) * KV); \
+  }
+  if constexpr (NT > 0) DDG_S2_TAP(0, 0)
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    if (t + 1 < NT) DDG_S2_TAP(t + 1, (t + 1) & 1)
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int c = 0; c < CPT; ++c)
+#pragma unroll
+      for (int i = 0; i < MB; ++i) {
+        frag_t f = xf[t & 1][c][i];
+        keep_frag(f);
+        if (!ok[t & 1][i]) f = M_::zero();
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[i][nb] = M_::mma(wf[t & 1][c][nb], f, acc[i][nb]);
+      }
+  }
+#undef DDG_S2_TAP
+
+#pragma unroll
+  for (int i = 0; i < MB; ++i) {
+    if (!pv[i]) continue;
+    const size_t m = ((size_t)pn[i] * a.OH + 2 * pi[i] + PR) * a.OW + 2 * pj[i] + PC;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const size_t idx = m * a.OC + (cb0 + nb) * 16 + lg * 4;
+      float v[4] = {acc[i][nb][0], acc[i][nb][1], acc[i][nb][2], acc[i][nb][3]};
+      if (addg) {
+        float g[4];
+        S_::load4(addg + idx, g);
+        if (addm) {
+          float mk[4];
+          S_::load4(addm + idx, mk);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) g[j] = (mk[j] > 0.f) ? g[j] : 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] += g[j];
+      }
+      S_::store4(out + idx, S_::round(v[0]), S_::round(v[1]), S_::round(v[2]), S_::round(v[3]));
+    }
+  }
+}
+
+// one wave per tile; the classes with most taps first
+template <typename T, int MB, int NB, int CPT, int R>
+__global__ __launch_bounds__(256) void conv_dgrad_s2_kernel(ConvArgs a, int t11, int t10, int t01, int t00) {
+  int tile = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int cb0 = blockIdx.y * NB;
+  if (tile < t11) { dgrad_s2_tile<T, MB, NB, CPT, R, 1, 1>(a, tile, cb0); return; }
+  tile -= t11;
+  if (tile < t10) { dgrad_s2_tile<T, MB, NB, CPT, R, 1, 0>(a, tile, cb0); return; }
+  tile -= t10;
+  if (tile < t01) { dgrad_s2_tile<T, MB, NB, CPT, R, 0, 1>(a, tile, cb0); return; }
+  tile -= t01;
+  if (tile < t00) dgrad_s2_tile<T, MB, NB, CPT, R, 0, 0>(a, tile, cb0);
+}
+
+// Covered: whole k-steps per tap (1, 2 or 4 of them: 32-128 channels in bf16, 16-64 in fp32). Two pixel blocks per
+// wave once that leaves a wave per SIMD; 32 output channels per wave in bf16 (its matrix instructions are
+// cheap, the gathers are not), 16 in fp32.
+template <typename T>
+static bool conv_dgrad_s2_launch(const ConvArgs& a, hipStream_t s) {
+  constexpr int KSTEP = Mma<T>::KSTEP;
+  if (!a.dgrad || a.stride != 2 || a.stat_partial || a.in_b || (a.R != 1 && a.R != 3) || a.pad != (a.R == 3 ? 1 : 0)) return false;
+  if (a.IC % KSTEP != 0 || (1 << a.log2cp) != a.IC || a.IH != (a.OH + 1) / 2 || a.IW != (a.OW + 1) / 2) return false;
+  const int cpt = a.IC / KSTEP;
+  if (cpt != 1 && cpt != 2 && cpt != 4) return false;
+  const int nb = KSTEP == 32 && (a.OC / 16) % 2 == 0 ? 2 : 1, gy = a.OC / 16 / nb;
+  const int mb = (size_t)a.M / 32 * gy >= 1024 ? 2 : 1;
+  const int h0 = (a.OH + 1) / 2, h1 = a.OH / 2, w0 = (a.OW + 1) / 2, w1 = a.OW / 2;
+  auto tiles = [&](int h, int w) { return (a.N * h * w + 16 * mb - 1) / (16 * mb); };
+  const int t11 = tiles(h1, w1), t10 = tiles(h1, w0), t01 = tiles(h0, w1), t00 = tiles(h0, w0);
+  const dim3 grid((t11 + t10 + t01 + t00 + 3) / 4, gy), block(256);
+#define DDG_S2_CASE(MB_, NB_, CPT_)                                                                              \
+  if (mb == MB_ && nb == NB_ && cpt == CPT_) {                                                                   \
+    if (a.R == 3) DDG_LAUNCH((conv_dgrad_s2_kernel<T, MB_, NB_, CPT_, 3>), grid, block, 0, s, a, t11, t10, t01, t00); \
+    else DDG_LAUNCH((conv_dgrad_s2_kernel<T, MB_, NB_, CPT_, 1>), grid, block, 0, s, a, t11, t10, t01, t00);     \
+    return true;                                                                                                 \
+  }
+  DDG_S2_CASE(1, 1, 1) DDG_S2_CASE(1, 1, 2) DDG_S2_CASE(1, 1, 4)
+  DDG_S2_CASE(2, 1, 1) DDG_S2_CASE(2, 1, 2) DDG_S2_CASE(2, 1, 4)
+  if constexpr (KSTEP == 32) {
+    DDG_S2_CASE(1, 2, 1) DDG_S2_CASE(1, 2, 2) DDG_S2_CASE(1, 2, 4)
+    DDG_S2_CASE(2, 2, 1) DDG_S2_CASE(2, 2, 2) DDG_S2_CASE(2, 2, 4)
+  }
+#undef DDG_S2_CASE
+  return false;
+}
+
 static int ceil_log2(int v) {
   int l = 0;
   while ((1 << l) < v) ++l;
@@ -258,6 +409,7 @@ static hipError_t conv_dispatch(const ConvArgs& a, hipStream_t s) {
 hipError_t conv_launch(const ConvArgs& a, hipStream_t s) {
   // the gathers form 32-bit element offsets
   if ((size_t)a.N * a.IH * a.IW * a.IC >= ((size_t)1 << 32)) return hipErrorInvalidValue;
+  if (a.dtype == BF16 ? conv_dgrad_s2_launch<bf16_t>(a, s) : conv_dgrad_s2_launch<float>(a, s)) return hipGetLastError();
   return a.dtype == BF16 ? conv_dispatch<bf16_t>(a, s) : conv_dispatch<float>(a, s);
 }
 

@@ -73,3 +73,55 @@ def test_one_wide_block_matches_the_oracle(dtype, batch, hw, cin, cmid, cout, pr
         mod.update(t, 0.0)
         oracle.update(2, 0.0)
     mod.close()
+
+
+# the stride-2 input gradient by pixel parity: odd and even heights, one pixel, a single row of tiles, all widths that
+# select one, two and four k-steps per tap, with a projection (its own stride-2 1x1 launch and the sum of the two)
+# (1 x 1 images in a batch of 5: with a single pixel per channel the batch norm's gradient is exactly zero, and a relative
+# error against rounding noise says nothing)
+S2_CASES = [("f32", 2, 9, 16, 32), ("f32", 5, 1, 32, 64), ("f32", 65, 32, 16, 32), ("f32", 3, 7, 32, 64),
+            ("bf16", 2, 9, 16, 32), ("bf16", 3, 2, 32, 64), ("bf16", 130, 32, 16, 32), ("bf16", 2, 11, 64, 128),
+            ("bf16", 5, 16, 32, 64)]
+
+
+@pytest.mark.parametrize("dtype,batch,hw,cin,cout", S2_CASES)
+def test_stride_two_block_matches_the_oracle(dtype, batch, hw, cin, cout):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    import paper_1804_10574_amd as ddg
+    from paper_1804_10574_amd.ddg import make_desc
+    from oracle import ddg_oracle as orc
+    from tests import gpu_harness as H
+    print(f"case stride-two block {dtype} batch={batch} hw={hw} {cin}-{cout}", flush=True)
+    blocks = [(wk.BLOCK_BASIC, cin, 0, cout, 2, 1)]
+    shape, ho = (batch, cin, hw, hw), (hw - 1) // 2 + 1
+    mod = ddg.Module(make_desc(2, 2, batch, (cin, hw, hw), blocks, 0, ddg.DDG_BF16 if dtype == "bf16" else ddg.DDG_F32,
+                               0.9, 0.0, 1e-3))
+    oracle = orc.OracleNet(2, [blocks], batch, (cin, hw, hw), 0, 0.9, 0.0, 1e-3, "f64", k_first=2,
+                           store_bf16=(dtype == "bf16"))
+    theta = (wk.normal(21, 1, oracle.param_count(2)) * 0.1 + 0.05).astype(np.float32)
+    oracle.set_params(2, theta.astype(np.float64))
+    mod.set_params(theta)
+
+    class WL:
+        pass
+    wl = WL(); wl.dtype = dtype
+    h_in = wk.normal(23, 0, int(np.prod(shape))).reshape(shape)
+    delta = wk.normal(27, 0, batch * cout * ho * ho).reshape(batch, cout, ho, ho)
+    hd, dd = H.to_dev_nhwc(h_in, wl), H.to_dev_nhwc(delta, wl)
+    if dtype == "bf16":
+        h_in, delta = H.from_dev_nhwc(hd), H.from_dev_nhwc(dd)
+    h_out = torch.empty((batch, ho, ho, cout), dtype=H.tdtype(wl), device="cuda")
+    d_out = torch.full_like(hd, float("nan"))
+    torch.cuda.synchronize()
+    mod.forward(0, hd, h_out)
+    mod.backward_delayed(0, delta_in=dd, delta_out=d_out)
+    mod.sync()
+    ref_h = oracle.forward(2, 0, h_in)
+    _, ref_d, _ = oracle.backward_delayed(2, 0, delta, None, in_shape=shape)
+    e_h, e_d = H.rel_err(H.from_dev_nhwc(h_out), ref_h), H.rel_err(H.from_dev_nhwc(d_out), ref_d)
+    print(f"  h {e_h:.2e} dx {e_d:.2e}", flush=True)
+    # as above; one ReLU layer lies between the error gradient and dx
+    assert e_h <= (1e-4 if dtype == "f32" else 2e-2) and e_d <= (1e-3 if dtype == "f32" else 3e-2)
+    mod.close()
