@@ -501,7 +501,7 @@ ddg_status build_plan(ddg_module* m) {
       w.partial = u.wg_partial; w.dW = m->grad + u.ow; w.rows = u.wg.msplit; w.Cout = u.cout; w.Cin = u.cin;
       w.R = u.R; w.log2cp = u.wg.log2cp; w.Jp = u.wg.JB * 16;
       wd.push_back(w);
-      if (w.Cout * w.Jp > m->wred_max) m->wred_max = w.Cout * w.Jp;
+      if (wgrad_reduce_blocks(w) > m->wred_max) m->wred_max = wgrad_reduce_blocks(w);
     }
   m->n_pack = (int)pd.size(); m->n_wred = (int)wd.size();
   if (!d.dry_run && m->n_pack) {
