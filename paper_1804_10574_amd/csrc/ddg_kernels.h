@@ -100,6 +100,15 @@ struct PackDesc { const float* W; void* wpack; int Cout, Cin, R, mode, log2cp, k
 struct WredDesc { const float* partial; float* dW; int rows, Cout, Cin, R, log2cp, Jp; };
 // max_total: the largest `total` among the n operands (sizes the grid)
 hipError_t pack_all_launch(const PackDesc* dev_descs, int n, int dtype, hipStream_t s, unsigned max_total = 0);
+// Optimizer step and repacking in one launch, for modules of at most UPDATE_PACK_MAX parameters. A segment of the
+// parameter vector: conv weights [Cout][Cin][R][R] (none: conv = 0) followed by `plain` values; pack_d may be null.
+constexpr size_t UPDATE_PACK_MAX = (size_t)1 << 20;
+struct UpdDesc { size_t off; unsigned conv, plain; void *pack_f, *pack_d; unsigned Cin, ocb_f, ocb_d; int R, l2f, l2d, mirror; };
+struct UpdArgs {
+  float *w, *v, *m2; const float* g; float lr; const float* lr_dev; float mu, wd;     // v: velocity, or Adam's first moment
+  float b1, b2, eps; double b1d, b2d; double* pw; unsigned* pw_readers;                // Adam
+};
+hipError_t update_pack_launch(const UpdDesc* dev_descs, int n, unsigned max_len, const UpdArgs& a, int dtype, bool adam, hipStream_t s);
 // max_blocks: the largest wgrad_reduce_blocks() among the n layers (sizes the grid)
 int wgrad_reduce_blocks(const WredDesc& d);
 hipError_t wgrad_reduce_all_launch(const WredDesc* dev_descs, int n, int max_blocks, hipStream_t s);

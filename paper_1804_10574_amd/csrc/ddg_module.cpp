@@ -118,6 +118,9 @@ struct ddg_module {
   hipStream_t bstream = nullptr;   // backward / update stream (desc.stream)
   hipStream_t fstream = nullptr;   // forward stream (== bstream unless two_streams)
   bool two_streams = false;
+  UpdDesc* upd_descs = nullptr;    // small modules: update and repacking in one launch
+  int n_upd = 0; unsigned upd_max = 0;
+  unsigned* pw_readers = nullptr;
   Readback readback;               // device -> host copies of weights, optimizer state, stored inputs
   bool external_sync = false;      // a pipeline orders the two streams; the module records/waits nothing
   hipEvent_t ev_fwd[2] = {nullptr, nullptr};   // forward(t) done, by parity of t
@@ -456,10 +459,11 @@ ddg_status build_plan(ddg_module* m) {
     hb.pooled = (float*)p; hb.dlogits = hb.pooled + (size_t)N * hb.C; hb.loss_n = hb.dlogits + (size_t)N * d.num_classes;
   }
   void* p = nullptr;
-  DDG_OKAY(dev_alloc(m, &p, 4 * m->nparams * sizeof(float) + 2 * sizeof(double)));
+  DDG_OKAY(dev_alloc(m, &p, 4 * m->nparams * sizeof(float) + 3 * sizeof(double)));
   m->theta = (float*)p; m->vel = m->theta + m->nparams; m->grad = m->vel + m->nparams;
   m->mom2 = m->grad + m->nparams;
   m->adam_pw = (double*)((char*)p + ((4 * m->nparams * sizeof(float) + 7) & ~(size_t)7));
+  m->pw_readers = (unsigned*)(m->adam_pw + 2);
   m->delay = d.K - d.k;
   m->nslots = m->delay + 1;
   m->ring.resize(m->nslots, nullptr);
@@ -521,6 +525,33 @@ ddg_status build_plan(ddg_module* m) {
         return fail(DDG_ERR_DEVICE, "copying the layer tables failed");
     }
   }
+  if (!d.dry_run && m->nparams <= UPDATE_PACK_MAX) {
+    std::vector<UpdDesc> ud;
+    for (Blk& b : m->blocks) {
+      for (Unit& u : b.u) {
+        UpdDesc x{};
+        x.off = u.ow; x.conv = (unsigned)((size_t)u.cout * u.cin * u.R * u.R); x.plain = 2u * u.cout;   // conv.W, bn.gamma, bn.beta
+        x.pack_f = u.wpack_f; x.pack_d = m->stale || !u.has_dgrad ? nullptr : u.wpack_d;
+        x.Cin = u.cin; x.R = u.R; x.mirror = u.tiled_grid > 0 || u.wide_d;
+        int ks = 0;
+        conv_wpack_elems(u.cin, u.cout, u.R, dt, &x.l2f, &ks);
+        conv_wpack_elems(u.cout, u.cin, u.R, dt, &x.l2d, &ks);
+        x.ocb_f = u.cout / 16; x.ocb_d = u.cin / 16;
+        ud.push_back(x);
+      }
+      if (b.kind == DDG_BLOCK_HEAD) {
+        UpdDesc x{};
+        x.off = b.ofcw; x.plain = (unsigned)(m->nparams - b.ofcw); x.Cin = 1; x.R = 1;   // fc.W, fc.b end the vector
+        ud.push_back(x);
+      }
+    }
+    for (const UpdDesc& x : ud) if (x.conv + x.plain > m->upd_max) m->upd_max = x.conv + x.plain;
+    m->n_upd = (int)ud.size();
+    DDG_OKAY(dev_alloc(m, &p, ud.size() * sizeof(UpdDesc)));
+    m->upd_descs = (UpdDesc*)p;
+    if (hipMemcpy(m->upd_descs, ud.data(), ud.size() * sizeof(UpdDesc), hipMemcpyHostToDevice) != hipSuccess)
+      return fail(DDG_ERR_DEVICE, "copying the layer tables failed");
+  }
   if (m->stale && !d.dry_run) {
     DDG_OKAY(dev_alloc(m, &p, (size_t)m->nslots * m->nparams * sizeof(float)));
     m->theta_snap = (float*)p;
@@ -529,10 +560,12 @@ ddg_status build_plan(ddg_module* m) {
   if (!d.dry_run) {
     hipError_t e = hipMemsetAsync(m->theta, 0, 4 * m->nparams * sizeof(float), m->stream);
     if (e == hipSuccess) {
-      const double one[2] = {1.0, 1.0};   // beta^0
+      const double one[3] = {1.0, 1.0, 0.0};   // beta^0; no readers
       e = hipMemcpy(m->adam_pw, one, sizeof one, hipMemcpyHostToDevice);
     }
     if (e != hipSuccess) return fail(DDG_ERR_DEVICE, "hipMemsetAsync: %s", hipGetErrorString(e));
+    // the operands' padding is written here and by ddg_set_params only (an update leaves it alone)
+    if (m->n_pack) DDG_TRY(pack_all_launch(m->pack_descs, m->n_pack, m->d.compute, m->stream, m->pack_max));
   }
   return DDG_OK;
 }
@@ -1800,6 +1833,18 @@ ddg_status ddg_update(ddg_module* m, long t, float lr) {
   const bool self_sync = m->two_streams && !m->external_sync;
   // the forward pass of this iteration must have finished reading the weights
   if (self_sync) DDG_TRY(hipStreamWaitEvent(m->bstream, m->ev_fwd[t & 1], 0));
+  if (m->upd_descs) {
+    const bool adam = m->opt == DDG_OPT_ADAM;
+    UpdArgs a{};
+    a.w = m->theta; a.v = m->vel; a.m2 = m->mom2; a.g = m->grad; a.lr = lr; a.lr_dev = m->lr_dev;
+    a.mu = m->d.momentum; a.wd = m->d.weight_decay;
+    a.b1 = m->beta1; a.b2 = m->beta2; a.eps = m->adam_eps; a.b1d = (double)m->beta1; a.b2d = (double)m->beta2;
+    a.pw = m->adam_pw; a.pw_readers = m->pw_readers;
+    Launch L(m, adam ? PK_ADAM : PK_SGD, (double)m->nparams * (adam ? 28.0 : 20.0));
+    DDG_TRY(update_pack_launch(m->upd_descs, m->n_upd, m->upd_max, a, m->d.compute, adam, m->stream));
+    if (self_sync) DDG_TRY(hipEventRecord(m->ev_upd, m->bstream));
+    return DDG_OK;
+  }
   if (m->opt == DDG_OPT_ADAM) {
     { Launch L(m, PK_ADAM); DDG_TRY(adam_advance_launch(m->adam_pw, m->beta1, m->beta2, m->stream)); }
     Launch L(m, PK_ADAM, (double)m->nparams * 28.0);   // w, m, v read and written, g read
