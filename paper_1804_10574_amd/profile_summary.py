@@ -63,7 +63,7 @@ def kind_of(kernel_name: str) -> str:
     m = re.match(r"wgrad_tiled_kernel<(\d+), (\d+), (\d+), (\d+), (\d+)>", n)
     if m:   # <Cin, Cout, output width, stride, kernel size>
         return "conv_wgrad.tiled_stride2" if m.group(4) == "2" else f"conv_wgrad.tiled_c{m.group(1)}_w{m.group(3)}"
-    m = re.match(r"conv_wide_kernel<(\d+), ", n)
+    m = re.match(r"conv_(?:wide|halo)_kernel<(\d+), ", n)
     if m:   # <STATS, ...>: 1 = forward statistics (the forward conv); 0 / 2 = the input gradient
         return "conv_fprop.wide" if m.group(1) == "1" else "conv_dgrad.wide"
     if n.startswith("wgrad_wide_kernel"):
@@ -71,7 +71,11 @@ def kind_of(kernel_name: str) -> str:
     m = re.match(r"conv_mfma_kernel<\w+, \d+, \d+, (true|false)", n)
     if m:   # <T, MB, NB, DGRAD, VEC>
         return "conv_dgrad.generic" if m.group(1) == "true" else "conv_fprop.generic"
-    table = [("wgrad_mfma_kernel", "conv_wgrad.generic"), ("wgrad_mfma_vec_kernel", "conv_wgrad.generic"), ("wgrad_reduce", "wgrad_reduce"),
+    m = re.match(r"update_pack_kernel<[\w:]+, (true|false)>", n)
+    if m:   # <T, ADAM>: the optimizer step and the repacking
+        return "adam" if m.group(1) == "true" else "sgd"
+    table = [("conv_dgrad_s2_kernel", "conv_dgrad.generic"), ("bn_apply_wide_kernel", "bn_apply"),
+             ("bn_bwd_apply_wide_kernel", "bn_bwd_apply"), ("wgrad_mfma_kernel", "conv_wgrad.generic"), ("wgrad_mfma_vec_kernel", "conv_wgrad.generic"), ("wgrad_reduce", "wgrad_reduce"),
              ("bn_bwd_apply_kernel", "bn_bwd_apply"), ("bn_bwd_apply_chunk_kernel", "bn_bwd_apply"), ("bn_bwd_reduce_kernel", "bn_bwd_reduce"),
              ("bn_bwd_finalize", "bn_bwd_finalize"), ("bn_apply_kernel", "bn_apply"),
              ("bn_apply_chunk_kernel", "bn_apply"), ("bn_apply_pair_kernel", "bn_apply"),
