@@ -16,6 +16,8 @@ CASES = [("bf16", 1, 5, 128, 128, 128, 0),       # 25 pixels: less than one tile
          ("bf16", 129, 8, 128, 128, 128, 0),     # 8256 pixels = 129 rows: finalise launches
          ("bf16", 2, 12, 256, 256, 512, 1),      # projection, several channel groups everywhere
          ("bf16", 2, 40, 128, 256, 128, 0),      # rows longer than a tile's halo of a 14 x 14 image
+         ("bf16", 1, 31, 128, 512, 128, 0),      # the widest image whose halo fits, four slices
+         ("bf16", 7, 1, 128, 128, 128, 0),       # 1 x 1 images: no neighbour exists
          ("f32", 3, 9, 128, 128, 256, 1)]
 
 
