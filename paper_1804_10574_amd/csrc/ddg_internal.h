@@ -11,6 +11,8 @@ void ddg_internal_skip_launches(ddg_module* m, bool skip);
 // The update reads its step size from this device float instead of the call argument.
 void ddg_internal_lr_from(ddg_module* m, const float* lr_dev);
 bool ddg_internal_profiling(const ddg_module* m);
+// What ddg_forward_eval refuses, without its launches.
+ddg_status ddg_internal_eval_ok(ddg_module* m, const void* h_in, void* h_out, const int32_t* labels, float* loss_out);
 // Evaluation passes of the module go to stream s (on) or to its own stream again (off).
 void ddg_internal_eval_stream(ddg_module* m, bool on, hipStream_t s);
 // A pipeline orders the module's two streams itself (events around graph launches); the module

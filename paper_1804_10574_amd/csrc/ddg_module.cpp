@@ -1706,10 +1706,15 @@ static ddg_status eval_args_ok(ddg_module* m, const void* h_in, void* h_out, con
   return DDG_OK;
 }
 
-ddg_status ddg_forward_eval(ddg_module* m, const void* h_in, void* h_out, const int32_t* labels, float* loss_out,
-                            float* logits_out) {
+ddg_status ddg_internal_eval_ok(ddg_module* m, const void* h_in, void* h_out, const int32_t* labels, float* loss_out) {
   DDG_OKAY(eval_args_ok(m, h_in, h_out, labels, loss_out));
   if (m->stale) return fail(DDG_ERR_STATE, "no evaluation forward in stale-Jacobian mode: every set of forward buffers holds a kept tape");
+  return DDG_OK;
+}
+
+ddg_status ddg_forward_eval(ddg_module* m, const void* h_in, void* h_out, const int32_t* labels, float* loss_out,
+                            float* logits_out) {
+  DDG_OKAY(ddg_internal_eval_ok(m, h_in, h_out, labels, loss_out));
   if (m->d.dry_run) return DDG_OK;
   m->tape_is_current = false;     // the forward buffers of group 0 now hold this pass
   HeadScratch hs{};

@@ -293,24 +293,29 @@ ddg_status ddg_pipeline_set_bn_momentum(ddg_pipeline* p, float rho) {
 // Evaluation of the whole network between iterations. Module k writes into the buffer that
 // iteration p->t will overwrite anyway (the one ddg_pipeline_get_h does not read). Everything
 // before it has been waited for, so the modules run one after the other on the last module's stream:
-// no wait on another stream (5-10 us each) and one for the host.
+// no wait on another stream (5-10 us each) and one for the host. The next step's streams do not wait
+// for that stream, so nothing is launched before every module has accepted its call, and no
+// return after the first launch leaves without the wait.
 ddg_status ddg_pipeline_forward_eval(ddg_pipeline* p, const void* x, const int32_t* labels, float* loss_out,
                                      float* logits_out) {
   if (!p || !x) return DDG_ERR_INVALID_ARG;
+  auto out_of = [&](int k) -> void* { return k == p->K ? nullptr : (p->t & 1) ? p->h_odd[k] : p->h[k]; };
+  auto in_of = [&](int k) -> const void* { return k == 1 ? x : out_of(k - 1); };
+  for (int k = 1; k <= p->K; ++k) {
+    const ddg_status st = ddg_internal_eval_ok(p->mods[k], in_of(k), out_of(k), k == p->K ? labels : nullptr,
+                                               k == p->K ? loss_out : nullptr);
+    if (st != DDG_OK) return st;
+  }
   if (p->dry) return DDG_OK;
   ddg_status st = ddg_pipeline_sync(p);
-  if (st != DDG_OK) return st;
-  const void* in = x;
-  for (int k = 1; k <= p->K; ++k) {
-    void* out = (k < p->K) ? ((p->t & 1) ? p->h_odd[k] : p->h[k]) : nullptr;
+  for (int k = 1; k <= p->K && st == DDG_OK; ++k) {
     ddg_internal_eval_stream(p->mods[k], true, p->streams[p->K]);
-    st = ddg_forward_eval(p->mods[k], in, out, k == p->K ? labels : nullptr, k == p->K ? loss_out : nullptr,
+    st = ddg_forward_eval(p->mods[k], in_of(k), out_of(k), k == p->K ? labels : nullptr, k == p->K ? loss_out : nullptr,
                           k == p->K ? logits_out : nullptr);
     ddg_internal_eval_stream(p->mods[k], false, nullptr);
-    if (st != DDG_OK) return st;
-    in = out;
   }
-  return hipStreamSynchronize(p->streams[p->K]) == hipSuccess ? DDG_OK : DDG_ERR_DEVICE;
+  const hipError_t e = hipStreamSynchronize(p->streams[p->K]);
+  return st != DDG_OK ? st : e == hipSuccess ? DDG_OK : DDG_ERR_DEVICE;
 }
 
 ddg_status ddg_pipeline_step(ddg_pipeline* p, const void* x, const int32_t* labels, float lr, float* loss_out) {

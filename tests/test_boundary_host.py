@@ -175,6 +175,28 @@ def test_a_module_may_be_the_head_alone():
     m.close()
 
 
+def test_pipeline_evaluation_is_refused_before_anything_runs():
+    """ddg_pipeline_forward_eval asks every module before it launches the first one: what the head, or any
+    module, refuses is refused in a dry run too (which stops after those checks)."""
+    wl = wk.get_workload("resnet110_k4")
+    fake = 4096
+    p = ddg.Pipeline(descs_for(wl, dry_run=True))
+    p.forward_eval(fake)
+    p.forward_eval(fake, labels=fake, loss_out=fake, logits_out=fake)
+    for bad in (dict(x=fake, labels=None, loss_out=fake),      # the head: a loss needs labels
+                dict(x=fake + 4)):                             # the first module: tensors are 16-byte aligned
+        with pytest.raises(ddg.DDGError) as e:
+            p.forward_eval(**bad)
+        assert e.value.status == 1
+    p.forward_eval(fake)                                       # a refusal changes nothing
+    p.close()
+    stale = ddg.Pipeline(descs_for(wl, dry_run=True, stale_jacobian=True))
+    with pytest.raises(ddg.DDGError) as e:
+        stale.forward_eval(fake)
+    assert e.value.status == 3
+    stale.close()
+
+
 def test_dry_run_pipeline_schedule():
     wl = wk.get_workload("resnet110_k4")
     p = ddg.Pipeline(descs_for(wl, dry_run=True))
