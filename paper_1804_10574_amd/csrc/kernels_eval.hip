@@ -76,6 +76,11 @@ struct Conv {
   typedef typename Mma<T>::frag_t frag_t;
   static constexpr int KV = Mma<T>::KV, KSTEP = Mma<T>::KSTEP, PIX = pix_bytes<T>(CIN);
   static constexpr int KSTEPS = (R * R * CIN + KSTEP - 1) / KSTEP, KPW = KSTEPS / KS;
+  // Lanes of the last k-step past the last tap (16 channels in bf16, the stem) multiply zero weights; what they
+  // read has to be zero as well, or an infinite activation becomes NaN in every channel: the padding
+  // behind tap 0's pixel, or, where a pixel is one chunk without padding (PIX 16), whatever is there, zeroed.
+  static constexpr bool RAGGED = R * R * CIN % KSTEP != 0, PADDED = PIX > CIN * (int)sizeof(T);
+  static_assert(PADDED || KS == 1, "the last k-step is the last of every wave");
   static constexpr int NCB_ = NCB, KS_ = KS, U_ = U, OCB = COUT / 16, CBG = OCB / NCB, PG = 8 / (CBG * KS), PAD = R / 2;
   static_assert(KSTEPS % KS == 0 && OCB % NCB == 0 && 8 % (CBG * KS) == 0 && (KS == 1 || (PG == 1 && NCB == 1 && U % 2 == 0)), "wave layout");
 
@@ -102,15 +107,13 @@ struct Conv {
     }
   }
   // per-lane LDS offset of k-step ks relative to the top left tap of an output pixel (WC: columns
-  // of the source buffer); lanes past the last tap read tap 0 (their weights are zero)
+  // of the source buffer); lanes past the last tap read the padding of tap 0's pixel
   __device__ static __forceinline__ void addresses(int (&ka)[KPW], int wave, int lane, int WC) {
 #pragma unroll
     for (int ks = 0; ks < KPW; ++ks) {
       const int k = ((kh(wave) * KPW + ks) * 4 + (lane >> 4)) * KV;
-      int tap = k / CIN;
-      const int c0 = k % CIN;
-      if (tap >= R * R) tap = 0;
-      ka[ks] = ((tap / R) * WC + tap % R) * PIX + c0 * (int)sizeof(T);
+      const int tap = k / CIN, c0 = k % CIN;
+      ka[ks] = tap < R * R ? ((tap / R) * WC + tap % R) * PIX + c0 * (int)sizeof(T) : PADDED ? CIN * (int)sizeof(T) : 0;
     }
   }
   template <int V>
@@ -119,7 +122,10 @@ struct Conv {
     for (int ks = 0; ks < KPW; ++ks) {
       frag_t x[V];
 #pragma unroll
-      for (int u = 0; u < V; ++u) x[u] = *reinterpret_cast<const frag_t*>(lds() + src + pa[u] + ka[ks]);
+      for (int u = 0; u < V; ++u) {
+        x[u] = *reinterpret_cast<const frag_t*>(lds() + src + pa[u] + ka[ks]);
+        if (RAGGED && !PADDED && ks == KPW - 1 && (ks * 4 + (int)(threadIdx.x & 63) / 16) * KV >= R * R * CIN) x[u] = Mma<T>::zero();
+      }
 #pragma unroll
       for (int b = 0; b < NCB; ++b)
 #pragma unroll
@@ -388,7 +394,7 @@ __device__ __forceinline__ void down_block(const EvalConvDesc* cv, int tab, Bufs
 #pragma unroll
     for (int ks = 0; ks < KP::KPW; ++ks) {
       const int k = (ks * 4 + (lane >> 4)) * KP::KV;
-      kp[ks] = (k < C ? k : 0) * (int)sizeof(T);         // (channels past the last have zero weights)
+      kp[ks] = (k < C ? k : C) * (int)sizeof(T);         // (past the last channel: the pixel's padding, zero)
     }
     K2::pass(B.o, orow0, WCo, lo, hi, Wo, ka, w2, red, flip, wave, lane,
              [&](const f32x4_t& acc, int b, int row, int col, bool ok) __attribute__((always_inline)) {
