@@ -1659,13 +1659,23 @@ ddg_status ddg_set_running(ddg_module* m, const float* host_src) {
 // The evaluation forward through `blocks` (the module's own forward buffers, or a view of them
 // whose buffers lie elsewhere); hs: the head's per-sample scratch.
 struct HeadScratch { float* pooled; float* dlogits; float* loss_n; };
+// May the many-layer kernel write h_out? Not if a workgroup's output can lie in what another one has still to read: one
+// launch from h_in to h_out with the two overlapping, unless every workgroup takes one image to its own place. The
+// per-layer kernels write h_out in their last launch, which reads h_in pixel by pixel at most.
+static bool eval_fused_ok(const ddg_module* m, const void* h_in, const void* h_out) {
+  if (m->eval.launches.empty()) return false;
+  if (m->d.num_classes > 0 || m->eval.launches.size() > 1) return true;
+  const char *a = (const char*)h_in, *b = (const char*)h_out;
+  const bool apart = a + m->in_elems * m->esz <= b || b + m->out_elems * m->esz <= a;
+  return apart || (a == b && m->in_elems == m->out_elems && m->eval.launches[0].strips == 1);
+}
 static ddg_status eval_forward(ddg_module* m, std::vector<Blk>& blocks, const HeadScratch& hs, const void* h_in,
                                void* h_out, const int32_t* labels, float* loss_out, float* logits_out) {
-  const bool head = m->d.num_classes > 0;
+  const bool head = m->d.num_classes > 0, fused = eval_fused_ok(m, h_in, h_out);
   m->stream = m->eval_elsewhere ? m->estream : m->bstream;
-  if (m->n_run && m->eval.launches.empty()) DDG_TRY(eval_vectors_launch(m->run_descs[0], m->n_run, m->run_max_c, m->stream));
+  if (m->n_run && !fused) DDG_TRY(eval_vectors_launch(m->run_descs[0], m->n_run, m->run_max_c, m->stream));
   const int nres = (int)blocks.size() - (head ? 1 : 0);
-  if (!m->eval.launches.empty()) {
+  if (fused) {
     const void* in = h_in;
     for (const EvalLaunch& l : m->eval.launches) {
       const int last = l.first + l.count - 1;
