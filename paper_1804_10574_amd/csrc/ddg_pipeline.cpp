@@ -325,6 +325,7 @@ ddg_status ddg_pipeline_step(ddg_pipeline* p, const void* x, const int32_t* labe
   const int cur = (int)(t & 1), prev = cur ^ 1;
   bool use_graph = !p->dry && p->graphs && t >= K;   // steady state: every module has a gradient
   if (use_graph) for (int k = 1; k <= K; ++k) if (ddg_internal_profiling(p->mods[k])) use_graph = false;
+  const bool steady = use_graph || (p->dry && p->graphs && t >= K);   // (a dry run models the order of the graphs)
 #define DDG_P(expr) do { if ((expr) != hipSuccess) return DDG_ERR_DEVICE; } while (0)
   // Every wait and record goes through these two, so that the ordering model sees exactly the
   // dependencies the streams get. Event numbers: fwd_done[sl][k] = sl*(K+1)+k, bwd_done after them.
@@ -408,9 +409,12 @@ ddg_status ddg_pipeline_step(ddg_pipeline* p, const void* x, const int32_t* labe
     const int sf = p->sid_f[k];
     const bool split = sf != p->sid_b[k];
     // The last module's whole iteration as one graph: its backward pass only has to wait until
-    // module K-1 has read mailbox slot `cur` during t-1, and module K-1's stream did that before it
-    // ran the forward pass whose output this module waits for here anyway.
-    const bool whole = use_graph && k == K && !split;
+    // module K-1 has read mailbox slot `cur` during t-1, and that came before the forward pass whose
+    // output this module waits for here anyway: on the same stream, or, where module K-1 has a forward
+    // stream of its own, because that stream waits for update(t-1) below. (Likewise fwd_done, now
+    // recorded after the update: module K-1's forward(t+2), which waits for it, comes after its own
+    // update(t+1) and so after the backward pass of module K that wrote the mailbox during t.)
+    const bool whole = steady && k == K && !split;
     if (whole && k > 1 && t > 0) DDG_P(wait_b(sf, fs, prev, k - 1));
     if (k > 1) DDG_P(wait_f(sf, fs, cur, k - 1));
     // this iteration's h[k] buffer was last read by module k+1's forward two iterations ago
@@ -451,7 +455,7 @@ ddg_status ddg_pipeline_step(ddg_pipeline* p, const void* x, const int32_t* labe
     hipStream_t bs = p->dry ? nullptr : p->streams[k];
     const int sb = p->sid_b[k];
     const bool split = p->sid_f[k] != sb;
-    const bool whole = use_graph && k == K && !split;   // already run, above
+    const bool whole = steady && k == K && !split;   // already run, above
     if (!whole && s >= 0 && t > 0) {
       // read-after-write: the error gradient for iteration s was written by module k+1 during t-1
       if (k < K) DDG_P(wait_b(sb, bs, prev, k + 1));
@@ -496,6 +500,13 @@ ddg_status ddg_pipeline_step(ddg_pipeline* p, const void* x, const int32_t* labe
 // has seen, and the running number of a wait it is to ignore.
 long ddg_internal_pipeline_waits(const ddg_pipeline* p) { return p ? p->order.waits : -1; }
 void ddg_internal_pipeline_drop_wait(ddg_pipeline* p, long n) { if (p) p->order.drop = n; }
+// Calls of module j's backward stream that a stream has not waited for, directly or not, which waits for
+// module k's forward pass of the last step (its `fwd_done` event).
+long ddg_internal_pipeline_behind(const ddg_pipeline* p, int k, int j) {
+  if (!p || p->t < 1 || k < 1 || k > p->K || j < 1 || j > p->K) return -1;
+  const auto it = p->order.ev.find((int)((p->t - 1) & 1) * (p->K + 1) + k);
+  return it == p->order.ev.end() ? -1 : p->order.clk[p->sid_b[j]][p->sid_b[j]] - it->second[p->sid_b[j]];
+}
 
 ddg_status ddg_pipeline_sync(ddg_pipeline* p) {
   if (!p) return DDG_ERR_INVALID_ARG;

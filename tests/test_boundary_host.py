@@ -297,6 +297,8 @@ def _order_hooks():
     lib.ddg_internal_pipeline_waits.argtypes = [C.c_void_p]
     lib.ddg_internal_pipeline_drop_wait.restype = None
     lib.ddg_internal_pipeline_drop_wait.argtypes = [C.c_void_p, C.c_long]
+    lib.ddg_internal_pipeline_behind.restype = C.c_long
+    lib.ddg_internal_pipeline_behind.argtypes = [C.c_void_p, C.c_int, C.c_int]
     return lib
 
 
@@ -358,6 +360,30 @@ def test_a_missing_wait_is_found(own_forward_streams):
     if own_forward_streams:
         want |= {"read-after-write w", "write-after-read w", "write-after-read mail"}
     assert want <= kinds, kinds
+
+
+@pytest.mark.parametrize("own_forward_streams", [False, True])
+@pytest.mark.parametrize("K", [2, 3, 4, 5])
+def test_one_graph_per_iteration_of_the_last_module_waits_for_nothing_new(K, own_forward_streams):
+    """The last module's iteration as one graph waits for module K-1's backward pass of t-1 before its forward pass, and is
+    done, for those who wait for its forward pass, when its update is. Neither orders anything that the separate calls leave
+    unordered: module K-1's forward pass, which it waits for in both, already comes after that backward pass."""
+    lib = _order_hooks()
+    fake = 4096
+    behind = {}
+    for graphs in (False, True):
+        p = _dry_pipeline(K, own_forward_streams)
+        p.set_graphs(graphs)
+        log = []
+        for t in range(3 * K + 6):
+            p.step(fake, fake, 0.01)
+            # forward passes of all modules against the backward passes of all others; the last module's own calls are one
+            # in the graph
+            log.append([lib.ddg_internal_pipeline_behind(p._h, k, j) for k in range(1, K + 1) for j in range(1, K + 1)
+                        if j != k and (k, j) != (K, K)])
+        p.close()
+        behind[graphs] = log
+    assert behind[True] == behind[False]
 
 
 def test_bench_names_kernels_as_the_profiler_does():
