@@ -1,7 +1,8 @@
 """The evaluation kernel that keeps activations in LDS across layers, against the oracle: both
 operand types (bf16: whole images; fp32: strips of rows), pixel counts that fill no 16-pixel block,
 odd heights under stride 2, one and several images, an image too large for LDS in bf16 (strips), a
-module that starts with a block between stages, and every channel count as first and last."""
+module whose stages together are, a module that starts with a block between stages, and every channel
+count as first and last. The launches that ran are counted: no other convolution kernel may have."""
 import numpy as np
 import pytest
 
@@ -15,7 +16,8 @@ CASES = [(1, [2, 3], 1, 32),        # one image; modules that start with a block
          (1, [], 3, 10),            # 100 / 25 / 9 pixels: ragged everywhere, odd sizes under stride 2
          (2, [3, 5], 2, 24),        # 576 / 144 / 36 pixels
          (3, [4, 7], 2, 28),        # runs of identity blocks at 16, 32 and 64 channels
-         (1, [1, 2], 1, 44)]        # bf16: two 16-channel buffers do not fit LDS
+         (1, [1, 2], 1, 44),        # bf16: two 16-channel buffers do not fit LDS
+         (1, [], 2, 32)]            # bf16: the buffers of all three stages together do not (strips, one block per launch)
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
@@ -47,7 +49,12 @@ def test_fused_evaluation_matches_the_oracle(dtype, units, cuts, batch, hw):
     x, y = wk.minibatch(wl, 9)
     xd, yd = H.to_dev_nhwc(x, wl), torch.from_numpy(y).to("cuda")
     torch.cuda.synchronize()
+    for m in mods.values():
+        m.profile_enable(True)
     pipe.forward_eval(xd, yd, loss, logits)
+    for m in wl.modules:
+        ran = {kind for kind, v in mods[m.k].profile_read().items() if v[0]}
+        assert ran == ({"eval_blocks"} if len(m.blocks) > (m.k == K) else set()), (m.k, ran)
     h = H.from_dev_nhwc(xd) if dtype == "bf16" else x
     for k in range(1, K):
         h = oracle.forward_eval(k, h)
