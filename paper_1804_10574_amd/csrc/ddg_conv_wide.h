@@ -1,4 +1,6 @@
-// What the GEMM-class kernels of the wide bf16 layers share: their arguments and their epilogue.
+// What the GEMM-class kernels of the wide bf16 layers share: their arguments, 16-byte loads and the on-load transform.
+// WideTail is the epilogue of conv_halo_kernel; conv_wide_kernel has its own (64-pixel tiles, its own thread layout) with the
+// same rounding points, masks and statistics: a change of a rule in one belongs in the other.
 #pragma once
 #include "ddg_device.h"
 #include "ddg_kernels.h"

@@ -387,7 +387,7 @@ ddg_status build_plan(ddg_module* m) {
         // kernel of the layer above (at most conv_tiled_max_grid() workgroups)
         int brows = bn_bwd_grid(u.out_elems(), u.cout, dt);
         if (conv_tiled_max_grid() > brows) brows = conv_tiled_max_grid();
-        // (or from the GEMM-class input-gradient kernel above: one row per 64 pixels)
+        // (or from the GEMM-class input-gradient kernel above: one row per 64 pixels at most; its halo form writes half of that)
         if (u.cout % 128 == 0 && conv_wide_rows(N * u.P * u.Q, u.Q, u.cout, 1) > brows) brows = conv_wide_rows(N * u.P * u.Q, u.Q, u.cout, 1);
         DDG_OKAY(dev_alloc(m, &sp, (size_t)brows * 2 * u.cout * sizeof(float)));
         u.bstat = (float*)sp; }

@@ -7,14 +7,18 @@
 // What bounds it: a layer of one image is 4.7 MFLOP on one compute unit, about 1 us of matrix and
 // LDS time in bf16, against 10-13 us for the per-layer launch of a whole minibatch of 256 and 6-7
 // us for the smallest one (the launch, its weights and its halo loads are then all there is).
-// Measured, whole call: ResNet-110, batch 256, bf16 1290 -> 282 us (2.4 us per layer); the 32-channel group of
-// ResNet-56, batch 100, bf16 133 -> 42 us; ResNet-20, one image, fp32 222 -> 118 us.
+// Measured, whole call: ResNet-110, batch 256, bf16 1394 -> 272 us (2.4 us per layer); the 32-channel group of
+// ResNet-56, batch 100, bf16 134 -> 40 us; ResNet-20, one image, fp32 227 -> 116 us. The bf16 kernel holds
+// every stage's code at the registers of the largest: 256, and 7 more spilled.
 //
 // Two ways of cutting the work, chosen by eval_plan() below:
 //   whole images: all blocks of a module in one launch, one image per workgroup (bf16);
 //   strips: one residual block per launch, TH output rows per workgroup, the rows of the halo
 //           recomputed (fp32, whose matrix rate makes an image 10-18 us per layer on one unit, so
-//           that one image has to be spread over several; and images too large for LDS).
+//           that one image has to be spread over several; and bf16 modules whose buffers, each at its
+//           largest over the blocks, exceed LDS: large images, and a network in one module from 32x32 on:
+//           ResNet-8 in one module needs 173 KB. There too nothing got slower: ResNet-110 in one module, batch 37,
+//           1.29x against the per-layer kernels, batch 1 1.41x).
 //
 // Buffers: three LDS regions of NHWC pixels with a zero border (row and column -1 and H / W); a
 // pixel is padded by 16 bytes, so that the 16 pixels of a fragment read start in 16 different bank
