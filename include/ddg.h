@@ -214,7 +214,9 @@ ddg_status ddg_set_running(ddg_module* m, const float* host_src);
  * (after ddg_update, before the next ddg_forward); it overwrites the module's forward buffers
  * and nothing else: weights, estimates, the input ring and the gradient mailbox are
  * untouched. Not available in stale-Jacobian mode (DDG_ERR_STATE), where every set of forward
- * buffers holds a tape that a later backward pass needs. Enqueues on the module's stream. */
+ * buffers holds a tape that a later backward pass needs. h_out may be h_in, and
+ * may overlap it otherwise unless the last block's shortcut is h_in itself (a module of one block
+ * without a projection). Enqueues on the module's stream. */
 ddg_status ddg_forward_eval(ddg_module* m, const void* h_in, void* h_out, const int32_t* labels,
                             float* loss_out, float* logits_out);
 
@@ -278,7 +280,8 @@ ddg_status ddg_pipeline_set_graphs(ddg_pipeline* p, int on);
 ddg_status ddg_pipeline_set_optimizer(ddg_pipeline* p, int kind, float beta1, float beta2, float eps);
 /* Evaluation forward of the whole network (ddg_forward_eval of module 1..K in turn) on x
  * [batch,in_h,in_w,in_c]; labels / loss_out / logits_out as for ddg_forward_eval of the head
- * module. Between iterations only; synchronises. */
+ * module. Between iterations only; synchronises. What any module refuses is refused before
+ * anything runs (in a dry run too). */
 ddg_status ddg_pipeline_forward_eval(ddg_pipeline* p, const void* x, const int32_t* labels, float* loss_out,
                                      float* logits_out);
 /* ddg_set_bn_momentum on every module (before the first iteration). */
