@@ -1,5 +1,5 @@
 """A refused evaluation of a pipeline leaves nothing behind: training goes on bit for bit as in a pipeline that was never
-evaluated, whichever module refuses."""
+evaluated, whether the first module refuses or the last."""
 import numpy as np
 import pytest
 
@@ -32,7 +32,10 @@ def test_training_goes_on_after_a_refused_evaluation(dtype):
             torch.cuda.synchronize()
             if evaluate:
                 with pytest.raises(ddg.DDGError) as e:
-                    pipe.forward_eval(xd, None, scratch)          # the loss needs labels: the last module refuses
+                    pipe.forward_eval(xd, None, scratch)                  # the loss needs labels: the last module refuses
+                assert e.value.status == 1
+                with pytest.raises(ddg.DDGError) as e:
+                    pipe.forward_eval(xd.flatten()[1:], yd, scratch)      # not 16-byte aligned: the first one does
                 assert e.value.status == 1
             pipe.step(xd, yd, 0.05, loss[t:t + 1])
         pipe.sync()
