@@ -205,14 +205,17 @@ hipError_t conv_wide_launch(const void* in, const void* wpack, void* out, float*
                             const float* scale = nullptr, const float* shift = nullptr,
                             const ConvWideSecond* second = nullptr, const ConvStat* below = nullptr);
 
-// Weight gradient of the same wide layers (Cin a power of two >= 128, Cout a multiple of 128):
-// partial tiles [splits][Cout][R*R*Cin] over `splits` slices of the pixels, to be added by
+// Weight gradient of the same wide layers (Cin a power of two >= 128, Cout a multiple of 128), several layers per
+// launch: partial tiles [splits][Cout][R*R*Cin] over `splits` slices of the pixels, to be added by
 // wgrad_reduce_all_launch. x [N*H*W][Cin], dz [N*H*W][Cout].
 bool wgrad_wide_ok(int Cin, int Cout, int R, int stride, int dtype);
-int wgrad_wide_splits(int M, int Cin, int Cout, int R);
+constexpr int WGRAD_WIDE_LAYERS = 24;      // layers per launch, at most
+// For a module's wide layers in the order of its backward pass: slices of each, and after which of them a launch is due.
+struct WgradWidePlan { int M, Cin, Cout, R; int splits; bool launch; };
+void wgrad_wide_plan(std::vector<WgradWidePlan>& layers);
 // scale/shift (optional): x is relu(x*scale + shift) per input channel, applied while staging.
-hipError_t wgrad_wide_launch(const void* x, const void* dz, float* partial, int N, int H, int W, int Cin, int Cout,
-                             int R, int splits, hipStream_t s, const float* scale = nullptr, const float* shift = nullptr);
+struct WgradWideLayer { const void* x; const void* dz; const float* scale; const float* shift; float* partial; int N, H, W, Cin, Cout, R, splits; };
+hipError_t wgrad_wide_launch(const WgradWideLayer* layers, int n, hipStream_t s);
 
 // Batch-norm statistics from per-workgroup partial sums -> mean, invstd, scale=gamma*invstd,
 // shift=beta-mean*scale.

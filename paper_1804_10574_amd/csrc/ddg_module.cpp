@@ -82,6 +82,8 @@ struct Unit {  // convolution + batch normalisation
   float *escale = nullptr, *eshift = nullptr;  // evaluation-time scale and shift derived from them
   bool wide_f = false, wide_d = false;   // the GEMM-class kernel runs the forward conv / the input gradient
   int wide_splits = 0;                   // > 0: the GEMM-class weight-gradient kernel, this many pixel slices
+  size_t wide_dz = 0;                    // its dz lies there in the module's wide_dz buffer until the launch that reads it
+  bool wide_launch = false;              // that launch is due once this layer has joined
   bool small_c() const { return cout == 16 || cout == 32 || cout == 64; }
   bool fin_in_apply = false;   // more channels, few rows: the normalise-add-ReLU kernel finalises the statistics
   int tiled_instance() const { return cin == 16 ? 1 : cin == 32 ? 2 : 3; }   // offset of a tiled kernel's profile kind
@@ -152,6 +154,9 @@ struct ddg_module {
     bool on = false; const Unit* u = nullptr;
     const void* x = nullptr; const float* xsc = nullptr; const float* xsh = nullptr; const void* dz = nullptr;
   } pend_w;
+  // Weight gradients of wide layers collect, each dz in its own place of wide_dz, until a launch is due.
+  std::vector<WgradWideLayer> pend_wide; double pend_wide_bytes = 0.0, pend_wide_flops = 0.0;
+  char* wide_dz = nullptr;
   bool defer_wgrad = true;         // DDG_NO_BWD_PAIR=1 switches the deferred weight gradient off
   bool no_defer = false;           // DDG_NO_DEFER=1: every residual block runs its own normalise-add-ReLU pass
   bool premasked = true;           // DDG_NO_PREMASK=1: readers of a stored masked gradient apply the mask again
@@ -259,6 +264,33 @@ struct Launch {
 int out_dim(int h, int stride) { return (h - 1) / stride + 1; }
 
 // ---- plan ---------------------------------------------------------------------------------
+
+// Slices and launches of the wide layers' weight gradients, in the order unit_backward meets them.
+ddg_status plan_wide_wgrad(ddg_module* m) {
+  std::vector<Unit*> us;
+  for (size_t bi = m->blocks.size(); bi-- > 0;) {
+    Blk& b = m->blocks[bi];
+    if (b.proj) us.push_back(&b.u[b.nmain]);
+    for (int i = b.nmain - 1; i >= 0; --i) us.push_back(&b.u[i]);
+  }
+  std::vector<WgradWidePlan> plan;
+  for (Unit* u : us) if (u->wide_splits > 0) plan.push_back({u->wg.M, u->cin, u->cout, u->R, 0, false});
+  wgrad_wide_plan(plan);
+  size_t k = 0, at = 0, most = 0;
+  for (Unit* u : us) {
+    if (u->wide_splits == 0) continue;
+    u->wide_splits = plan[k].splits; u->wide_launch = plan[k].launch; ++k;
+    u->wg.msplit = u->wide_splits;
+    u->wide_dz = at;
+    at += (u->out_elems() * m->esz + 255) & ~(size_t)255;
+    if (at > most) most = at;
+    if (u->wide_launch) at = 0;
+  }
+  void* p = nullptr;
+  DDG_OKAY(dev_alloc(m, &p, most));
+  m->wide_dz = (char*)p;
+  return DDG_OK;
+}
 
 ddg_status validate(const ddg_module_desc* d) {
   if (!d) return fail(DDG_ERR_INVALID_ARG, "desc is null");
@@ -409,13 +441,7 @@ ddg_status build_plan(ddg_module* m) {
       wgrad_plan(wgd);
       u.wg_tiled_rows = (dt == DDG_F32 && no_lds32) ? 0 : wgrad_tiled_rows(N, u.H, u.W, u.cin, u.cout, u.R, u.stride, dt);
       if (u.wg_tiled_rows > 0) wgd.msplit = u.wg_tiled_rows;  // the reduce kernel sums this many rows
-      if (wgrad_wide_ok(u.cin, u.cout, u.R, u.stride, dt) && !getenv("DDG_NO_WIDE")) {
-        u.wide_splits = wgrad_wide_splits(wgd.M, u.cin, u.cout, u.R);
-        wgd.msplit = u.wide_splits;
-      }
-      { void* wp = nullptr;
-        DDG_OKAY(dev_alloc(m, &wp, wgrad_partial_elems(wgd) * sizeof(float)));
-        u.wg_partial = (float*)wp; }
+      u.wide_splits = wgrad_wide_ok(u.cin, u.cout, u.R, u.stride, dt) && !getenv("DDG_NO_WIDE") ? 1 : 0;   // (plan_wide_wgrad: how many)
       const int bg = bn_bwd_grid(u.out_elems(), u.cout, dt);
       st_e = (size_t)bg * 2 * u.cout;
       if (st_e > m->ws_stat_elems) m->ws_stat_elems = st_e;
@@ -480,6 +506,12 @@ ddg_status build_plan(ddg_module* m) {
   // device tables: one entry per packed operand / per layer
   // (stale-Jacobian mode: the input-gradient operands are packed per ring slot when a forward
   // pass is kept, from tables of their own; the main table then holds the forward operands only)
+  DDG_OKAY(plan_wide_wgrad(m));
+  for (Blk& b : m->blocks)
+    for (Unit& u : b.u) {
+      DDG_OKAY(dev_alloc(m, &p, wgrad_partial_elems(u.wg) * sizeof(float)));
+      u.wg_partial = (float*)p;
+    }
   std::vector<PackDesc> pd;
   std::vector<std::vector<PackDesc>> pdd(m->stale ? m->nslots : 0);
   std::vector<WredDesc> wd;
@@ -960,6 +992,17 @@ ddg_status flush_pending_wgrad(ddg_module* m) {
   return DDG_OK;
 }
 
+// The launch of the wide layers' weight gradients that have collected.
+ddg_status flush_wide_wgrad(ddg_module* m) {
+  if (m->pend_wide.empty()) return DDG_OK;
+  std::vector<WgradWideLayer> l;
+  l.swap(m->pend_wide);
+  Launch L(m, PK_CONV_WGRAD_WIDE, m->pend_wide_bytes, m->pend_wide_flops);
+  m->pend_wide_bytes = m->pend_wide_flops = 0.0;
+  DDG_TRY(wgrad_wide_launch(l.data(), (int)l.size(), m->stream));
+  return DDG_OK;
+}
+
 // BN backward + weight gradient (+ input gradient) of one unit.
 //   dy: gradient w.r.t. the ReLU output that follows this unit's BN; the ReLU was active where
 //       mask > 0 (or mask*mscale+mshift > 0); mask == null: no ReLU in between
@@ -978,8 +1021,12 @@ ddg_status unit_backward(ddg_module* m, Unit& u, const void* dy, const void* mas
   const int dt = m->d.compute;
   const size_t E = u.out_elems();
   if (below_rows) *below_rows = 0;
-  dz_buf = m->dz_flip ? m->D1b : m->D1;   // not the buffer a pending weight gradient reads
-  m->dz_flip ^= 1;
+  if (u.wide_splits > 0) {
+    dz_buf = m->wide_dz + u.wide_dz;
+  } else {
+    dz_buf = m->dz_flip ? m->D1b : m->D1;   // not the buffer a pending weight gradient reads
+    m->dz_flip ^= 1;
+  }
   if (stats_rows <= 0) {
     stats_rows = bn_bwd_grid(E, u.cout, dt);
     Launch L(m, PK_BN_BWD_REDUCE, (mask && mask != u.z ? 3.0 : 2.0) * E * m->esz);
@@ -1060,13 +1107,15 @@ ddg_status unit_backward(ddg_module* m, Unit& u, const void* dy, const void* mas
       DDG_TRY(bn_bwd_apply_launch(dy, mask, mscale, mshift, u.z, u.coef, nullptr, dz_buf, E, u.cout, dt, m->stream));
     }
     if (x_scale && u.wide_splits == 0) return fail(DDG_ERR_STATE, "internal: generic weight gradient needs a materialised input");
-    Launch L(m, u.wide_splits > 0 ? PK_CONV_WGRAD_WIDE : PK_CONV_WGRAD,
-             (u.in_elems() + E) * (double)m->esz + wbytes(m, u) * 4.0 / m->esz, conv_flops(u));
-    if (u.wide_splits > 0)
-      DDG_TRY(wgrad_wide_launch(x_in, dz_buf, u.wg_partial, u.N, u.H, u.W, u.cin, u.cout, u.R, u.wide_splits, m->stream,
-                                x_scale, x_shift));
-    else
+    const double bytes = (u.in_elems() + E) * (double)m->esz + wbytes(m, u) * 4.0 / m->esz;
+    if (u.wide_splits > 0) {
+      m->pend_wide.push_back({x_in, dz_buf, x_scale, x_shift, u.wg_partial, u.N, u.H, u.W, u.cin, u.cout, u.R, u.wide_splits});
+      m->pend_wide_bytes += bytes; m->pend_wide_flops += conv_flops(u);
+      if (u.wide_launch) DDG_OKAY(flush_wide_wgrad(m));
+    } else {
+      Launch L(m, PK_CONV_WGRAD, bytes, conv_flops(u));
       DDG_TRY(wgrad_launch(w, m->stream));
+    }
   }
   if (dx) {
     // reads dz and the weights, writes dx; plus the shortcut term (and its mask), plus the mask
@@ -1197,6 +1246,7 @@ ddg_status run_backward(ddg_module* m, std::vector<Blk>& blocks, const void* in,
     top_rows = next_top_rows;
     if (bi > 0) { dy = gnext; gnext = (gnext == m->Ga) ? m->Gb : m->Ga; }
   }
+  DDG_OKAY(flush_wide_wgrad(m));
   return flush_pending_wgrad(m);
 }
 

@@ -255,7 +255,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradArgs a) {
 // Few rows (RED_FEW; the wide layers: 7-16 rows of up to 590 thousand outputs): a thread adds all rows of its
 // outputs with every load in flight, a workgroup covers 1024 outputs (1x1: stored as they come) or one output
 // channel (3x3: through LDS into the [ci][r][s] order, so that memory sees whole lines instead of four bytes in every
-// 36). 23 bottleneck blocks, 1.15 GB: 297 -> 251 us.
+// 36). 23 bottleneck blocks, 1.15 GB: 297 -> 251 us; with the 2 rows the wide layers have since, 0.2 GB, four loads instead of sixteen.
 constexpr int RED_FEW = 16, RED_J_MAX = 9 * 512;
 
 __host__ __device__ static inline bool red_few(int rows, int Cout, int Cin, int R, int Jp) {
@@ -274,8 +274,13 @@ __global__ __launch_bounds__(256) void wgrad_reduce_all_kernel(const WredDesc* _
     for (int k = threadIdx.x; k < per; k += 256) {
       const float4* __restrict__ p = reinterpret_cast<const float4*>(d.partial) + (size_t)blockIdx.x * per + k;
       float4 v[RED_FEW];
+      if (d.rows <= 4) {
 #pragma unroll
-      for (int r = 0; r < RED_FEW; ++r) v[r] = p[(size_t)(r < d.rows ? r : d.rows - 1) * total4];
+        for (int r = 0; r < 4; ++r) v[r] = p[(size_t)(r < d.rows ? r : d.rows - 1) * total4];
+      } else {
+#pragma unroll
+        for (int r = 0; r < RED_FEW; ++r) v[r] = p[(size_t)(r < d.rows ? r : d.rows - 1) * total4];
+      }
       float4 c[4];
 #pragma unroll
       for (int rc = 0; rc < 4; ++rc) c[rc] = make_float4(0.f, 0.f, 0.f, 0.f);
