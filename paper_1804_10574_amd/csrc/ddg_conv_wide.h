@@ -39,6 +39,10 @@ __device__ __forceinline__ uint4 wide_load(wide_rsrc_t r, unsigned lane_off, uns
   return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, uniform_off, 0));
 }
 
+__device__ __forceinline__ void wide_store(wide_rsrc_t r, uint4 v, unsigned lane_off) {   // (past the end: dropped)
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), r, lane_off, 0, 0);
+}
+
 // relu(v*sc + sh) of eight bf16 values, rounded back to bf16
 __device__ __forceinline__ uint4 wide_act(uint4 v, const float* sc, const float* sh) {
   float f[8];
@@ -85,6 +89,10 @@ template <int STATS> struct WideTail {
     }
   }
   __device__ __forceinline__ void finish(const ConvWideArgs& a, bf16_t* out, size_t idx, const Ops& o, float (&v)[8]) {
+    *reinterpret_cast<uint4*>(out + idx) = result(a, o, v, true);
+  }
+  // The eight values to store, their sums taken; zeros, and nothing added to the sums, unless `valid` (no branch).
+  __device__ __forceinline__ uint4 result(const ConvWideArgs& a, const Ops& o, float (&v)[8], bool valid) {
     if (a.add_g) {
       float g[8];
       Store<bf16_t>::unpack_vec(o.g, g);
@@ -100,6 +108,7 @@ template <int STATS> struct WideTail {
     uint4 q;
     q.x = Store<bf16_t>::pack2(v[0], v[1]); q.y = Store<bf16_t>::pack2(v[2], v[3]);
     q.z = Store<bf16_t>::pack2(v[4], v[5]); q.w = Store<bf16_t>::pack2(v[6], v[7]);
+    q.x = valid ? q.x : 0u; q.y = valid ? q.y : 0u; q.z = valid ? q.z : 0u; q.w = valid ? q.w : 0u;
     if (STATS == 1) {
       float r[8];
       Store<bf16_t>::unpack_vec(q, r);            // the values as stored
@@ -123,7 +132,7 @@ template <int STATS> struct WideTail {
       q.x = Store<bf16_t>::pack2(r[0], r[1]); q.y = Store<bf16_t>::pack2(r[2], r[3]);   // (exact: bf16 values or zeros)
       q.z = Store<bf16_t>::pack2(r[4], r[5]); q.w = Store<bf16_t>::pack2(r[6], r[7]);
     }
-    *reinterpret_cast<uint4*>(out + idx) = q;
+    return q;
   }
   // Adds the 512 threads' sums per channel in a fixed order and stores the workgroup's row. Thread
   // tid holds channels (tid % (BN/8))*8 ..; red: LDS scratch of 2*BN*(4096/BN + 512/(2*BN)) floats,
@@ -157,5 +166,9 @@ template <int STATS> struct WideTail {
 bool conv_halo_ok(int IC, int W, int R);
 int conv_halo_rows(int M);
 hipError_t conv_halo_launch(const ConvWideArgs& a, int sets, int stats, bool xform, hipStream_t s);
+// 1x1 layers with few contraction channels (kernels_conv_point.hip)
+bool conv_point_ok(int IC, int R);
+int conv_point_rows(int M, int OC, int sets);
+hipError_t conv_point_launch(const ConvWideArgs& a, int sets, int stats, bool xform, hipStream_t s);
 
 }  // namespace ddg

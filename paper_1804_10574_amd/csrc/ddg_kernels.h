@@ -193,7 +193,9 @@ int wgrad_tiled_f32_rows(int N, int H, int W, int Cin, int Cout, int R, int stri
 // stat_partial (optional): [conv_wide_rows()][2][OC] sums / sums of squares of the stored
 // values; add_g / add_mask as in ConvArgs.
 bool conv_wide_ok(int IC, int OC, int R, int stride, int dtype);
-int conv_wide_rows(int M, int W, int IC, int R);   // statistics rows of a launch (one per pixel tile)
+// statistics rows a launch writes per minibatch (sets: minibatches it carries); never more than conv_wide_rows_max()
+int conv_wide_rows(int M, int W, int IC, int OC, int R, int sets);
+int conv_wide_rows_max(int M);
 // scale/shift (optional, forward only): the conv input is relu(in*scale + shift) per input
 // channel, applied while staging.
 // second (optional, forward only): a second minibatch in the same launch, same weights.

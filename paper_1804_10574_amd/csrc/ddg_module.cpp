@@ -407,9 +407,13 @@ ddg_status build_plan(ddg_module* m) {
       if (u.tiled_grid > 0) f.grid_x = u.tiled_grid;   // the generic kernel never runs this layer
       u.wide_f = conv_wide_ok(u.cin, u.cout, u.R, u.stride, dt) && !getenv("DDG_NO_WIDE");
       u.wide_d = u.has_dgrad && conv_wide_ok(u.cout, u.cin, u.R, u.stride, dt) && !getenv("DDG_NO_WIDE");
-      if (u.wide_f) f.grid_x = conv_wide_rows(f.M, u.W, u.cin, u.R);
+      if (u.wide_f) {
+        f.grid_x = conv_wide_rows(f.M, u.W, u.cin, u.cout, u.R, 1);
+        const int two = conv_wide_rows(f.M, u.W, u.cin, u.cout, u.R, 2);
+        if (two > f.grid_x) f.grid_x = two;
+      }
       u.fcap = f.grid_x;
-      u.frows = u.fcap;    // what the forward conv of this layer writes (the same every time)
+      u.frows = u.fcap;    // what the last forward conv of this layer wrote per group
       size_t st_e = (size_t)f.grid_x * 2 * u.cout;
       if (st_e > m->ws_stat_elems) m->ws_stat_elems = st_e;
       { void* sp = nullptr;
@@ -419,8 +423,8 @@ ddg_status build_plan(ddg_module* m) {
         // kernel of the layer above (at most conv_tiled_max_grid() workgroups)
         int brows = bn_bwd_grid(u.out_elems(), u.cout, dt);
         if (conv_tiled_max_grid() > brows) brows = conv_tiled_max_grid();
-        // (or from the GEMM-class input-gradient kernel above: one row per 64 pixels at most; its halo form writes half of that)
-        if (u.cout % 128 == 0 && conv_wide_rows(N * u.P * u.Q, u.Q, u.cout, 1) > brows) brows = conv_wide_rows(N * u.P * u.Q, u.Q, u.cout, 1);
+        // (or from the GEMM-class input-gradient kernel above: one row per 64 pixels at most)
+        if (u.cout % 128 == 0 && conv_wide_rows_max(N * u.P * u.Q) > brows) brows = conv_wide_rows_max(N * u.P * u.Q);
         DDG_OKAY(dev_alloc(m, &sp, (size_t)brows * 2 * u.cout * sizeof(float)));
         u.bstat = (float*)sp; }
       // input gradient
@@ -682,7 +686,7 @@ ddg_status unit_forward(ddg_module* m, Unit& u, const void* in, Unit* src, const
   } else {
     if (src && !u.wide_f) return fail(DDG_ERR_STATE, "internal: generic conv needs a materialised input");
     if (u.wide_f) {
-      u.frows = conv_wide_rows(u.N * u.P * u.Q, u.W, u.cin, u.R);
+      u.frows = conv_wide_rows(u.N * u.P * u.Q, u.W, u.cin, u.cout, u.R, 1);
       const int svo = src ? g * src->vec_stride() : 0;   // (a wide producer's vectors are final: it ran its finalise launch)
       Launch L(m, PK_CONV_FPROP_WIDE, (u.in_elems() + u.out_elems()) * (double)m->esz + wbytes(m, u), conv_flops(u));
       DDG_TRY(conv_wide_launch(in, u.wpack_f, z, fstat, nullptr, nullptr, u.N, u.H, u.W, u.cin, u.cout, u.R, m->stream,
@@ -781,7 +785,7 @@ ddg_status unit_forward_two(ddg_module* m, Unit& u, const void* in0, const void*
   float* fstat1 = u.fstat + (size_t)u.fcap * 2 * u.cout;
   const double bytes = 2.0 * ((u.in_elems() + u.out_elems()) * (double)m->esz) + wbytes(m, u);
   if (u.wide_f) {
-    u.frows = conv_wide_rows(u.N * u.P * u.Q, u.W, u.cin, u.R);
+    u.frows = conv_wide_rows(u.N * u.P * u.Q, u.W, u.cin, u.cout, u.R, 2);
     const int sv = src ? src->vec_stride() : 0;
     ConvWideSecond sec{in1, z1, fstat1, src ? src->scale + sv : nullptr, src ? src->shift + sv : nullptr};
     Launch L(m, PK_CONV_FPROP_WIDE, bytes, 2.0 * conv_flops(u));
@@ -1133,7 +1137,7 @@ ddg_status unit_backward(ddg_module* m, Unit& u, const void* dy, const void* mas
         st.mode = 2; st.partial = below->u->bstat;
         st.mask = below->mask; st.mscale = below->mscale; st.mshift = below->mshift;
         st.z = below->u->z; st.zmean = below->u->mean; st.zinvstd = below->u->invstd;
-        if (below_rows) *below_rows = conv_wide_rows(u.N * u.H * u.W, u.W, u.cout, u.R);
+        if (below_rows) *below_rows = conv_wide_rows(u.N * u.H * u.W, u.W, u.cout, u.cin, u.R, 1);
       }
       DDG_TRY(conv_wide_launch(dz_buf, u.wpack_d, dx, nullptr, add_g, add_mask, u.N, u.P, u.Q, u.cout, u.cin, u.R, m->stream,
                                nullptr, nullptr, nullptr, wide_below ? &st : nullptr));

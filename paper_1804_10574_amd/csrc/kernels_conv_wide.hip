@@ -368,7 +368,10 @@ bool conv_wide_ok(int IC, int OC, int R, int stride, int dtype) {
   if (IC < 64 || (IC & (IC - 1)) != 0) return false;      // power of two: k = tap*IC + channel in the packed operand
   return OC % wide::BN == 0;
 }
-int conv_wide_rows(int M, int W, int IC, int R) { return conv_halo_ok(IC, W, R) ? conv_halo_rows(M) : (M + wide::BM - 1) / wide::BM; }
+int conv_wide_rows_max(int M) { return (M + wide::BM - 1) / wide::BM; }
+int conv_wide_rows(int M, int W, int IC, int OC, int R, int sets) {
+  return conv_point_ok(IC, R) ? conv_point_rows(M, OC, sets) : conv_halo_ok(IC, W, R) ? conv_halo_rows(M) : conv_wide_rows_max(M);
+}
 
 hipError_t conv_wide_launch(const void* in, const void* wpack, void* out, float* stat_partial, const void* add_g,
                             const void* add_mask, int N, int H, int W, int IC, int OC, int R, hipStream_t s,
@@ -397,7 +400,8 @@ hipError_t conv_wide_launch(const void* in, const void* wpack, void* out, float*
   const bool xf = scale != nullptr;
   if (xf && (add_g || IC > 2048)) return hipErrorInvalidValue;   // forward only; the table lives in LDS
   if (conv_halo_ok(IC, W, R)) return conv_halo_launch(a, second ? 2 : 1, stats, xf, s);
-  const dim3 grid(conv_wide_rows((int)M, W, IC, R), OC / wide::BN, second ? 2 : 1);
+  if (conv_point_ok(IC, R)) return conv_point_launch(a, second ? 2 : 1, stats, xf, s);
+  const dim3 grid(conv_wide_rows_max((int)M), OC / wide::BN, second ? 2 : 1);
   // few tiles (one workgroup per compute unit at most): the long chunk; else two workgroups per unit
   const bool long_chunk = IC >= 128 && grid.x * grid.y * grid.z <= 256;
   if (R == 3)

@@ -63,7 +63,7 @@ def kind_of(kernel_name: str) -> str:
     m = re.match(r"wgrad_tiled_kernel<(\d+), (\d+), (\d+), (\d+), (\d+)>", n)
     if m:   # <Cin, Cout, output width, stride, kernel size>
         return "conv_wgrad.tiled_stride2" if m.group(4) == "2" else f"conv_wgrad.tiled_c{m.group(1)}_w{m.group(3)}"
-    m = re.match(r"conv_(?:wide|halo)_kernel<(\d+), ", n)
+    m = re.match(r"conv_(?:wide|halo|point)_kernel<(\d+), ", n)
     if m:   # <STATS, ...>: 1 = forward statistics (the forward conv); 0 / 2 = the input gradient
         return "conv_fprop.wide" if m.group(1) == "1" else "conv_dgrad.wide"
     if n.startswith("wgrad_wide_kernel"):

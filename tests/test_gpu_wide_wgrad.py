@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 CASES = [(9, 2, 3, 128, 128),      # 27 layers: more than a launch takes
          (8, 1, 5, 1024, 256),     # 25 pixels, one step: 544 tiles for 512 places
          (1, 50, 8, 128, 128),     # 3200 pixels, 50 steps: one more than a slice may have
-         (2, 130, 7, 256, 128)]    # 6370 pixels, ragged last step, several image rows per advance
+         (2, 130, 7, 256, 128),    # 6370 pixels, ragged last step, several image rows per advance
+         (1, 129, 8, 512, 128)]    # 129 statistics rows behind the 512-channel layers, 43 behind the 128-channel 1x1 layer
 
 
 @pytest.mark.parametrize("blocks,batch,hw,c,cmid", CASES)
