@@ -57,6 +57,9 @@ struct ConvArgs {
   const void* in_b; void* out_b; float* stat_partial_b;
   const void* add_g;        // optional: out += add_g (masked where add_mask <= 0), same layout as out
   const void* add_mask;
+  // optional (3x3 stride-2 input gradient that conv_dgrad_s2_ok accepts): the block's projection, 1x1 with the same stride
+  // and channels, whose input gradient is added: its error gradient and its packed operand
+  const void* proj_in; const void* proj_wpack;
   int N, IH, IW, IC, OH, OW, OC;
   int R, stride, pad;
   int log2cp;               // log2 of the padded contraction channels per tap
@@ -68,7 +71,10 @@ struct ConvArgs {
   int mb, nb;               // tile shape chosen by conv_plan
 };
 void conv_plan(ConvArgs& a);                       // chooses tile shape and grid
-hipError_t conv_launch(const ConvArgs& a, hipStream_t s);
+// other (optional, forward): a second convolution in the same launch, one that conv_shares_launch accepts
+hipError_t conv_launch(const ConvArgs& a, hipStream_t s, const ConvArgs* other = nullptr);
+bool conv_shares_launch(const ConvArgs& a, const ConvArgs& b);
+bool conv_dgrad_s2_ok(const ConvArgs& a);     // does the kernel for stride-2 input gradients cover it?
 size_t conv_wpack_elems(int kchannels, int nchannels, int R, int dtype, int* log2cp, int* ksteps);
 // Packs fp32 master weights W[Cout][Cin][R][R] into the operand layout of conv_launch.
 // dgrad: 0 forward operand, 1 input-gradient operand (taps as stored), 2 input-gradient operand
@@ -92,6 +98,9 @@ void wgrad_plan(WgradArgs& a);
 size_t wgrad_partial_elems(const WgradArgs& a);
 hipError_t wgrad_launch(const WgradArgs& a, hipStream_t s);
 hipError_t wgrad_reduce_launch(const WgradArgs& a, hipStream_t s);
+// A layer's weight gradient and input gradient in one launch (generic kernels).
+bool bwd_generic_ok(const WgradArgs& w, const ConvArgs& a);
+hipError_t bwd_generic_launch(const WgradArgs& w, const ConvArgs& a, hipStream_t s);
 
 // Whole-module variants driven by a device-side table (one launch per module instead of one
 // per layer): repack every conv operand after an update; add up every layer's weight-gradient
@@ -132,7 +141,13 @@ int wgrad_tiled_rows(int N, int H, int W, int Cin, int Cout, int R, int stride, 
 hipError_t wgrad_tiled_launch(const void* x, const float* scale, const float* shift, const void* dz,
                               const WgradFuse* fuse, float* partial, int N, int H, int W, int C, int rows,
                               hipStream_t s, int Cout = 0, int R = 3, int stride = 1);
-
+// The three weight gradients of a stage's first block in one launch: the 3x3 stride-2 layer and the 1x1 projection (both
+// form their dz from a WgradFuse; x [N][H][W][C], Cout = 2*C) and the plain one of the block's second layer.
+hipError_t wgrad_down_launch(const void* x, int N, int H, int W, int C, const WgradFuse& f3, float* partial3, int rows3,
+                             const WgradFuse& f1, float* partial1, int rows1, const WgradPair& second, hipStream_t s);
+// The same for fp32, where the stride-2 layers run the generic kernel (a3, a1: their plans with x, dz, partial filled in).
+hipError_t wgrad_down_f32_launch(const WgradArgs& a3, const WgradArgs& a1, const WgradPair& second, hipStream_t s);
+bool wgrad_down_f32_ok(const WgradArgs& a3, const WgradArgs& a1);
 
 // LDS-tiled 3x3/stride-1 convolution for 16/32/64 channels (bf16). Returns the grid (= number of
 // statistics rows), 0 if the shape is not covered. scale/shift: optional relu(in*scale+shift)
@@ -252,17 +267,19 @@ hipError_t bn_bwd_apply_wide_launch(const void* dy, const void* mask, const floa
 // mask*mscale+mshift > 0 when mscale is given (the mask tensor is then the conv output the
 // activation derives from); mask == nullptr: g = dy. partial[grid][2][C] = (sum g, sum g*xhat)
 int bn_bwd_grid(size_t elems, int C, int dtype);
-hipError_t bn_bwd_reduce_launch(const void* dy, const void* mask, const float* mscale, const float* mshift,
-                                const void* z, const float* mean, const float* invstd, float* partial,
-                                size_t elems, int C, int dtype, hipStream_t s);
+// One layer's share of a backward launch: what the two kernels below read and write.
+struct BnBwdSet {
+  const void* dy; const void* mask; const float* mscale; const float* mshift; const void* z;
+  const float* mean; const float* invstd; float* partial;    // reduce
+  const float* coef; BnBwdRows rows; void* dz;               // apply: final coefficients [3][C], or rows (C <= 64) to derive them from
+};
+// other (optional): a second layer of the same shape in the launch.
+hipError_t bn_bwd_reduce_launch(const BnBwdSet& q, const BnBwdSet* other, size_t elems, int C, int dtype, hipStream_t s);
 // dgamma, dbeta and the coefficients of dz = A*g + B*z + C0 (per channel; coef = [3][C])
 hipError_t bn_bwd_finalize_launch(const float* partial, int rows, int C, const float* gamma,
                                   const float* mean, const float* invstd, float count, float* dgamma,
                                   float* dbeta, float* coef, hipStream_t s);
-// coef: final coefficients [3][C], or rows (optional, C <= 64) to derive them from.
-hipError_t bn_bwd_apply_launch(const void* dy, const void* mask, const float* mscale, const float* mshift,
-                               const void* z, const float* coef, const BnBwdRows* rows, void* dz, size_t elems,
-                               int C, int dtype, hipStream_t s);
+hipError_t bn_bwd_apply_launch(const BnBwdSet& q, const BnBwdSet* other, size_t elems, int C, int dtype, hipStream_t s);
 
 // Head: global average pool, linear, softmax cross-entropy (mean over the batch) and its gradients.
 struct HeadArgs {

@@ -653,6 +653,34 @@ BnRows fwd_rows(ddg_module* m, Unit& u, int g = 0) {
   return r;
 }
 
+// May the forward convolutions of two units share a launch (generic kernel, same input)?
+bool shares_forward(const Unit& a, const Unit& b) {
+  return a.tiled_grid == 0 && b.tiled_grid == 0 && !a.wide_f && !b.wide_f && conv_shares_launch(a.fprop, b.fprop);
+}
+// The block's projection, if it can join the launch of the block's first convolution.
+Unit* forward_partner(Blk& b) { return b.proj && shares_forward(b.u[0], b.u[b.nmain]) ? &b.u[b.nmain] : nullptr; }
+
+// The generic forward launch of group g of a unit.
+ConvArgs forward_args(ddg_module* m, Unit& u, const void* in, int g) {
+  ConvArgs a = u.fprop;
+  conv_plan(a);
+  u.frows = a.grid_x;
+  a.in = in; a.wpack = u.wpack_f; a.out = grp(u.z, u.out_elems() * m->esz, g);
+  a.stat_partial = u.fstat + (size_t)g * u.fcap * 2 * u.cout; a.add_g = nullptr; a.add_mask = nullptr;
+  return a;
+}
+// The launch that finalises the statistics of a unit none of whose consumers does (evaluation normalises with the
+// running estimates).
+ddg_status finalize_forward(ddg_module* m, Unit& u, int g) {
+  if (u.small_c() || u.fin_in_apply || m->eval_mode) return DDG_OK;
+  const int vo = g * u.vec_stride();
+  Launch L(m, PK_BN_FINALIZE);
+  DDG_TRY(bn_finalize_launch(u.fstat + (size_t)g * u.fcap * 2 * u.cout, u.frows, u.cout, m->theta + u.og, m->theta + u.ob,
+                             (float)((size_t)u.N * u.P * u.Q), m->d.bn_eps, u.mean + vo, u.invstd + vo, u.scale + vo,
+                             u.shift + vo, m->stream));
+  return DDG_OK;
+}
+
 // conv of one unit: in -> u.z plus partial rows of its batch statistics. For 16/32/64 channels
 // the consumer of the BN output derives mean/invstd/scale/shift from the rows (and stores
 // them); wider layers get a finalise launch here. `src`, if given, is the unit whose BN + ReLU
@@ -661,13 +689,13 @@ BnRows fwd_rows(ddg_module* m, Unit& u, int g = 0) {
 // stores to y_store: that block's separate normalise-add-ReLU pass is absorbed.
 // Groups: the launch covers G minibatches starting with group g (G = 2 needs g = 0 and the
 // tiled kernel); in, res and y_store point at group g, whose successors follow contiguously.
+// partner (optional): the block's projection, whose convolution of the same input joins the launch (shares_forward).
 ddg_status unit_forward(ddg_module* m, Unit& u, const void* in, Unit* src, const void* res = nullptr,
-                        void* y_store = nullptr, int G = 1, int g = 0) {
+                        void* y_store = nullptr, int G = 1, int g = 0, Unit* partner = nullptr) {
   if (res && !(u.tiled_grid > 0 && src)) return fail(DDG_ERR_STATE, "internal: residual input needs the tiled kernel");
   if (G > 1 && !(u.tiled_grid > 0 && g == 0 && G <= m->groups)) return fail(DDG_ERR_STATE, "internal: grouped launch needs the tiled kernel");
   void* z = grp(u.z, u.out_elems() * m->esz, g);
   float* fstat = u.fstat + (size_t)g * u.fcap * 2 * u.cout;
-  const int vo = g * u.vec_stride();
   if (u.tiled_grid > 0) {
     u.frows = u.tiled_grid;
     ConvStat st{};
@@ -693,23 +721,20 @@ ddg_status unit_forward(ddg_module* m, Unit& u, const void* in, Unit* src, const
                                !src ? nullptr : (m->eval_mode ? src->escale : src->scale + svo),
                                !src ? nullptr : (m->eval_mode ? src->eshift : src->shift + svo)));
     } else {
-      ConvArgs a = u.fprop;
-      conv_plan(a);
-      u.frows = a.grid_x;
-      a.in = in; a.wpack = u.wpack_f; a.out = z; a.stat_partial = fstat; a.add_g = nullptr; a.add_mask = nullptr;
-      Launch L(m, PK_CONV_FPROP, (u.in_elems() + u.out_elems()) * (double)m->esz + wbytes(m, u), conv_flops(u));
-      DDG_TRY(conv_launch(a, m->stream));
+      const ConvArgs a = forward_args(m, u, in, g);
+      ConvArgs q{};
+      double bytes = (u.in_elems() + u.out_elems()) * (double)m->esz + wbytes(m, u), flops = conv_flops(u);
+      if (partner) {
+        q = forward_args(m, *partner, in, g);
+        bytes += partner->out_elems() * (double)m->esz + wbytes(m, *partner); flops += conv_flops(*partner);
+      }
+      Launch L(m, PK_CONV_FPROP, bytes, flops);
+      DDG_TRY(conv_launch(a, m->stream, partner ? &q : nullptr));
     }
   }
-  if (!u.small_c() && !u.fin_in_apply && !m->eval_mode) {   // (evaluation normalises with the running estimates)
-    Launch L(m, PK_BN_FINALIZE);
-    DDG_TRY(bn_finalize_launch(fstat, u.frows, u.cout, m->theta + u.og, m->theta + u.ob,
-                               (float)((size_t)u.N * u.P * u.Q), m->d.bn_eps, u.mean + vo, u.invstd + vo, u.scale + vo,
-                               u.shift + vo, m->stream));
-  }
-  return DDG_OK;
+  if (partner) DDG_OKAY(finalize_forward(m, *partner, g));
+  return finalize_forward(m, u, g);
 }
-
 // What bn_apply_wide_launch needs for group g of a unit whose statistics that kernel finalises.
 BnApplySet wide_apply_set(ddg_module* m, Unit& u, const void* res, Unit* ru, void* y, int g) {
   BnApplySet q{};
@@ -747,9 +772,10 @@ ddg_status apply_bn(ddg_module* m, Unit& u, const void* res, Unit* ru, void* y, 
 ddg_status block_forward(ddg_module* m, Blk& b, const void* x, void* y, int g) {
   const void* cur = x;
   Unit* src = nullptr;   // pending relu(bn(.)) of `cur`
+  Unit* partner = forward_partner(b);
   for (int i = 0; i < b.nmain; ++i) {
     Unit& u = b.u[i];
-    DDG_OKAY(unit_forward(m, u, cur, src, nullptr, nullptr, 1, g));
+    DDG_OKAY(unit_forward(m, u, cur, src, nullptr, nullptr, 1, g, i == 0 ? partner : nullptr));
     src = nullptr;
     if (i + 1 < b.nmain) {
       if (b.act[i]) {
@@ -765,7 +791,7 @@ ddg_status block_forward(ddg_module* m, Blk& b, const void* x, void* y, int g) {
   if (b.kind == DDG_BLOCK_STEM) return apply_bn(m, ul, nullptr, nullptr, y, g);
   if (b.proj) {
     Unit& up = b.u[b.nmain];
-    DDG_OKAY(unit_forward(m, up, x, nullptr, nullptr, nullptr, 1, g));
+    if (!partner) DDG_OKAY(unit_forward(m, up, x, nullptr, nullptr, nullptr, 1, g));
     return apply_bn(m, ul, nullptr, &up, y, g);
   }
   return apply_bn(m, ul, x, nullptr, y, g);
@@ -774,7 +800,7 @@ ddg_status block_forward(ddg_module* m, Blk& b, const void* x, void* y, int g) {
 // The same conv for the two minibatches of a paired forward pass (groups 0 and 1) in one launch
 // where the kernel can: the tiled kernel when the two inputs lie one group apart, the generic
 // and the GEMM-class kernels always (they take a second set of pointers).
-ddg_status unit_forward_two(ddg_module* m, Unit& u, const void* in0, const void* in1, Unit* src) {
+ddg_status unit_forward_two(ddg_module* m, Unit& u, const void* in0, const void* in1, Unit* src, Unit* partner = nullptr) {
   if (u.tiled_grid > 0) {
     if ((const char*)in1 == (const char*)in0 + u.in_elems() * m->esz) return unit_forward(m, u, in0, src, nullptr, nullptr, 2, 0);
     DDG_OKAY(unit_forward(m, u, in0, src, nullptr, nullptr, 1, 0));
@@ -792,19 +818,25 @@ ddg_status unit_forward_two(ddg_module* m, Unit& u, const void* in0, const void*
     DDG_TRY(conv_wide_launch(in0, u.wpack_f, u.z, u.fstat, nullptr, nullptr, u.N, u.H, u.W, u.cin, u.cout, u.R, m->stream,
                              src ? src->scale : nullptr, src ? src->shift : nullptr, &sec));
   } else {
-    ConvArgs a = u.fprop;
-    conv_plan(a);
-    u.frows = a.grid_x;
-    a.in = in0; a.wpack = u.wpack_f; a.out = u.z; a.stat_partial = u.fstat; a.add_g = nullptr; a.add_mask = nullptr;
-    a.in_b = in1; a.out_b = z1; a.stat_partial_b = fstat1;
-    Launch L(m, PK_CONV_FPROP, bytes, 2.0 * conv_flops(u));
-    DDG_TRY(conv_launch(a, m->stream));
+    auto two = [&](Unit& q) {
+      ConvArgs a = forward_args(m, q, in0, 0);
+      const ConvArgs b = forward_args(m, q, in1, 1);
+      a.in_b = b.in; a.out_b = b.out; a.stat_partial_b = b.stat_partial;
+      return a;
+    };
+    const ConvArgs a = two(u);
+    ConvArgs q{};
+    if (partner) q = two(*partner);
+    Launch L(m, PK_CONV_FPROP, bytes + (partner ? 2.0 * partner->out_elems() * m->esz + wbytes(m, *partner) : 0.0),
+             2.0 * (conv_flops(u) + (partner ? conv_flops(*partner) : 0.0)));
+    DDG_TRY(conv_launch(a, m->stream, partner ? &q : nullptr));
   }
-  if (!u.small_c() && !u.fin_in_apply) {
+  for (Unit* f : {partner, &u}) {
+    if (!f || f->small_c() || f->fin_in_apply) continue;
     Launch L(m, PK_BN_FINALIZE);
-    DDG_TRY(bn_finalize_launch(u.fstat, u.frows, u.cout, m->theta + u.og, m->theta + u.ob,
-                               (float)((size_t)u.N * u.P * u.Q), m->d.bn_eps, u.mean, u.invstd, u.scale, u.shift, m->stream,
-                               fstat1, u.mean + u.vec_stride()));
+    DDG_TRY(bn_finalize_launch(f->fstat, f->frows, f->cout, m->theta + f->og, m->theta + f->ob,
+                               (float)((size_t)f->N * f->P * f->Q), m->d.bn_eps, f->mean, f->invstd, f->scale, f->shift, m->stream,
+                               f->fstat + (size_t)f->fcap * 2 * f->cout, f->mean + f->vec_stride()));
   }
   return DDG_OK;
 }
@@ -847,9 +879,10 @@ ddg_status apply_bn_two(ddg_module* m, Unit& u, const void* res0, const void* re
 ddg_status block_forward_two(ddg_module* m, Blk& b, const void* x0, const void* x1, void* y0, void* y1) {
   const void* c0 = x0; const void* c1 = x1;
   Unit* src = nullptr;   // pending relu(bn(.)) of the current tensors
+  Unit* partner = forward_partner(b);
   for (int i = 0; i < b.nmain; ++i) {
     Unit& u = b.u[i];
-    DDG_OKAY(unit_forward_two(m, u, c0, c1, src));
+    DDG_OKAY(unit_forward_two(m, u, c0, c1, src, i == 0 ? partner : nullptr));
     src = nullptr;
     if (i + 1 < b.nmain) {
       if (b.act[i]) {
@@ -865,7 +898,7 @@ ddg_status block_forward_two(ddg_module* m, Blk& b, const void* x0, const void* 
   if (b.kind == DDG_BLOCK_STEM) return apply_bn_two(m, ul, nullptr, nullptr, nullptr, y0, y1);
   if (b.proj) {
     Unit& up = b.u[b.nmain];
-    DDG_OKAY(unit_forward_two(m, up, x0, x1, nullptr));
+    if (!partner) DDG_OKAY(unit_forward_two(m, up, x0, x1, nullptr));
     return apply_bn_two(m, ul, nullptr, nullptr, &up, y0, y1);
   }
   return apply_bn_two(m, ul, x0, x1, nullptr, y0, y1);
@@ -940,9 +973,10 @@ ddg_status run_forward(ddg_module* m, std::vector<Blk>& blocks, const void* in, 
       x = pend.y;          // materialised by this block's first conv
       pend.u = nullptr;
     }
+    Unit* partner = forward_partner(b);
     for (int i = 0; i < b.nmain; ++i) {
       Unit& u = b.u[i];
-      DDG_OKAY(unit_forward(m, u, cur, src, i == 0 ? res_in : nullptr, i == 0 ? y_store : nullptr));
+      DDG_OKAY(unit_forward(m, u, cur, src, i == 0 ? res_in : nullptr, i == 0 ? y_store : nullptr, 1, 0, i == 0 ? partner : nullptr));
       src = nullptr;
       if (i + 1 < b.nmain) {
         if (b.act[i]) {
@@ -958,7 +992,7 @@ ddg_status run_forward(ddg_module* m, std::vector<Blk>& blocks, const void* in, 
       DDG_OKAY(apply_bn(m, ul, nullptr, nullptr, yout));
     } else if (b.proj) {
       Unit& up = b.u[b.nmain];
-      DDG_OKAY(unit_forward(m, up, x, nullptr));
+      if (!partner) DDG_OKAY(unit_forward(m, up, x, nullptr));
       DDG_OKAY(apply_bn(m, ul, nullptr, &up, yout));
     } else {
       bool defer = false;
@@ -994,6 +1028,27 @@ ddg_status flush_pending_wgrad(ddg_module* m) {
   DDG_TRY(wgrad_tiled_any(m, w.x, w.xsc, w.xsh, w.dz, nullptr, u.wg_partial, u.N, u.H, u.W, u.cin, u.wg_tiled_rows,
                              m->stream));
   return DDG_OK;
+}
+
+// The BN-backward sums of u as partial rows for a consuming kernel.
+BnBwdRows bwd_rows(ddg_module* m, const Unit& u, int rows) {
+  BnBwdRows br{};
+  br.partial = u.bstat; br.rows = rows; br.gamma = m->theta_bwd + u.og; br.mean = u.mean; br.invstd = u.invstd;
+  br.inv_count = 1.0 / (double)((size_t)u.N * u.P * u.Q); br.dgamma = m->grad + u.og; br.dbeta = m->grad + u.ob;
+  return br;
+}
+
+// A layer's share of the reduction and of the elementwise launch of the batch-norm backward (rows null: final coefficients).
+BnBwdSet reduce_set(const Unit& u, const void* dy, const void* mask, const float* mscale, const float* mshift) {
+  BnBwdSet q{};
+  q.dy = dy; q.mask = mask; q.mscale = mscale; q.mshift = mshift; q.z = u.z; q.mean = u.mean; q.invstd = u.invstd; q.partial = u.bstat;
+  return q;
+}
+BnBwdSet apply_set(const Unit& u, const void* dy, const void* mask, const float* mscale, const float* mshift, const BnBwdRows* rows, void* dz) {
+  BnBwdSet q{};
+  q.dy = dy; q.mask = mask; q.mscale = mscale; q.mshift = mshift; q.z = u.z; q.dz = dz;
+  if (rows) q.rows = *rows; else q.coef = u.coef;
+  return q;
 }
 
 // The launch of the wide layers' weight gradients that have collected.
@@ -1034,11 +1089,9 @@ ddg_status unit_backward(ddg_module* m, Unit& u, const void* dy, const void* mas
   if (stats_rows <= 0) {
     stats_rows = bn_bwd_grid(E, u.cout, dt);
     Launch L(m, PK_BN_BWD_REDUCE, (mask && mask != u.z ? 3.0 : 2.0) * E * m->esz);
-    DDG_TRY(bn_bwd_reduce_launch(dy, mask, mscale, mshift, u.z, u.mean, u.invstd, u.bstat, E, u.cout, dt, m->stream));
+    DDG_TRY(bn_bwd_reduce_launch(reduce_set(u, dy, mask, mscale, mshift), nullptr, E, u.cout, dt, m->stream));
   }
-  BnBwdRows br{};
-  br.partial = u.bstat; br.rows = stats_rows; br.gamma = m->theta_bwd + u.og; br.mean = u.mean; br.invstd = u.invstd;
-  br.inv_count = 1.0 / (double)((size_t)u.N * u.P * u.Q); br.dgamma = m->grad + u.og; br.dbeta = m->grad + u.ob;
+  const BnBwdRows br = bwd_rows(m, u, stats_rows);
   if (m->defer_wgrad && u.wg_tiled_rows > 0 && u.tiled_grid > 0 && dx && dx != dy) {   // (a halo kernel cannot work in place)
     // The input-gradient kernel forms dz = BN-backward(dy) while staging (coefficients from the
     // rows), stores it, convolves it, and forms the sums of the unit below in its epilogue. The
@@ -1099,7 +1152,7 @@ ddg_status unit_backward(ddg_module* m, Unit& u, const void* dy, const void* mas
     if (u.small_c()) {
       // the apply kernel derives dgamma, dbeta and its coefficients from the rows
       Launch L(m, PK_BN_BWD_APPLY, (mask && mask != u.z ? 4.0 : 3.0) * E * m->esz);
-      DDG_TRY(bn_bwd_apply_launch(dy, mask, mscale, mshift, u.z, nullptr, &br, dz_buf, E, u.cout, dt, m->stream));
+      DDG_TRY(bn_bwd_apply_launch(apply_set(u, dy, mask, mscale, mshift, &br, dz_buf), nullptr, E, u.cout, dt, m->stream));
     } else if (bn_rows_wide_ok(stats_rows, u.cout)) {
       Launch L(m, PK_BN_BWD_APPLY, (mask && mask != u.z ? 4.0 : 3.0) * E * m->esz);
       DDG_TRY(bn_bwd_apply_wide_launch(dy, mask, mscale, mshift, u.z, br, dz_buf, u.N * u.P * u.Q, u.cout, dt, m->stream));
@@ -1108,7 +1161,7 @@ ddg_status unit_backward(ddg_module* m, Unit& u, const void* dy, const void* mas
         DDG_TRY(bn_bwd_finalize_launch(u.bstat, stats_rows, u.cout, m->theta_bwd + u.og, u.mean, u.invstd,
                                        (float)((size_t)u.N * u.P * u.Q), m->grad + u.og, m->grad + u.ob, u.coef, m->stream)); }
       Launch L(m, PK_BN_BWD_APPLY, (mask && mask != u.z ? 4.0 : 3.0) * E * m->esz);
-      DDG_TRY(bn_bwd_apply_launch(dy, mask, mscale, mshift, u.z, u.coef, nullptr, dz_buf, E, u.cout, dt, m->stream));
+      DDG_TRY(bn_bwd_apply_launch(apply_set(u, dy, mask, mscale, mshift, nullptr, dz_buf), nullptr, E, u.cout, dt, m->stream));
     }
     if (x_scale && u.wide_splits == 0) return fail(DDG_ERR_STATE, "internal: generic weight gradient needs a materialised input");
     const double bytes = (u.in_elems() + E) * (double)m->esz + wbytes(m, u) * 4.0 / m->esz;
@@ -1116,6 +1169,13 @@ ddg_status unit_backward(ddg_module* m, Unit& u, const void* dy, const void* mas
       m->pend_wide.push_back({x_in, dz_buf, x_scale, x_shift, u.wg_partial, u.N, u.H, u.W, u.cin, u.cout, u.R, u.wide_splits});
       m->pend_wide_bytes += bytes; m->pend_wide_flops += conv_flops(u);
       if (u.wide_launch) DDG_OKAY(flush_wide_wgrad(m));
+    } else if (dx && u.tiled_grid == 0 && !u.wide_d && bwd_generic_ok(w, u.dgrad)) {
+      ConvArgs a = u.dgrad;
+      a.in = dz_buf; a.wpack = u.wpack_d; a.out = dx; a.stat_partial = nullptr;
+      a.add_g = add_g; a.add_mask = add_mask;
+      Launch L(m, PK_CONV_DGRAD, bytes + (E + (add_g ? (add_mask ? 3.0 : 2.0) : 1.0) * u.in_elems()) * m->esz + wbytes(m, u), 2.0 * conv_flops(u));
+      DDG_TRY(bwd_generic_launch(w, a, m->stream));
+      return DDG_OK;
     } else {
       Launch L(m, PK_CONV_WGRAD, bytes, conv_flops(u));
       DDG_TRY(wgrad_launch(w, m->stream));
@@ -1158,6 +1218,63 @@ ddg_status unit_backward(ddg_module* m, Unit& u, const void* dy, const void* mas
       DDG_TRY(conv_launch(a, m->stream));
     }
   }
+  return DDG_OK;
+}
+
+// The first block of a stage (stride 2, projection) whose second layer has the tiled kernels: its parts that do not depend on
+// each other share launches.
+bool down_block(const ddg_module* m, const Blk& b) {
+  return b.kind == DDG_BLOCK_BASIC && b.proj && b.nmain == 2 && b.u[0].stride == 2 && b.u[1].tiled_grid > 0 && !b.act[0] && m->defer_wgrad &&
+         b.u[1].wg_tiled_rows > 0 &&
+         (m->d.compute == DDG_F32 ? wgrad_down_f32_ok(b.u[0].wg, b.u[2].wg) : b.u[0].wg_tiled_rows > 0 && b.u[2].wg_tiled_rows > 0);
+}
+// Backward of such a block, dy and ymask as in run_backward; dx: its input gradient, or null.
+ddg_status down_block_backward(ddg_module* m, Blk& b, const void* dy, const void* ymask, int top_rows, const void* x, void* dx) {
+  Unit &u0 = b.u[0], &u1 = b.u[1], &up = b.u[2];
+  const size_t E = up.out_elems();
+  const int prows = bn_bwd_grid(E, up.cout, m->d.compute);
+  { // (both layers' sums, where the kernel that produced dy did not form those of the second layer)
+    const BnBwdSet qp = reduce_set(up, dy, ymask, nullptr, nullptr), q1 = reduce_set(u1, dy, ymask, nullptr, nullptr);
+    Launch L(m, PK_BN_BWD_REDUCE, (top_rows > 0 ? 1.0 : 2.0) * (ymask ? 3.0 : 2.0) * E * m->esz);
+    DDG_TRY(bn_bwd_reduce_launch(qp, top_rows > 0 ? nullptr : &q1, E, up.cout, m->d.compute, m->stream));
+    if (top_rows <= 0) top_rows = prows; }
+  BelowBn below;
+  below.u = &u0; below.mask = u0.z; below.mscale = u0.scale; below.mshift = u0.shift;
+  int done = 0;
+  DDG_OKAY(unit_backward(m, u1, dy, ymask, nullptr, nullptr, top_rows, u0.z, u0.scale, u0.shift, nullptr, m->D2, nullptr, nullptr, &below, &done));
+  if (done <= 0 || !m->pend_w.on || m->pend_w.u != &u1) return fail(DDG_ERR_STATE, "internal: the second layer of a stage's first block left no weight gradient");
+  // the weight gradients; the two error gradients formed on the way are stored for the input gradient
+  void* dz0 = m->dz_flip ? m->D1b : m->D1;
+  m->dz_flip ^= 1;
+  const BnBwdRows r0 = bwd_rows(m, u0, done), rp = bwd_rows(m, up, prows);
+  const void* m0 = m->premasked ? nullptr : u0.z;
+  const float *s0 = m0 ? u0.scale : nullptr, *h0 = m0 ? u0.shift : nullptr;
+  const ddg_module::PendingWgrad pw = m->pend_w;
+  m->pend_w.on = false;
+  const WgradPair second{pw.x, pw.xsc, pw.xsh, pw.dz, u1.wg_partial, u1.wg_tiled_rows};
+  const double wgrad_flops = conv_flops(u0) + conv_flops(u1) + conv_flops(up);
+  const double wgrad_bytes = (2.0 * u0.in_elems() + 4.0 * E) * m->esz + (wbytes(m, u0) + wbytes(m, u1) + wbytes(m, up)) * 4.0 / m->esz;
+  const double form_bytes = (ymask ? 7.0 : 6.0) * E * m->esz;
+  if (m->d.compute == DDG_F32) {
+    { Launch L(m, PK_BN_BWD_APPLY, form_bytes);
+      const BnBwdSet q0 = apply_set(u0, m->D2, m0, s0, h0, &r0, dz0), qp = apply_set(up, dy, ymask, nullptr, nullptr, &rp, m->D3);
+      DDG_TRY(bn_bwd_apply_launch(q0, &qp, E, u0.cout, m->d.compute, m->stream)); }
+    WgradArgs w0 = u0.wg, wp = up.wg;
+    w0.x = wp.x = x; w0.dz = dz0; wp.dz = m->D3; w0.partial = u0.wg_partial; wp.partial = up.wg_partial;
+    Launch L(m, PK_CONV_WGRAD_S2, wgrad_bytes, wgrad_flops);
+    DDG_TRY(wgrad_down_f32_launch(w0, wp, second, m->stream));
+  } else {
+    WgradFuse f0{}, fp{};
+    f0.dy = m->D2; f0.mask = m0; f0.mscale = s0; f0.mshift = h0; f0.z = u0.z; f0.rows = &r0; f0.dz_out = dz0;
+    fp.dy = dy; fp.mask = ymask; fp.z = up.z; fp.rows = &rp; fp.dz_out = m->D3;
+    Launch L(m, PK_CONV_WGRAD_S2, wgrad_bytes + form_bytes - 2.0 * E * m->esz, wgrad_flops);
+    DDG_TRY(wgrad_down_launch(x, u0.N, u0.H, u0.W, u0.cin, f0, u0.wg_partial, u0.wg_tiled_rows, fp, up.wg_partial, up.wg_tiled_rows, second, m->stream));
+  }
+  if (!dx) return DDG_OK;
+  ConvArgs a = u0.dgrad;
+  a.in = dz0; a.wpack = u0.wpack_d; a.out = dx; a.proj_in = m->D3; a.proj_wpack = up.wpack_d;
+  Launch L(m, PK_CONV_DGRAD, (2.0 * E + u0.in_elems()) * m->esz + wbytes(m, u0) + wbytes(m, up), conv_flops(u0) + conv_flops(up));
+  DDG_TRY(conv_launch(a, m->stream));
   return DDG_OK;
 }
 
@@ -1204,7 +1321,9 @@ ddg_status run_backward(ddg_module* m, std::vector<Blk>& blocks, const void* in,
     // the ReLU mask of this block's output: already applied to dy by the kernel that produced
     // it, if that kernel also formed the sums (top_rows > 0)
     const void* ymask = (top_rows > 0 && premasked) ? nullptr : b.y;
-    if (b.kind == DDG_BLOCK_STEM) {
+    if (down_block(m, b) && (!dx_dst || conv_dgrad_s2_ok(b.u[0].dgrad))) {
+      DDG_OKAY(down_block_backward(m, b, dy, ymask, top_rows, x, dx_dst));
+    } else if (b.kind == DDG_BLOCK_STEM) {
       DDG_OKAY(unit_backward(m, b.u[0], dy, ymask, nullptr, nullptr, top_rows, x, nullptr, nullptr, m->D1,
                              dx_dst, nullptr, nullptr, bi > 0 ? &below_blk : nullptr, &next_top_rows));
     } else {

@@ -14,6 +14,7 @@
 // in a fixed order, so the statistics are deterministic.
 #include "ddg_device.h"
 #include "ddg_kernels.h"
+#include "ddg_wgrad_vec.h"
 #include <cstdlib>
 
 namespace ddg {
@@ -26,20 +27,26 @@ __device__ __forceinline__ void keep_frag(float4& f) { asm volatile("" : "+v"(f.
 
 // VEC: the contraction channel count is a multiple of the fragment width (every layer but a
 // 3-channel stem): gathers are whole fragments and none of them is conditional.
+// Two convolutions of the same tile shape may share a launch (a stage's first 3x3 layer and its projection, which read the
+// same input): blockIdx.z = convolution * minibatches + minibatch. A launch that waits for the one before costs 4-5 us
+// whatever it does, and these are 5-7 us.
+struct ConvPair { ConvArgs c[2]; };
+
+// bx of gx, by: this workgroup's index among those that walk over the pixels, its group of channel blocks.
 template <typename T, int MB, int NB, bool DGRAD, bool VEC>
-__global__ __launch_bounds__(256) void conv_mfma_kernel(ConvArgs a) {
+__device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, bool second, int bx, int by, int gx) {
   using M_ = Mma<T>;
   using S_ = Store<T>;
   constexpr int KV = M_::KV;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l16 = lane & 15, lg = lane >> 4;
-  const int cb0 = blockIdx.y * NB;
+  const int cb0 = by * NB;
   const int OCB = a.OC >> 4;
-  // blockIdx.z = 1: the second minibatch of a two-group launch (same weights, own tensors)
-  const T* __restrict__ in = reinterpret_cast<const T*>(blockIdx.z ? a.in_b : a.in);
+  // second: the second minibatch of a two-group launch (same weights, own tensors)
+  const T* __restrict__ in = reinterpret_cast<const T*>(second ? a.in_b : a.in);
   const T* __restrict__ wp = reinterpret_cast<const T*>(a.wpack);
-  T* __restrict__ out = reinterpret_cast<T*>(blockIdx.z ? a.out_b : a.out);
-  float* __restrict__ stat_partial = blockIdx.z ? a.stat_partial_b : a.stat_partial;
+  T* __restrict__ out = reinterpret_cast<T*>(second ? a.out_b : a.out);
+  float* __restrict__ stat_partial = second ? a.stat_partial_b : a.stat_partial;
   const T* __restrict__ addg = reinterpret_cast<const T*>(a.add_g);
   const T* __restrict__ addm = reinterpret_cast<const T*>(a.add_mask);
   const int tiles = (a.M + 16 * MB - 1) / (16 * MB);
@@ -53,7 +60,7 @@ __global__ __launch_bounds__(256) void conv_mfma_kernel(ConvArgs a) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) { ssum[nb][j] = 0.f; ssq[nb][j] = 0.f; }
 
-  for (int tile = blockIdx.x * 4 + wave; tile < tiles; tile += gridDim.x * 4) {
+  for (int tile = bx * 4 + wave; tile < tiles; tile += gx * 4) {
     int pn[MB], ph[MB], pw[MB];
     bool pv[MB];
 #pragma unroll
@@ -188,9 +195,26 @@ __global__ __launch_bounds__(256) void conv_mfma_kernel(ConvArgs a) {
     if (threadIdx.x < 2 * NB * 16) {
       const int which = threadIdx.x / (NB * 16), c = threadIdx.x % (NB * 16);
       const float t = ((red[0][which][c] + red[1][which][c]) + red[2][which][c]) + red[3][which][c];
-      stat_partial[((size_t)blockIdx.x * 2 + which) * a.OC + cb0 * 16 + c] = t;
+      stat_partial[((size_t)bx * 2 + which) * a.OC + cb0 * 16 + c] = t;
     }
   }
+}
+
+template <typename T, int MB, int NB, bool DGRAD, bool VEC>
+__global__ __launch_bounds__(256) void conv_mfma_kernel(ConvPair ab, int sets) {
+  const int conv = (int)blockIdx.z >= sets ? 1 : 0;
+  conv_mfma_body<T, MB, NB, DGRAD, VEC>(ab.c[conv], (int)blockIdx.z != conv * sets, blockIdx.x, blockIdx.y, gridDim.x);
+}
+
+// Weight gradient (vector gathers) and input gradient of a layer in one launch: both need its dz and nothing of each
+// other. Layers of the generic kernels are small or few, and a launch that waits for the one before costs
+// 4-5 us whatever it does.
+template <typename T, int MB, int NB>
+__global__ __launch_bounds__(256) void bwd_generic_kernel(WgradArgs w, ConvArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int b = blockIdx.x, nw = w.msplit * (w.Cout / 16);      // (column group slowest, as in a launch of its own)
+  if (b < nw * w.jgroups) wgrad_vec_body<T>(w, smem, b % nw % w.msplit, b % nw / w.msplit, b / nw);
+  else conv_mfma_body<T, MB, NB, true, true>(a, false, (b - nw * w.jgroups) % a.grid_x, (b - nw * w.jgroups) / a.grid_x, a.grid_x);
 }
 
 // Input gradient of a stride-2 convolution (the first block of a stage and its projection). A pixel of the
@@ -201,8 +225,11 @@ __global__ __launch_bounds__(256) void conv_mfma_kernel(ConvArgs a) {
 // keep their order (a skipped tap added zero), so results are bit-identical.
 // Bound by memory and latency. 3x3 and 1x1 launch together, in a running pipeline: fp32 batch 128, 32 -> 16 channels
 // 56 -> 26 us, 64 -> 32 channels 36 -> 18 us.
+// PROJ: the launch also carries the gradient that comes through the projection (a.proj_in, a.proj_wpack: a 1x1 kernel, so
+// only pixels of even row and column receive any): rounded as a tensor of its own would be, then added. One launch of
+// 5 us and a tensor written and read less per stage.
 // CPT: k-steps per tap (contraction channels / KSTEP). PR, PC: parity of the pixel's row and column.
-template <typename T, int MB, int NB, int CPT, int R, int PR, int PC>
+template <typename T, int MB, int NB, int CPT, int R, int PR, int PC, bool PROJ>
 __device__ __forceinline__ void dgrad_s2_tile(const ConvArgs& a, int tile, int cb0) {
   using M_ = Mma<T>;
   using S_ = Store<T>;
@@ -255,6 +282,20 @@ __device__ __forceinline__ void dgrad_s2_tile(const ConvArgs& a, int tile, int c
       _Pragma("unroll") for (int nb = 0; nb < NB; ++nb)                                            \
         wf[set][c][nb] = M_::load(wp + ((size_t)(((r * R + sc) * CPT + c) * OCB + cb0 + nb) * 64 + lane) * KV); \
   }
+  constexpr bool PRJ = PROJ && PR == 0 && PC == 0;
+  frag_t pw[PRJ ? CPT : 1][NB], px[PRJ ? CPT : 1][MB];
+  if constexpr (PRJ) {     // source pixel (pi, pj), which exists
+    const T* __restrict__ pin = reinterpret_cast<const T*>(a.proj_in);
+    const T* __restrict__ pwp = reinterpret_cast<const T*>(a.proj_wpack);
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) {
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+        px[c][i] = M_::load(pin + ((unsigned)((pn[i] * a.IH + pi[i]) * a.IW + pj[i]) * (unsigned)a.IC + (unsigned)((c * 4 + lg) * KV)));
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) pw[c][nb] = M_::load(pwp + ((size_t)(c * OCB + cb0 + nb) * 64 + lane) * KV);
+    }
+  }
   if constexpr (NT > 0) DDG_S2_TAP(0, 0)
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
@@ -272,6 +313,17 @@ __device__ __forceinline__ void dgrad_s2_tile(const ConvArgs& a, int tile, int c
       }
   }
 #undef DDG_S2_TAP
+  f32x4_t pacc[PRJ ? MB : 1][NB];
+  if constexpr (PRJ) {
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        pacc[i][nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) pacc[i][nb] = M_::mma(pw[c][nb], pv[i] ? px[c][i] : M_::zero(), pacc[i][nb]);
+      }
+  }
 
 #pragma unroll
   for (int i = 0; i < MB; ++i) {
@@ -281,6 +333,10 @@ __device__ __forceinline__ void dgrad_s2_tile(const ConvArgs& a, int tile, int c
     for (int nb = 0; nb < NB; ++nb) {
       const size_t idx = m * a.OC + (cb0 + nb) * 16 + lg * 4;
       float v[4] = {acc[i][nb][0], acc[i][nb][1], acc[i][nb][2], acc[i][nb][3]};
+      if (PROJ) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] += PRJ ? S_::round(pacc[PRJ ? i : 0][nb][j]) : 0.f;
+      }
       if (addg) {
         float g[4];
         S_::load4(addg + idx, g);
@@ -299,39 +355,47 @@ __device__ __forceinline__ void dgrad_s2_tile(const ConvArgs& a, int tile, int c
 }
 
 // one wave per tile; the classes with most taps first
-template <typename T, int MB, int NB, int CPT, int R>
-__global__ __launch_bounds__(256) void conv_dgrad_s2_kernel(ConvArgs a, int t11, int t10, int t01, int t00) {
+struct S2Tiles { int t11, t10, t01, t00; };
+template <typename T, int MB, int NB, int CPT, int R, bool PROJ>
+__global__ __launch_bounds__(256) void conv_dgrad_s2_kernel(ConvArgs a, S2Tiles t) {
   int tile = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int cb0 = blockIdx.y * NB;
-  if (tile < t11) { dgrad_s2_tile<T, MB, NB, CPT, R, 1, 1>(a, tile, cb0); return; }
-  tile -= t11;
-  if (tile < t10) { dgrad_s2_tile<T, MB, NB, CPT, R, 1, 0>(a, tile, cb0); return; }
-  tile -= t10;
-  if (tile < t01) { dgrad_s2_tile<T, MB, NB, CPT, R, 0, 1>(a, tile, cb0); return; }
-  tile -= t01;
-  if (tile < t00) dgrad_s2_tile<T, MB, NB, CPT, R, 0, 0>(a, tile, cb0);
+  if (tile < t.t11) { dgrad_s2_tile<T, MB, NB, CPT, R, 1, 1, PROJ>(a, tile, cb0); return; }
+  tile -= t.t11;
+  if (tile < t.t10) { dgrad_s2_tile<T, MB, NB, CPT, R, 1, 0, PROJ>(a, tile, cb0); return; }
+  tile -= t.t10;
+  if (tile < t.t01) { dgrad_s2_tile<T, MB, NB, CPT, R, 0, 1, PROJ>(a, tile, cb0); return; }
+  tile -= t.t01;
+  if (tile < t.t00) dgrad_s2_tile<T, MB, NB, CPT, R, 0, 0, PROJ>(a, tile, cb0);
 }
 
 // Covered: whole k-steps per tap (1, 2 or 4 of them: 32-128 channels in bf16, 16-64 in fp32). Two pixel blocks per
 // wave once that leaves a wave per SIMD; 32 output channels per wave in bf16 (its matrix instructions are
 // cheap, the gathers are not), 16 in fp32.
+bool conv_dgrad_s2_ok(const ConvArgs& a) {
+  const int kstep = a.dtype == BF16 ? Mma<bf16_t>::KSTEP : Mma<float>::KSTEP;
+  if (!a.dgrad || a.stride != 2 || a.stat_partial || a.in_b || (a.R != 1 && a.R != 3) || a.pad != (a.R == 3 ? 1 : 0)) return false;
+  if (a.IC % kstep != 0 || (1 << a.log2cp) != a.IC || a.IH != (a.OH + 1) / 2 || a.IW != (a.OW + 1) / 2) return false;
+  const int cpt = a.IC / kstep;
+  return cpt == 1 || cpt == 2 || cpt == 4;
+}
+
 template <typename T>
 static bool conv_dgrad_s2_launch(const ConvArgs& a, hipStream_t s) {
   constexpr int KSTEP = Mma<T>::KSTEP;
-  if (!a.dgrad || a.stride != 2 || a.stat_partial || a.in_b || (a.R != 1 && a.R != 3) || a.pad != (a.R == 3 ? 1 : 0)) return false;
-  if (a.IC % KSTEP != 0 || (1 << a.log2cp) != a.IC || a.IH != (a.OH + 1) / 2 || a.IW != (a.OW + 1) / 2) return false;
+  if (!conv_dgrad_s2_ok(a)) return false;
   const int cpt = a.IC / KSTEP;
-  if (cpt != 1 && cpt != 2 && cpt != 4) return false;
   const int nb = KSTEP == 32 && (a.OC / 16) % 2 == 0 ? 2 : 1, gy = a.OC / 16 / nb;
   const int mb = (size_t)a.M / 32 * gy >= 1024 ? 2 : 1;
   const int h0 = (a.OH + 1) / 2, h1 = a.OH / 2, w0 = (a.OW + 1) / 2, w1 = a.OW / 2;
   auto tiles = [&](int h, int w) { return (a.N * h * w + 16 * mb - 1) / (16 * mb); };
-  const int t11 = tiles(h1, w1), t10 = tiles(h1, w0), t01 = tiles(h0, w1), t00 = tiles(h0, w0);
-  const dim3 grid((t11 + t10 + t01 + t00 + 3) / 4, gy), block(256);
+  const S2Tiles t{tiles(h1, w1), tiles(h1, w0), tiles(h0, w1), tiles(h0, w0)};
+  const dim3 grid((t.t11 + t.t10 + t.t01 + t.t00 + 3) / 4, gy), block(256);
 #define DDG_S2_CASE(MB_, NB_, CPT_)                                                                              \
   if (mb == MB_ && nb == NB_ && cpt == CPT_) {                                                                   \
-    if (a.R == 3) DDG_LAUNCH((conv_dgrad_s2_kernel<T, MB_, NB_, CPT_, 3>), grid, block, 0, s, a, t11, t10, t01, t00); \
-    else DDG_LAUNCH((conv_dgrad_s2_kernel<T, MB_, NB_, CPT_, 1>), grid, block, 0, s, a, t11, t10, t01, t00);     \
+    if (a.R == 3 && a.proj_in) DDG_LAUNCH((conv_dgrad_s2_kernel<T, MB_, NB_, CPT_, 3, true>), grid, block, 0, s, a, t); \
+    else if (a.R == 3) DDG_LAUNCH((conv_dgrad_s2_kernel<T, MB_, NB_, CPT_, 3, false>), grid, block, 0, s, a, t); \
+    else DDG_LAUNCH((conv_dgrad_s2_kernel<T, MB_, NB_, CPT_, 1, false>), grid, block, 0, s, a, t);               \
     return true;                                                                                                 \
   }
   DDG_S2_CASE(1, 1, 1) DDG_S2_CASE(1, 1, 2) DDG_S2_CASE(1, 1, 4)
@@ -383,17 +447,19 @@ void conv_plan(ConvArgs& a) {
 }
 
 template <typename T>
-static hipError_t conv_dispatch(const ConvArgs& a, hipStream_t s) {
-  dim3 grid(a.grid_x, (a.OC / 16) / a.nb, a.in_b ? 2 : 1), block(256);
+static hipError_t conv_dispatch(const ConvArgs& a, const ConvArgs* other, hipStream_t s) {
+  const int sets = a.in_b ? 2 : 1;
+  dim3 grid(a.grid_x, (a.OC / 16) / a.nb, other ? 2 * sets : sets), block(256);
+  const ConvPair ab{{a, other ? *other : a}};
   const bool vec = a.IC % Mma<T>::KV == 0;
 #define DDG_CONV_CASE(MB_, NB_)                                                                   \
   if (a.mb == MB_ && a.nb == NB_) {                                                               \
     if (vec) {                                                                                    \
-      if (a.dgrad) DDG_LAUNCH((conv_mfma_kernel<T, MB_, NB_, true, true>), grid, block, 0, s, a);   \
-      else DDG_LAUNCH((conv_mfma_kernel<T, MB_, NB_, false, true>), grid, block, 0, s, a);          \
+      if (a.dgrad) DDG_LAUNCH((conv_mfma_kernel<T, MB_, NB_, true, true>), grid, block, 0, s, ab, sets);   \
+      else DDG_LAUNCH((conv_mfma_kernel<T, MB_, NB_, false, true>), grid, block, 0, s, ab, sets);          \
     } else {                                                                                      \
-      if (a.dgrad) DDG_LAUNCH((conv_mfma_kernel<T, MB_, NB_, true, false>), grid, block, 0, s, a);  \
-      else DDG_LAUNCH((conv_mfma_kernel<T, MB_, NB_, false, false>), grid, block, 0, s, a);         \
+      if (a.dgrad) DDG_LAUNCH((conv_mfma_kernel<T, MB_, NB_, true, false>), grid, block, 0, s, ab, sets);  \
+      else DDG_LAUNCH((conv_mfma_kernel<T, MB_, NB_, false, false>), grid, block, 0, s, ab, sets);         \
     }                                                                                             \
     return hipGetLastError();                                                                     \
   }
@@ -406,11 +472,47 @@ static hipError_t conv_dispatch(const ConvArgs& a, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
-hipError_t conv_launch(const ConvArgs& a, hipStream_t s) {
+bool conv_shares_launch(const ConvArgs& a, const ConvArgs& b) {
+  return !a.dgrad && !b.dgrad && a.dtype == b.dtype && a.M == b.M && a.IC == b.IC && a.OC == b.OC && a.mb == b.mb && a.nb == b.nb &&
+         a.grid_x == b.grid_x;
+}
+
+hipError_t conv_launch(const ConvArgs& a, hipStream_t s, const ConvArgs* other) {
   // the gathers form 32-bit element offsets
   if ((size_t)a.N * a.IH * a.IW * a.IC >= ((size_t)1 << 32)) return hipErrorInvalidValue;
+  if (other) {
+    if (!conv_shares_launch(a, *other) || (a.in_b != nullptr) != (other->in_b != nullptr)) return hipErrorInvalidValue;
+    return a.dtype == BF16 ? conv_dispatch<bf16_t>(a, other, s) : conv_dispatch<float>(a, other, s);
+  }
   if (a.dtype == BF16 ? conv_dgrad_s2_launch<bf16_t>(a, s) : conv_dgrad_s2_launch<float>(a, s)) return hipGetLastError();
-  return a.dtype == BF16 ? conv_dispatch<bf16_t>(a, s) : conv_dispatch<float>(a, s);
+  if (a.proj_in) return hipErrorInvalidValue;   // (the caller asks conv_dgrad_s2_ok)
+  return a.dtype == BF16 ? conv_dispatch<bf16_t>(a, nullptr, s) : conv_dispatch<float>(a, nullptr, s);
+}
+
+bool bwd_generic_ok(const WgradArgs& w, const ConvArgs& a) {
+  return w.vec && a.dgrad && !a.proj_in && w.dtype == a.dtype && a.IC % mma_kv(a.dtype) == 0 && !conv_dgrad_s2_ok(a);
+}
+
+template <typename T>
+static hipError_t bwd_generic_dispatch(const WgradArgs& w, const ConvArgs& a, hipStream_t s) {
+  const dim3 grid(w.msplit * (w.Cout / 16) * w.jgroups + a.grid_x * (a.OC / 16 / a.nb));
+#define DDG_BWD_CASE(MB_, NB_)                                                                    \
+  if (a.mb == MB_ && a.nb == NB_) {                                                               \
+    DDG_LAUNCH((bwd_generic_kernel<T, MB_, NB_>), grid, dim3(256), WGV_LDS, s, w, a);             \
+    return hipGetLastError();                                                                     \
+  }
+  DDG_BWD_CASE(4, 1)
+  if constexpr (Mma<T>::KV == 4) { DDG_BWD_CASE(2, 1) DDG_BWD_CASE(1, 1) }
+  else { DDG_BWD_CASE(2, 2) DDG_BWD_CASE(2, 4) }
+#undef DDG_BWD_CASE
+  return hipErrorInvalidValue;
+}
+
+hipError_t bwd_generic_launch(const WgradArgs& w, const ConvArgs& a, hipStream_t s) {
+  if (!bwd_generic_ok(w, a) || a.stat_partial || a.in_b) return hipErrorInvalidValue;
+  // 32-bit element offsets inside
+  if ((size_t)w.N * w.H * w.W * w.Cin >= ((size_t)1 << 32) || (size_t)w.M * w.Cout >= ((size_t)1 << 32)) return hipErrorInvalidValue;
+  return a.dtype == BF16 ? bwd_generic_dispatch<bf16_t>(w, a, s) : bwd_generic_dispatch<float>(w, a, s);
 }
 
 // wpack[((ks*OCB + cb)*64 + lane)*KV + j] = W-element for row cb*16+lane%16 and

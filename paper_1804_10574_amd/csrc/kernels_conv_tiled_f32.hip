@@ -22,6 +22,7 @@
 #include "ddg_device.h"
 #include "ddg_kernels.h"
 #include "ddg_stats.h"
+#include "ddg_wgrad_vec.h"
 #include <cstdlib>
 
 namespace ddg {
@@ -681,6 +682,49 @@ hipError_t wgrad_tiled_f32_launch(const void* x, const float* scale, const float
   if (C == 32 && W == 16) return wgrad_tiled_f32_launch_t<32, 16>(a, rows, s);
   if (C == 64 && W == 8) return wgrad_tiled_f32_launch_t<64, 8>(a, rows, s);
   return hipErrorInvalidValue;
+}
+
+// The weight gradients of a stage's first block in one launch: the stride-2 3x3 layer and the projection (generic body), and the
+// second layer (tiled body; C, W: its shape). They do not depend on each other, and each alone left most of the chip idle.
+template <int C, int W>
+__global__ __launch_bounds__(256) void wgrad_down_f32_kernel(WgradArgs a3, WgradArgs a1, WgradTiledF32Args a2, int g3, int g1, int rows2) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int b = blockIdx.x, n3 = g3 * (a3.Cout / 16);      // (column group slowest, as in a launch of its own)
+  if (b < n3 * a3.jgroups) {
+    wgrad_vec_body<float>(a3, smem, b % n3 % g3, b % n3 / g3, b / n3);
+  } else if (b < n3 * a3.jgroups + g1 * (a1.Cout / 16) * a1.jgroups) {
+    const int v = b - n3 * a3.jgroups, n1 = g1 * (a1.Cout / 16);
+    wgrad_vec_body<float>(a1, smem, v % n1 % g1, v % n1 / g1, v / n1);
+  } else {
+    wgrad_tiled_f32_body<C, W, false>(a2, smem, b - n3 * a3.jgroups - g1 * (a1.Cout / 16) * a1.jgroups, rows2);
+  }
+}
+
+bool wgrad_down_f32_ok(const WgradArgs& a3, const WgradArgs& a1) {
+  return a3.dtype == F32 && a1.dtype == F32 && a3.vec && a1.vec && a3.R == 3 && a1.R == 1 && a3.stride == 2 && a1.stride == 2 &&
+         a3.Cout == a1.Cout && a3.M == a1.M && ((a3.Cout == 32 && a3.Q == 16) || (a3.Cout == 64 && a3.Q == 8)) && a3.P % 8 == 0;
+}
+
+template <int C, int W>
+static hipError_t wgrad_down_f32_run(const WgradArgs& a3, const WgradArgs& a1, const WgradTiledF32Args& a2, int rows2, hipStream_t s) {
+  constexpr int lds = WGV_LDS > WgradTiledF32Cfg<C, W>::LDS ? WGV_LDS : WgradTiledF32Cfg<C, W>::LDS;
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&wgrad_down_f32_kernel<C, W>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (attr != hipSuccess) return attr;
+  const unsigned grid = a3.msplit * (a3.Cout / 16) * a3.jgroups + a1.msplit * (a1.Cout / 16) * a1.jgroups + rows2;
+  DDG_LAUNCH((wgrad_down_f32_kernel<C, W>), dim3(grid), dim3(256), lds, s, a3, a1, a2, a3.msplit, a1.msplit, rows2);
+  return hipGetLastError();
+}
+
+hipError_t wgrad_down_f32_launch(const WgradArgs& a3, const WgradArgs& a1, const WgradPair& second, hipStream_t s) {
+  if (!wgrad_down_f32_ok(a3, a1)) return hipErrorInvalidValue;
+  if ((size_t)a3.N * a3.H * a3.W * a3.Cin >= ((size_t)1 << 32) || (size_t)a3.M * a3.Cout >= ((size_t)1 << 31)) return hipErrorInvalidValue;   // 32-bit element offsets inside
+  const int wtiles = a3.N * (a3.P / (a3.Cout == 64 ? 4 : 8));
+  if (second.rows < 1 || second.rows > wtiles) return hipErrorInvalidValue;
+  WgradTiledF32Args a2{};
+  a2.x = (const float*)second.x; a2.scale = second.scale; a2.shift = second.shift; a2.dz = (const float*)second.dz;
+  a2.partial = second.partial; a2.N = a3.N; a2.H = a3.P; a2.tiles = wtiles;
+  return a3.Cout == 32 ? wgrad_down_f32_run<32, 16>(a3, a1, a2, second.rows, s) : wgrad_down_f32_run<64, 8>(a3, a1, a2, second.rows, s);
 }
 
 }  // namespace ddg

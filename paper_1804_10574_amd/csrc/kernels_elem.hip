@@ -260,13 +260,18 @@ hipError_t bn_apply_launch(const void* z, const float* scale, const float* shift
 // ---------------------------------------------------------------------------------
 // BN backward, pass 1: g = dy masked by (mask > 0); partial sums of g and g*xhat.
 // ---------------------------------------------------------------------------------
+// blockIdx.y: one of two layers of the same shape (the last layer of a stage's first block and its projection).
 template <typename T>
-__global__ __launch_bounds__(256) void bn_bwd_reduce_kernel(const T* __restrict__ dy, const T* __restrict__ mask,
-                                                            const float* __restrict__ mscale,
-                                                            const float* __restrict__ mshift,
-                                                            const T* __restrict__ z, const float* __restrict__ mean,
-                                                            const float* __restrict__ invstd,
-                                                            float* __restrict__ partial, size_t nvec, int C) {
+__global__ __launch_bounds__(256) void bn_bwd_reduce_kernel(BnBwdSet q0, BnBwdSet q1, size_t nvec, int C) {
+  const BnBwdSet& q = blockIdx.y ? q1 : q0;
+  const T* __restrict__ dy = reinterpret_cast<const T*>(q.dy);
+  const T* __restrict__ mask = reinterpret_cast<const T*>(q.mask);
+  const float* __restrict__ mscale = q.mscale;
+  const float* __restrict__ mshift = q.mshift;
+  const T* __restrict__ z = reinterpret_cast<const T*>(q.z);
+  const float* __restrict__ mean = q.mean;
+  const float* __restrict__ invstd = q.invstd;
+  float* __restrict__ partial = q.partial;
   constexpr int V = Store<T>::VEC;
   const size_t stride = (size_t)gridDim.x * blockDim.x;
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -345,31 +350,33 @@ __global__ void zero_f32_kernel(float* p, size_t n) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0.f;
 }
 
-hipError_t bn_bwd_reduce_launch(const void* dy, const void* mask, const float* mscale, const float* mshift,
-                                const void* z, const float* mean, const float* invstd, float* partial,
-                                size_t elems, int C, int dtype, hipStream_t s) {
+hipError_t bn_bwd_reduce_launch(const BnBwdSet& q, const BnBwdSet* other, size_t elems, int C, int dtype, hipStream_t s) {
   const int V = dtype == BF16 ? 8 : 4;
   const int grid = bn_bwd_grid(elems, C, dtype);
   if (C > 256 * V) {  // a block's row is only partly written: clear the rows first
     const size_t n = (size_t)grid * 2 * C;
-    DDG_LAUNCH(zero_f32_kernel<float>, dim3(256), dim3(256), 0, s, partial, n);
+    DDG_LAUNCH(zero_f32_kernel<float>, dim3(256), dim3(256), 0, s, q.partial, n);
+    if (other) DDG_LAUNCH(zero_f32_kernel<float>, dim3(256), dim3(256), 0, s, other->partial, n);
   }
-  if (dtype == BF16)
-    DDG_LAUNCH(bn_bwd_reduce_kernel<bf16_t>, dim3(grid), dim3(256), 0, s, (const bf16_t*)dy,
-                       (const bf16_t*)mask, mscale, mshift, (const bf16_t*)z, mean, invstd, partial, elems / 8, C);
-  else
-    DDG_LAUNCH(bn_bwd_reduce_kernel<float>, dim3(grid), dim3(256), 0, s, (const float*)dy,
-                       (const float*)mask, mscale, mshift, (const float*)z, mean, invstd, partial, elems / 4, C);
+  const BnBwdSet& o = other ? *other : q;
+  if (dtype == BF16) DDG_LAUNCH(bn_bwd_reduce_kernel<bf16_t>, dim3(grid, other ? 2 : 1), dim3(256), 0, s, q, o, elems / 8, C);
+  else DDG_LAUNCH(bn_bwd_reduce_kernel<float>, dim3(grid, other ? 2 : 1), dim3(256), 0, s, q, o, elems / 4, C);
   return hipGetLastError();
 }
 
 // dz = A*g + B*z + C0 (coefficients from bn_bwd_finalize_launch, or derived from the rows)
+// blockIdx.y: one of two layers of the same shape
 template <typename T>
-__global__ __launch_bounds__(256) void bn_bwd_apply_kernel(const T* __restrict__ dy, const T* __restrict__ mask,
-                                                           const float* __restrict__ mscale,
-                                                           const float* __restrict__ mshift,
-                                                           const T* __restrict__ z, const float* __restrict__ coef,
-                                                           BnBwdRows rows, T* __restrict__ dz, size_t nvec, int C) {
+__global__ __launch_bounds__(256) void bn_bwd_apply_kernel(BnBwdSet q0, BnBwdSet q1, size_t nvec, int C) {
+  const BnBwdSet& q = blockIdx.y ? q1 : q0;
+  const T* __restrict__ dy = reinterpret_cast<const T*>(q.dy);
+  const T* __restrict__ mask = reinterpret_cast<const T*>(q.mask);
+  const float* __restrict__ mscale = q.mscale;
+  const float* __restrict__ mshift = q.mshift;
+  const T* __restrict__ z = reinterpret_cast<const T*>(q.z);
+  const float* coef = q.coef;
+  const BnBwdRows rows = q.rows;
+  T* __restrict__ dz = reinterpret_cast<T*>(q.dz);
   constexpr int V = Store<T>::VEC;
   const size_t stride = (size_t)gridDim.x * blockDim.x;
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -471,28 +478,23 @@ static bool bn_bwd_apply_chunked(const T* dy, const T* mask, const float* mscale
   return true;
 }
 
-hipError_t bn_bwd_apply_launch(const void* dy, const void* mask, const float* mscale, const float* mshift,
-                               const void* z, const float* coef, const BnBwdRows* rows, void* dz, size_t elems,
-                               int C, int dtype, hipStream_t s) {
-  const BnBwdRows br = rows ? *rows : BnBwdRows{};
+hipError_t bn_bwd_apply_launch(const BnBwdSet& q, const BnBwdSet* other, size_t elems, int C, int dtype, hipStream_t s) {
+  const bool rows = q.rows.partial != nullptr;
+  if (other && (other->rows.partial != nullptr) != rows) return hipErrorInvalidValue;
   const int maxb = rows ? 512 : 2048;
-  if (!rows) {
+  if (!rows && !other) {
     const bool done = dtype == BF16
-        ? bn_bwd_apply_chunked<bf16_t>((const bf16_t*)dy, (const bf16_t*)mask, mscale, mshift, (const bf16_t*)z, coef,
-                                       (bf16_t*)dz, elems / 8, C, s)
-        : bn_bwd_apply_chunked<float>((const float*)dy, (const float*)mask, mscale, mshift, (const float*)z, coef,
-                                      (float*)dz, elems / 4, C, s);
+        ? bn_bwd_apply_chunked<bf16_t>((const bf16_t*)q.dy, (const bf16_t*)q.mask, q.mscale, q.mshift, (const bf16_t*)q.z, q.coef,
+                                       (bf16_t*)q.dz, elems / 8, C, s)
+        : bn_bwd_apply_chunked<float>((const float*)q.dy, (const float*)q.mask, q.mscale, q.mshift, (const float*)q.z, q.coef,
+                                      (float*)q.dz, elems / 4, C, s);
     if (done) return hipGetLastError();
   }
-  if (dtype == BF16) {
-    const size_t nvec = elems / 8;
-    DDG_LAUNCH(bn_bwd_apply_kernel<bf16_t>, dim3(elem_grid(nvec, C, 8, maxb)), dim3(256), 0, s,
-                       (const bf16_t*)dy, (const bf16_t*)mask, mscale, mshift, (const bf16_t*)z, coef, br, (bf16_t*)dz, nvec, C);
-  } else {
-    const size_t nvec = elems / 4;
-    DDG_LAUNCH(bn_bwd_apply_kernel<float>, dim3(elem_grid(nvec, C, 4, maxb)), dim3(256), 0, s,
-                       (const float*)dy, (const float*)mask, mscale, mshift, (const float*)z, coef, br, (float*)dz, nvec, C);
-  }
+  const BnBwdSet& o = other ? *other : q;
+  const int V = dtype == BF16 ? 8 : 4;
+  const dim3 grid(elem_grid(elems / V, C, V, maxb), other ? 2 : 1);
+  if (dtype == BF16) DDG_LAUNCH(bn_bwd_apply_kernel<bf16_t>, grid, dim3(256), 0, s, q, o, elems / 8, C);
+  else DDG_LAUNCH(bn_bwd_apply_kernel<float>, grid, dim3(256), 0, s, q, o, elems / 4, C);
   return hipGetLastError();
 }
 
