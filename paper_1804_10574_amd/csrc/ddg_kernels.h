@@ -42,6 +42,15 @@ struct BnBwdRows {     // backward: rows of (sum g, sum g*xhat)
   float* dgamma; float* dbeta;                              // written by workgroup 0
 };
 
+// One layer's share of a backward launch: what bn_bwd_reduce_launch and bn_bwd_apply_launch read and write.
+struct BnBwdSet {
+  const void* dy; const void* mask; const float* mscale; const float* mshift; const void* z;
+  const float* mean; const float* invstd; float* partial;    // reduce
+  const float* coef; BnBwdRows rows; void* dz;               // apply: final coefficients [3][C], or rows (C <= 64) to derive them from
+};
+// The sums of a layer that ride in another launch: `grid` workgroups (bn_bwd_grid()) of a tensor of `elems` elements, C channels.
+struct BnReduceRide { BnBwdSet q; size_t elems; int C, grid; };
+
 // Implicit-GEMM convolution on the matrix cores. One kernel serves the forward
 // convolution and the gradient w.r.t. the input:
 //   fprop: out[n,oh,ow,:] = sum_taps in[n, oh*st+r-pad, ow*st+s-pad, :] . W
@@ -179,6 +188,8 @@ int conv_tiled_grid(int N, int H, int W, int Cin, int Cout, int R, int stride, i
 // apply (optional, input gradient only): `in` is apply->dy, the gradient after a batch norm's
 // ReLU; the kernel forms dz = BN-backward(dy) from apply->rows while staging (as the fused
 // weight-gradient kernel does), convolves dz, and stores it to apply->dz_out.
+// ride (optional, with apply, statistics mode 2, 32 or 64 channels): the launch also carries the batch-norm backward sums of another layer, on
+// workgroups of its own.
 // pair (optional, with apply): the launch also carries the plain weight gradient of another
 // layer of the same shape (input x, or relu(x*scale+shift); error gradient dz; `rows` partial
 // tiles as wgrad_tiled_rows() says), on workgroups of its own.
@@ -186,7 +197,8 @@ hipError_t conv_tiled_launch(const void* in, const float* scale, const float* sh
                              const void* wpack, void* out, const ConvStat& st, const void* add_g,
                              const void* add_mask, int N, int H, int W, int C, int grid, hipStream_t s,
                              const void* res = nullptr, void* y_out = nullptr, int groups = 1,
-                             int vec_stride = 0, const WgradFuse* apply = nullptr, const WgradPair* pair = nullptr);
+                             int vec_stride = 0, const WgradFuse* apply = nullptr, const WgradPair* pair = nullptr,
+                             const BnReduceRide* ride = nullptr);
 
 
 // The same kernels with fp32 operands (kernels_conv_tiled_f32.hip): same arguments and rules;
@@ -195,7 +207,8 @@ hipError_t conv_tiled_f32_launch(const void* in, const float* scale, const float
                                  const void* wpack, void* out, const ConvStat& st, const void* add_g,
                                  const void* add_mask, int N, int H, int W, int C, int grid, hipStream_t s,
                                  const void* res = nullptr, void* y_out = nullptr, int groups = 1,
-                                 int vec_stride = 0, const WgradFuse* apply = nullptr, const WgradPair* pair = nullptr);
+                                 int vec_stride = 0, const WgradFuse* apply = nullptr, const WgradPair* pair = nullptr,
+                             const BnReduceRide* ride = nullptr);
 hipError_t wgrad_tiled_f32_launch(const void* x, const float* scale, const float* shift, const void* dz,
                                   const WgradFuse* fuse, float* partial, int N, int H, int W, int C, int rows,
                                   hipStream_t s);
@@ -267,12 +280,6 @@ hipError_t bn_bwd_apply_wide_launch(const void* dy, const void* mask, const floa
 // mask*mscale+mshift > 0 when mscale is given (the mask tensor is then the conv output the
 // activation derives from); mask == nullptr: g = dy. partial[grid][2][C] = (sum g, sum g*xhat)
 int bn_bwd_grid(size_t elems, int C, int dtype);
-// One layer's share of a backward launch: what the two kernels below read and write.
-struct BnBwdSet {
-  const void* dy; const void* mask; const float* mscale; const float* mshift; const void* z;
-  const float* mean; const float* invstd; float* partial;    // reduce
-  const float* coef; BnBwdRows rows; void* dz;               // apply: final coefficients [3][C], or rows (C <= 64) to derive them from
-};
 // other (optional): a second layer of the same shape in the launch.
 hipError_t bn_bwd_reduce_launch(const BnBwdSet& q, const BnBwdSet* other, size_t elems, int C, int dtype, hipStream_t s);
 // dgamma, dbeta and the coefficients of dz = A*g + B*z + C0 (per channel; coef = [3][C])

@@ -619,12 +619,13 @@ static hipError_t conv_tiled_any(const ddg_module* m, const void* in, const floa
                                  const BnRows* in_rows, const void* wpack, void* out, const ConvStat& st, const void* add_g,
                                  const void* add_mask, int N, int H, int W, int C, int grid, hipStream_t s,
                                  const void* res = nullptr, void* y_out = nullptr, int groups = 1, int vec_stride = 0,
-                                 const WgradFuse* apply = nullptr, const WgradPair* pair = nullptr) {
+                                 const WgradFuse* apply = nullptr, const WgradPair* pair = nullptr,
+                                 const BnReduceRide* ride = nullptr) {
   if (m->d.compute == DDG_BF16)
     return conv_tiled_launch(in, scale, shift, in_rows, wpack, out, st, add_g, add_mask, N, H, W, C, grid, s, res, y_out,
-                             groups, vec_stride, apply, pair);
+                             groups, vec_stride, apply, pair, ride);
   return conv_tiled_f32_launch(in, scale, shift, in_rows, wpack, out, st, add_g, add_mask, N, H, W, C, grid, s, res, y_out,
-                               groups, vec_stride, apply, pair);
+                               groups, vec_stride, apply, pair, ride);
 }
 static hipError_t wgrad_tiled_any(const ddg_module* m, const void* x, const float* scale, const float* shift, const void* dz,
                                   const WgradFuse* fuse, float* partial, int N, int H, int W, int C, int rows, hipStream_t s,
@@ -1073,10 +1074,11 @@ ddg_status flush_wide_wgrad(ddg_module* m) {
 //   below: if given and the input-gradient kernel supports it, that kernel also forms the
 //       BN-backward sums of the unit below from dx and stores dx multiplied by that unit's ReLU
 //       mask; *below_rows > 0 reports that it did (the readers of dx then pass mask = null)
+//   sums: the sums of another layer that are to ride in the input-gradient launch (tiled kernel that forms dz)
 ddg_status unit_backward(ddg_module* m, Unit& u, const void* dy, const void* mask, const float* mscale,
                          const float* mshift, int stats_rows, const void* x_in, const float* x_scale,
                          const float* x_shift, void* dz_buf, void* dx, const void* add_g, const void* add_mask,
-                         const BelowBn* below, int* below_rows) {
+                         const BelowBn* below, int* below_rows, const BnReduceRide* sums = nullptr) {
   const int dt = m->d.compute;
   const size_t E = u.out_elems();
   if (below_rows) *below_rows = 0;
@@ -1128,7 +1130,7 @@ ddg_status unit_backward(ddg_module* m, Unit& u, const void* dy, const void* mas
       }
       Launch L(m, (ride ? PK_BWD_PAIR : PK_CONV_DGRAD) + u.tiled_instance(), bytes, flops);
       DDG_TRY(conv_tiled_any(m, dy, nullptr, nullptr, nullptr, u.wpack_d, dx, st, add_g, add_mask, u.N, u.H, u.W,
-                                u.cin, u.tiled_grid, m->stream, nullptr, nullptr, 1, 0, &f, ride ? &wp : nullptr));
+                                u.cin, u.tiled_grid, m->stream, nullptr, nullptr, 1, 0, &f, ride ? &wp : nullptr, sums));
     }
     m->pend_w.on = true; m->pend_w.u = &u; m->pend_w.x = x_in; m->pend_w.xsc = x_scale; m->pend_w.xsh = x_shift;
     m->pend_w.dz = dz_buf;
@@ -1233,15 +1235,22 @@ ddg_status down_block_backward(ddg_module* m, Blk& b, const void* dy, const void
   Unit &u0 = b.u[0], &u1 = b.u[1], &up = b.u[2];
   const size_t E = up.out_elems();
   const int prows = bn_bwd_grid(E, up.cout, m->d.compute);
-  { // (both layers' sums, where the kernel that produced dy did not form those of the second layer)
-    const BnBwdSet qp = reduce_set(up, dy, ymask, nullptr, nullptr), q1 = reduce_set(u1, dy, ymask, nullptr, nullptr);
-    Launch L(m, PK_BN_BWD_REDUCE, (top_rows > 0 ? 1.0 : 2.0) * (ymask ? 3.0 : 2.0) * E * m->esz);
-    DDG_TRY(bn_bwd_reduce_launch(qp, top_rows > 0 ? nullptr : &q1, E, up.cout, m->d.compute, m->stream));
-    if (top_rows <= 0) top_rows = prows; }
+  // the projection's sums: in the second layer's launch, or with that layer's own sums where the kernel that produced dy
+  // did not form those
+  BnReduceRide ride{};
+  ride.q = reduce_set(up, dy, ymask, nullptr, nullptr); ride.elems = E; ride.C = up.cout; ride.grid = prows;
+  const bool rides = top_rows > 0;
+  if (!rides) {
+    const BnBwdSet q1 = reduce_set(u1, dy, ymask, nullptr, nullptr);
+    Launch L(m, PK_BN_BWD_REDUCE, 2.0 * (ymask ? 3.0 : 2.0) * E * m->esz);
+    DDG_TRY(bn_bwd_reduce_launch(ride.q, &q1, E, up.cout, m->d.compute, m->stream));
+    top_rows = prows;
+  }
   BelowBn below;
   below.u = &u0; below.mask = u0.z; below.mscale = u0.scale; below.mshift = u0.shift;
   int done = 0;
-  DDG_OKAY(unit_backward(m, u1, dy, ymask, nullptr, nullptr, top_rows, u0.z, u0.scale, u0.shift, nullptr, m->D2, nullptr, nullptr, &below, &done));
+  DDG_OKAY(unit_backward(m, u1, dy, ymask, nullptr, nullptr, top_rows, u0.z, u0.scale, u0.shift, nullptr, m->D2, nullptr, nullptr, &below, &done,
+                         rides ? &ride : nullptr));
   if (done <= 0 || !m->pend_w.on || m->pend_w.u != &u1) return fail(DDG_ERR_STATE, "internal: the second layer of a stage's first block left no weight gradient");
   // the weight gradients; the two error gradients formed on the way are stored for the input gradient
   void* dz0 = m->dz_flip ? m->D1b : m->D1;

@@ -16,6 +16,7 @@
 #include "ddg_device.h"
 #include "ddg_kernels.h"
 #include "ddg_stats.h"
+#include "ddg_bn_reduce.h"
 #include "ddg_wgrad_tiled.h"
 #include <cstdlib>
 
@@ -414,6 +415,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(conv_tiled_
   }
 }
 
+// The input gradient of the second layer of a stage's first block: beside it the sums of the block's projection, which wait for
+// the same gradient, and (wg_rows > 0) the plain weight gradient of the unit above.
+template <int C, int W, int XF>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(conv_tiled_waves(C, 2, XF)))) void bwd_down_kernel(ConvTiledArgs ca, WgradTiledArgs wa, BnReduceRide rd, int conv_grid, int wg_rows, int wg_blocks) {
+  extern __shared__ __align__(16) unsigned char tile[];
+  const int b = blockIdx.x;
+  if (b < conv_grid) {
+    conv3x3_tiled_body<C, W, 2, XF>(ca, tile, b, conv_grid);
+  } else if (b < conv_grid + wg_blocks) {
+    const int v = b - conv_grid;
+    wgrad_tiled_body<C, C, W, false>(wa, tile, v % wg_rows, v / wg_rows, wg_rows);
+  } else {
+    bn_bwd_reduce_body<bf16_t>(rd.q, rd.elems / 8, C, b - conv_grid - wg_blocks, rd.grid);
+  }
+}
+
 // Workgroups per launch for a layer with C channels (and so the number of partial statistics
 // rows the launch writes). Every workgroup loads its wave's weights and adds up the rows of the
 // layer before, so on the small feature maps fewer, longer-running workgroups mean less L2
@@ -447,8 +464,22 @@ int conv_tiled_grid(int N, int H, int W, int Cin, int Cout, int R, int stride, i
 }
 
 template <int C, int W>
-static hipError_t conv_tiled_launch_t(const ConvTiledArgs& a, int grid, hipStream_t s, const WgradTiledArgs* wa, int wg_rows) {
+static hipError_t conv_tiled_launch_t(const ConvTiledArgs& a, int grid, hipStream_t s, const WgradTiledArgs* wa, int wg_rows, const BnReduceRide* ride) {
   using Cfg = ConvTiledCfg<C, W>;
+  if (ride) {
+    using WCfg = WgradTiledCfg<C, C, W>;
+    if (!a.bz || a.st.mode != 2 || a.scale || a.in_rows.partial || !a.brows.partial || !a.dz_out || C == 16 || ride->C != C || ride->grid < 1)
+      return hipErrorInvalidValue;
+    constexpr int lds = Cfg::TILE_BYTES > WCfg::LDS ? Cfg::TILE_BYTES : WCfg::LDS;
+    if constexpr (C != 16) {
+      const int wgb = wa ? wg_rows * WCfg::OT : 0;
+      const dim3 g(grid + wgb + ride->grid);
+      const WgradTiledArgs none{};
+      if (a.bmask && a.bmask != a.bz) DDG_LAUNCH((bwd_down_kernel<C, W, XF_APPLY_MASK>), g, dim3(256), lds, s, a, wa ? *wa : none, *ride, grid, wg_rows, wgb);
+      else DDG_LAUNCH((bwd_down_kernel<C, W, XF_APPLY>), g, dim3(256), lds, s, a, wa ? *wa : none, *ride, grid, wg_rows, wgb);
+    }
+    return hipGetLastError();
+  }
   if (wa) {
     using WCfg = WgradTiledCfg<C, C, W>;
     if (!a.bz || a.st.mode == 1 || a.scale || a.in_rows.partial || !a.brows.partial || !a.dz_out || wg_rows < 1)
@@ -490,7 +521,7 @@ hipError_t conv_tiled_launch(const void* in, const float* scale, const float* sh
                              const void* wpack, void* out, const ConvStat& st, const void* add_g,
                              const void* add_mask, int N, int H, int W, int C, int grid, hipStream_t s,
                              const void* res, void* y_out, int groups, int vec_stride, const WgradFuse* apply,
-                             const WgradPair* pair) {
+                             const WgradPair* pair, const BnReduceRide* ride) {
   if (groups < 1 || N % groups != 0 || grid % groups != 0) return hipErrorInvalidValue;
   if (groups > 1 && (st.mode != 1 || add_g)) return hipErrorInvalidValue;   // forward only
   ConvTiledArgs a{};
@@ -515,9 +546,9 @@ hipError_t conv_tiled_launch(const void* in, const float* scale, const float* sh
   }
   const WgradTiledArgs* wp = pair ? &wa : nullptr;
   const int wr = pair ? pair->rows : 0;
-  if (C == 16 && W == 32) return conv_tiled_launch_t<16, 32>(a, grid, s, wp, wr);
-  if (C == 32 && W == 16) return conv_tiled_launch_t<32, 16>(a, grid, s, wp, wr);
-  if (C == 64 && W == 8) return conv_tiled_launch_t<64, 8>(a, grid, s, wp, wr);
+  if (C == 16 && W == 32) return conv_tiled_launch_t<16, 32>(a, grid, s, wp, wr, ride);
+  if (C == 32 && W == 16) return conv_tiled_launch_t<32, 16>(a, grid, s, wp, wr, ride);
+  if (C == 64 && W == 8) return conv_tiled_launch_t<64, 8>(a, grid, s, wp, wr, ride);
   return hipErrorInvalidValue;
 }
 

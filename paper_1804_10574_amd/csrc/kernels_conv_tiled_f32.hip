@@ -22,6 +22,7 @@
 #include "ddg_device.h"
 #include "ddg_kernels.h"
 #include "ddg_stats.h"
+#include "ddg_bn_reduce.h"
 #include "ddg_wgrad_vec.h"
 #include <cstdlib>
 
@@ -545,6 +546,16 @@ __global__ __launch_bounds__(256) void bwd_pair_f32_kernel(ConvTiledF32Args ca, 
   else wgrad_tiled_f32_body<C, W, false>(wa, smem, b - conv_grid, wg_rows);
 }
 
+// As bwd_down_kernel in the bf16 path: with the sums of the block's projection and, wg_rows > 0, the weight gradient of the unit above.
+template <int C, int W, int XF>
+__global__ __launch_bounds__(256) void bwd_down_f32_kernel(ConvTiledF32Args ca, WgradTiledF32Args wa, BnReduceRide rd, int conv_grid, int wg_rows) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int b = blockIdx.x;
+  if (b < conv_grid) conv3x3_tiled_f32_body<C, W, 2, XF>(ca, smem, b, conv_grid);
+  else if (b < conv_grid + wg_rows) wgrad_tiled_f32_body<C, W, false>(wa, smem, b - conv_grid, wg_rows);
+  else bn_bwd_reduce_body<float>(rd.q, rd.elems / 4, C, b - conv_grid - wg_rows, rd.grid);
+}
+
 template <int C, int W>
 __global__ __launch_bounds__(256) void wgrad_tiled_f32_kernel(WgradTiledF32Args a) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -579,8 +590,21 @@ int wgrad_tiled_f32_rows(int N, int H, int W, int Cin, int Cout, int R, int stri
 }
 
 template <int C, int W>
-static hipError_t conv_tiled_f32_launch_t(const ConvTiledF32Args& a, int grid, hipStream_t s, const WgradTiledF32Args* wa, int wg_rows) {
+static hipError_t conv_tiled_f32_launch_t(const ConvTiledF32Args& a, int grid, hipStream_t s, const WgradTiledF32Args* wa, int wg_rows, const BnReduceRide* ride) {
   using Cfg = ConvTiledF32Cfg<C, W>;
+  if (ride) {
+    using WCfg = WgradTiledF32Cfg<C, W>;
+    if (!a.bz || a.st.mode != 2 || a.scale || a.in_rows.partial || !a.brows.partial || !a.dz_out || C == 16 || ride->C != C || ride->grid < 1)
+      return hipErrorInvalidValue;
+    constexpr int lds = Cfg::TILE_BYTES > WCfg::LDS ? Cfg::TILE_BYTES : WCfg::LDS;
+    if constexpr (C != 16) {
+      const dim3 g(grid + wg_rows + ride->grid);
+      const WgradTiledF32Args none{};
+      if (a.bmask && a.bmask != a.bz) DDG_LAUNCH((bwd_down_f32_kernel<C, W, XF32_APPLY_MASK>), g, dim3(256), lds, s, a, wa ? *wa : none, *ride, grid, wg_rows);
+      else DDG_LAUNCH((bwd_down_f32_kernel<C, W, XF32_APPLY>), g, dim3(256), lds, s, a, wa ? *wa : none, *ride, grid, wg_rows);
+    }
+    return hipGetLastError();
+  }
   static_assert(Cfg::TILE_BYTES <= 48 * 1024, "dynamic LDS within the default limit");
   if (wa) {
     using WCfg = WgradTiledF32Cfg<C, W>;
@@ -623,7 +647,7 @@ hipError_t conv_tiled_f32_launch(const void* in, const float* scale, const float
                                  const void* wpack, void* out, const ConvStat& st, const void* add_g,
                                  const void* add_mask, int N, int H, int W, int C, int grid, hipStream_t s,
                                  const void* res, void* y_out, int groups, int vec_stride, const WgradFuse* apply,
-                                 const WgradPair* pair) {
+                                 const WgradPair* pair, const BnReduceRide* ride) {
   if (groups < 1 || N % groups != 0 || grid % groups != 0) return hipErrorInvalidValue;
   if (groups > 1 && (st.mode != 1 || add_g)) return hipErrorInvalidValue;   // forward only
   if ((size_t)N * H * W * C >= ((size_t)1 << 31)) return hipErrorInvalidValue;   // 32-bit element offsets inside
@@ -649,9 +673,9 @@ hipError_t conv_tiled_f32_launch(const void* in, const float* scale, const float
   }
   const WgradTiledF32Args* wp = pair ? &wa : nullptr;
   const int wr = pair ? pair->rows : 0;
-  if (C == 16 && W == 32) return conv_tiled_f32_launch_t<16, 32>(a, grid, s, wp, wr);
-  if (C == 32 && W == 16) return conv_tiled_f32_launch_t<32, 16>(a, grid, s, wp, wr);
-  if (C == 64 && W == 8) return conv_tiled_f32_launch_t<64, 8>(a, grid, s, wp, wr);
+  if (C == 16 && W == 32) return conv_tiled_f32_launch_t<16, 32>(a, grid, s, wp, wr, ride);
+  if (C == 32 && W == 16) return conv_tiled_f32_launch_t<32, 16>(a, grid, s, wp, wr, ride);
+  if (C == 64 && W == 8) return conv_tiled_f32_launch_t<64, 8>(a, grid, s, wp, wr, ride);
   return hipErrorInvalidValue;
 }
 

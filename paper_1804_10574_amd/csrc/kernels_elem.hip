@@ -9,6 +9,7 @@
 #include "ddg_device.h"
 #include "ddg_kernels.h"
 #include "ddg_stats.h"
+#include "ddg_bn_reduce.h"
 
 namespace ddg {
 
@@ -263,78 +264,7 @@ hipError_t bn_apply_launch(const void* z, const float* scale, const float* shift
 // blockIdx.y: one of two layers of the same shape (the last layer of a stage's first block and its projection).
 template <typename T>
 __global__ __launch_bounds__(256) void bn_bwd_reduce_kernel(BnBwdSet q0, BnBwdSet q1, size_t nvec, int C) {
-  const BnBwdSet& q = blockIdx.y ? q1 : q0;
-  const T* __restrict__ dy = reinterpret_cast<const T*>(q.dy);
-  const T* __restrict__ mask = reinterpret_cast<const T*>(q.mask);
-  const float* __restrict__ mscale = q.mscale;
-  const float* __restrict__ mshift = q.mshift;
-  const T* __restrict__ z = reinterpret_cast<const T*>(q.z);
-  const float* __restrict__ mean = q.mean;
-  const float* __restrict__ invstd = q.invstd;
-  float* __restrict__ partial = q.partial;
-  constexpr int V = Store<T>::VEC;
-  const size_t stride = (size_t)gridDim.x * blockDim.x;
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int c0 = (int)((i * V) % C);
-  float mu[V], is[V], s1[V], s2[V], ms[V], mh[V];
-#pragma unroll
-  for (int j = 0; j < V; ++j) {
-    mu[j] = mean[c0 + j]; is[j] = invstd[c0 + j]; s1[j] = 0.f; s2[j] = 0.f;
-    ms[j] = mscale ? mscale[c0 + j] : 1.f; mh[j] = mscale ? mshift[c0 + j] : 0.f;
-  }
-  // four vectors per trip, all requested before any is used (the sums keep their order)
-  typedef typename Store<T>::vec_t vec_t;
-  constexpr int U = 4;
-  const bool own_mask = mask && mask != z;
-  for (; i < nvec; i += U * stride) {
-    vec_t gq[U], zq[U], mq[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const size_t iu = i + u * stride;
-      if (iu < nvec) {
-        gq[u] = *reinterpret_cast<const vec_t*>(dy + iu * V);
-        zq[u] = *reinterpret_cast<const vec_t*>(z + iu * V);
-        if (own_mask) mq[u] = *reinterpret_cast<const vec_t*>(mask + iu * V);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (i + u * stride >= nvec) continue;
-      float g[V], zz[V];
-      Store<T>::unpack_vec(gq[u], g);
-      Store<T>::unpack_vec(zq[u], zz);
-      if (mask) {
-        float mk[V];
-        Store<T>::unpack_vec(own_mask ? mq[u] : zq[u], mk);
-#pragma unroll
-        for (int j = 0; j < V; ++j) g[j] = (mk[j] * ms[j] + mh[j]) > 0.f ? g[j] : 0.f;
-      }
-#pragma unroll
-      for (int j = 0; j < V; ++j) {
-        s1[j] += g[j];
-        s2[j] += g[j] * ((zz[j] - mu[j]) * is[j]);
-      }
-    }
-  }
-  // Threads with equal (threadIdx.x*V) % C hold the same channels; their sums are added in thread
-  // order, one thread per sum. (Two threads that added all sums of 128 rows were most of this kernel for
-  // 16 channels: 11.3 -> 7.2 us at 37 x 32 x 32 x 16 in a running
-  // pipeline.)
-  const int per = C / V < 256 ? C / V : 256;  // distinct channel vectors among the block's threads
-  __shared__ float red[2][256][V + 1];
-#pragma unroll
-  for (int j = 0; j < V; ++j) { red[0][threadIdx.x][j] = s1[j]; red[1][threadIdx.x][j] = s2[j]; }
-  __syncthreads();
-  // sum e of 2 * per * V: (which, channel vector, element); block b, thread t covers channels ((b*256+t)*V) % C
-  const int nper = per * V, rows = 256 / per;
-  for (int e = threadIdx.x; e < 2 * nper; e += 256) {
-    const int which = e / nper, k = e - which * nper, t0 = k / V, j = k - t0 * V;
-    float t = 0.f;
-#pragma unroll 16
-    for (int r = 0; r < rows; ++r) t += red[which][r * per + t0][j];
-    const int cb = (int)((((size_t)blockIdx.x * 256 + t0) * V) % C);
-    partial[((size_t)blockIdx.x * 2 + which) * C + cb + j] = t;
-  }
+  bn_bwd_reduce_body<T>(blockIdx.y ? q1 : q0, nvec, C, blockIdx.x, gridDim.x);
 }
 
 // When C > 256*V a block covers only part of the channels; the other entries of its
