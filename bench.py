@@ -34,18 +34,18 @@ HIP_KERNEL_OF = {
     "conv_dgrad.tiled_c32_w16": "ddg::conv3x3_tiled_kernel<32, 16, 2|0, XF>",
     "conv_dgrad.tiled_c64_w8": "ddg::conv3x3_tiled_kernel<64, 8, 2|0, XF>",
     "conv_bwd_pair.tiled_c16_w32": "ddg::bwd_pair_kernel<16, 32, 2|0, XF>",
-    "conv_bwd_pair.tiled_c32_w16": "ddg::bwd_pair_kernel<32, 16, 2|0, XF>",
-    "conv_bwd_pair.tiled_c64_w8": "ddg::bwd_pair_kernel<64, 8, 2|0, XF>",
+    "conv_bwd_pair.tiled_c32_w16": "ddg::bwd_pair_kernel<32, 16, 2|0, XF>, ddg::bwd_down_kernel<32, 16, XF>",
+    "conv_bwd_pair.tiled_c64_w8": "ddg::bwd_pair_kernel<64, 8, 2|0, XF>, ddg::bwd_down_kernel<64, 8, XF>",
     "bn_apply": "ddg::bn_apply_chunk_kernel<bf16_t, U>",
     "conv_wgrad.tiled_c16_w32": "ddg::wgrad_tiled_kernel<16, 16, 32, 1, 3>",
     "conv_wgrad.tiled_c32_w16": "ddg::wgrad_tiled_kernel<32, 32, 16, 1, 3>",
     "conv_wgrad.tiled_c64_w8": "ddg::wgrad_tiled_kernel<64, 64, 8, 1, 3>",
-    "conv_wgrad.tiled_stride2": "ddg::wgrad_tiled_kernel<Cin, 2*Cin, W, 2, R>",
+    "conv_wgrad.tiled_stride2": "ddg::wgrad_down_kernel<Cin, W>, ddg::wgrad_tiled_kernel<Cin, 2*Cin, W, 2, R>",
     "conv_fprop.wide": "ddg::conv_wide_kernel<1, XFORM, BK, R>, ddg::conv_halo_kernel<1, XFORM, BN>, ddg::conv_point_kernel<1, XFORM, K>",
     "conv_dgrad.wide": "ddg::conv_wide_kernel<0|2, false, BK, R>, ddg::conv_halo_kernel<0|2, false, BN>, ddg::conv_point_kernel<0|2, false, K>",
     "conv_wgrad.wide": "ddg::wgrad_wide_kernel",
     "conv_fprop.generic": "ddg::conv_mfma_kernel<T, MB, NB, false, VEC>",
-    "conv_dgrad.generic": "ddg::conv_mfma_kernel<T, MB, NB, true, VEC>",
+    "conv_dgrad.generic": "ddg::conv_dgrad_s2_kernel<T, ...>, ddg::bwd_generic_kernel<T, MB, NB>, ddg::conv_mfma_kernel<T, MB, NB, true, VEC>",
     "conv_wgrad.generic": "ddg::wgrad_mfma_vec_kernel<T> / wgrad_mfma_kernel<T>",
 }
 

@@ -18,6 +18,8 @@ void ddg_internal_eval_stream(ddg_module* m, bool on, hipStream_t s);
 // A pipeline orders the module's two streams itself (events around graph launches); the module
 // then records and waits on nothing.
 void ddg_internal_external_sync(ddg_module* m, bool on);
+// While on, ddg_backward_delayed may leave sums of weight gradients to the ddg_update that the caller issues right after it.
+void ddg_internal_fuse_update(ddg_module* m, bool on);
 // The streams ddg_forward and ddg_backward_delayed/ddg_update enqueue on (equal unless the
 // module runs its forward pass on a stream of its own).
 void ddg_internal_streams(ddg_module* m, hipStream_t* fwd, hipStream_t* bwd);

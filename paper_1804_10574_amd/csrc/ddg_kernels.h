@@ -127,6 +127,12 @@ struct UpdArgs {
   float b1, b2, eps; double b1d, b2d; double* pw; unsigned* pw_readers;                // Adam
 };
 hipError_t update_pack_launch(const UpdDesc* dev_descs, int n, unsigned max_len, const UpdArgs& a, int dtype, bool adam, hipStream_t s);
+// Weight-gradient sums, optimizer step and repacking in one launch (modules of at most UPDATE_PACK_MAX parameters): nlayers
+// descriptors of each kind in the same order, then, with `head`, the head's segment, whose gradients (and the mean loss) the
+// launch forms from what the head's per-sample launch left.
+struct HeadSums { const float *pooled, *dlogits, *loss_n; float* loss_out; int N, C, classes; };
+hipError_t reduce_update_launch(const WredDesc* wdescs, const UpdDesc* udescs, int nlayers, int max_blocks, const UpdArgs& a, const HeadSums* head,
+                                int dtype, bool adam, hipStream_t s);
 // max_blocks: the largest wgrad_reduce_blocks() among the n layers (sizes the grid)
 int wgrad_reduce_blocks(const WredDesc& d);
 hipError_t wgrad_reduce_all_launch(const WredDesc* dev_descs, int n, int max_blocks, hipStream_t s);
@@ -295,6 +301,7 @@ struct HeadArgs {
   float* dfcw; float* dfcb; void* dh;
   int N, HW, C, classes, dtype;
   float* logits_out;     // optional [N][classes]
+  int sums_later;        // 1: the gradients of the classifier and the mean loss are left to reduce_update_launch
 };
 // dfcw == nullptr: evaluation (no gradients; dh must be null too).
 hipError_t head_launch(const HeadArgs& a, hipStream_t s);

@@ -187,6 +187,9 @@ struct ddg_module {
   bool has_grad = false;
   bool tape_is_current = false;  // saved activations belong to forward(t) with current weights
   ddg_status sticky = DDG_OK;
+  // pipeline: the update follows the backward pass at once, so the sums of the weight gradients (and the head's, with the
+  // loss) are left to its launch
+  bool fuse_update = false, sums_left = false; float* loss_left = nullptr;
   bool skip = false;               // advance state only (a captured graph is replayed instead)
   const float* lr_dev = nullptr;   // step size in device memory, if set
   // profiling
@@ -1304,6 +1307,8 @@ ddg_status run_backward(ddg_module* m, std::vector<Blk>& blocks, const void* in,
     a.pooled = hb.pooled; a.dlogits = hb.dlogits; a.loss_n = hb.loss_n; a.loss_out = loss_out;
     a.dfcw = m->grad + hb.ofcw; a.dfcb = m->grad + hb.ofcb; a.dh = nres > 0 ? m->Ga : delta_out;
     a.N = m->d.batch; a.HW = hb.HW; a.C = hb.C; a.classes = m->d.num_classes; a.dtype = dt;
+    a.sums_later = m->fuse_update && m->upd_descs ? 1 : 0;
+    m->loss_left = loss_out;
     Launch L(m, PK_HEAD);
     DDG_TRY(head_launch(a, m->stream));
     dy = m->Ga;
@@ -2013,6 +2018,8 @@ ddg_status ddg_backward_delayed(ddg_module* m, long t, const void* delta_in, con
   } else {
     DDG_OKAY(run_backward(m, m->blocks, slot, delta_in, labels, m->d.k > 1 ? delta_out : nullptr, loss_out));
   }
+  m->sums_left = m->fuse_update && m->upd_descs;
+  if (m->sums_left) return DDG_OK;
   // every layer's weight-gradient partials -> g (one launch for the module, fixed order)
   Launch L(m, PK_WGRAD_REDUCE, (double)m->nparams * 4.0);
   DDG_TRY(wgrad_reduce_all_launch(m->wred_descs, m->n_wred, m->wred_max, m->stream));
@@ -2038,6 +2045,18 @@ ddg_status ddg_update(ddg_module* m, long t, float lr) {
     a.b1 = m->beta1; a.b2 = m->beta2; a.eps = m->adam_eps; a.b1d = (double)m->beta1; a.b2d = (double)m->beta2;
     a.pw = m->adam_pw; a.pw_readers = m->pw_readers;
     Launch L(m, adam ? PK_ADAM : PK_SGD, (double)m->nparams * (adam ? 28.0 : 20.0));
+    if (m->sums_left) {
+      m->sums_left = false;
+      HeadSums h{};
+      const bool head = m->d.num_classes > 0;
+      if (head) {
+        const Blk& hb = m->blocks.back();
+        h.pooled = hb.pooled; h.dlogits = hb.dlogits; h.loss_n = hb.loss_n; h.loss_out = m->loss_left;
+        h.N = m->d.batch; h.C = hb.C; h.classes = m->d.num_classes;
+      }
+      DDG_TRY(reduce_update_launch(m->wred_descs, m->upd_descs, m->n_wred, m->wred_max, a, head ? &h : nullptr, m->d.compute, adam, m->stream));
+      return DDG_OK;
+    }
     DDG_TRY(update_pack_launch(m->upd_descs, m->n_upd, m->upd_max, a, m->d.compute, adam, m->stream));
     if (self_sync) DDG_TRY(hipEventRecord(m->ev_upd, m->bstream));
     return DDG_OK;
@@ -2063,6 +2082,7 @@ ddg_status ddg_module_sync(ddg_module* m) {
 }
 
 void ddg_internal_skip_launches(ddg_module* m, bool skip) { m->skip = skip; }
+void ddg_internal_fuse_update(ddg_module* m, bool on) { m->fuse_update = on; }
 void ddg_internal_eval_stream(ddg_module* m, bool on, hipStream_t s) { m->eval_elsewhere = on; m->estream = s; }
 void ddg_internal_external_sync(ddg_module* m, bool on) { m->external_sync = on; }
 void ddg_internal_streams(ddg_module* m, hipStream_t* fwd, hipStream_t* bwd) { *fwd = m->fstream; *bwd = m->bstream; }

@@ -385,6 +385,15 @@ ddg_status ddg_pipeline_step(ddg_pipeline* p, const void* x, const int32_t* labe
     std::vector<void*>& hb = cur ? p->h_odd : p->h;
     return ddg_forward(p->mods[k], t, k == 1 ? x_in : hb[k - 1], k < K ? hb[k] : nullptr);
   };
+  // backward and update in one go: the module may join the two
+  auto call_backward_update = [&](int k) -> ddg_status {
+    const bool on = t - K + k >= 0;
+    ddg_internal_fuse_update(p->mods[k], true);
+    ddg_status r = ddg_backward_delayed(p->mods[k], t, (on && k < K) ? p->mail[prev][k] : nullptr, k == K ? lab : nullptr,
+                                        k > 1 ? p->mail[cur][k - 1] : nullptr, k == K ? (p->dry ? loss_out : p->loss_dev) : nullptr, nullptr);
+    ddg_internal_fuse_update(p->mods[k], false);
+    return r == DDG_OK ? ddg_update(p->mods[k], t, lr) : r;
+  };
   auto call_backward = [&](int k) -> ddg_status {
     const bool on = t - K + k >= 0;
     return ddg_backward_delayed(p->mods[k], t, (on && k < K) ? p->mail[prev][k] : nullptr, k == K ? lab : nullptr,
@@ -442,8 +451,7 @@ ddg_status ddg_pipeline_step(ddg_pipeline* p, const void* x, const int32_t* labe
     }
     ddg_status st = run(k, fs, p->gfwd[k], [&]() {
       ddg_status r = call_forward(k);
-      if (r == DDG_OK && whole) r = call_backward(k);
-      if (r == DDG_OK && whole) r = ddg_update(p->mods[k], t, lr);
+      if (r == DDG_OK && whole) r = call_backward_update(k);
       return r; });
     if (st != DDG_OK) return st;
     if (model) om.record(ev_f(cur, k), sf);
@@ -466,10 +474,7 @@ ddg_status ddg_pipeline_step(ddg_pipeline* p, const void* x, const int32_t* labe
     }
     if (!whole) {
       model_backward(k);
-      ddg_status st = run(k, bs, p->gbwd[k], [&]() {
-        ddg_status r = call_backward(k);
-        if (r == DDG_OK && !split) r = ddg_update(p->mods[k], t, lr);
-        return r; });
+      ddg_status st = run(k, bs, p->gbwd[k], [&]() { return split ? call_backward(k) : call_backward_update(k); });
       if (st != DDG_OK) return st;
       if (split) {
         // the update overwrites the weights that this iteration's forward pass reads

@@ -15,6 +15,7 @@
 #include "ddg_device.h"
 #include "ddg_kernels.h"
 #include "ddg_wgrad_vec.h"
+#include "ddg_update.h"
 #include <cstdlib>
 
 namespace ddg {
@@ -587,53 +588,18 @@ hipError_t pack_all_launch(const PackDesc* dev_descs, int n, int dtype, hipStrea
 // ResNet-110 even). The stores are scattered, so the line lies where a module's operands stop fitting an XCD's
 // 4 MiB L2 with room (UPDATE_PACK_MAX parameters): larger ones keep the separate launches, which stream.
 // blockIdx.y: a segment of the parameter vector, `conv` weights (maybe none) followed by `plain` values.
-// Adam: pw holds beta1^n, beta2^n; every workgroup uses the powers of this update, and the last one to have read
-// them (pw_readers counts) stores them.
 template <typename T, bool ADAM>
 __global__ __launch_bounds__(256) void update_pack_kernel(const UpdDesc* __restrict__ descs, UpdArgs a) {
-  constexpr int KV = Mma<T>::KV;
   const UpdDesc d = descs[blockIdx.y];
-  const float lr = a.lr_dev ? *a.lr_dev : a.lr;
-  float c1 = 1.f, c2 = 1.f;
-  if (ADAM) {
-    const double p1 = a.pw[0] * a.b1d, p2 = a.pw[1] * a.b2d;
-    c1 = (float)(1.0 - p1); c2 = (float)(1.0 - p2);
-    __shared__ unsigned s_seen;
-    asm volatile("" ::"v"(c1), "v"(c2));            // (read before it is counted)
-    __syncthreads();
-    if (threadIdx.x == 0) s_seen = atomicAdd(a.pw_readers, 1u);
-    __syncthreads();
-    if (threadIdx.x == 0 && s_seen + 1 == gridDim.x * gridDim.y) {
-      a.pw[0] = p1; a.pw[1] = p2;
-      *a.pw_readers = 0u;
-    }
-  }
+  UpdStep<ADAM> u;
+  u.init(a, gridDim.x * gridDim.y);
   const unsigned n = d.conv + d.plain, RR = (unsigned)(d.R * d.R);
   for (unsigned i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
-    const size_t e = d.off + i;
-    const float wi = a.w[e];
-    float wn;
-    if (ADAM) {
-      const float gi = a.g[e] + a.wd * wi;
-      const float mi = a.b1 * a.v[e] + (1.f - a.b1) * gi;
-      const float vi = a.b2 * a.m2[e] + (1.f - a.b2) * gi * gi;
-      a.v[e] = mi; a.m2[e] = vi;
-      wn = wi - lr * (mi / c1) / (sqrtf(vi / c2) + a.eps);
-    } else {
-      const float vi = a.mu * a.v[e] + (a.g[e] + a.wd * wi);
-      a.v[e] = vi;
-      wn = wi - lr * vi;
-    }
-    a.w[e] = wn;
+    const float wn = u.step(a, d.off + i, a.g[d.off + i]);
     if (i >= d.conv) continue;
     const unsigned t = RR == 9 ? i / 9u : i, tap = RR == 9 ? i - t * 9u : 0u;
     const unsigned co = t / d.Cin, ci = t - co * d.Cin;
-    auto at = [&](unsigned k, unsigned row, unsigned ocb) __attribute__((always_inline)) {
-      return (((k / (4 * KV)) * ocb + (row >> 4)) * 64 + (k / KV % 4) * 16 + (row & 15)) * KV + k % KV;
-    };
-    Store<T>::store1(reinterpret_cast<T*>(d.pack_f) + at((tap << d.l2f) + ci, co, d.ocb_f), wn);
-    if (d.pack_d)
-      Store<T>::store1(reinterpret_cast<T*>(d.pack_d) + at(((d.mirror ? RR - 1 - tap : tap) << d.l2d) + co, ci, d.ocb_d), wn);
+    upd_pack<T>(d, co, ci, tap, wn);
   }
 }
 

@@ -690,6 +690,7 @@ hipError_t head_launch(const HeadArgs& a, hipStream_t s) {
   if (a.C % 4 != 0) return hipErrorInvalidValue;
   hipError_t e = a.dtype == BF16 ? head_sample_any<bf16_t>(a, s) : head_sample_any<float>(a, s);
   if (e != hipSuccess) return e;
+  if (a.sums_later) return hipGetLastError();
   if (!a.dfcw) {   // evaluation: no gradients; the mean loss if asked for
     if (a.loss_out) DDG_LAUNCH(loss_mean_kernel, dim3(1), dim3(256), 0, s, a.loss_n, a.N, a.loss_out);
     return hipGetLastError();

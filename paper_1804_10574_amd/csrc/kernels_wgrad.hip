@@ -9,6 +9,7 @@
 #include "ddg_device.h"
 #include "ddg_kernels.h"
 #include "ddg_wgrad_vec.h"
+#include "ddg_update.h"
 #include <cstdlib>
 
 namespace ddg {
@@ -234,6 +235,155 @@ __global__ __launch_bounds__(256) void wgrad_reduce_all_kernel(const WredDesc* _
       }
     }
   }
+}
+
+// Adding up, update and repacking of a small module in one launch (see update_pack_kernel), for callers whose update follows
+// at once: a weight's sum is applied by the thread that formed it, the gradient vector is written but not read again, and a
+// launch in the chain goes. blockIdx.y: a segment of the parameter vector. A layer: its sums as above (same order), then one
+// workgroup for batch-norm scales and shifts, whose gradients are complete. The head: a workgroup per class, which forms
+// the class's gradient as head_wgrad_kernel does.
+template <typename T, bool ADAM>
+__global__ __launch_bounds__(256) void reduce_update_kernel(const WredDesc* __restrict__ wdescs, const UpdDesc* __restrict__ udescs, int nlayers,
+                                                            UpdArgs a, HeadSums h) {
+  UpdStep<ADAM> u;
+  u.init(a, gridDim.x * gridDim.y);
+  const UpdDesc ud = udescs[blockIdx.y];
+  float* g = const_cast<float*>(a.g);
+  const int tid = threadIdx.x;
+  __shared__ float4 red[RED_J_MAX / 4];
+  float* redf = reinterpret_cast<float*>(red);
+  if ((int)blockIdx.y >= nlayers) {               // the head: dfcw[j][:] = sum_n dlogits[n][j] * pooled[n][:], dfcb[j], loss
+    const int j = blockIdx.x, C = h.C;
+    if (j >= h.classes) return;
+    float b = 0.f, l = 0.f;
+    for (int n = tid; n < h.N; n += 256) {
+      b += h.dlogits[(size_t)n * h.classes + j];
+      if (j == 0) l += h.loss_n[n];
+    }
+    redf[256 + tid] = b; redf[512 + tid] = l;
+    const int cpt = C < 256 ? C : 256, groups = 256 / cpt;
+    const int cl = tid % cpt, gr = tid / cpt;
+    for (int c0 = 0; c0 < C; c0 += cpt) {
+      const int c = c0 + cl;
+      float t = 0.f;
+      if (gr < groups && c < C) {
+#pragma unroll 16
+        for (int n = gr; n < h.N; n += groups) t += h.dlogits[(size_t)n * h.classes + j] * h.pooled[(size_t)n * C + c];
+      }
+      redf[tid] = t;
+      __syncthreads();
+      if (gr == 0 && c < C) {
+        float q = 0.f;
+        for (int k = 0; k < groups; ++k) q += redf[k * cpt + cl];
+        const size_t e = ud.off + (size_t)j * C + c;
+        g[e] = q;
+        u.step(a, e, q);
+      }
+      __syncthreads();
+    }
+    const int terms = h.N < 256 ? h.N : 256;
+    if (tid == 0) {
+      float t = 0.f;
+#pragma unroll 16
+      for (int q = 0; q < terms; ++q) t += redf[256 + q];
+      const size_t e = ud.off + (size_t)h.classes * C + j;
+      g[e] = t;
+      u.step(a, e, t);
+    }
+    if (tid == 64 && j == 0 && h.loss_out) {
+      float t = 0.f;
+#pragma unroll 16
+      for (int q = 0; q < terms; ++q) t += redf[512 + q];
+      *h.loss_out = t / (float)h.N;
+    }
+    return;
+  }
+  const WredDesc d = wdescs[blockIdx.y];
+  const int total4 = d.Cout * d.Jp / 4;
+  const bool few = red_few(d.rows, d.Cout, d.Cin, d.R, d.Jp);
+  const int per = few ? (d.R == 1 ? 256 : d.Jp / 4) : 64;      // groups of 4 outputs of a workgroup
+  const int nb = (total4 + per - 1) / per;
+  if ((int)blockIdx.x > nb) return;
+  if ((int)blockIdx.x == nb) {
+    for (unsigned i = tid; i < ud.plain; i += 256) u.step(a, ud.off + ud.conv + i, a.g[ud.off + ud.conv + i]);
+    return;
+  }
+  const int RR = d.R * d.R;
+  auto apply = [&](int co, int ci, int tap, float s) __attribute__((always_inline)) {
+    const size_t e = ud.off + ((size_t)co * d.Cin + ci) * RR + tap;
+    g[e] = s;
+    upd_pack<T>(ud, co, ci, tap, u.step(a, e, s));
+  };
+  if (few) {
+    for (int k = tid; k < per; k += 256) {
+      const float4* __restrict__ p = reinterpret_cast<const float4*>(d.partial) + (size_t)blockIdx.x * per + k;
+      float4 v[RED_FEW];
+#pragma unroll
+      for (int r = 0; r < RED_FEW; ++r) v[r] = p[(size_t)(r < d.rows ? r : d.rows - 1) * total4];
+      float4 c[4];
+#pragma unroll
+      for (int rc = 0; rc < 4; ++rc) c[rc] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int r = 0; r < RED_FEW; ++r)
+        if (r < d.rows) { c[r & 3].x += v[r].x; c[r & 3].y += v[r].y; c[r & 3].z += v[r].z; c[r & 3].w += v[r].w; }
+      const float t[4] = {((c[0].x + c[1].x) + c[2].x) + c[3].x, ((c[0].y + c[1].y) + c[2].y) + c[3].y,
+                          ((c[0].z + c[1].z) + c[2].z) + c[3].z, ((c[0].w + c[1].w) + c[2].w) + c[3].w};
+      const int j = k * 4, tap = RR == 9 ? j >> d.log2cp : 0, ci = RR == 9 ? j & ((1 << d.log2cp) - 1) : j;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) redf[(ci + i) * RR + tap] = t[i];
+    }
+    __syncthreads();
+    // in the order of the parameter vector: 3x3, one output channel; 1x1, 1024 consecutive weights
+    for (int k = tid; k < per * 4; k += 256) {
+      const int e = (int)blockIdx.x * per * 4 + k, q = RR == 9 ? k / 9 : 0;
+      if (RR == 9) apply(blockIdx.x, q, k - q * 9, redf[k]);
+      else apply(e / d.Cin, e % d.Cin, 0, redf[k]);
+    }
+    return;
+  }
+  const int cl = tid & 63, rc = tid >> 6;
+  const int col = blockIdx.x * 64 + cl;
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (col < total4) {
+    const float4* __restrict__ p = reinterpret_cast<const float4*>(d.partial) + col;
+    for (int r0 = rc; r0 < d.rows; r0 += 32) {
+      float4 v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int r = r0 + 4 * q;
+        v[q] = r < d.rows ? p[(size_t)r * total4] : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q) { s.x += v[q].x; s.y += v[q].y; s.z += v[q].z; s.w += v[q].w; }
+    }
+  }
+  red[rc * 64 + cl] = s;
+  __syncthreads();
+  const int e = (int)blockIdx.x * 256 + tid;      // one output per thread
+  if (e < total4 * 4) {
+    const float t = ((redf[tid] + redf[256 + tid]) + redf[512 + tid]) + redf[768 + tid];
+    const int co = e / d.Jp, j = e - co * d.Jp;
+    const int tap = j >> d.log2cp, ci = j & ((1 << d.log2cp) - 1);
+    if (tap < RR && ci < d.Cin) apply(co, ci, tap, t);
+  }
+}
+
+hipError_t reduce_update_launch(const WredDesc* wdescs, const UpdDesc* udescs, int nlayers, int max_blocks, const UpdArgs& a, const HeadSums* head,
+                                int dtype, bool adam, hipStream_t s) {
+  int gx = nlayers > 0 ? max_blocks + 1 : 0;      // and the batch-norm values' workgroup
+  if (head && head->classes > gx) gx = head->classes;
+  const int gy = nlayers + (head ? 1 : 0);
+  if (gx <= 0 || gy <= 0) return hipSuccess;
+  const dim3 grid(gx, gy), block(256);
+  const HeadSums h = head ? *head : HeadSums{};
+  if (dtype == BF16) {
+    if (adam) DDG_LAUNCH((reduce_update_kernel<bf16_t, true>), grid, block, 0, s, wdescs, udescs, nlayers, a, h);
+    else DDG_LAUNCH((reduce_update_kernel<bf16_t, false>), grid, block, 0, s, wdescs, udescs, nlayers, a, h);
+  } else {
+    if (adam) DDG_LAUNCH((reduce_update_kernel<float, true>), grid, block, 0, s, wdescs, udescs, nlayers, a, h);
+    else DDG_LAUNCH((reduce_update_kernel<float, false>), grid, block, 0, s, wdescs, udescs, nlayers, a, h);
+  }
+  return hipGetLastError();
 }
 
 int wgrad_reduce_blocks(const WredDesc& d) {

@@ -54,7 +54,7 @@ def kind_of(kernel_name: str) -> str:
     if m:   # the fp32 instances book the same kinds
         fam = "conv_fprop" if m.group(3) == "1" else "conv_dgrad"
         return f"{fam}.tiled_c{m.group(1)}_w{m.group(2)}"
-    m = re.match(r"bwd_pair(?:_f32)?_kernel<(\d+), (\d+), ", n)
+    m = re.match(r"bwd_(?:pair|down)(?:_f32)?_kernel<(\d+), (\d+), ", n)
     if m:
         return f"conv_bwd_pair.tiled_c{m.group(1)}_w{m.group(2)}"
     m = re.match(r"wgrad_tiled_f32_kernel<(\d+), (\d+)>", n)
@@ -71,10 +71,12 @@ def kind_of(kernel_name: str) -> str:
     m = re.match(r"conv_mfma_kernel<\w+, \d+, \d+, (true|false)", n)
     if m:   # <T, MB, NB, DGRAD, VEC>
         return "conv_dgrad.generic" if m.group(1) == "true" else "conv_fprop.generic"
-    m = re.match(r"update_pack_kernel<[\w:]+, (true|false)>", n)
-    if m:   # <T, ADAM>: the optimizer step and the repacking
+    if re.match(r"wgrad_down(?:_f32)?_kernel<", n):   # a stage's first block: its three weight gradients
+        return "conv_wgrad.tiled_stride2"
+    m = re.match(r"(?:update_pack|reduce_update)_kernel<[\w:]+, (true|false)>", n)
+    if m:   # <T, ADAM>: the optimizer step and the repacking (and the sums of the weight gradients)
         return "adam" if m.group(1) == "true" else "sgd"
-    table = [("conv_dgrad_s2_kernel", "conv_dgrad.generic"), ("bn_apply_wide_kernel", "bn_apply"),
+    table = [("conv_dgrad_s2_kernel", "conv_dgrad.generic"), ("bwd_generic_kernel", "conv_dgrad.generic"), ("bn_apply_wide_kernel", "bn_apply"),
              ("bn_bwd_apply_wide_kernel", "bn_bwd_apply"), ("wgrad_mfma_kernel", "conv_wgrad.generic"), ("wgrad_mfma_vec_kernel", "conv_wgrad.generic"), ("wgrad_reduce", "wgrad_reduce"),
              ("bn_bwd_apply_kernel", "bn_bwd_apply"), ("bn_bwd_apply_chunk_kernel", "bn_bwd_apply"), ("bn_bwd_reduce_kernel", "bn_bwd_reduce"),
              ("bn_bwd_finalize", "bn_bwd_finalize"), ("bn_apply_kernel", "bn_apply"),
