@@ -41,7 +41,7 @@ HIP_KERNEL_OF = {
     "conv_wgrad.tiled_c32_w16": "ddg::wgrad_tiled_kernel<32, 32, 16, 1, 3>",
     "conv_wgrad.tiled_c64_w8": "ddg::wgrad_tiled_kernel<64, 64, 8, 1, 3>",
     "conv_wgrad.tiled_stride2": "ddg::wgrad_down_kernel<Cin, W>, ddg::wgrad_tiled_kernel<Cin, 2*Cin, W, 2, R>",
-    "conv_fprop.wide": "ddg::conv_wide_kernel<1, XFORM, BK, R>, ddg::conv_halo_kernel<1, XFORM, BN>, ddg::conv_point_kernel<1, XFORM, K>",
+    "conv_fprop.wide": "ddg::conv_wide_kernel<1, XFORM, BK, R>, ddg::conv_halo_kernel<1, XFORM, BN>, ddg::conv_point_kernel<1, XFORM, K>, ddg::conv_form_kernel<OC>",
     "conv_dgrad.wide": "ddg::conv_wide_kernel<0|2, false, BK, R>, ddg::conv_halo_kernel<0|2, false, BN>, ddg::conv_point_kernel<0|2, false, K>",
     "conv_wgrad.wide": "ddg::wgrad_wide_kernel",
     "conv_fprop.generic": "ddg::conv_mfma_kernel<T, MB, NB, false, VEC>",

@@ -241,6 +241,13 @@ hipError_t conv_wide_launch(const void* in, const void* wpack, void* out, float*
                             const float* scale = nullptr, const float* shift = nullptr,
                             const ConvWideSecond* second = nullptr, const ConvStat* below = nullptr);
 
+// A 1x1 layer (IC a multiple of 256, OC = 128 or 256) whose input is y = relu(bn(z) + res): formed from z's statistics
+// rows (as many as conv_form_ok allows) and stored to y. f1, out_b, stat_partial_b (optional): the second minibatch. Statistics rows: conv_wide_rows_max().
+struct FormSet { const void* z; const void* res; void* y; BnRows rows; };
+bool conv_form_ok(int IC, int OC, int R, int rows);
+hipError_t conv_form_launch(const FormSet& f0, const FormSet* f1, const void* wpack, void* out, float* stat_partial, void* out_b, float* stat_partial_b,
+                            int N, int H, int W, int IC, int OC, hipStream_t s);
+
 // Weight gradient of the same wide layers (Cin a power of two >= 128, Cout a multiple of 128), several layers per
 // launch: partial tiles [splits][Cout][R*R*Cin] over `splits` slices of the pixels, to be added by
 // wgrad_reduce_all_launch. x [N*H*W][Cin], dz [N*H*W][Cout].

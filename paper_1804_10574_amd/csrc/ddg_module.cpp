@@ -685,6 +685,16 @@ ddg_status finalize_forward(ddg_module* m, Unit& u, int g) {
   return DDG_OK;
 }
 
+// The same for both groups of a paired forward pass.
+ddg_status finalize_forward_two(ddg_module* m, Unit& u) {
+  if (u.small_c() || u.fin_in_apply) return DDG_OK;
+  Launch L(m, PK_BN_FINALIZE);
+  DDG_TRY(bn_finalize_launch(u.fstat, u.frows, u.cout, m->theta + u.og, m->theta + u.ob,
+                             (float)((size_t)u.N * u.P * u.Q), m->d.bn_eps, u.mean, u.invstd, u.scale, u.shift, m->stream,
+                             u.fstat + (size_t)u.fcap * 2 * u.cout, u.mean + u.vec_stride()));
+  return DDG_OK;
+}
+
 // conv of one unit: in -> u.z plus partial rows of its batch statistics. For 16/32/64 channels
 // the consumer of the BN output derives mean/invstd/scale/shift from the rows (and stores
 // them); wider layers get a finalise launch here. `src`, if given, is the unit whose BN + ReLU
@@ -835,14 +845,8 @@ ddg_status unit_forward_two(ddg_module* m, Unit& u, const void* in0, const void*
              2.0 * (conv_flops(u) + (partner ? conv_flops(*partner) : 0.0)));
     DDG_TRY(conv_launch(a, m->stream, partner ? &q : nullptr));
   }
-  for (Unit* f : {partner, &u}) {
-    if (!f || f->small_c() || f->fin_in_apply) continue;
-    Launch L(m, PK_BN_FINALIZE);
-    DDG_TRY(bn_finalize_launch(f->fstat, f->frows, f->cout, m->theta + f->og, m->theta + f->ob,
-                               (float)((size_t)f->N * f->P * f->Q), m->d.bn_eps, f->mean, f->invstd, f->scale, f->shift, m->stream,
-                               f->fstat + (size_t)f->fcap * 2 * f->cout, f->mean + f->vec_stride()));
-  }
-  return DDG_OK;
+  if (partner) DDG_OKAY(finalize_forward_two(m, *partner));
+  return finalize_forward_two(m, u);
 }
 
 // y = relu(bn(u.z) [+ shortcut]) for both groups in one launch (see apply_bn).
@@ -879,14 +883,44 @@ ddg_status apply_bn_two(ddg_module* m, Unit& u, const void* res0, const void* re
   return DDG_OK;
 }
 
-// One block for both groups of a paired forward pass, nothing deferred: (x0, x1) -> (y0, y1).
-ddg_status block_forward_two(ddg_module* m, Blk& b, const void* x0, const void* x1, void* y0, void* y1) {
+// A wide identity block whose output the first layer of the next one can form while it loads (kernels_conv_form.hip).
+static bool forms_output(const ddg_module* m, const std::vector<Blk>& blocks, int bi, int nres) {
+  if (m->no_defer || m->eval_mode || bi + 1 >= nres) return false;
+  const Blk &b = blocks[bi], &n = blocks[bi + 1];
+  if (b.kind != DDG_BLOCK_BOTTLENECK || b.proj || n.kind != DDG_BLOCK_BOTTLENECK || n.proj) return false;
+  const Unit &ul = b.u[b.nmain - 1], &u0 = n.u[0];
+  return ul.fin_in_apply && u0.wide_f && conv_form_ok(u0.cin, u0.cout, u0.R, ul.fcap) && conv_wide_rows_max(u0.fprop.M) <= u0.fcap;
+}
+// That output, not formed yet: y = relu(bn(u->z) + res), for group 0 or for both groups.
+struct PendWide { Unit* u = nullptr; const void* res[2] = {nullptr, nullptr}; void* y[2] = {nullptr, nullptr}; };
+// The layer that forms it; `G` groups from g on.
+ddg_status unit_forward_form(ddg_module* m, Unit& u, const PendWide& p, int G, int g) {
+  FormSet f[2] = {};
+  for (int k = 0; k < G; ++k) {
+    f[k].z = grp(p.u->z, p.u->out_elems() * m->esz, g + k); f[k].res = p.res[k]; f[k].y = p.y[k];
+    f[k].rows = fwd_rows(m, *p.u, g + k);
+  }
+  u.frows = conv_wide_rows_max(u.N * u.P * u.Q);
+  const size_t so = (size_t)u.fcap * 2 * u.cout, zb = u.out_elems() * m->esz;
+  { Launch L(m, PK_CONV_FPROP_WIDE, G * (3.0 * u.in_elems() + u.out_elems()) * m->esz + wbytes(m, u), G * conv_flops(u));
+    DDG_TRY(conv_form_launch(f[0], G > 1 ? &f[1] : nullptr, u.wpack_f, grp(u.z, zb, g), u.fstat + g * so, G > 1 ? grp(u.z, zb, g + 1) : nullptr,
+                             G > 1 ? u.fstat + (g + 1) * so : nullptr, u.N, u.H, u.W, u.cin, u.cout, m->stream)); }
+  for (int k = 0; k < G && G == 1; ++k) DDG_OKAY(finalize_forward(m, u, g + k));
+  if (G > 1) DDG_OKAY(finalize_forward_two(m, u));
+  return DDG_OK;
+}
+
+// One block for both groups of a paired forward pass: (x0, x1) -> (y0, y1). pend: x0, x1 are still to be formed by this block's
+// first layer. defer: this block's own output is left in *defer.
+ddg_status block_forward_two(ddg_module* m, Blk& b, const void* x0, const void* x1, void* y0, void* y1, const PendWide* pend = nullptr,
+                             PendWide* defer = nullptr) {
   const void* c0 = x0; const void* c1 = x1;
   Unit* src = nullptr;   // pending relu(bn(.)) of the current tensors
   Unit* partner = forward_partner(b);
   for (int i = 0; i < b.nmain; ++i) {
     Unit& u = b.u[i];
-    DDG_OKAY(unit_forward_two(m, u, c0, c1, src, i == 0 ? partner : nullptr));
+    if (i == 0 && pend) DDG_OKAY(unit_forward_form(m, u, *pend, 2, 0));
+    else DDG_OKAY(unit_forward_two(m, u, c0, c1, src, i == 0 ? partner : nullptr));
     src = nullptr;
     if (i + 1 < b.nmain) {
       if (b.act[i]) {
@@ -904,6 +938,10 @@ ddg_status block_forward_two(ddg_module* m, Blk& b, const void* x0, const void* 
     Unit& up = b.u[b.nmain];
     if (!partner) DDG_OKAY(unit_forward_two(m, up, x0, x1, nullptr));
     return apply_bn_two(m, ul, nullptr, nullptr, &up, y0, y1);
+  }
+  if (defer) {
+    defer->u = &ul; defer->res[0] = x0; defer->res[1] = x1; defer->y[0] = y0; defer->y[1] = y1;
+    return DDG_OK;
   }
   return apply_bn_two(m, ul, x0, x1, nullptr, y0, y1);
 }
@@ -925,6 +963,7 @@ ddg_status run_forward_pair(ddg_module* m, std::vector<Blk>& blocks, const void*
   const bool no_defer = m->no_defer;
   const void* x0 = in0; const void* x1 = in1;
   struct { Unit* u = nullptr; const void* res = nullptr; void* y = nullptr; } pend;   // group-0 pointers
+  PendWide wide;
   for (int bi = 0; bi < nres; ++bi) {
     Blk& b = blocks[bi];
     const bool last = bi == nres - 1;
@@ -934,7 +973,9 @@ ddg_status run_forward_pair(ddg_module* m, std::vector<Blk>& blocks, const void*
     const bool both = bi >= 1 && tiled_identity_block(b);
     if (!both) {
       if (pend.u) return fail(DDG_ERR_STATE, "internal: deferred block output without a consumer");
-      DDG_OKAY(block_forward_two(m, b, x0, x1, y0, y1));
+      const PendWide in = wide;
+      wide = PendWide{};
+      DDG_OKAY(block_forward_two(m, b, x0, x1, y0, y1, in.u ? &in : nullptr, forms_output(m, blocks, bi, nres) ? &wide : nullptr));
     } else {
       Unit& u0 = b.u[0]; Unit& u1 = b.u[1];
       if (pend.u) {
@@ -965,6 +1006,7 @@ ddg_status run_forward(ddg_module* m, std::vector<Blk>& blocks, const void* in, 
   // loading and stores it (`pend` carries what that conv needs).
   const bool no_defer = m->no_defer;
   struct { Unit* u = nullptr; const void* res = nullptr; void* y = nullptr; } pend;
+  PendWide wide;
   for (int bi = 0; bi < nres; ++bi) {
     Blk& b = blocks[bi];
     void* yout = (bi == nres - 1 && final_out) ? final_out : b.y;
@@ -972,6 +1014,8 @@ ddg_status run_forward(ddg_module* m, std::vector<Blk>& blocks, const void* in, 
     Unit* src = nullptr;   // pending relu(bn(.)) of `cur`
     const void* res_in = nullptr;
     void* y_store = nullptr;
+    const PendWide formed = wide;
+    wide = PendWide{};
     if (pend.u) {
       cur = pend.u->z; src = pend.u; res_in = pend.res; y_store = pend.y;
       x = pend.y;          // materialised by this block's first conv
@@ -980,7 +1024,8 @@ ddg_status run_forward(ddg_module* m, std::vector<Blk>& blocks, const void* in, 
     Unit* partner = forward_partner(b);
     for (int i = 0; i < b.nmain; ++i) {
       Unit& u = b.u[i];
-      DDG_OKAY(unit_forward(m, u, cur, src, i == 0 ? res_in : nullptr, i == 0 ? y_store : nullptr, 1, 0, i == 0 ? partner : nullptr));
+      if (i == 0 && formed.u) DDG_OKAY(unit_forward_form(m, u, formed, 1, 0));
+      else DDG_OKAY(unit_forward(m, u, cur, src, i == 0 ? res_in : nullptr, i == 0 ? y_store : nullptr, 1, 0, i == 0 ? partner : nullptr));
       src = nullptr;
       if (i + 1 < b.nmain) {
         if (b.act[i]) {
@@ -1006,6 +1051,7 @@ ddg_status run_forward(ddg_module* m, std::vector<Blk>& blocks, const void* in, 
                 nb.u[0].H == ul.P && nb.u[0].W == ul.Q;
       }
       if (defer) { pend.u = &ul; pend.res = x; pend.y = yout; }
+      else if (forms_output(m, blocks, bi, nres)) { wide.u = &ul; wide.res[0] = x; wide.y[0] = yout; }
       else DDG_OKAY(apply_bn(m, ul, x, nullptr, yout));
     }
     x = yout;
