@@ -121,12 +121,18 @@ hipError_t pack_all_launch(const PackDesc* dev_descs, int n, int dtype, hipStrea
 // Optimizer step and repacking in one launch, for modules of at most UPDATE_PACK_MAX parameters. A segment of the
 // parameter vector: conv weights [Cout][Cin][R][R] (none: conv = 0) followed by `plain` values; pack_d may be null.
 constexpr size_t UPDATE_PACK_MAX = (size_t)1 << 20;
-struct UpdDesc { size_t off; unsigned conv, plain; void *pack_f, *pack_d; unsigned Cin, ocb_f, ocb_d; int R, l2f, l2d, mirror; };
+struct UpdDesc { size_t off; unsigned conv, plain; void *pack_f, *pack_d; unsigned Cin, ocb_f, ocb_d; int R, l2f, l2d, mirror; unsigned cols; };
+// Momentum SGD, or Adam: m <- b1 m + (1-b1) g', v <- b2 v + (1-b2) g'^2, w <- w - lr (m/(1-b1^n)) / (sqrt(v/(1-b2^n)) + eps) with
+// g' = g + wd*w. lr_dev != nullptr: the step size is read from device memory (a captured graph replays with another one).
 struct UpdArgs {
   float *w, *v, *m2; const float* g; float lr; const float* lr_dev; float mu, wd;     // v: velocity, or Adam's first moment
   float b1, b2, eps; double b1d, b2d; double* pw; unsigned* pw_readers;                // Adam
 };
 hipError_t update_pack_launch(const UpdDesc* dev_descs, int n, unsigned max_len, const UpdArgs& a, int dtype, bool adam, hipStream_t s);
+// The same for larger modules. cols: input channels of a tile, update_tile_cols() (0: the layer goes element by element; the
+// segment starts at element `off`). Adam: pw already moved to this update (adam_advance_launch), pw_readers null.
+unsigned update_tile_cols(unsigned Cin, unsigned Cout, int R, size_t off);
+hipError_t update_tiles_launch(const UpdDesc* dev_descs, int n, unsigned max_len, const UpdArgs& a, int dtype, bool adam, hipStream_t s);
 // Weight-gradient sums, optimizer step and repacking in one launch (modules of at most UPDATE_PACK_MAX parameters): nlayers
 // descriptors of each kind in the same order, then, with `head`, the head's segment, whose gradients (and the mean loss) the
 // launch forms from what the head's per-sample launch left.
@@ -342,18 +348,10 @@ bool eval_plan(const EvalBlockShape* b, int nb, int N, int H, int W, int dtype, 
 hipError_t eval_blocks_launch(const EvalBlockDesc* dev_blocks, const EvalConvDesc* dev_convs, const EvalLaunch& l, const void* in,
                               void* out, int N, int C, int dtype, hipStream_t s);
 
-// lr_dev != nullptr: the step size is read from device memory (lets a captured graph be replayed
-// with a different step size).
-hipError_t sgd_launch(float* w, float* v, const float* g, size_t n, float lr, const float* lr_dev,
-                      float mu, float wd, hipStream_t s);
 hipError_t set_scalar_launch(float* dst, float v, hipStream_t s);
-// Adam (Algorithm 2). pw[0], pw[1] hold beta1^n, beta2^n in device memory: adam_advance_launch
-// multiplies them by beta1, beta2 (one more executed update), adam_launch then applies
-// m <- b1 m + (1-b1) g', v <- b2 v + (1-b2) g'^2, w <- w - lr (m/(1-pw0)) / (sqrt(v/(1-pw1)) + eps)
-// with g' = g + wd*w. Device-resident so that a captured graph replays correctly.
+// Adam (Algorithm 2): pw[0], pw[1] hold beta1^n, beta2^n in device memory, so that a captured graph replays correctly; multiplied
+// by beta1, beta2 (one more executed update).
 hipError_t adam_advance_launch(double* pw, float b1, float b2, hipStream_t s);
-hipError_t adam_launch(float* w, float* m1, float* m2, const float* g, size_t n, float lr, const float* lr_dev,
-                       float b1, float b2, float eps, float wd, const double* pw, hipStream_t s);
 hipError_t copy_launch(const void* src, void* dst, size_t bytes, hipStream_t s);
 hipError_t to_f32_launch(const void* src, float* dst, size_t elems, int dtype, hipStream_t s);
 

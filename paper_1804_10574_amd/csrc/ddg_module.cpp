@@ -120,7 +120,8 @@ struct ddg_module {
   hipStream_t bstream = nullptr;   // backward / update stream (desc.stream)
   hipStream_t fstream = nullptr;   // forward stream (== bstream unless two_streams)
   bool two_streams = false;
-  UpdDesc* upd_descs = nullptr;    // small modules: update and repacking in one launch
+  UpdDesc* upd_descs = nullptr;    // update and repacking in one launch
+  bool upd_small = false;          // of at most UPDATE_PACK_MAX parameters
   int n_upd = 0; unsigned upd_max = 0;
   unsigned* pw_readers = nullptr;
   Readback readback;               // device -> host copies of weights, optimizer state, stored inputs
@@ -492,10 +493,11 @@ ddg_status build_plan(ddg_module* m) {
     hb.pooled = (float*)p; hb.dlogits = hb.pooled + (size_t)N * hb.C; hb.loss_n = hb.dlogits + (size_t)N * d.num_classes;
   }
   void* p = nullptr;
-  DDG_OKAY(dev_alloc(m, &p, 4 * m->nparams * sizeof(float) + 3 * sizeof(double)));
-  m->theta = (float*)p; m->vel = m->theta + m->nparams; m->grad = m->vel + m->nparams;
-  m->mom2 = m->grad + m->nparams;
-  m->adam_pw = (double*)((char*)p + ((4 * m->nparams * sizeof(float) + 7) & ~(size_t)7));
+  const size_t vec = (m->nparams + 3) & ~(size_t)3;    // each vector on a 16-byte boundary
+  DDG_OKAY(dev_alloc(m, &p, 4 * vec * sizeof(float) + 3 * sizeof(double)));
+  m->theta = (float*)p; m->vel = m->theta + vec; m->grad = m->vel + vec;
+  m->mom2 = m->grad + vec;
+  m->adam_pw = (double*)(m->mom2 + vec);
   m->pw_readers = (unsigned*)(m->adam_pw + 2);
   m->delay = d.K - d.k;
   m->nslots = m->delay + 1;
@@ -564,7 +566,8 @@ ddg_status build_plan(ddg_module* m) {
         return fail(DDG_ERR_DEVICE, "copying the layer tables failed");
     }
   }
-  if (!d.dry_run && m->nparams <= UPDATE_PACK_MAX) {
+  if (!d.dry_run) {
+    m->upd_small = m->nparams <= UPDATE_PACK_MAX;
     std::vector<UpdDesc> ud;
     for (Blk& b : m->blocks) {
       for (Unit& u : b.u) {
@@ -576,12 +579,17 @@ ddg_status build_plan(ddg_module* m) {
         conv_wpack_elems(u.cin, u.cout, u.R, dt, &x.l2f, &ks);
         conv_wpack_elems(u.cout, u.cin, u.R, dt, &x.l2d, &ks);
         x.ocb_f = u.cout / 16; x.ocb_d = u.cin / 16;
+        if (!m->upd_small) x.cols = update_tile_cols(u.cin, u.cout, u.R, u.ow);
         ud.push_back(x);
       }
       if (b.kind == DDG_BLOCK_HEAD) {
-        UpdDesc x{};
-        x.off = b.ofcw; x.plain = (unsigned)(m->nparams - b.ofcw); x.Cin = 1; x.R = 1;   // fc.W, fc.b end the vector
-        ud.push_back(x);
+        // fc.W, fc.b end the vector; in a large module as segments of a size that many workgroups share
+        const size_t step = m->upd_small ? m->nparams : (size_t)1 << 16;
+        for (size_t o = b.ofcw; o < m->nparams; o += step) {
+          UpdDesc x{};
+          x.off = o; x.plain = (unsigned)(m->nparams - o < step ? m->nparams - o : step); x.Cin = 1; x.R = 1;
+          ud.push_back(x);
+        }
       }
     }
     for (const UpdDesc& x : ud) if (x.conv + x.plain > m->upd_max) m->upd_max = x.conv + x.plain;
@@ -597,7 +605,7 @@ ddg_status build_plan(ddg_module* m) {
   }
   m->theta_bwd = m->theta;
   if (!d.dry_run) {
-    hipError_t e = hipMemsetAsync(m->theta, 0, 4 * m->nparams * sizeof(float), m->stream);
+    hipError_t e = hipMemsetAsync(m->theta, 0, 4 * vec * sizeof(float), m->stream);
     if (e == hipSuccess) {
       const double one[3] = {1.0, 1.0, 0.0};   // beta^0; no readers
       e = hipMemcpy(m->adam_pw, one, sizeof one, hipMemcpyHostToDevice);
@@ -1353,7 +1361,7 @@ ddg_status run_backward(ddg_module* m, std::vector<Blk>& blocks, const void* in,
     a.pooled = hb.pooled; a.dlogits = hb.dlogits; a.loss_n = hb.loss_n; a.loss_out = loss_out;
     a.dfcw = m->grad + hb.ofcw; a.dfcb = m->grad + hb.ofcb; a.dh = nres > 0 ? m->Ga : delta_out;
     a.N = m->d.batch; a.HW = hb.HW; a.C = hb.C; a.classes = m->d.num_classes; a.dtype = dt;
-    a.sums_later = m->fuse_update && m->upd_descs ? 1 : 0;
+    a.sums_later = m->fuse_update && m->upd_small ? 1 : 0;
     m->loss_left = loss_out;
     Launch L(m, PK_HEAD);
     DDG_TRY(head_launch(a, m->stream));
@@ -2064,7 +2072,7 @@ ddg_status ddg_backward_delayed(ddg_module* m, long t, const void* delta_in, con
   } else {
     DDG_OKAY(run_backward(m, m->blocks, slot, delta_in, labels, m->d.k > 1 ? delta_out : nullptr, loss_out));
   }
-  m->sums_left = m->fuse_update && m->upd_descs;
+  m->sums_left = m->fuse_update && m->upd_small;
   if (m->sums_left) return DDG_OK;
   // every layer's weight-gradient partials -> g (one launch for the module, fixed order)
   Launch L(m, PK_WGRAD_REDUCE, (double)m->nparams * 4.0);
@@ -2083,40 +2091,31 @@ ddg_status ddg_update(ddg_module* m, long t, float lr) {
   const bool self_sync = m->two_streams && !m->external_sync;
   // the forward pass of this iteration must have finished reading the weights
   if (self_sync) DDG_TRY(hipStreamWaitEvent(m->bstream, m->ev_fwd[t & 1], 0));
-  if (m->upd_descs) {
-    const bool adam = m->opt == DDG_OPT_ADAM;
-    UpdArgs a{};
-    a.w = m->theta; a.v = m->vel; a.m2 = m->mom2; a.g = m->grad; a.lr = lr; a.lr_dev = m->lr_dev;
-    a.mu = m->d.momentum; a.wd = m->d.weight_decay;
-    a.b1 = m->beta1; a.b2 = m->beta2; a.eps = m->adam_eps; a.b1d = (double)m->beta1; a.b2d = (double)m->beta2;
-    a.pw = m->adam_pw; a.pw_readers = m->pw_readers;
-    Launch L(m, adam ? PK_ADAM : PK_SGD, (double)m->nparams * (adam ? 28.0 : 20.0));
-    if (m->sums_left) {
-      m->sums_left = false;
-      HeadSums h{};
-      const bool head = m->d.num_classes > 0;
-      if (head) {
-        const Blk& hb = m->blocks.back();
-        h.pooled = hb.pooled; h.dlogits = hb.dlogits; h.loss_n = hb.loss_n; h.loss_out = m->loss_left;
-        h.N = m->d.batch; h.C = hb.C; h.classes = m->d.num_classes;
-      }
-      DDG_TRY(reduce_update_launch(m->wred_descs, m->upd_descs, m->n_wred, m->wred_max, a, head ? &h : nullptr, m->d.compute, adam, m->stream));
-      return DDG_OK;
+  const bool adam = m->opt == DDG_OPT_ADAM;
+  UpdArgs a{};
+  a.w = m->theta; a.v = m->vel; a.m2 = m->mom2; a.g = m->grad; a.lr = lr; a.lr_dev = m->lr_dev;
+  a.mu = m->d.momentum; a.wd = m->d.weight_decay;
+  a.b1 = m->beta1; a.b2 = m->beta2; a.eps = m->adam_eps; a.b1d = (double)m->beta1; a.b2d = (double)m->beta2;
+  a.pw = m->adam_pw; a.pw_readers = m->pw_readers;
+  if (adam && !m->upd_small) {
+    Launch L(m, PK_ADAM);
+    DDG_TRY(adam_advance_launch(m->adam_pw, m->beta1, m->beta2, m->stream));
+    a.pw_readers = nullptr;
+  }
+  Launch L(m, adam ? PK_ADAM : PK_SGD, (double)m->nparams * (adam ? 28.0 : 20.0));
+  if (m->sums_left) {
+    m->sums_left = false;
+    HeadSums h{};
+    const bool head = m->d.num_classes > 0;
+    if (head) {
+      const Blk& hb = m->blocks.back();
+      h.pooled = hb.pooled; h.dlogits = hb.dlogits; h.loss_n = hb.loss_n; h.loss_out = m->loss_left;
+      h.N = m->d.batch; h.C = hb.C; h.classes = m->d.num_classes;
     }
-    DDG_TRY(update_pack_launch(m->upd_descs, m->n_upd, m->upd_max, a, m->d.compute, adam, m->stream));
-    if (self_sync) DDG_TRY(hipEventRecord(m->ev_upd, m->bstream));
+    DDG_TRY(reduce_update_launch(m->wred_descs, m->upd_descs, m->n_wred, m->wred_max, a, head ? &h : nullptr, m->d.compute, adam, m->stream));
     return DDG_OK;
   }
-  if (m->opt == DDG_OPT_ADAM) {
-    { Launch L(m, PK_ADAM); DDG_TRY(adam_advance_launch(m->adam_pw, m->beta1, m->beta2, m->stream)); }
-    Launch L(m, PK_ADAM, (double)m->nparams * 28.0);   // w, m, v read and written, g read
-    DDG_TRY(adam_launch(m->theta, m->vel, m->mom2, m->grad, m->nparams, lr, m->lr_dev, m->beta1, m->beta2,
-                        m->adam_eps, m->d.weight_decay, m->adam_pw, m->stream));
-  } else {
-    Launch L(m, PK_SGD, (double)m->nparams * 20.0);
-    DDG_TRY(sgd_launch(m->theta, m->vel, m->grad, m->nparams, lr, m->lr_dev, m->d.momentum, m->d.weight_decay, m->stream));
-  }
-  DDG_OKAY(pack_all(m));
+  DDG_TRY((m->upd_small ? update_pack_launch : update_tiles_launch)(m->upd_descs, m->n_upd, m->upd_max, a, m->d.compute, adam, m->stream));
   if (self_sync) DDG_TRY(hipEventRecord(m->ev_upd, m->bstream));
   return DDG_OK;
 }

@@ -1,4 +1,4 @@
-// Optimizer step of one parameter (momentum SGD or Adam, the formulas of sgd_kernel / adam_kernel) and its place in a layer's
+// Optimizer step of one parameter (momentum SGD or Adam) and its place in a layer's
 // packed operands; shared by the launches that update.
 #pragma once
 #include "ddg_device.h"
@@ -7,15 +7,17 @@
 namespace ddg {
 
 // What every workgroup needs before its first parameter. Adam: pw holds beta1^n, beta2^n; every workgroup uses the powers of
-// this update, and the last one to have read them (pw_readers counts, `workgroups` in all) stores them.
+// this update, and the last one to have read them (pw_readers counts, `workgroups` in all) stores them. Without pw_readers a
+// launch before (adam_advance_launch) has moved them to this update.
 template <bool ADAM> struct UpdStep {
   float lr, c1, c2;
   __device__ __forceinline__ void init(const UpdArgs& a, unsigned workgroups) {
     lr = a.lr_dev ? *a.lr_dev : a.lr;
     c1 = 1.f; c2 = 1.f;
     if (ADAM) {
-      const double p1 = a.pw[0] * a.b1d, p2 = a.pw[1] * a.b2d;
+      const double p1 = a.pw_readers ? a.pw[0] * a.b1d : a.pw[0], p2 = a.pw_readers ? a.pw[1] * a.b2d : a.pw[1];
       c1 = (float)(1.0 - p1); c2 = (float)(1.0 - p2);
+      if (!a.pw_readers) return;
       __shared__ unsigned s_seen;
       asm volatile("" ::"v"(c1), "v"(c2));            // (read before it is counted)
       __syncthreads();
@@ -27,21 +29,25 @@ template <bool ADAM> struct UpdStep {
       }
     }
   }
-  // parameter e with gradient g -> its new value, stored
-  __device__ __forceinline__ float step(const UpdArgs& a, size_t e, float g) const {
-    const float wi = a.w[e];
-    float wn;
+  // new value of a parameter w with gradient g and optimizer state v, m2 (moved)
+  __device__ __forceinline__ float calc(const UpdArgs& a, float wi, float g, float& v, float& m2) const {
     if (ADAM) {
       const float gi = g + a.wd * wi;
-      const float mi = a.b1 * a.v[e] + (1.f - a.b1) * gi;
-      const float vi = a.b2 * a.m2[e] + (1.f - a.b2) * gi * gi;
-      a.v[e] = mi; a.m2[e] = vi;
-      wn = wi - lr * (mi / c1) / (sqrtf(vi / c2) + a.eps);
-    } else {
-      const float vi = a.mu * a.v[e] + (g + a.wd * wi);
-      a.v[e] = vi;
-      wn = wi - lr * vi;
+      const float mi = a.b1 * v + (1.f - a.b1) * gi;
+      const float vi = a.b2 * m2 + (1.f - a.b2) * gi * gi;
+      v = mi; m2 = vi;
+      return wi - lr * (mi / c1) / (sqrtf(vi / c2) + a.eps);
     }
+    const float vi = a.mu * v + (g + a.wd * wi);
+    v = vi;
+    return wi - lr * vi;
+  }
+  // parameter e with gradient g -> its new value, stored
+  __device__ __forceinline__ float step(const UpdArgs& a, size_t e, float g) const {
+    float v = a.v[e], m2 = ADAM ? a.m2[e] : 0.f;
+    const float wn = calc(a, a.w[e], g, v, m2);
+    a.v[e] = v;
+    if (ADAM) a.m2[e] = m2;
     a.w[e] = wn;
     return wn;
   }

@@ -66,6 +66,8 @@ def kind_of(kernel_name: str) -> str:
     m = re.match(r"conv_(?:wide|halo|point)_kernel<(\d+), ", n)
     if m:   # <STATS, ...>: 1 = forward statistics (the forward conv); 0 / 2 = the input gradient
         return "conv_fprop.wide" if m.group(1) == "1" else "conv_dgrad.wide"
+    if n.startswith("conv_form_kernel"):   # also forms the block input it multiplies
+        return "conv_fprop.wide"
     if n.startswith("wgrad_wide_kernel"):
         return "conv_wgrad.wide"
     m = re.match(r"conv_mfma_kernel<\w+, \d+, \d+, (true|false)", n)
@@ -73,7 +75,7 @@ def kind_of(kernel_name: str) -> str:
         return "conv_dgrad.generic" if m.group(1) == "true" else "conv_fprop.generic"
     if re.match(r"wgrad_down(?:_f32)?_kernel<", n):   # a stage's first block: its three weight gradients
         return "conv_wgrad.tiled_stride2"
-    m = re.match(r"(?:update_pack|reduce_update)_kernel<[\w:]+, (true|false)>", n)
+    m = re.match(r"(?:update_pack|update_tiles|reduce_update)_kernel<[\w:]+, (true|false)>", n)
     if m:   # <T, ADAM>: the optimizer step and the repacking (and the sums of the weight gradients)
         return "adam" if m.group(1) == "true" else "sgd"
     table = [("conv_dgrad_s2_kernel", "conv_dgrad.generic"), ("bwd_generic_kernel", "conv_dgrad.generic"), ("bn_apply_wide_kernel", "bn_apply"),
@@ -82,7 +84,7 @@ def kind_of(kernel_name: str) -> str:
              ("bn_bwd_finalize", "bn_bwd_finalize"), ("bn_apply_kernel", "bn_apply"),
              ("bn_apply_chunk_kernel", "bn_apply"), ("bn_apply_pair_kernel", "bn_apply"),
              ("running_update_kernel", "bn_running"), ("eval_vectors_kernel", "bn_running"),
-             ("bn_finalize", "bn_finalize"), ("head_", "head"), ("sgd_kernel", "sgd"),
+             ("bn_finalize", "bn_finalize"), ("head_", "head"), ("adam_advance_kernel", "adam"),
              ("pack_", "pack_weights"), ("copy_kernel", "copy")]
     for prefix, kind in table:
         if n.startswith(prefix):
