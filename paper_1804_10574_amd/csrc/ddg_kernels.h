@@ -327,7 +327,8 @@ struct RunDesc {
   float* escale; float* eshift;                // what the evaluation forward normalises with
   int C; float count, eps;
 };
-hipError_t running_update_launch(const RunDesc* dev_descs, int n, int max_c, float rho, hipStream_t s);
+// The running estimates (n layers, maybe none) and a copy of `bytes` bytes (src may be null) in one launch.
+hipError_t forward_tail_launch(const void* src, void* dst, size_t bytes, const RunDesc* dev_descs, int n, int max_c, float rho, hipStream_t s);
 hipError_t eval_vectors_launch(const RunDesc* dev_descs, int n, int max_c, hipStream_t s);
 
 // Evaluation forward of stem / basic blocks with 16, 32 or 64 channels, many layers per launch

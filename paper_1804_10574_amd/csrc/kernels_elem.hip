@@ -429,15 +429,13 @@ hipError_t bn_bwd_apply_launch(const BnBwdSet& q, const BnBwdSet* other, size_t 
 }
 
 // ---------------------------------------------------------------------------------
-// Running batch-norm estimates (for evaluation) of all layers of a module in one launch:
+// Running batch-norm estimates (for evaluation) of all layers of a module (see forward_tail_kernel):
 //   rmean <- (1-rho)*rmean + rho*mean,  rvar <- (1-rho)*rvar + rho*var*m/(m-1)
 // with the batch statistics of the forward pass that just ran (var = 1/invstd^2 - eps), and
 // the per-channel vectors the evaluation forward normalises with:
 //   escale = gamma/sqrt(rvar + eps),  eshift = beta - rmean*escale.
 // ---------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void running_update_kernel(const RunDesc* __restrict__ descs, float rho) {
-  const RunDesc d = descs[blockIdx.y];
-  const int c = blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ void running_update_body(const RunDesc& d, float rho, int c) {
   if (c >= d.C) return;
   const float is = d.invstd[c];
   const float var = 1.f / (is * is) - d.eps;
@@ -452,12 +450,6 @@ __global__ __launch_bounds__(256) void eval_vectors_kernel(const RunDesc* __rest
   const float sc = d.gamma[c] / sqrtf(d.rvar[c] + d.eps);
   d.escale[c] = sc;
   d.eshift[c] = d.beta[c] - d.rmean[c] * sc;
-}
-
-hipError_t running_update_launch(const RunDesc* dev_descs, int n, int max_c, float rho, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  DDG_LAUNCH(running_update_kernel, dim3((max_c + 255) / 256, n), dim3(256), 0, s, dev_descs, rho);
-  return hipGetLastError();
 }
 
 hipError_t eval_vectors_launch(const RunDesc* dev_descs, int n, int max_c, hipStream_t s) {
@@ -714,22 +706,40 @@ hipError_t set_scalar_launch(float* dst, float v, hipStream_t s) {
   return hipGetLastError();
 }
 
-__global__ void copy_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst, size_t nvec,
-                            const unsigned char* __restrict__ srcb, unsigned char* __restrict__ dstb, size_t tail0,
-                            size_t bytes) {
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nvec; i += (size_t)gridDim.x * blockDim.x)
-    dst[i] = src[i];
-  if (blockIdx.x == 0)
-    for (size_t b = tail0 + threadIdx.x; b < bytes; b += blockDim.x) dstb[b] = srcb[b];
+__device__ __forceinline__ void copy_body(const uint4* __restrict__ src, uint4* __restrict__ dst, size_t bytes, unsigned block, unsigned blocks) {
+  const size_t nvec = bytes / 16;
+  for (size_t i = (size_t)block * 256 + threadIdx.x; i < nvec; i += (size_t)blocks * 256) dst[i] = src[i];
+  if (block == 0)
+    for (size_t b = nvec * 16 + threadIdx.x; b < bytes; b += 256)
+      reinterpret_cast<unsigned char*>(dst)[b] = reinterpret_cast<const unsigned char*>(src)[b];
+}
+__global__ __launch_bounds__(256) void copy_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst, size_t bytes) {
+  copy_body(src, dst, bytes, blockIdx.x, gridDim.x);
+}
+// What ends a training forward pass, in one launch: the running estimates (the first n*per workgroups) and the copy of the
+// module's input into its ring (the rest). Neither needs the other; each was a launch of 4 to 5 us that a stream waits for
+// (16 iterations, one of the two launches saved: 4 images in fp32 3.73 -> 3.66 ms, ResNet-20 bf16 batch 37 4.98 -> 4.91).
+__global__ __launch_bounds__(256) void forward_tail_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst, size_t bytes,
+                                                           const RunDesc* __restrict__ descs, int n, int per, float rho) {
+  const int b = blockIdx.x, first = n * per;
+  if (b < first) running_update_body(descs[b / per], rho, b % per * 256 + threadIdx.x);
+  else copy_body(src, dst, bytes, b - first, gridDim.x - first);
+}
+
+static int copy_grid(size_t bytes) {
+  const size_t g = (bytes / 16 + 255) / 256;
+  return g < 1 ? 1 : g > 2048 ? 2048 : (int)g;
+}
+
+hipError_t forward_tail_launch(const void* src, void* dst, size_t bytes, const RunDesc* dev_descs, int n, int max_c, float rho, hipStream_t s) {
+  const int per = (max_c + 255) / 256, grid = n * per + (src ? copy_grid(bytes) : 0);
+  if (grid <= 0) return hipSuccess;
+  DDG_LAUNCH(forward_tail_kernel, dim3(grid), dim3(256), 0, s, (const uint4*)src, (uint4*)dst, bytes, dev_descs, n, per, rho);
+  return hipGetLastError();
 }
 
 hipError_t copy_launch(const void* src, void* dst, size_t bytes, hipStream_t s) {
-  const size_t nvec = bytes / 16;
-  int grid = (int)((nvec + 255) / 256);
-  if (grid > 2048) grid = 2048;
-  if (grid < 1) grid = 1;
-  DDG_LAUNCH(copy_kernel, dim3(grid), dim3(256), 0, s, (const uint4*)src, (uint4*)dst, nvec,
-                     (const unsigned char*)src, (unsigned char*)dst, nvec * 16, bytes);
+  DDG_LAUNCH(copy_kernel, dim3(copy_grid(bytes)), dim3(256), 0, s, (const uint4*)src, (uint4*)dst, bytes);
   return hipGetLastError();
 }
 

@@ -83,7 +83,7 @@ def kind_of(kernel_name: str) -> str:
              ("bn_bwd_apply_kernel", "bn_bwd_apply"), ("bn_bwd_apply_chunk_kernel", "bn_bwd_apply"), ("bn_bwd_reduce_kernel", "bn_bwd_reduce"),
              ("bn_bwd_finalize", "bn_bwd_finalize"), ("bn_apply_kernel", "bn_apply"),
              ("bn_apply_chunk_kernel", "bn_apply"), ("bn_apply_pair_kernel", "bn_apply"),
-             ("running_update_kernel", "bn_running"), ("eval_vectors_kernel", "bn_running"),
+             ("forward_tail_kernel", "copy"), ("eval_vectors_kernel", "bn_running"),
              ("bn_finalize", "bn_finalize"), ("head_", "head"), ("adam_advance_kernel", "adam"),
              ("pack_", "pack_weights"), ("copy_kernel", "copy")]
     for prefix, kind in table:
