@@ -15,16 +15,24 @@
 // to be cut into 7-16 slices of 6-14 steps, and start-up, the tiles' partial sums (64 KB a workgroup, written
 // here and read again by the reduction) and the last wave cost more than the contraction: 45 us for the
 // three layers of a bottleneck block, 1.15 GB of partial sums for 23 blocks. With layers collected until
-// their tiles fill the 512 places of the chip, slices are as long as SLICE_MAX allows: 25 us a block, 0.2 GB
-// (2548 pixels: 37 -> 12 us; 6272 pixels at 28x28, 512-128-512: 29 -> 9 us; 441 at 7x7, 2048-512-2048: 31 -> 21 us).
+// their tiles fill the 512 places of the chip, slices are as long as SLICE_MAX allows: 27 us a block, 0.2 GB.
 //
-// Eight waves as 2 (pixel halves of a step) x 2 (co) x 2 (ci), 64 x 64 each = four accumulators of
-// mfma_f32_32x32x16_bf16 (16x16x32 runs at little more than half the rate); the two pixel halves meet in LDS
-// at the end. 128 registers and 72 KB of LDS: two workgroups a compute unit, one of which multiplies while
-// the other waits for its rows (one workgroup with two steps in flight: 34 against 27 us). What bounds it: the
-// LDS port. With the loads taken out of the loop 16 of 25 us are left, the transposing reads of 64 KB a step at about
-// 64 bytes a clock and the stores of 32 KB; 6 us are matrix instructions.
+// The sums. A matrix instruction rounds its accumulator once per 16 pixels, and over a slice of 49 steps that adds up: 1.9e-7
+// of the gradient (2-norm, against 64 bits) where slices of 6 steps had 8.6e-8. So an accumulator runs over two steps only
+// (one, in slices of up to 8 steps) and is then added to a second one, and what this addition rounds off is what the
+// accumulator starts from again: 6.1e-8, whatever the length of the slice. Slices of one or two steps
+// add up the halves of their steps apart, four roundings each. Never a larger error than with a layer on its own in 256
+// workgroups (88 sets of layers, 1 to 784 steps). Folding costs 3 of the 27 us, and every step instead of every second
+// one 2.7 more; every third one would save 0.7 but is 6.9e-8, more than slices of 2 or 3 steps had at 2548 pixels.
+//
+// Four waves as 2 (co) x 2 (ci), 64 x 64 each = four accumulators of mfma_f32_32x32x16_bf16 (16x16x32 runs at little more
+// than half the rate) and their sums, 231 registers; 72 KB of LDS: two workgroups a compute unit, one of which multiplies
+// while the other waits for its rows. Eight waves, which halve the pixels of a step between them, have room for one set of
+// accumulators only (21.9 us a block). What bounds it: the LDS port (transposing reads of 64 KB a step at about
+// 64 bytes a clock, stores of 32 KB), and the vector instructions that fold beside the matrix instructions.
 #include "ddg_conv_wide.h"
+#include <algorithm>
+#include <type_traits>
 
 namespace ddg {
 
@@ -45,8 +53,7 @@ constexpr int OPB = BP * ROW;              // one operand, one buffer: 18432
 constexpr int BUF = 2 * OPB;
 constexpr int LDS = 2 * BUF;               // 73728
 constexpr int PLACES = 512;                // workgroups that run at the same time: two per compute unit
-constexpr int SLICE_MAX = 49;              // steps an accumulator runs through: the fp32 sums get no longer than a layer of
-                                           // 144 tiles on its own (512 channels 3x3, 3136 pixels) has always had them
+constexpr int SLICE_MAX = 49;              // steps of a slice, unless its layer alone fills the chip
 constexpr unsigned NOWHERE = 0xfffffff0u;  // past the end of any tensor: the load gives zeros
 }
 
@@ -60,17 +67,16 @@ __device__ __forceinline__ bf16x8_t wide_frag_tr(const unsigned char* p) {
   return __builtin_bit_cast(bf16x8_t, make_uint4(l.x, l.y, h.x, h.y));
 }
 
-// A thread's share of one step on its way to LDS: rows prow and prow + 32 of dz and x.
-struct WgwSet { uint4 z0, z1, x0, x1; };
+// A thread's share of one step on its way to LDS: rows prow, prow + 16, .. of dz and x.
+struct WgwSet { uint4 z[4], x[4]; };
 
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) void wgrad_wide_kernel(WgwArgs args) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void wgrad_wide_kernel(WgwArgs args) {
   using namespace wgw;
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, l32 = lane & 31, half = lane >> 5;
-  const int wa = wave & 1, wb = (wave >> 1) & 1;     // co half, ci half
-  const int kg = wave >> 2;                          // pixels 32*kg .. 32*kg + 31 of every step
+  const int wa = wave & 1, wb = wave >> 1;           // co half, ci half
   // Workgroups go to the 8 XCDs round-robin in launch order. All tiles of one pixel slice read
   // the same rows of x and dz, so the (layer, slice, tile) triples are numbered in that order and XCD j is
   // given the j-th eighth of that sequence: the rows of a slice then come from memory once into
@@ -94,32 +100,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
   const int s0 = split * nsteps / a.splits, s1 = (split + 1) * nsteps / a.splits;
   const int m_end = s1 * BP < a.M ? s1 * BP : a.M;
 
-  // staging map: 16-byte unit tid + q*512 of a 64 x 128 tile = pixel (tid>>4) + 32*q, chunk tid&15
+  // staging map: 16-byte unit tid + q*256 of a 64 x 128 tile = pixel (tid>>4) + 16*q, chunk tid&15
   const int ch = tid & 15, prow = tid >> 4;
   const unsigned zst = a.Cout * 2, xst = a.Cin * 2;
   const wide_rsrc_t rz = wide_rsrc(a.dz, (size_t)a.M * zst), rx = wide_rsrc(a.x, (size_t)a.M * xst);
-  // pixel, image row and column, and byte offsets of the thread's two rows in the step that is requested next
-  int m0 = s0 * BP + prow, h0, w0, h1, w1;
-  unsigned zo = (unsigned)m0 * zst + (co0 + ch * 8) * 2, xo = (unsigned)(m0 + dr * a.W + ds) * xst + (ci0 + ch * 8) * 2;
-  {
-    const int HW = a.H * a.W, r0 = m0 % HW, r1 = (m0 + 32) % HW;
-    h0 = r0 / a.W; w0 = r0 - h0 * a.W; h1 = r1 / a.W; w1 = r1 - h1 * a.W;
-  }
-  const int dh = (BP / a.W) % a.H, dw = BP % a.W;
-  auto issue = [&](WgwSet& r) __attribute__((always_inline)) {
-    bool i0 = m0 < m_end, i1 = m0 + 32 < m_end;
-    if (r3) {
-      i0 = i0 && (unsigned)(h0 + dr) < (unsigned)a.H && (unsigned)(w0 + ds) < (unsigned)a.W;
-      i1 = i1 && (unsigned)(h1 + dr) < (unsigned)a.H && (unsigned)(w1 + ds) < (unsigned)a.W;
-      w0 += dw; h0 += dh; if (w0 >= a.W) { w0 -= a.W; ++h0; } if (h0 >= a.H) h0 -= a.H;
-      w1 += dw; h1 += dh; if (w1 >= a.W) { w1 -= a.W; ++h1; } if (h1 >= a.H) h1 -= a.H;
-    }
-    r.z0 = wide_load(rz, i0 ? zo : NOWHERE, 0);
-    r.x0 = wide_load(rx, i0 ? xo : NOWHERE, 0);
-    r.z1 = wide_load(rz, i1 ? zo + 32 * zst : NOWHERE, 0);
-    r.x1 = wide_load(rx, i1 ? xo + 32 * xst : NOWHERE, 0);
-    m0 += BP; zo += BP * zst; xo += BP * xst;
-  };
+  const int dh = (16 / a.W) % a.H, dw = 16 % a.W;    // 16 pixels further
   // per-channel constants of this thread's 8 input channels (the same in every step)
   const bool xform = a.scale != nullptr;
   float tsc[8], tsh[8];
@@ -133,79 +118,141 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
   auto stash = [&](WgwSet r, int bufo) __attribute__((always_inline)) {
     unsigned char* Z = smem + bufo + prow * ROW + ch * 16;
     unsigned char* X = Z + OPB;
-    *reinterpret_cast<uint4*>(Z) = r.z0;
-    *reinterpret_cast<uint4*>(Z + 32 * ROW) = r.z1;
-    if (xform) { r.x0 = wide_act(r.x0, tsc, tsh); r.x1 = wide_act(r.x1, tsc, tsh); }
-    *reinterpret_cast<uint4*>(X) = r.x0;
-    *reinterpret_cast<uint4*>(X + 32 * ROW) = r.x1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      *reinterpret_cast<uint4*>(Z + q * 16 * ROW) = r.z[q];
+      if (xform) r.x[q] = wide_act(r.x[q], tsc, tsh);
+      *reinterpret_cast<uint4*>(X + q * 16 * ROW) = r.x[q];
+    }
   };
+  // fragment address of (k-step 0, block 0): a group of 16 lanes takes 16 channels (groups 0, 2 the first, 1, 3 the
+  // second half of a block) of 8 pixels (groups 0, 1 the first, 2, 3 the second eight); within it lane s points at
+  // channels 4*(s%4).. of pixel s/4, the second read is 4 pixels further
+  const int frag = (half * 8 + (l16 >> 2)) * ROW + ((lane >> 4) & 1) * 32 + (l16 & 3) * 8;
+  const int zoff = frag + wa * 128;   // + i*64 (channel block)
+  const int xoff = OPB + frag + wb * 128;
 
-  f32x16_t acc[2][2];                                // [co block][ci block]: rows = ci, columns = co
+  f32x16_t acc[2][2], sum[2][2];                     // [co block][ci block]: rows = ci, columns = co
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+      for (int e = 0; e < 16; ++e) sum[i][j][e] = 0.f;
+  const int period = s1 - s0 <= 8 ? 1 : 2;
 
-  // fragment address of (k-step 0, block 0): a group of 16 lanes takes 16 channels (groups 0, 2 the first, 1, 3 the
-  // second half of a block) of 8 pixels (groups 0, 1 the first, 2, 3 the second eight); within it lane s points at
-  // channels 4*(s%4).. of pixel s/4, the second read is 4 pixels further
-  const int frag = (half * 8 + (l16 >> 2)) * ROW + ((lane >> 4) & 1) * 32 + (l16 & 3) * 8;
-  const int zoff = frag + wa * 128 + kg * 32 * ROW;   // + i*64 (channel block)
-  const int xoff = OPB + frag + wb * 128 + kg * 32 * ROW;
-  auto contract = [&](int bufo) __attribute__((always_inline)) {
-    const unsigned char* B = smem + bufo;
+  // One pass over the slice. HOW 0: acc takes all; 1: acc takes the first half of every step, sum the second; 2: acc takes all
+  // and is folded into sum every `period` steps.
+  auto run = [&](auto how) __attribute__((always_inline)) {
+    constexpr int HOW = decltype(how)::value;
+    // pixel, image row and column, and byte offsets of the thread's row that is requested next
+    int m0 = s0 * BP + prow, h, w;
+    unsigned zo = (unsigned)m0 * zst + (co0 + ch * 8) * 2, xo = (unsigned)(m0 + dr * a.W + ds) * xst + (ci0 + ch * 8) * 2;
+    {
+      const int r = m0 % (a.H * a.W);
+      h = r / a.W; w = r - h * a.W;
+    }
+    auto issue = [&](WgwSet& r) __attribute__((always_inline)) {
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      bf16x8_t zf[2], xf[2];
+      for (int q = 0; q < 4; ++q) {
+        bool in = m0 + 16 * q < m_end;
+        if (r3) {
+          in = in && (unsigned)(h + dr) < (unsigned)a.H && (unsigned)(w + ds) < (unsigned)a.W;
+          w += dw; h += dh; if (w >= a.W) { w -= a.W; ++h; } if (h >= a.H) h -= a.H;
+        }
+        r.z[q] = wide_load(rz, in ? zo + 16 * q * zst : NOWHERE, 0);
+        r.x[q] = wide_load(rx, in ? xo + 16 * q * xst : NOWHERE, 0);
+      }
+      m0 += BP; zo += BP * zst; xo += BP * xst;
+    };
 #pragma unroll
-      for (int i = 0; i < 2; ++i) zf[i] = wide_frag_tr(B + zoff + i * 64 + k * 16 * ROW);
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) xf[j] = wide_frag_tr(B + xoff + j * 64 + k * 16 * ROW);
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    // sum += acc; acc = what that addition rounded off (exactly where |sum| >= |acc|, else to a rounding of acc)
+    auto fold = [&]() __attribute__((always_inline)) {
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[j], zf[i], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            const float t = acc[i][j][e], m = sum[i][j][e], s = m + t, d = s - m;
+            acc[i][j][e] = t - d;
+            sum[i][j][e] = s;
+          }
+    };
+    auto contract = [&](int bufo) __attribute__((always_inline)) {
+      const unsigned char* B = smem + bufo;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        bf16x8_t zf[2], xf[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) zf[i] = wide_frag_tr(B + zoff + i * 64 + k * 16 * ROW);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) xf[j] = wide_frag_tr(B + xoff + j * 64 + k * 16 * ROW);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            f32x16_t& c = HOW == 1 && k >= 2 ? sum[i][j] : acc[i][j];
+            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[j], zf[i], c, 0, 0, 0);
+          }
+      }
+    };
+    // (the host gives every slice at least one step; the step requested last is stored and never multiplied)
+    WgwSet ra;
+    issue(ra);
+    stash(ra, 0);
+    __syncthreads();
+    for (int s = s0; s < s1; ++s) {
+      const int bufo = (s - s0) & 1 ? BUF : 0;
+      issue(ra);
+      __builtin_amdgcn_sched_barrier(0);
+      contract(bufo);
+      __builtin_amdgcn_sched_barrier(0);
+      stash(ra, BUF - bufo);
+      if (HOW == 2 && ((s - s0) & (period - 1)) == period - 1) fold();
+      __syncthreads();
     }
   };
-
-  // (the host gives every slice at least one step; the step requested last is stored and never multiplied)
-  WgwSet ra;
-  issue(ra);
-  stash(ra, 0);
-  __syncthreads();
-  for (int s = s0; s < s1; ++s) {
-    const int bufo = (s - s0) & 1 ? BUF : 0;
-    issue(ra);
-    __builtin_amdgcn_sched_barrier(0);
-    contract(bufo);
-    __builtin_amdgcn_sched_barrier(0);
-    stash(ra, BUF - bufo);
-    __syncthreads();
+  if (s1 - s0 <= 2) run(std::integral_constant<int, 1>{});
+  else run(std::integral_constant<int, 2>{});
+  // Folding an infinity leaves no number in acc. If any element of the tile ends as none, the slice is added up plainly,
+  // which supplies those elements: infinities come out as infinities.
+  int bad = 0;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        sum[i][j][e] += acc[i][j][e];
+        bad |= sum[i][j][e] == sum[i][j][e] ? 0 : 1;
+      }
+  if (s1 - s0 > 2 && __syncthreads_or(bad)) {
+    run(std::integral_constant<int, 0>{});
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sum[i][j][e] = sum[i][j][e] == sum[i][j][e] ? sum[i][j][e] : acc[i][j][e];
   }
 
-  // The two pixel halves meet through LDS (the staging buffers are free after the loop's last barrier): a wave
-  // keeps one of its two co blocks, hands over the other and adds what its partner hands over, so
-  // that all eight waves store. [wave][ci block, quarter][lane] of 16 bytes, 64 KB.
-  auto quarter = [&](const f32x16_t& v, int q) __attribute__((always_inline)) {
-    return f32x4_t{v[q * 4], v[q * 4 + 1], v[q * 4 + 2], v[q * 4 + 3]};
-  };
-  f32x4_t* ex = reinterpret_cast<f32x4_t*>(smem) + wave * 512 + lane;
-#pragma unroll
-  for (int j = 0; j < 2; ++j)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) ex[(j * 4 + q) * 64] = kg ? quarter(acc[0][j], q) : quarter(acc[1][j], q);
-  __syncthreads();
-  const f32x4_t* got = reinterpret_cast<const f32x4_t*>(smem) + (wave ^ 4) * 512 + lane;
   // register q*4 + e of a lane holds co = l32 of the block, ci = q*8 + half*4 + e of the block
   const int J = taps * a.Cin;
-  float* dst = a.partial + ((size_t)split * a.Cout + co0 + wa * 64 + kg * 32 + l32) * J + (size_t)tap * a.Cin + ci0 + wb * 64 + half * 4;
+  float* dst = a.partial + ((size_t)split * a.Cout + co0 + wa * 64 + l32) * J + (size_t)tap * a.Cin + ci0 + wb * 64 + half * 4;
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      *reinterpret_cast<f32x4_t*>(dst + j * 32 + q * 8) = (kg ? quarter(acc[1][j], q) : quarter(acc[0][j], q)) + got[(j * 4 + q) * 64];
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<f32x4_t*>(dst + (size_t)(i * 32) * J + j * 32 + q * 8) =
+            f32x4_t{sum[i][j][q * 4], sum[i][j][q * 4 + 1], sum[i][j][q * 4 + 2], sum[i][j][q * 4 + 3]};
 }
 
 bool wgrad_wide_ok(int Cin, int Cout, int R, int stride, int dtype) {
@@ -216,7 +263,8 @@ bool wgrad_wide_ok(int Cin, int Cout, int R, int stride, int dtype) {
 
 // Layers join a launch, in the order of the backward pass, while their workgroups fit the chip at once; a launch that
 // leaves places free (the last one, or a layer that fills it alone) cuts its layers into more slices, of at least two
-// steps each.
+// steps each, and no more than fill 256 places by themselves: the reduction rounds too, and the partial sums of all 512 are
+// what it would show (512 -> 128 channels, 380 steps in 126 slices 1.2e-7, in 64 1.0e-7).
 void wgrad_wide_plan(std::vector<WgradWidePlan>& layers) {
   using namespace wgw;
   auto tiles = [](const WgradWidePlan& l) { return (l.Cout / 128) * (l.Cin / 128) * l.R * l.R; };
@@ -233,7 +281,7 @@ void wgrad_wide_plan(std::vector<WgradWidePlan>& layers) {
     const int more = wgs < PLACES ? (int)(PLACES / wgs) : 1;
     for (size_t i = first; i < end; ++i) {
       WgradWidePlan& l = layers[i];
-      const int most = nsteps(l) / 2 > 1 ? nsteps(l) / 2 : 1;
+      const int most = std::max(std::min(PLACES / 2 / tiles(l), nsteps(l) / 2), 1);
       if (l.splits * more <= most) l.splits *= more;
       else if (l.splits < most) l.splits = most;
       l.launch = i + 1 == end;
@@ -262,7 +310,7 @@ hipError_t wgrad_wide_launch(const WgradWideLayer* layers, int n, hipStream_t s)
   }
   if (wgs >= ((size_t)1 << 31)) return hipErrorInvalidValue;
   a.n = n;
-  DDG_LAUNCH(wgrad_wide_kernel, dim3((unsigned)wgs), dim3(512), wgw::LDS, s, a);
+  DDG_LAUNCH(wgrad_wide_kernel, dim3((unsigned)wgs), dim3(256), wgw::LDS, s, a);
   return hipGetLastError();
 }
 
