@@ -168,7 +168,8 @@ int conv_halo_rows(int M);
 hipError_t conv_halo_launch(const ConvWideArgs& a, int sets, int stats, bool xform, hipStream_t s);
 // 1x1 layers with few contraction channels (kernels_conv_point.hip)
 bool conv_point_ok(int IC, int R);
-int conv_point_rows(int M, int OC, int sets);
+int conv_point_groups(int M, int OC, int sets);      // sums a launch forms per channel and minibatch
+int conv_point_rows(int M, int OC, int sets);        // rows they take: one each, or two
 hipError_t conv_point_launch(const ConvWideArgs& a, int sets, int stats, bool xform, hipStream_t s);
 
 }  // namespace ddg

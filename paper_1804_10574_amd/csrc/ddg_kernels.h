@@ -236,6 +236,7 @@ bool conv_wide_ok(int IC, int OC, int R, int stride, int dtype);
 // statistics rows a launch writes per minibatch (sets: minibatches it carries); never more than conv_wide_rows_max()
 int conv_wide_rows(int M, int W, int IC, int OC, int R, int sets);
 int conv_wide_rows_max(int M);
+int conv_wide_sums(int M, int W, int IC, int OC, int R, int sets);   // of these, those that are no rest of another
 // scale/shift (optional, forward only): the conv input is relu(in*scale + shift) per input
 // channel, applied while staging.
 // second (optional, forward only): a second minibatch in the same launch, same weights.
@@ -248,9 +249,9 @@ hipError_t conv_wide_launch(const void* in, const void* wpack, void* out, float*
                             const ConvWideSecond* second = nullptr, const ConvStat* below = nullptr);
 
 // A 1x1 layer (IC a multiple of 256, OC = 128 or 256) whose input is y = relu(bn(z) + res): formed from z's statistics
-// rows (as many as conv_form_ok allows) and stored to y. f1, out_b, stat_partial_b (optional): the second minibatch. Statistics rows: conv_wide_rows_max().
+// rows (of as many sums as conv_form_ok allows) and stored to y. f1, out_b, stat_partial_b (optional): the second minibatch. Statistics rows: conv_wide_rows_max().
 struct FormSet { const void* z; const void* res; void* y; BnRows rows; };
-bool conv_form_ok(int IC, int OC, int R, int rows);
+bool conv_form_ok(int IC, int OC, int R, int sums);
 hipError_t conv_form_launch(const FormSet& f0, const FormSet* f1, const void* wpack, void* out, float* stat_partial, void* out_b, float* stat_partial_b,
                             int N, int H, int W, int IC, int OC, hipStream_t s);
 

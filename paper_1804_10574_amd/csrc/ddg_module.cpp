@@ -9,6 +9,7 @@
 
 #include <hip/hip_runtime_api.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -76,6 +77,7 @@ struct Unit {  // convolution + batch normalisation
   float* fstat = nullptr;       // partial rows of the forward statistics [group][fcap][2][cout]
   float* bstat = nullptr;       // partial rows of the BN-backward sums [brows][2][cout]
   int fcap = 0;                 // rows reserved per group in fstat
+  int fsums = 0;                // of these, sums per channel (a wide 1x1 layer may write a rest beside each)
   int frows = 0;                // rows written by the last forward conv (per group)
   // consumers finalise the partial rows themselves (their reduction is built for these widths)
   float *rmean = nullptr, *rvar = nullptr;     // running estimates for evaluation
@@ -416,7 +418,8 @@ ddg_status build_plan(ddg_module* m) {
         const int two = conv_wide_rows(f.M, u.W, u.cin, u.cout, u.R, 2);
         if (two > f.grid_x) f.grid_x = two;
       }
-      u.fcap = f.grid_x;
+      u.fcap = u.fsums = f.grid_x;
+      if (u.wide_f) u.fsums = std::max(conv_wide_sums(f.M, u.W, u.cin, u.cout, u.R, 1), conv_wide_sums(f.M, u.W, u.cin, u.cout, u.R, 2));
       u.frows = u.fcap;    // what the last forward conv of this layer wrote per group
       size_t st_e = (size_t)f.grid_x * 2 * u.cout;
       if (st_e > m->ws_stat_elems) m->ws_stat_elems = st_e;
@@ -897,7 +900,7 @@ static bool forms_output(const ddg_module* m, const std::vector<Blk>& blocks, in
   const Blk &b = blocks[bi], &n = blocks[bi + 1];
   if (b.kind != DDG_BLOCK_BOTTLENECK || b.proj || n.kind != DDG_BLOCK_BOTTLENECK || n.proj) return false;
   const Unit &ul = b.u[b.nmain - 1], &u0 = n.u[0];
-  return ul.fin_in_apply && u0.wide_f && conv_form_ok(u0.cin, u0.cout, u0.R, ul.fcap) && conv_wide_rows_max(u0.fprop.M) <= u0.fcap;
+  return ul.fin_in_apply && u0.wide_f && conv_form_ok(u0.cin, u0.cout, u0.R, ul.fsums) && conv_wide_rows_max(u0.fprop.M) <= u0.fcap;
 }
 // That output, not formed yet: y = relu(bn(u->z) + res), for group 0 or for both groups.
 struct PendWide { Unit* u = nullptr; const void* res[2] = {nullptr, nullptr}; void* y[2] = {nullptr, nullptr}; };

@@ -8,15 +8,16 @@
 //   waves 8-11: z and x, 16-byte loads four chunks of 64 channels ahead (64 KB in flight a workgroup; the launch is bound by
 //             memory), form y, store it and leave it in LDS. Loads complete in order, so a wave that also waited for weights from
 //             L2 would wait for everything it had requested from memory before them (29.6 us)
-//   batch norm: the workgroup adds the producer's statistics rows itself (fp64; 32 rows at most, which
-//             conv_point_kernel writes), so there is no launch in between; workgroup 0 stores the vectors
+//   batch norm: the workgroup adds the producer's statistics rows itself (fp64; 32 sums at most, in as
+//             many rows or, behind conv_point_kernel, twice as many), so there is no launch in between; workgroup 0 stores the vectors
 //   pixels:   a chunk at a time through two LDS buffers, one barrier a chunk
 //   weights:  fragments straight from the packed operand into the registers of the wave that uses them, two chunks ahead
 //   waves 0-7: OC/32 (32 channels) x 256/OC (32 or 64 pixels) with mfma_f32_32x32x16_bf16, rows fed as in conv_point_kernel
 //
 // Bottleneck stage of 23 blocks, batch 32, 1024 -> 256 at 14x14, two minibatches (77 MB moved): 26.9 us, for 14.8 (normalise-add-
 // ReLU) + 16.8 (conv_wide_kernel); a training step 4.39 -> 4.25 ms. Workgroups that all start at the same columns: 29.0. Every
-// wave loading both kinds of operand: 29.6. Without the sums' prologue it would take 3 us less, without multiplying 2, without
+// wave loading both kinds of operand: 29.6. With a rest beside each sum, 28 rows instead of 14, it takes
+// 1.7 us more (2.6 with 8 rows in flight instead of 16). Without the sums' prologue it would take 3 us less, without multiplying 2, without
 // loading z and x 8; weights four chunks ahead do not fit the registers (spills: 32.4).
 #include "ddg_conv_wide.h"
 
@@ -25,7 +26,7 @@ namespace ddg {
 namespace form {
 constexpr int BM = 64, CK = 64, DEPTH = 4;
 constexpr int PITCH = CK * 2 + 16, BUF = BM * PITCH;
-constexpr int ICMAX = 2048, ROWS_MAX = 32;
+constexpr int ICMAX = 2048, SUMS_MAX = 32;
 constexpr int opitch(int OC) { return OC * 2 + 16; }
 constexpr int max3(int a, int b, int c) { return a > b ? (a > c ? a : c) : (b > c ? b : c); }
 // the table of scales and shifts; then the chunks, later the finished tile, later the sums per row class
@@ -67,12 +68,6 @@ __global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     return m < a.M && chunk < nch ? ((unsigned)m * IC + pc * 8 + turned(chunk) * CK) * 2u : NOWHERE;
   };
   uint4 zq[DEPTH][2], rq[DEPTH][2];
-  if (producer) {
-#pragma unroll
-    for (int j = 0; j < DEPTH; ++j)
-#pragma unroll
-      for (int q = 0; q < 2; ++q) { zq[j][q] = wide_load(rz, at(j, q), 0); rq[j][q] = wide_load(rr, at(j, q), 0); }
-  }
   // ---- weights: matrix row l32 holds channel (l32 >> 2 & 1)*16 + (l32 >> 3)*4 + (l32 & 3) of the wave's 32
   const unsigned wl = (((l32 >> 2) & 1) * 64 + half * 16 + (l32 >> 3) * 4 + (l32 & 3)) * 16 + wn * 2048;
   constexpr unsigned kstep = (OC / 16) * 1024;                   // bytes per 32 contraction channels of the operand
@@ -82,40 +77,45 @@ __global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     _Pragma("unroll") for (int s = 0; s < KS; ++s)                                    \
       w[slot][s] = __builtin_bit_cast(bf16x8_t, wide_load(rw, wl, (turned(chunk) * (CK / 32) + (s >> 1)) * kstep + (s & 1) * 512)); \
   }
-  if (!producer) {
+  if (producer) {
+#pragma unroll
+    for (int j = 0; j < DEPTH; ++j)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) { zq[j][q] = wide_load(rz, at(j, q), 0); rq[j][q] = wide_load(rr, at(j, q), 0); }
+  } else {
     DDG_FORM_W(0, 0)
     DDG_FORM_W(1, 1)
-  }
-
-  // ---- scale and shift of all input channels
-  for (int c = tid * 2; c < IC; c += 1536) {
-    const float2 gm = *reinterpret_cast<const float2*>(f.rows.gamma + c), bt = *reinterpret_cast<const float2*>(f.rows.beta + c);
-    double s0 = 0.0, s1 = 0.0, q0 = 0.0, q1 = 0.0;
-    for (int r0 = 0; r0 < f.rows.rows; r0 += 8) {
-      float2 sv[8], qv[8];
+    // scale and shift of all input channels, here because the other waves' registers are full of z and x: 16 rows in flight
+    for (int c = tid * 2; c < IC; c += 1024) {
+      constexpr int RU = 16;
+      const float2 gm = *reinterpret_cast<const float2*>(f.rows.gamma + c), bt = *reinterpret_cast<const float2*>(f.rows.beta + c);
+      double s0 = 0.0, s1 = 0.0, q0 = 0.0, q1 = 0.0;
+      for (int r0 = 0; r0 < f.rows.rows; r0 += RU) {
+        float2 sv[RU], qv[RU];
 #pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        const float* p = f.rows.partial + (size_t)(r0 + r < f.rows.rows ? r0 + r : f.rows.rows - 1) * 2 * IC + c;
-        sv[r] = *reinterpret_cast<const float2*>(p);
-        qv[r] = *reinterpret_cast<const float2*>(p + IC);
-      }
+        for (int r = 0; r < RU; ++r) {
+          const float* p = f.rows.partial + (size_t)(r0 + r < f.rows.rows ? r0 + r : f.rows.rows - 1) * 2 * IC + c;
+          sv[r] = *reinterpret_cast<const float2*>(p);
+          qv[r] = *reinterpret_cast<const float2*>(p + IC);
+        }
 #pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        const bool on = r0 + r < f.rows.rows;
-        s0 += (double)(on ? sv[r].x : 0.f); s1 += (double)(on ? sv[r].y : 0.f);
-        q0 += (double)(on ? qv[r].x : 0.f); q1 += (double)(on ? qv[r].y : 0.f);
+        for (int r = 0; r < RU; ++r) {
+          const bool on = r0 + r < f.rows.rows;
+          s0 += (double)(on ? sv[r].x : 0.f); s1 += (double)(on ? sv[r].y : 0.f);
+          q0 += (double)(on ? qv[r].x : 0.f); q1 += (double)(on ? qv[r].y : 0.f);
+        }
       }
+      auto put = [&](int ch, double t1, double t2, float gamma, float beta) __attribute__((always_inline)) {
+        const double mu = t1 * f.rows.inv_count;
+        double var = t2 * f.rows.inv_count - mu * mu;
+        if (var < 0.0) var = 0.0;
+        const float is = (float)rsqrt(var + (double)f.rows.eps), sc = gamma * is, sh = beta - (float)mu * sc;
+        s_sc[ch] = sc; s_sh[ch] = sh;
+        if (blockIdx.x == 0) { f.rows.mean[ch] = (float)mu; f.rows.invstd[ch] = is; f.rows.scale[ch] = sc; f.rows.shift[ch] = sh; }
+      };
+      put(c, s0, q0, gm.x, bt.x);
+      put(c + 1, s1, q1, gm.y, bt.y);
     }
-    auto put = [&](int ch, double t1, double t2, float gamma, float beta) __attribute__((always_inline)) {
-      const double mu = t1 * f.rows.inv_count;
-      double var = t2 * f.rows.inv_count - mu * mu;
-      if (var < 0.0) var = 0.0;
-      const float is = (float)rsqrt(var + (double)f.rows.eps), sc = gamma * is, sh = beta - (float)mu * sc;
-      s_sc[ch] = sc; s_sh[ch] = sh;
-      if (blockIdx.x == 0) { f.rows.mean[ch] = (float)mu; f.rows.invstd[ch] = is; f.rows.scale[ch] = sc; f.rows.shift[ch] = sh; }
-    };
-    put(c, s0, q0, gm.x, bt.x);
-    put(c + 1, s1, q1, gm.y, bt.y);
   }
   __syncthreads();
 
@@ -229,8 +229,8 @@ __global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   }
 }
 
-bool conv_form_ok(int IC, int OC, int R, int rows) {
-  return R == 1 && (OC == 128 || OC == 256) && IC % (form::CK * form::DEPTH) == 0 && (IC & (IC - 1)) == 0 && IC <= form::ICMAX && rows >= 1 && rows <= form::ROWS_MAX;
+bool conv_form_ok(int IC, int OC, int R, int sums) {
+  return R == 1 && (OC == 128 || OC == 256) && IC % (form::CK * form::DEPTH) == 0 && (IC & (IC - 1)) == 0 && IC <= form::ICMAX && sums >= 1 && sums <= form::SUMS_MAX;
 }
 
 template <int OC>
@@ -245,7 +245,8 @@ static hipError_t form_run(const ConvWideArgs& a, const FormSet& f0, const FormS
 hipError_t conv_form_launch(const FormSet& f0, const FormSet* f1, const void* wpack, void* out, float* stat_partial, void* out_b, float* stat_partial_b,
                             int N, int H, int W, int IC, int OC, hipStream_t s) {
   const size_t M = (size_t)N * H * W;
-  if (!conv_form_ok(IC, OC, 1, f0.rows.rows) || (f1 && !conv_form_ok(IC, OC, 1, f1->rows.rows))) return hipErrorInvalidValue;
+  auto sums = [](const FormSet& f) { return (f.rows.rows + 1) / 2; };   // (at least: each may have a rest)
+  if (!conv_form_ok(IC, OC, 1, sums(f0)) || (f1 && !conv_form_ok(IC, OC, 1, sums(*f1)))) return hipErrorInvalidValue;
   if (M * (size_t)(IC > OC ? IC : OC) >= ((size_t)1 << 31)) return hipErrorInvalidValue;   // 32-bit byte offsets inside
   ConvWideArgs a{};
   a.wpack = (const bf16_t*)wpack; a.out = (bf16_t*)out; a.stat_partial = stat_partial; a.out_b = (bf16_t*)out_b; a.stat_partial_b = stat_partial_b;

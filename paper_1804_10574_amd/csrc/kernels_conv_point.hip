@@ -9,7 +9,8 @@
 //
 //   grid:   (pixel groups) x (minibatches) x OC/128 workgroups, at most one per compute unit; the groups share the
 //           64-pixel tiles evenly. Workgroups are numbered so that those of one pixel group run on one XCD and find
-//           its rows in that L2. One statistics row per pixel group (16 instead of 98 at 6272 pixels).
+//           its rows in that L2. One or two statistics rows per pixel group (6272 pixels x 1024 channels: 2*14 for two
+//           minibatches, 2*25 for one, where 64-pixel tiles of their own had 98).
 //   waves:  4 (32 channels) x 2 (32 pixels), mfma_f32_32x32x16_bf16 with channels as rows. Which channel feeds which row
 //           is free, and here lane half h is given channels h*16 .. h*16 + 15, so that a lane's accumulator is 16
 //           consecutive channels of one pixel. It goes through LDS (two buffers) so that memory sees 256 bytes per pixel:
@@ -17,9 +18,15 @@
 //           than the whole launch takes now (input gradient 37.6 us).
 //   order:  one barrier per 64 pixels. Between two of them tile t is multiplied, tile t-1 finished and stored (what its
 //           epilogue reads was requested a tile earlier), tile t+1 put into LDS and tile t+2 requested.
+//   sums:   a thread adds the values of eight tiles at most in fp32 (16 additions); from there on, over the threads and
+//           over the tiles, everything is added in fp64. A row of several tiles is a larger sum, which fp32 rounds more than
+//           rows of a tile each: it is kept in two rows, the sum and what rounding it to fp32 leaves (readers add
+//           rows in fp64). So the statistics are no less exact than with a row per 64 pixels, however many pixels there are:
+//           against 64 bits, values of a normal distribution, 7 tiles a row: sums 0.3, sums of squares 0.4, of
+//           products 0.6 times that error; 43 tiles 0.3, 0.4, 0.6 (in one fp32 row: 3.8, 0.5, 0.9 and 11, 2.8, 1.6).
 //
 // 256 -> 1024 channels: two minibatches of 6272 pixels with on-load batch norm 22.4 (64-pixel tiles) -> 17.2 us, input
-// gradient of one with the sums of the layer below 21.5 -> 17.4. What bounds it: of the forward launch 3.9 us are start and
+// gradient of one with the sums of the layer below 21.5 -> 17.4; sums in fp64 0.5 more and the same. What bounds it: of the forward launch 3.9 us are start and
 // end, the seven tiles 1.9 us each, of which matrix instructions with their fragment reads 0.7, finishing 0.6 and
 // staging 0.5: the parts add, two waves a SIMD hide little of each other. The input gradient waits for the three
 // tensors of its epilogue (8 us without them). Tried: two tiles in flight (the same), one wave of each SIMD finishing
@@ -33,12 +40,14 @@ namespace point {
 constexpr int BM = 64;
 constexpr int pitch(int K) { return K * 2 + 16; }              // bytes per staged pixel: the fragment reads of consecutive lanes fall into distinct banks
 constexpr int opitch(int stats) { return stats == 1 ? 128 * 2 + 16 : 128 * 4 + 16; }   // bytes per pixel of a finished tile: as stored, or fp32 where something is added to it
-constexpr int lds_bytes(int K, int stats) { return 2 * BM * (pitch(K) + opitch(stats)); }
+constexpr int RED = 32 * 128 * 4;                              // where sums of the 32 pixel classes meet
+constexpr int lds_bytes(int K, int stats) { return 2 * BM * (pitch(K) + opitch(stats)) + (stats ? RED : 0); }
+constexpr int CHAIN = 8;                                       // tiles whose values a thread adds in fp32 (a power of two)
 constexpr unsigned NOWHERE = 0xfffffff0u;                      // past the end of any tensor: the load gives zeros
 }
 
 template <int STATS, bool XFORM, int K>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void conv_point_kernel(ConvWideArgs a, int groups) {
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void conv_point_kernel(ConvWideArgs a, int groups, bool rests) {
   using namespace point;
   constexpr int PITCH = pitch(K), BUF = BM * PITCH, UPR = K / 8, NU = BM * UPR / 512, RPP = 512 / UPR, KS = K / 16;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -133,6 +142,24 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       wide_store(rout, o, ok ? (unsigned)m * (unsigned)(a.OC * 2) + (c0 + oc * 8) * 2 : NOWHERE);
     }
   };
+  // the threads' sums so far, by thread: channel tid & 127, pixel classes (tid >> 7)*8 .. +7
+  double tot[2] = {0.0, 0.0};
+  unsigned char* redb = smem + 2 * (BUF + OBUF);
+  auto gather = [&]() __attribute__((always_inline)) {
+    float* red = reinterpret_cast<float*>(redb);
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+      float (&v)[8] = w ? tail.ssq : tail.ssum;
+#pragma unroll
+      for (int e = 0; e < 8; e += 4) *reinterpret_cast<float4*>(&red[orow * 128 + oc * 8 + e]) = make_float4(v[e], v[e + 1], v[e + 2], v[e + 3]);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = 0.f;
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < 8; ++r) tot[w] += (double)red[((tid >> 7) * 8 + r) * 128 + (tid & 127)];
+      __syncthreads();
+    }
+  };
   const int frag = (wp * 32 + l32) * PITCH + half * 16;
   const int odst = (wp * 32 + l32) * OP + (wn * 32 + half * 16) * (STATS == 1 ? 2 : 4);
   for (int t = t0; t < t1; ++t) {
@@ -144,6 +171,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int s = 0; s < KS; ++s)
       acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[s], *reinterpret_cast<const bf16x8_t*>(B + s * 32), acc, 0, 0, 0);
     finish(t - 1);
+    if (STATS && ((t - t0) & (CHAIN - 1)) == CHAIN - 1) gather();
     fetch(t);
     stash(sa, (t + 1 - t0) & 1);                   // (free since the barrier that ended tile t-1)
     issue(sa);
@@ -164,20 +192,35 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
   finish(t1 - 1);
   if (STATS) {
-    __syncthreads();                               // the tiles have been read
-    tail.template store_row<128>(reinterpret_cast<float*>(smem), g_stat + (size_t)grp * 2 * a.OC, a.OC, c0);
+    gather();
+    double* red = reinterpret_cast<double*>(redb);         // [quarter of the classes][2][128]
+#pragma unroll
+    for (int w = 0; w < 2; ++w) red[((tid >> 7) * 2 + w) * 128 + (tid & 127)] = tot[w];
+    __syncthreads();
+    if (tid < 256) {
+      const double t = (red[tid] + red[256 + tid]) + (red[512 + tid] + red[768 + tid]);
+      const size_t at = (size_t)(tid >> 7) * a.OC + c0 + (tid & 127);
+      const float sum = (float)t, rest = (float)(t - (double)sum);
+      g_stat[(size_t)grp * 2 * a.OC + at] = sum;
+      // (an infinite sum has no rest)
+      if (rests) g_stat[(size_t)(groups + grp) * 2 * a.OC + at] = fabsf(rest) <= 3.4e38f ? rest : 0.f;
+    }
   }
 }
 
 bool conv_point_ok(int IC, int R) { return R == 1 && (IC == 128 || IC == 256); }
 // Pixel groups per minibatch: as many as keep the launch at one workgroup per compute unit, and no more than share the
 // longest group's tiles.
-int conv_point_rows(int M, int OC, int sets) {
+int conv_point_groups(int M, int OC, int sets) {
   const int tiles = (M + point::BM - 1) / point::BM;
   int g = 256 / ((OC / 128) * sets);
   g = g < 1 ? 1 : g > tiles ? tiles : g;
   const int most = (tiles + g - 1) / g;
   return (tiles + most - 1) / most;
+}
+int conv_point_rows(int M, int OC, int sets) {     // (a group of one tile rounds its sum as a row per tile always has been)
+  const int groups = conv_point_groups(M, OC, sets);
+  return groups < (M + point::BM - 1) / point::BM ? 2 * groups : groups;
 }
 
 template <int STATS, bool XFORM, int K>
@@ -185,9 +228,10 @@ static hipError_t point_run(const ConvWideArgs& a, int sets, hipStream_t s) {
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_point_kernel<STATS, XFORM, K>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, point::lds_bytes(K, STATS));
   if (attr != hipSuccess) return attr;
-  static_assert(point::lds_bytes(K, STATS) >= (2 * 128 * 32 + 512) * 4, "the sums fit");
-  const int groups = conv_point_rows(a.M, a.OC, sets);
-  DDG_LAUNCH((conv_point_kernel<STATS, XFORM, K>), dim3(groups * sets * (a.OC / 128)), dim3(512), point::lds_bytes(K, STATS), s, a, groups);
+  static_assert(point::lds_bytes(K, STATS) <= 160 * 1024, "one compute unit's LDS");
+  const int groups = conv_point_groups(a.M, a.OC, sets);
+  DDG_LAUNCH((conv_point_kernel<STATS, XFORM, K>), dim3(groups * sets * (a.OC / 128)), dim3(512), point::lds_bytes(K, STATS), s, a, groups,
+             conv_point_rows(a.M, a.OC, sets) > groups);
   return hipGetLastError();
 }
 

@@ -372,6 +372,9 @@ int conv_wide_rows_max(int M) { return (M + wide::BM - 1) / wide::BM; }
 int conv_wide_rows(int M, int W, int IC, int OC, int R, int sets) {
   return conv_point_ok(IC, R) ? conv_point_rows(M, OC, sets) : conv_halo_ok(IC, W, R) ? conv_halo_rows(M) : conv_wide_rows_max(M);
 }
+int conv_wide_sums(int M, int W, int IC, int OC, int R, int sets) {
+  return conv_point_ok(IC, R) ? conv_point_groups(M, OC, sets) : conv_wide_rows(M, W, IC, OC, R, sets);
+}
 
 hipError_t conv_wide_launch(const void* in, const void* wpack, void* out, float* stat_partial, const void* add_g,
                             const void* add_mask, int N, int H, int W, int IC, int OC, int R, hipStream_t s,
