@@ -32,6 +32,7 @@
 // 64 bytes a clock, stores of 32 KB), and the vector instructions that fold beside the matrix instructions.
 #include "ddg_conv_wide.h"
 #include <algorithm>
+#include <cstdlib>
 #include <type_traits>
 
 namespace ddg {
@@ -44,7 +45,7 @@ struct WgwLayer {
   float* partial;        // [splits][Cout][taps*Cin]
   int M, H, W, Cin, Cout, R, splits, wg0;   // wg0: first workgroup of the layer
 };
-struct WgwArgs { WgwLayer l[WGRAD_WIDE_LAYERS]; int n; };
+struct WgwArgs { WgwLayer l[WGRAD_WIDE_LAYERS]; int n, by_xcd; };
 
 namespace wgw {
 constexpr int BP = 64;                     // pixels per step
@@ -81,8 +82,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // the same rows of x and dz, so the (layer, slice, tile) triples are numbered in that order and XCD j is
   // given the j-th eighth of that sequence: the rows of a slice then come from memory once into
   // one XCD's L2 (two at a boundary) and every other tile finds them there.
-  int V;
-  {
+  int V = blockIdx.x;
+  if (args.by_xcd) {
     const int T = gridDim.x, L = blockIdx.x, xcd = L & 7, q = T >> 3, r = T & 7;
     V = xcd * q + (xcd < r ? xcd : r) + (L >> 3);    // XCD j holds q (+1 if j < r) workgroups
   }
@@ -267,6 +268,11 @@ bool wgrad_wide_ok(int Cin, int Cout, int R, int stride, int dtype) {
 // what it would show (512 -> 128 channels, 380 steps in 126 slices 1.2e-7, in 64 1.0e-7).
 void wgrad_wide_plan(std::vector<WgradWidePlan>& layers) {
   using namespace wgw;
+  int places = PLACES;
+  if (const char* e = getenv("DDG_TUNE_WGRAD_WIDE_WGS")) {   // timing experiments, within [64, 2048]
+    const int v = atoi(e);
+    if (v >= 64 && v <= 2048) places = v;
+  }
   auto tiles = [](const WgradWidePlan& l) { return (l.Cout / 128) * (l.Cin / 128) * l.R * l.R; };
   auto nsteps = [](const WgradWidePlan& l) { return (l.M + BP - 1) / BP; };
   for (WgradWidePlan& l : layers) l.splits = (nsteps(l) + SLICE_MAX - 1) / SLICE_MAX;
@@ -274,14 +280,14 @@ void wgrad_wide_plan(std::vector<WgradWidePlan>& layers) {
     long wgs = 0;
     size_t end = first;
     while (end < layers.size() && end - first < (size_t)WGRAD_WIDE_LAYERS &&
-           (end == first || wgs + (long)tiles(layers[end]) * layers[end].splits <= PLACES)) {
+           (end == first || wgs + (long)tiles(layers[end]) * layers[end].splits <= places)) {
       wgs += (long)tiles(layers[end]) * layers[end].splits;
       ++end;
     }
-    const int more = wgs < PLACES ? (int)(PLACES / wgs) : 1;
+    const int more = wgs < places ? (int)(places / wgs) : 1;
     for (size_t i = first; i < end; ++i) {
       WgradWidePlan& l = layers[i];
-      const int most = std::max(std::min(PLACES / 2 / tiles(l), nsteps(l) / 2), 1);
+      const int most = std::max(std::min(places / 2 / tiles(l), nsteps(l) / 2), 1);
       if (l.splits * more <= most) l.splits *= more;
       else if (l.splits < most) l.splits = most;
       l.launch = i + 1 == end;
@@ -310,6 +316,7 @@ hipError_t wgrad_wide_launch(const WgradWideLayer* layers, int n, hipStream_t s)
   }
   if (wgs >= ((size_t)1 << 31)) return hipErrorInvalidValue;
   a.n = n;
+  a.by_xcd = getenv("DDG_NO_WGRAD_XCD") ? 0 : 1;
   DDG_LAUNCH(wgrad_wide_kernel, dim3((unsigned)wgs), dim3(256), wgw::LDS, s, a);
   return hipGetLastError();
 }
