@@ -107,8 +107,8 @@ void wgrad_plan(WgradArgs& a);
 size_t wgrad_partial_elems(const WgradArgs& a);
 hipError_t wgrad_launch(const WgradArgs& a, hipStream_t s);
 hipError_t wgrad_reduce_launch(const WgradArgs& a, hipStream_t s);
-// A layer's weight gradient and input gradient in one launch (generic kernels).
-bool bwd_generic_ok(const WgradArgs& w, const ConvArgs& a);
+// A layer's weight gradient and input gradient in one launch (generic kernels). alone: no other module runs beside it.
+bool bwd_generic_ok(const WgradArgs& w, const ConvArgs& a, bool alone);
 hipError_t bwd_generic_launch(const WgradArgs& w, const ConvArgs& a, hipStream_t s);
 
 // Whole-module variants driven by a device-side table (one launch per module instead of one

@@ -1231,7 +1231,7 @@ ddg_status unit_backward(ddg_module* m, Unit& u, const void* dy, const void* mas
       m->pend_wide.push_back({x_in, dz_buf, x_scale, x_shift, u.wg_partial, u.N, u.H, u.W, u.cin, u.cout, u.R, u.wide_splits});
       m->pend_wide_bytes += bytes; m->pend_wide_flops += conv_flops(u);
       if (u.wide_launch) DDG_OKAY(flush_wide_wgrad(m));
-    } else if (dx && u.tiled_grid == 0 && !u.wide_d && bwd_generic_ok(w, u.dgrad)) {
+    } else if (dx && u.tiled_grid == 0 && !u.wide_d && bwd_generic_ok(w, u.dgrad, m->d.K == 1)) {
       ConvArgs a = u.dgrad;
       a.in = dz_buf; a.wpack = u.wpack_d; a.out = dx; a.stat_partial = nullptr;
       a.add_g = add_g; a.add_mask = add_mask;

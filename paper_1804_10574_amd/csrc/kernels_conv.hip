@@ -208,8 +208,7 @@ __global__ __launch_bounds__(256) void conv_mfma_kernel(ConvPair ab, int sets) {
 }
 
 // Weight gradient (vector gathers) and input gradient of a layer in one launch: both need its dz and nothing of each
-// other. Layers of the generic kernels are small or few, and a launch that waits for the one before costs
-// 4-5 us whatever it does.
+// other, and a launch that waits for the one before costs 4-5 us whatever it does (bwd_generic_ok: how large a layer may be).
 template <typename T, int MB, int NB>
 __global__ __launch_bounds__(256) void bwd_generic_kernel(WgradArgs w, ConvArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -490,7 +489,14 @@ hipError_t conv_launch(const ConvArgs& a, hipStream_t s, const ConvArgs* other) 
   return a.dtype == BF16 ? conv_dispatch<bf16_t>(a, nullptr, s) : conv_dispatch<float>(a, nullptr, s);
 }
 
-bool bwd_generic_ok(const WgradArgs& w, const ConvArgs& a) {
+// Alone on the chip the shared launch is 2 to 26 us faster at every size (modules of 4 basic blocks with 16-64 channels at 7-28 wide
+// images, batch 32 to 512, and of 2 bottlenecks of 256 to 2048 channels in fp32, batch 1 to 16: 1 to 20 % of a step), and in bf16 pipelines up to
+// 7 %. In fp32 it holds the chip's places longer at the weight gradient's registers and LDS (three workgroups a compute unit), and what other
+// modules would have run beside it waits: two launches above 3 << 20 gradient values. 48 fp32 pipelines of two to four modules, 20 to 28 wide
+// images, batch 64 to 512, time against two launches everywhere: 0.973, without the line 0.980; of these from batch 256 on 0.993 and 1.005.
+// Twelve of one module: 0.949 without the line, so it does not hold there (`alone`).
+bool bwd_generic_ok(const WgradArgs& w, const ConvArgs& a, bool alone) {
+  if (w.dtype != BF16 && !alone && (size_t)w.M * w.Cout > (size_t)3 << 20) return false;
   return w.vec && a.dgrad && !a.proj_in && w.dtype == a.dtype && a.IC % mma_kv(a.dtype) == 0 && !conv_dgrad_s2_ok(a);
 }
 
@@ -510,7 +516,7 @@ static hipError_t bwd_generic_dispatch(const WgradArgs& w, const ConvArgs& a, hi
 }
 
 hipError_t bwd_generic_launch(const WgradArgs& w, const ConvArgs& a, hipStream_t s) {
-  if (!bwd_generic_ok(w, a) || a.stat_partial || a.in_b) return hipErrorInvalidValue;
+  if (!bwd_generic_ok(w, a, true) || a.stat_partial || a.in_b) return hipErrorInvalidValue;
   // 32-bit element offsets inside
   if ((size_t)w.N * w.H * w.W * w.Cin >= ((size_t)1 << 32) || (size_t)w.M * w.Cout >= ((size_t)1 << 32)) return hipErrorInvalidValue;
   return a.dtype == BF16 ? bwd_generic_dispatch<bf16_t>(w, a, s) : bwd_generic_dispatch<float>(w, a, s);
