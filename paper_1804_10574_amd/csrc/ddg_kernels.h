@@ -200,7 +200,7 @@ int conv_tiled_grid(int N, int H, int W, int Cin, int Cout, int R, int stride, i
 // apply (optional, input gradient only): `in` is apply->dy, the gradient after a batch norm's
 // ReLU; the kernel forms dz = BN-backward(dy) from apply->rows while staging (as the fused
 // weight-gradient kernel does), convolves dz, and stores it to apply->dz_out.
-// ride (optional, with apply, statistics mode 2, 32 or 64 channels): the launch also carries the batch-norm backward sums of another layer, on
+// ride (optional, with apply and pair, statistics mode 2, 32 or 64 channels): the launch also carries the batch-norm backward sums of another layer, on
 // workgroups of its own.
 // pair (optional, with apply): the launch also carries the plain weight gradient of another
 // layer of the same shape (input x, or relu(x*scale+shift); error gradient dz; `rows` partial

@@ -239,7 +239,7 @@ template <int K>
 static hipError_t point_dispatch(const ConvWideArgs& a, int sets, int stats, bool xform, hipStream_t s) {
   if (stats == 2) return xform ? hipErrorInvalidValue : point_run<2, false, K>(a, sets, s);
   if (stats == 1) return xform ? point_run<1, true, K>(a, sets, s) : point_run<1, false, K>(a, sets, s);
-  return xform ? point_run<0, true, K>(a, sets, s) : point_run<0, false, K>(a, sets, s);
+  return xform ? hipErrorInvalidValue : point_run<0, false, K>(a, sets, s);    // (a forward pass always keeps its statistics)
 }
 
 hipError_t conv_point_launch(const ConvWideArgs& a, int sets, int stats, bool xform, hipStream_t s) {

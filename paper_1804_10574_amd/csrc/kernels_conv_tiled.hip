@@ -416,7 +416,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(conv_tiled_
 }
 
 // The input gradient of the second layer of a stage's first block: beside it the sums of the block's projection, which wait for
-// the same gradient, and (wg_rows > 0) the plain weight gradient of the unit above.
+// the same gradient, and the plain weight gradient of the unit above.
 template <int C, int W, int XF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(conv_tiled_waves(C, 2, XF)))) void bwd_down_kernel(ConvTiledArgs ca, WgradTiledArgs wa, BnReduceRide rd, int conv_grid, int wg_rows, int wg_blocks) {
   extern __shared__ __align__(16) unsigned char tile[];
@@ -468,15 +468,14 @@ static hipError_t conv_tiled_launch_t(const ConvTiledArgs& a, int grid, hipStrea
   using Cfg = ConvTiledCfg<C, W>;
   if (ride) {
     using WCfg = WgradTiledCfg<C, C, W>;
-    if (!a.bz || a.st.mode != 2 || a.scale || a.in_rows.partial || !a.brows.partial || !a.dz_out || C == 16 || ride->C != C || ride->grid < 1)
+    if (!wa || !a.bz || a.st.mode != 2 || a.scale || a.in_rows.partial || !a.brows.partial || !a.dz_out || C == 16 || ride->C != C || ride->grid < 1)
       return hipErrorInvalidValue;
     constexpr int lds = Cfg::TILE_BYTES > WCfg::LDS ? Cfg::TILE_BYTES : WCfg::LDS;
     if constexpr (C != 16) {
-      const int wgb = wa ? wg_rows * WCfg::OT : 0;
+      const int wgb = wg_rows * WCfg::OT;
       const dim3 g(grid + wgb + ride->grid);
-      const WgradTiledArgs none{};
-      if (a.bmask && a.bmask != a.bz) DDG_LAUNCH((bwd_down_kernel<C, W, XF_APPLY_MASK>), g, dim3(256), lds, s, a, wa ? *wa : none, *ride, grid, wg_rows, wgb);
-      else DDG_LAUNCH((bwd_down_kernel<C, W, XF_APPLY>), g, dim3(256), lds, s, a, wa ? *wa : none, *ride, grid, wg_rows, wgb);
+      if (a.bmask && a.bmask != a.bz) DDG_LAUNCH((bwd_down_kernel<C, W, XF_APPLY_MASK>), g, dim3(256), lds, s, a, *wa, *ride, grid, wg_rows, wgb);
+      else DDG_LAUNCH((bwd_down_kernel<C, W, XF_APPLY>), g, dim3(256), lds, s, a, *wa, *ride, grid, wg_rows, wgb);
     }
     return hipGetLastError();
   }

@@ -546,7 +546,7 @@ __global__ __launch_bounds__(256) void bwd_pair_f32_kernel(ConvTiledF32Args ca, 
   else wgrad_tiled_f32_body<C, W, false>(wa, smem, b - conv_grid, wg_rows);
 }
 
-// As bwd_down_kernel in the bf16 path: with the sums of the block's projection and, wg_rows > 0, the weight gradient of the unit above.
+// As bwd_down_kernel in the bf16 path: with the sums of the block's projection and the weight gradient of the unit above.
 template <int C, int W, int XF>
 __global__ __launch_bounds__(256) void bwd_down_f32_kernel(ConvTiledF32Args ca, WgradTiledF32Args wa, BnReduceRide rd, int conv_grid, int wg_rows) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -594,14 +594,13 @@ static hipError_t conv_tiled_f32_launch_t(const ConvTiledF32Args& a, int grid, h
   using Cfg = ConvTiledF32Cfg<C, W>;
   if (ride) {
     using WCfg = WgradTiledF32Cfg<C, W>;
-    if (!a.bz || a.st.mode != 2 || a.scale || a.in_rows.partial || !a.brows.partial || !a.dz_out || C == 16 || ride->C != C || ride->grid < 1)
+    if (!wa || !a.bz || a.st.mode != 2 || a.scale || a.in_rows.partial || !a.brows.partial || !a.dz_out || C == 16 || ride->C != C || ride->grid < 1)
       return hipErrorInvalidValue;
     constexpr int lds = Cfg::TILE_BYTES > WCfg::LDS ? Cfg::TILE_BYTES : WCfg::LDS;
     if constexpr (C != 16) {
       const dim3 g(grid + wg_rows + ride->grid);
-      const WgradTiledF32Args none{};
-      if (a.bmask && a.bmask != a.bz) DDG_LAUNCH((bwd_down_f32_kernel<C, W, XF32_APPLY_MASK>), g, dim3(256), lds, s, a, wa ? *wa : none, *ride, grid, wg_rows);
-      else DDG_LAUNCH((bwd_down_f32_kernel<C, W, XF32_APPLY>), g, dim3(256), lds, s, a, wa ? *wa : none, *ride, grid, wg_rows);
+      if (a.bmask && a.bmask != a.bz) DDG_LAUNCH((bwd_down_f32_kernel<C, W, XF32_APPLY_MASK>), g, dim3(256), lds, s, a, *wa, *ride, grid, wg_rows);
+      else DDG_LAUNCH((bwd_down_f32_kernel<C, W, XF32_APPLY>), g, dim3(256), lds, s, a, *wa, *ride, grid, wg_rows);
     }
     return hipGetLastError();
   }
