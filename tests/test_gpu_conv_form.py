@@ -1,6 +1,7 @@
 """Blocks whose first layer forms the block's input while it loads (the output of the block before): pixels on both sides of a
-tile of 64, both tile shapes (128 and 256 output channels), the fewest and the most input channels, in paired forward passes;
-against the oracle."""
+tile of 64, both tile shapes (128 and 256 output channels), the fewest and the most input channels, statistics of as many rows as
+one trip of 16 takes and of more, with and without rests, in paired forward passes; against the oracle, the normalising launches
+counted."""
 import numpy as np
 import pytest
 
@@ -8,15 +9,17 @@ import workloads as wk
 
 pytestmark = pytest.mark.gpu
 
-CASES = [(1, 3, 256, 128),      # 9 pixels, four chunks of channels (the fewest)
-         (1, 8, 512, 256),      # 64 pixels: one tile exactly
-         (5, 5, 2048, 128),     # 125 pixels, the most input channels: the largest table of scales
-         (1, 13, 512, 256),     # 169 pixels: last tile of 41
-         (13, 5, 1024, 256)]    # 325 pixels: last tile of 5
+CASES = [(1, 3, 256, 128, 3),      # 9 pixels, four chunks of channels (the fewest)
+         (1, 8, 512, 256, 3),      # 64 pixels: one tile exactly
+         (5, 5, 2048, 128, 3),     # 125 pixels, the most input channels: the largest table of scales
+         (1, 13, 512, 256, 3),     # 169 pixels: last tile of 41
+         (13, 5, 1024, 256, 3),    # 325 pixels: last tile of 5
+         (10, 14, 512, 128, 2),    # 1960 pixels: 31 rows of a tile each, one fewer than the most sums
+         (20, 8, 2048, 128, 2)]    # 1280 pixels: rows of two and three tiles, with rests: 20 for one minibatch, 2*7 for two
 
 
-@pytest.mark.parametrize("batch,hw,c,cmid", CASES)
-def test_first_layer_forms_its_input(batch, hw, c, cmid):
+@pytest.mark.parametrize("batch,hw,c,cmid,blocks", CASES)
+def test_first_layer_forms_its_input(batch, hw, c, cmid, blocks):
     import torch
     if not torch.cuda.is_available():
         pytest.skip("needs a GPU")
@@ -25,7 +28,7 @@ def test_first_layer_forms_its_input(batch, hw, c, cmid):
     from oracle import ddg_oracle as orc
     from tests import gpu_harness as H
     print(f"case formed inputs batch={batch} hw={hw} {c}-{cmid}-{c}", flush=True)
-    net, shape = [(wk.BLOCK_BOTTLENECK, c, cmid, c, 1, 0)] * 3, (batch, c, hw, hw)
+    net, shape = [(wk.BLOCK_BOTTLENECK, c, cmid, c, 1, 0)] * blocks, (batch, c, hw, hw)
     mod = ddg.Module(make_desc(4, 2, batch, (c, hw, hw), net, 0, ddg.DDG_BF16, 0.9, 0.0, 1e-5))
     oracle = orc.OracleNet(4, [net], batch, (c, hw, hw), 0, 0.9, 0.0, 1e-5, "f64", k_first=2, store_bf16=True)
     theta = (wk.normal(31, 1, oracle.param_count(2)) * 0.05 + 0.02).astype(np.float32)
@@ -41,7 +44,12 @@ def test_first_layer_forms_its_input(batch, hw, c, cmid):
         h_out, d_out = torch.empty_like(hd), torch.zeros_like(hd)
         keep += [hd, dd, h_out, d_out]
         torch.cuda.synchronize()
+        mod.profile_reset()
+        mod.profile_enable(True)
         mod.forward(t, hd, h_out)
+        mod.profile_enable(False)
+        # the last block's output only; the others' are formed by the block behind
+        assert mod.profile_read()["bn_apply"][0] == 1
         did = mod.backward_delayed(t, delta_in=dd, delta_out=d_out)
         mod.sync()
         ref_h = oracle.forward(2, t, H.from_dev_nhwc(hd))
