@@ -1789,8 +1789,9 @@ ddg_status ddg_forward(ddg_module* m, long t, const void* h_in, void* h_out) {
   void* slot = m->ring[t % m->nslots];
   // The input is kept in the ring for the backward pass. This pass reads it where it is, so that the copy can go with the last
   // launch; where the output overlaps it, the copy comes first. So it does above 4 MiB, where moving the bytes takes longer
-  // than the launch that is saved and the first layer then finds them in cache (ResNet-20 fp32, batch 128, 8 MiB between the
-  // modules: 13.14 ms for 16 iterations, with its copy last 13.22; ResNet-20 bf16 batch 37, 1.2 MiB: 4.98, last 4.91).
+  // than the launch that is saved and the first layer then finds them in cache. us an iteration, copied first / last, by what two
+  // modules of ResNet-20 hand over: fp32 2 MiB 433/436, 3 MiB 492/482, 4 MiB 550/549, 6 MiB 711/708, 8 MiB 817/821, 16 MiB
+  // 1308/1324; bf16 1.2 MiB 306/303, 3 MiB 353/349, 4 MiB 402/397, 6 MiB 480/472, 8 MiB 568/567, 12 MiB 718/716.
   const size_t in_bytes = m->in_elems * m->esz;
   const char *ib = (const char*)h_in, *ob = (const char*)h_out;
   const bool copy_last = in_bytes <= ((size_t)4 << 20) && (!ob || ob + m->out_elems * m->esz <= ib || ib + in_bytes <= ob);

@@ -7,13 +7,14 @@
 // 64 of the C channels only. What bounds them: memory (3 tensors), and the row reads, which
 // cost (pixel groups) * rows * 2 * C * 4 bytes of L2 traffic for the launch: it grows with the square of
 // the pixel count, hence a line at WIDE_ROWS_MAX rows. In pixels that is 8192 behind conv_wide_kernel (a row per 64
-// pixels) and 16384 behind conv_halo_kernel (a row per 128); the generic convolution (fp32) writes at most 512 rows, by its
+// pixels) and 16384 behind conv_halo_kernel (a row per 128); behind conv_point_kernel, whose rows a launch's width bounds, it is
+// reached by 256 channels or fewer only (more than 8192 pixels). The generic convolution (fp32) writes at most 512 rows, by its
 // grid. Two blocks 512-128-128-512 at 28x28, a step, finalised here against in a launch of its own: 6272 pixels 291
 // against 314 us; behind the halo kernel alone 8624 pixels 361.1 against 363.2, 12544 408 against 409, 14112 430.0
 // against 427.0, 15680 453 against 450: even at about 100 rows, 1 % behind at 128.
-// 23 bottleneck blocks at 14x14, batch 32 (98 rows), per launch: normalise-add-ReLU of two 6272 x 1024
-// minibatches 28.3 -> 16.4 us against a finalise launch and bn_apply_pair_kernel; BN backward of 6272 x 256
-// 9.8 -> 5.6 us, of 6272 x 1024 12.0 -> 9.6 us (a launch that depends on the one before costs 4.7 us whatever it does).
+// 23 bottleneck blocks at 14x14, batch 32, with 98 rows, per launch: normalise-add-ReLU of two 6272 x 1024
+// minibatches 28.3 -> 16.4 us against a finalise launch and bn_apply_pair_kernel (conv_form_kernel does it now for all blocks but
+// the last); BN backward of 6272 x 256 9.8 -> 5.6 us, of 6272 x 1024 12.0 -> 9.6 us (a launch that depends on the one before costs 4.7 us whatever it does).
 #include "ddg_device.h"
 #include "ddg_kernels.h"
 

@@ -150,10 +150,11 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradArgs a) {
 // Many rows (the narrow layers: up to 128 rows of a few thousand outputs): a workgroup covers 64 groups of 4
 // outputs, one thread per class with 8 loads in flight (a wave reads 1 KiB of one row).
 //
-// Few rows (RED_FEW; the wide layers: 7-16 rows of up to 590 thousand outputs): a thread adds all rows of its
+// Few rows (RED_FEW; most wide layers: one row to eight of up to 590 thousand outputs): a thread adds all rows of its
 // outputs with every load in flight, a workgroup covers 1024 outputs (1x1: stored as they come) or one output
 // channel (3x3: through LDS into the [ci][r][s] order, so that memory sees whole lines instead of four bytes in every
-// 36). 23 bottleneck blocks, 1.15 GB: 297 -> 251 us; with the 2 rows the wide layers have since, 0.2 GB, four loads instead of sixteen.
+// 36). 23 bottleneck blocks with the 7 to 16 rows of layers in launches of their own, 1.15 GB: 297 -> 251 us; with the 2 rows (6 in the
+// last launch) of layers that share one, 0.2 GB, 52 us, four loads instead of sixteen.
 constexpr int RED_FEW = 16, RED_J_MAX = 9 * 512;
 
 __host__ __device__ static inline bool red_few(int rows, int Cout, int Cin, int R, int Jp) {

@@ -748,7 +748,7 @@ def test_wide_bottleneck_module_bf16(H, nblocks, batch, c, mid, hw, dmed, dmax):
 def test_full_size_bottleneck_module_bf16(H):
     """The ImageNet-shaped module exactly as `bench.py --workload r101_stage3_k4m2` runs it: 23
     bottleneck blocks 1024-256-256-1024 at 14x14, batch 32 (6272 pixels per layer: 98 pixel
-    tiles, the 16 / 7 pixel slices of the weight-gradient kernel), k = 2 of K = 4, bf16: two
+    tiles, 2 pixel slices in most launches of the weight-gradient kernel), k = 2 of K = 4, bf16: two
     warm-up iterations (forward only) and the first one with a delayed backward pass and an
     update. The oracle affords this size in fp32 arithmetic (five orders of magnitude finer
     than the storage type, three times faster than fp64).

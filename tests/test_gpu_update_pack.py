@@ -9,7 +9,7 @@ import workloads as wk
 pytestmark = pytest.mark.gpu
 
 # blocks, input channels, size, what is there: a 3-channel stem (padded contraction), LDS-tiled layers (mirrored taps), a stage
-# change (taps as stored, projection); a wide block above the line of 2^20 parameters (separate launches), one below
+# change (taps as stored, projection); a wide block above the line of 2^20 parameters (the launch that goes tile by tile), one below
 CASES = {"cifar": ([(wk.BLOCK_STEM, 3, 0, 16, 1, 0), (wk.BLOCK_BASIC, 16, 0, 16, 1, 0), (wk.BLOCK_BASIC, 16, 0, 32, 2, 1)], 3, 32),
          "wide_1114k": ([(wk.BLOCK_BOTTLENECK, 1024, 256, 1024, 1, 0)], 1024, 4),
          "wide_280k": ([(wk.BLOCK_BOTTLENECK, 512, 128, 512, 1, 0)], 512, 4)}
