@@ -20,16 +20,16 @@
 //           ResNet-8 in one module needs 173 KB. There too nothing got slower: ResNet-110 in one module, batch 37,
 //           1.29x against the per-layer kernels, batch 1 1.41x).
 //
-// Buffers: three LDS regions of NHWC pixels with a zero border (row and column -1 and H / W); a
-// pixel is padded by 16 bytes, so that the 16 pixels of a fragment read start in 16 different bank
-// groups. An identity block reads x, writes o = relu(bn1(conv1 x)), then adds relu(bn2(conv2 o) + x)
+// Buffers: three LDS regions of NHWC pixels with a zero border (row and column -1 and H / W); pixels are an
+// odd multiple of 32 bytes apart and rows continue that where a block of 16 pixels spans two, so that
+// fragment reads have no bank conflicts (4 cycles each; 8-12 with pixels an odd multiple of 16 bytes apart). An identity block reads x, writes o = relu(bn1(conv1 x)), then adds relu(bn2(conv2 o) + x)
 // back into x in place (an output pixel needs x at that pixel only). A block between stages writes
 // its output to the third region, and the regions change roles.
 //
 // Eight waves; a wave holds the weight fragments of one layer in registers (two sets: the next
 // layer's are requested before the current one is contracted) and walks over 16-pixel blocks:
-//   16 channels: every wave all channels, 8 pixel groups;  32 channels: bf16 the same with two
-//   channel blocks per wave (halves the LDS reads per matrix instruction), fp32 one block each;
+//   16 channels: every wave all channels, 8 pixel groups;  32 channels: one channel block and 4 pixel groups (both
+//   blocks in every wave would bring a layer's weights into the compute unit eight times, 147 KB at 64 bytes a cycle);
 //   64 channels: 4 channel blocks x 2 halves of the contraction (a layer's weights, 73 KB in bf16,
 //   then enter the compute unit once; the halves meet in LDS).
 // Rounding points are those of the per-layer kernels: the conv output and the activations are
@@ -62,7 +62,10 @@ __device__ __forceinline__ unsigned char* lds() {
   return smem;
 }
 
-template <typename T> constexpr int pix_bytes(int ch) { return ch == Mma<T>::KV ? 16 : ch * (int)sizeof(T) + 16; }
+// bytes of a pixel of ch channels (of esz bytes), and of a buffer row of W pixels and their border
+__host__ __device__ constexpr int pix_bytes_of(int ch, int esz) { return ch * esz <= 32 ? (ch * esz <= 16 ? 16 : 32) : ch * esz + 32; }
+template <typename T> __host__ __device__ constexpr int pix_bytes(int ch) { return pix_bytes_of(ch, (int)sizeof(T)); }
+__host__ __device__ constexpr int row_bytes(int W, int pix) { return W % 16 == 0 ? (W + 2) * pix : W * pix + (2 * pix + 255) / 256 * 256; }
 
 struct Args {
   const EvalBlockDesc* blocks; int nb;   // the blocks this launch runs
@@ -81,10 +84,10 @@ struct Conv {
   static constexpr int KV = Mma<T>::KV, KSTEP = Mma<T>::KSTEP, PIX = pix_bytes<T>(CIN);
   static constexpr int KSTEPS = (R * R * CIN + KSTEP - 1) / KSTEP, KPW = KSTEPS / KS;
   // Lanes of the last k-step past the last tap (16 channels in bf16, the stem) multiply zero weights; what they
-  // read has to be zero as well, or an infinite activation becomes NaN in every channel: the padding
-  // behind tap 0's pixel, or, where a pixel is one chunk without padding (PIX 16), whatever is there, zeroed.
-  static constexpr bool RAGGED = R * R * CIN % KSTEP != 0, PADDED = PIX > CIN * (int)sizeof(T);
-  static_assert(PADDED || KS == 1, "the last k-step is the last of every wave");
+  // read has to be zero as well, or an infinite activation becomes NaN in every channel: the buffer's first
+  // pixel, which is border.
+  static constexpr bool RAGGED = R * R * CIN % KSTEP != 0;
+  static_assert(!RAGGED || KS == 1, "the last k-step is the last of every wave");
   static constexpr int NCB_ = NCB, KS_ = KS, U_ = U, OCB = COUT / 16, CBG = OCB / NCB, PG = 8 / (CBG * KS), PAD = R / 2;
   static_assert(KSTEPS % KS == 0 && OCB % NCB == 0 && 8 % (CBG * KS) == 0 && (KS == 1 || (PG == 1 && NCB == 1 && U % 2 == 0)), "wave layout");
 
@@ -110,14 +113,14 @@ struct Conv {
       r.sh[b] = *reinterpret_cast<const float4*>(sc + COUT + c);
     }
   }
-  // per-lane LDS offset of k-step ks relative to the top left tap of an output pixel (WC: columns
-  // of the source buffer); lanes past the last tap read the padding of tap 0's pixel
-  __device__ static __forceinline__ void addresses(int (&ka)[KPW], int wave, int lane, int WC) {
+  // per-lane LDS offset of k-step ks relative to the top left tap of an output pixel (RB: bytes of a
+  // row of the source buffer)
+  __device__ static __forceinline__ void addresses(int (&ka)[KPW], int wave, int lane, int RB) {
 #pragma unroll
     for (int ks = 0; ks < KPW; ++ks) {
       const int k = ((kh(wave) * KPW + ks) * 4 + (lane >> 4)) * KV;
       const int tap = k / CIN, c0 = k % CIN;
-      ka[ks] = tap < R * R ? ((tap / R) * WC + tap % R) * PIX + c0 * (int)sizeof(T) : PADDED ? CIN * (int)sizeof(T) : 0;
+      ka[ks] = tap < R * R ? (tap / R) * RB + (tap % R) * PIX + c0 * (int)sizeof(T) : 0;
     }
   }
   template <int V>
@@ -127,8 +130,8 @@ struct Conv {
       frag_t x[V];
 #pragma unroll
       for (int u = 0; u < V; ++u) {
-        x[u] = *reinterpret_cast<const frag_t*>(lds() + src + pa[u] + ka[ks]);
-        if (RAGGED && !PADDED && ks == KPW - 1 && (ks * 4 + (int)(threadIdx.x & 63) / 16) * KV >= R * R * CIN) x[u] = Mma<T>::zero();
+        const bool past = RAGGED && ks == KPW - 1 && (ks * 4 + (int)(threadIdx.x & 63) / 16) * KV >= R * R * CIN;
+        x[u] = *reinterpret_cast<const frag_t*>(lds() + src + (past ? 0 : pa[u] + ka[ks]));
       }
 #pragma unroll
       for (int b = 0; b < NCB; ++b)
@@ -149,10 +152,10 @@ struct Conv {
 #pragma unroll
     for (int i = 0; i < U / 2; ++i) acc[i] = (h == 0 ? acc[i] : acc[U / 2 + i]) + ex[((cb * 2 + (1 - h)) * E + i) * 64 + lane];
   }
-  // Output rows [lo, hi) of W columns from the source buffer (its first row is image row srow0, WC
-  // columns). f(acc, channel block index, row, col, valid) once per 16-pixel block and channel block.
+  // Output rows [lo, hi) of W columns from the source buffer (its first row is image row srow0, RB
+  // bytes a row). f(acc, channel block index, row, col, valid) once per 16-pixel block and channel block.
   template <typename F>
-  __device__ static __forceinline__ void pass(int src, int srow0, int WC, int lo, int hi, int W,
+  __device__ static __forceinline__ void pass(int src, int srow0, int RB, int lo, int hi, int W,
                                               const int (&ka)[KPW], const Wts& wt, int red, int& flip,
                                               int wave, int lane, F f) {
     const int npx = (hi - lo) * W, npb = (npx + 15) >> 4;
@@ -167,7 +170,7 @@ struct Conv {
         const int pc = ok[u] ? p : npx - 1;
         const int q = (int)(((float)pc + 0.5f) * invW);     // exact: pc < 2^16
         row[u] = lo + q; col[u] = pc - q * W;
-        pa[u] = ((row[u] * S - PAD - srow0) * WC + col[u] * S - PAD + 1) * PIX;
+        pa[u] = (row[u] * S - PAD - srow0) * RB + (col[u] * S - PAD + 1) * PIX;
       }
       f32x4_t acc[NCB][U];
 #pragma unroll
@@ -197,7 +200,7 @@ struct Conv {
 
 template <typename T, int C> struct Same;       // 3x3, stride 1, C -> C
 template <> struct Same<bf16_t, 16> { typedef Conv<bf16_t, 16, 16, 3, 1, 1, 1, 4> type; };
-template <> struct Same<bf16_t, 32> { typedef Conv<bf16_t, 32, 32, 3, 1, 2, 1, 2> type; };
+template <> struct Same<bf16_t, 32> { typedef Conv<bf16_t, 32, 32, 3, 1, 1, 1, 4> type; };
 template <> struct Same<bf16_t, 64> { typedef Conv<bf16_t, 64, 64, 3, 1, 1, 2, 4> type; };
 template <> struct Same<float, 16> { typedef Conv<float, 16, 16, 3, 1, 1, 1, 1> type; };
 template <> struct Same<float, 32> { typedef Conv<float, 32, 32, 3, 1, 1, 1, 1> type; };
@@ -245,10 +248,10 @@ __device__ __forceinline__ void identity_images(const EvalConvDesc* cv, int tab,
   typedef typename Same<T, C>::type K;
   constexpr int PIX = K::PIX, U = K::U_, NCB = K::NCB_, F = K::KS_ == 1 ? U : U / 2;   // F: pixel blocks a wave finishes per group
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int W = B.W, WC = W + 2, npx = B.H * W;
+  const int W = B.W, RB = row_bytes(W, PIX), npx = B.H * W;
   int ka[K::KPW];
-  K::addresses(ka, wave, lane, WC);
-  const int centre = (WC + 1) * PIX + (K::cbg(wave) * NCB * 16 + (lane >> 4) * 4) * (int)sizeof(T);
+  K::addresses(ka, wave, lane, RB);
+  const int centre = RB + PIX + (K::cbg(wave) * NCB * 16 + (lane >> 4) * 4) * (int)sizeof(T);
   int pa[G][U], da[G][F];
   const float invW = 1.0f / (float)W;
 #pragma unroll
@@ -258,7 +261,7 @@ __device__ __forceinline__ void identity_images(const EvalConvDesc* cv, int tab,
     for (int u = 0; u < U; ++u) {
       const int p = ((g * U + u) * K::PG + K::pg(wave)) * 16 + (lane & 15), pc = p < npx ? p : npx - 1;
       const int q = (int)(((float)pc + 0.5f) * invW);
-      pa[g][u] = (q * WC + pc - q * W) * PIX;
+      pa[g][u] = q * RB + (pc - q * W) * PIX;
       ok[u] = p < npx ? pa[g][u] + centre : -1;
     }
 #pragma unroll
@@ -318,29 +321,29 @@ __device__ __forceinline__ void identity_run(const EvalConvDesc* cv, int tab, in
   typedef typename Same<T, C>::type K;
   constexpr int PIX = K::PIX;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int W = B.W, WC = W + 2;
+  const int W = B.W, RB = row_bytes(W, PIX);
   const int olo = lo > 0 ? lo - 1 : 0, ohi = hi < B.H ? hi + 1 : B.H;
   const int orow0 = lo - 1;
   const int cq = K::cbg(wave) * K::NCB_ * 16 + (lane >> 4) * 4;
   int ka[K::KPW];
-  K::addresses(ka, wave, lane, WC);
+  K::addresses(ka, wave, lane, RB);
   typename K::Wts w1, w2;
   K::load(cv[0], tab, w1, wave, lane);
   for (int i = 0; i < count; ++i) {
     K::load(cv[2 * i + 1], tab, w2, wave, lane);
-    K::pass(B.x, B.row0, WC, olo, ohi, W, ka, w1, red, flip, wave, lane,
+    K::pass(B.x, B.row0, RB, olo, ohi, W, ka, w1, red, flip, wave, lane,
             [&](const f32x4_t& acc, int b, int row, int col, bool ok) __attribute__((always_inline)) {
               float v[4];
               affine<T>(acc, w1.sc[b], w1.sh[b], v);
-              if (ok) store_relu<T>(B.o + ((row - orow0) * WC + col + 1) * PIX + (cq + b * 16) * (int)sizeof(T), v);
+              if (ok) store_relu<T>(B.o + (row - orow0) * RB + (col + 1) * PIX + (cq + b * 16) * (int)sizeof(T), v);
             });
     __syncthreads();
     if (i + 1 < count) K::load(cv[2 * i + 2], tab, w1, wave, lane);
-    K::pass(B.o, orow0, WC, lo, hi, W, ka, w2, red, flip, wave, lane,
+    K::pass(B.o, orow0, RB, lo, hi, W, ka, w2, red, flip, wave, lane,
             [&](const f32x4_t& acc, int b, int row, int col, bool ok) __attribute__((always_inline)) {
               float v[4], r[4];
               affine<T>(acc, w2.sc[b], w2.sh[b], v);
-              const int p = B.x + ((row - B.row0) * WC + col + 1) * PIX + (cq + b * 16) * (int)sizeof(T);
+              const int p = B.x + (row - B.row0) * RB + (col + 1) * PIX + (cq + b * 16) * (int)sizeof(T);
               Store<T>::load4(reinterpret_cast<const T*>(lds() + p), r);
 #pragma unroll
               for (int e = 0; e < 4; ++e) v[e] += r[e];
@@ -357,31 +360,31 @@ __device__ __forceinline__ void down_block(const EvalConvDesc* cv, int tab, Bufs
   typedef typename Same<T, 2 * C>::type K2;
   typedef Conv<T, C, 2 * C, 1, 2, K2::NCB_, 1, 1> KP;    // (only its weight layout: same channel blocks as K2)
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int WC = B.W + 2, WCo = Wo + 2;
+  const int RB = row_bytes(B.W, K1::PIX), RBo = row_bytes(Wo, K2::PIX);
   const int olo = lo > 0 ? lo - 1 : 0, ohi = hi < Ho ? hi + 1 : Ho;
   const int orow0 = lo - 1;
-  zero<T>(B.o, (hi - lo + 2) * WCo * K2::PIX);
-  zero<T>(B.y, (hi - lo + 2) * WCo * K2::PIX);
+  zero<T>(B.o, (hi - lo + 2) * RBo);
+  zero<T>(B.y, (hi - lo + 2) * RBo);
   typename K1::Wts w1;
   typename K2::Wts w2;
   K1::load(cv[0], tab, w1, wave, lane);
   __syncthreads();
   {
     int ka[K1::KPW];
-    K1::addresses(ka, wave, lane, WC);
+    K1::addresses(ka, wave, lane, RB);
     const int cq = K1::cbg(wave) * K1::NCB_ * 16 + (lane >> 4) * 4;
     K2::load(cv[1], tab, w2, wave, lane);
-    K1::pass(B.x, B.row0, WC, olo, ohi, Wo, ka, w1, red, flip, wave, lane,
+    K1::pass(B.x, B.row0, RB, olo, ohi, Wo, ka, w1, red, flip, wave, lane,
              [&](const f32x4_t& acc, int b, int row, int col, bool ok) __attribute__((always_inline)) {
                float v[4];
                affine<T>(acc, w1.sc[b], w1.sh[b], v);
-               if (ok) store_relu<T>(B.o + ((row - orow0) * WCo + col + 1) * K2::PIX + (cq + b * 16) * (int)sizeof(T), v);
+               if (ok) store_relu<T>(B.o + (row - orow0) * RBo + (col + 1) * K2::PIX + (cq + b * 16) * (int)sizeof(T), v);
              });
   }
   __syncthreads();
   {
     int ka[K2::KPW], kp[KP::KPW];
-    K2::addresses(ka, wave, lane, WCo);
+    K2::addresses(ka, wave, lane, RBo);
     const int cg = K2::cbg(wave), cq = cg * K2::NCB_ * 16 + (lane >> 4) * 4;
     // the projection: every wave the channel blocks it finishes, the whole contraction
     typename KP::frag_t wp[K2::NCB_][KP::KPW];
@@ -398,21 +401,21 @@ __device__ __forceinline__ void down_block(const EvalConvDesc* cv, int tab, Bufs
 #pragma unroll
     for (int ks = 0; ks < KP::KPW; ++ks) {
       const int k = (ks * 4 + (lane >> 4)) * KP::KV;
-      kp[ks] = (k < C ? k : C) * (int)sizeof(T);         // (past the last channel: the pixel's padding, zero)
+      kp[ks] = k < C ? k * (int)sizeof(T) : -1;          // (past the last channel: the buffer's first pixel, border)
     }
-    K2::pass(B.o, orow0, WCo, lo, hi, Wo, ka, w2, red, flip, wave, lane,
+    K2::pass(B.o, orow0, RBo, lo, hi, Wo, ka, w2, red, flip, wave, lane,
              [&](const f32x4_t& acc, int b, int row, int col, bool ok) __attribute__((always_inline)) {
-               const int xp = B.x + ((row * 2 - B.row0) * WC + col * 2 + 1) * K1::PIX;
+               const int xp = (row * 2 - B.row0) * RB + (col * 2 + 1) * K1::PIX;
                f32x4_t pa = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                for (int ks = 0; ks < KP::KPW; ++ks)
-                 pa = Mma<T>::mma(wp[b][ks], *reinterpret_cast<const typename KP::frag_t*>(lds() + xp + kp[ks]), pa);
+                 pa = Mma<T>::mma(wp[b][ks], *reinterpret_cast<const typename KP::frag_t*>(lds() + B.x + (kp[ks] < 0 ? 0 : xp + kp[ks])), pa);
                float v[4], r[4];
                affine<T>(acc, w2.sc[b], w2.sh[b], v);
                affine<T>(pa, psc[b], psh[b], r);
 #pragma unroll
                for (int e = 0; e < 4; ++e) v[e] += r[e];
-               if (ok) store_relu<T>(B.y + ((row - orow0) * WCo + col + 1) * K2::PIX + (cq + b * 16) * (int)sizeof(T), v);
+               if (ok) store_relu<T>(B.y + (row - orow0) * RBo + (col + 1) * K2::PIX + (cq + b * 16) * (int)sizeof(T), v);
              });
   }
   __syncthreads();
@@ -424,7 +427,7 @@ __device__ __forceinline__ void down_block(const EvalConvDesc* cv, int tab, Bufs
 template <typename T>
 __device__ __forceinline__ void load_rows(int buf, const T* img, int row0, int rows, int H, int W, int C, int pix) {
   constexpr int V = Store<T>::VEC;
-  const int cpp = pix / 16, per_row = (W + 2) * cpp, total = rows * per_row;   // 16-byte chunks, the pixel's padding included
+  const int cpp = pix / 16, per_row = row_bytes(W, pix) / 16, total = rows * per_row;   // 16-byte chunks, padding included
   const int ch = C / V;
   for (int i = threadIdx.x; i < total; i += NT) {
     const int r = i / per_row, e = i - r * per_row, px = e / cpp, k = e - px * cpp;
@@ -439,9 +442,9 @@ __device__ __forceinline__ void load_rows(int buf, const T* img, int row0, int r
 template <typename T>
 __device__ __forceinline__ void load_rows_stem(int buf, const T* img, int row0, int rows, int H, int W, int C) {
   constexpr int V = Store<T>::VEC;
-  const int total = rows * (W + 2);
+  const int per_row = row_bytes(W, 16) / 16, total = rows * per_row;
   for (int i = threadIdx.x; i < total; i += NT) {
-    const int r = i / (W + 2), w = i - r * (W + 2) - 1, h = row0 + r;
+    const int r = i / per_row, w = i - r * per_row - 1, h = row0 + r;
     float f[V];
 #pragma unroll
     for (int e = 0; e < V; ++e) f[e] = 0.f;
@@ -477,7 +480,7 @@ __global__ __launch_bounds__(NT) void eval_blocks_kernel(Args a) {
       load_rows_stem<T>(B.o, img, B.row0, rows, a.H, a.W, a.C);
     } else {
       load_rows<T>(B.x, img, B.row0, rows, a.H, a.W, a.C, pix_bytes<T>(a.C));
-      if (b0.kind == EVAL_IDENTITY) zero<T>(B.o, (hi - lo + 2) * (a.W + 2) * pix_bytes<T>(a.C));
+      if (b0.kind == EVAL_IDENTITY) zero<T>(B.o, (hi - lo + 2) * row_bytes(a.W, pix_bytes<T>(a.C)));
     }
   }
   // scale and shift of every batch norm of the launch, a wave per layer and four layers at a time
@@ -514,30 +517,31 @@ __global__ __launch_bounds__(NT) void eval_blocks_kernel(Args a) {
     const int Wo = (a.W - 1) / b0.stride + 1, srow0 = B.row0;
     constexpr int PIX = pix_bytes<T>(16);
     B.row0 = lo - 1;
-    zero<T>(B.x, (hi - lo + 2) * (Wo + 2) * PIX);
+    const int RBo = row_bytes(Wo, PIX), RBi = row_bytes(a.W, K1::PIX);
+    zero<T>(B.x, (hi - lo + 2) * RBo);
     typename K1::Wts w;
     __syncthreads();
     K1::load(a.convs[0], tab, w, wave, lane);
     int ka[K1::KPW];
-    K1::addresses(ka, wave, lane, a.W + 2);
+    K1::addresses(ka, wave, lane, RBi);
     __syncthreads();
     auto put = [&](const f32x4_t& acc, int b, int row, int col, bool ok) __attribute__((always_inline)) {
       float v[4];
       affine<T>(acc, w.sc[b], w.sh[b], v);
-      if (ok) store_relu<T>(B.x + ((row - B.row0) * (Wo + 2) + col + 1) * PIX + (lane >> 4) * 4 * (int)sizeof(T), v);
+      if (ok) store_relu<T>(B.x + (row - B.row0) * RBo + (col + 1) * PIX + (lane >> 4) * 4 * (int)sizeof(T), v);
     };
     if (b0.stride == 1) {
-      K1::pass(B.o, srow0, a.W + 2, lo, hi, Wo, ka, w, red, flip, wave, lane, put);
+      K1::pass(B.o, srow0, RBi, lo, hi, Wo, ka, w, red, flip, wave, lane, put);
     } else {
       typename K2::Wts v2;
 #pragma unroll
       for (int k = 0; k < K2::KPW; ++k) v2.w[0][k] = w.w[0][k];
-      K2::pass(B.o, srow0, a.W + 2, lo, hi, Wo, ka, v2, red, flip, wave, lane, put);
+      K2::pass(B.o, srow0, RBi, lo, hi, Wo, ka, v2, red, flip, wave, lane, put);
     }
     B.H = Ho0; B.W = Wo; C = 16;
     __syncthreads();
     bi = 1;
-    if (bi < a.nb) zero<T>(B.o, (B.H + 2) * (B.W + 2) * PIX);   // (the input image was there)
+    if (bi < a.nb) zero<T>(B.o, (B.H + 2) * row_bytes(B.W, PIX));   // (the input image was there)
   }
   __syncthreads();
   while (bi < a.nb) {
@@ -571,12 +575,12 @@ __global__ __launch_bounds__(NT) void eval_blocks_kernel(Args a) {
   }
   // the output rows of this workgroup
   constexpr int V = Store<T>::VEC;
-  const int ch = C / V, pix = pix_bytes<T>(C), per_row = B.W * ch, total = (hi - lo) * per_row;
+  const int ch = C / V, pix = pix_bytes<T>(C), RB = row_bytes(B.W, pix), per_row = B.W * ch, total = (hi - lo) * per_row;
   T* out = reinterpret_cast<T*>(a.out) + ((size_t)n * B.H + lo) * B.W * C;
   for (int i = tid; i < total; i += NT) {
     const int r = i / per_row, e = i - r * per_row, px = e / ch, k = e - px * ch;
     *reinterpret_cast<uint4*>(out + (size_t)i * V) =
-        *reinterpret_cast<const uint4*>(lds() + B.x + ((lo + r - B.row0) * (B.W + 2) + px + 1) * pix + k * 16);
+        *reinterpret_cast<const uint4*>(lds() + B.x + (lo + r - B.row0) * RB + (px + 1) * pix + k * 16);
   }
 }
 
@@ -585,7 +589,7 @@ __global__ __launch_bounds__(NT) void eval_blocks_kernel(Args a) {
 // LDS of a launch over `kinds`/`chans` (nb blocks) on H x W images with TH output rows per workgroup.
 static void eval_lds(const EvalBlockShape* b, int nb, int H, int W, int TH, int strips, int dtype, EvalLaunch* l) {
   const size_t esz = dtype_size(dtype);
-  auto pix = [&](int c) -> size_t { return c * esz + 16; };
+  auto row = [&](int w, int c) -> size_t { return ev::row_bytes(w, ev::pix_bytes_of(c, (int)esz)); };   // bytes of a row of w pixels
   size_t need[3] = {0, 0, 0};     // regions A, B, C
   int xi = 0, yi = 2;             // which region holds x, which is free
   auto want = [&](int region, size_t bytes) { if (bytes > need[region]) need[region] = bytes; };
@@ -595,19 +599,19 @@ static void eval_lds(const EvalBlockShape* b, int nb, int H, int W, int TH, int 
   int h = H, w = W;
   for (int i = 0; i < nb; ++i) {
     if (b[i].kind == EVAL_STEM) {
-      want(1, rows((TH - 1) * b[i].stride + 3, h) * (w + 2) * 16);
+      want(1, rows((TH - 1) * b[i].stride + 3, h) * ev::row_bytes(w, 16));
       h = (h - 1) / b[i].stride + 1; w = (w - 1) / b[i].stride + 1;
-      want(0, rows(TH + 2, h) * (w + 2) * pix(16));
-      if (nb > 1) want(1, (size_t)(h + 2) * (w + 2) * pix(16));
+      want(0, rows(TH + 2, h) * row(w, 16));
+      if (nb > 1) want(1, (size_t)(h + 2) * row(w, 16));
     } else if (b[i].kind == EVAL_IDENTITY) {
-      want(xi, rows(TH + 4, h) * (w + 2) * pix(b[i].c));
-      want(1, rows(TH + 2, h) * (w + 2) * pix(b[i].c));
+      want(xi, rows(TH + 4, h) * row(w, b[i].c));
+      want(1, rows(TH + 2, h) * row(w, b[i].c));
       if (b[i].c == 64) exch = true;
     } else {
-      want(xi, rows((TH + 1) * 2 + 3, h) * (w + 2) * pix(b[i].c));
+      want(xi, rows((TH + 1) * 2 + 3, h) * row(w, b[i].c));
       h = (h - 1) / 2 + 1; w = (w - 1) / 2 + 1;
-      want(1, rows(TH + 2, h) * (w + 2) * pix(2 * b[i].c));
-      want(yi, rows(TH + 2, h) * (w + 2) * pix(2 * b[i].c));
+      want(1, rows(TH + 2, h) * row(w, 2 * b[i].c));
+      want(yi, rows(TH + 2, h) * row(w, 2 * b[i].c));
       int t = xi; xi = yi; yi = t;
       if (2 * b[i].c == 64) exch = true;
     }
