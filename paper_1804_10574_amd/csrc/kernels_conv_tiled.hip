@@ -1,8 +1,8 @@
 // 3x3, stride-1, pad-1 convolution (forward and input-gradient) for the CIFAR layer shapes:
 // C = Cin = Cout in {16, 32, 64} on feature maps W = 32, 16, 8 wide, bf16 operands.
 //
-// A workgroup stages the (8+2) x (W+2) halo tile of the input once in LDS (NHWC, each pixel
-// padded by 16 bytes so that 16 pixels read 16 distinct LDS bank groups); the nine taps are
+// A workgroup stages the (8+2) x (W+2) halo tile of the input once in LDS (NHWC, pixels and rows
+// padded so that the fragment reads have no bank conflicts); the nine taps are
 // then shifted LDS addresses: the im2col matrix never exists. While staging, the input can be
 // turned into the activation it stands for, a = relu(x*scale + shift) (batch-norm + ReLU of
 // the previous layer), so that activation is never written to memory. Zero padding is
@@ -54,8 +54,12 @@ struct ConvTiledArgs {
 template <int C, int W>
 struct ConvTiledCfg {
   static constexpr int TH = 8, ROWS = TH + 2, WC = W + 2;
-  static constexpr int PIX = C * 2 + 16;                 // bytes per staged pixel
-  static constexpr int TILE_BYTES = ROWS * WC * PIX;
+  // Bytes per staged pixel and per tile row. A 16-byte fragment read takes 4 cycles if the 16 lanes it serves together
+  // (0-3, 12-15, 20-27, and so on) touch 16 different 16-byte groups of 256 bytes, else 8 or 12. Pixels an odd multiple of 32
+  // bytes apart do that; where a block of 16 pixels spans two rows (8 wide), the rows have to be a multiple of 256 apart too.
+  static constexpr int PIX = C == 16 ? 32 : C * 2 + 32;
+  static constexpr int ROWB = W == 8 ? (WC * PIX + 255) / 256 * 256 : WC * PIX;
+  static constexpr int TILE_BYTES = ROWS * ROWB;
   static constexpr int CH = C / 8;                       // 16-byte chunks per pixel
   static constexpr int NCHUNK = ROWS * WC * CH;          // chunks per tile (halo columns included)
   static constexpr int PER_THREAD = (NCHUNK + 255) / 256;
@@ -92,7 +96,7 @@ template <int C, int W, int MODE, int XF>
 __device__ __forceinline__ void conv3x3_tiled_body(const ConvTiledArgs& a, unsigned char* tile, int bidx, int gdim) {
   using Cfg = ConvTiledCfg<C, W>;
   constexpr bool RES = XF == XF_RES, APPLY = XF == XF_APPLY || XF == XF_APPLY_MASK;
-  constexpr int TH = Cfg::TH, WC = Cfg::WC, PIX = Cfg::PIX, CH = Cfg::CH, NCHUNK = Cfg::NCHUNK;
+  constexpr int TH = Cfg::TH, WC = Cfg::WC, PIX = Cfg::PIX, ROWB = Cfg::ROWB, CH = Cfg::CH, NCHUNK = Cfg::NCHUNK;
   constexpr int PT = Cfg::PER_THREAD, KSTEPS = Cfg::KSTEPS, PG = Cfg::PG, COB = Cfg::COB;
   constexpr bool RAGGED_K = (9 * C) % 32 != 0;   // the last k-step runs past tap 8 for some lanes
 
@@ -118,7 +122,7 @@ __device__ __forceinline__ void conv3x3_tiled_body(const ConvTiledArgs& a, unsig
     const bool col_ok = v < NCHUNK && cc >= 1 && cc <= W;
     srows |= (col_ok ? (unsigned)(rr + 1) : 0u) << (4 * i);
     goff[i] = ((rr - 1) * W + (cc - 1)) * C + my_ch * 8;
-    loff[i] = v < NCHUNK ? px * PIX + my_ch * 16 : -1;
+    loff[i] = v < NCHUNK ? rr * ROWB + cc * PIX + my_ch * 16 : -1;
   }
   uint4 stage[PT], stage2[(RES || APPLY) ? PT : 1], stage3[XF == XF_APPLY_MASK ? PT : 1];
   unsigned inimg = 0;   // bit i: chunk i of the tile in flight lies inside the image
@@ -154,7 +158,7 @@ __device__ __forceinline__ void conv3x3_tiled_body(const ConvTiledArgs& a, unsig
   // ---- LDS fragment addresses: lane part + k-step part in a register, pixel block as immediate
   // pixel of block i, lane l16: pt = (pgrp*4 + i)*16 + l16; its row/column split is additive in i
   const int ptl = pgrp * 64 + l16;
-  const int lane_base = ((ptl / W) * WC + (ptl % W)) * PIX;
+  const int lane_base = (ptl / W) * ROWB + (ptl % W) * PIX;
   int kaddr[KSTEPS];
   bool klast_ok = true;
 #pragma unroll
@@ -164,7 +168,7 @@ __device__ __forceinline__ void conv3x3_tiled_body(const ConvTiledArgs& a, unsig
     const bool ok = tap < 9;
     if (ks == KSTEPS - 1) klast_ok = ok;
     const int tp = ok ? tap : 0;
-    kaddr[ks] = lane_base + ((tp / 3) * WC + (tp % 3)) * PIX + c0 * 2;
+    kaddr[ks] = lane_base + (tp / 3) * ROWB + (tp % 3) * PIX + c0 * 2;
   }
 
   // ---- per-channel transform of the input (while the first tile's loads are in flight); the
@@ -305,7 +309,7 @@ __device__ __forceinline__ void conv3x3_tiled_body(const ConvTiledArgs& a, unsig
       const unsigned char* kp = tile + kaddr[ks];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int blk = (((i * 16) / W) * WC + (i * 16) % W) * PIX;   // constant after unrolling
+        const int blk = ((i * 16) / W) * ROWB + ((i * 16) % W) * PIX;   // constant after unrolling
         uint4 af = *reinterpret_cast<const uint4*>(kp + blk);
         if (RAGGED_K && ks == KSTEPS - 1 && !klast_ok) af = make_uint4(0, 0, 0, 0);
         acc[i] = Mma<bf16_t>::mma(wf[ks], af, acc[i]);
