@@ -7,18 +7,18 @@
 // What bounds it: a layer of one image is 4.7 MFLOP on one compute unit, about 1 us of matrix and
 // LDS time in bf16, against 10-13 us for the per-layer launch of a whole minibatch of 256 and 6-7
 // us for the smallest one (the launch, its weights and its halo loads are then all there is).
-// Measured, whole call: ResNet-110, batch 256, bf16 1394 -> 272 us (2.4 us per layer); the 32-channel group of
-// ResNet-56, batch 100, bf16 134 -> 40 us; ResNet-20, one image, fp32 227 -> 116 us. The bf16 kernel holds
-// every stage's code at the registers of the largest: 256, and 7 more spilled.
+// Measured, whole call: ResNet-110, batch 256, bf16 1394 -> 214 us (1.4-1.7 us per layer); the 32-channel group of
+// ResNet-56, batch 100, bf16 134 -> 29 us; ResNet-20, one image, fp32 227 -> 116 us.
 //
 // Two ways of cutting the work, chosen by eval_plan() below:
 //   whole images: all blocks of a module in one launch, one image per workgroup (bf16);
 //   strips: one residual block per launch, TH output rows per workgroup, the rows of the halo
 //           recomputed (fp32, whose matrix rate makes an image 10-18 us per layer on one unit, so
 //           that one image has to be spread over several; and bf16 modules whose buffers, each at its
-//           largest over the blocks, exceed LDS: large images, and a network in one module from 32x32 on:
-//           ResNet-8 in one module needs 173 KB. There too nothing got slower: ResNet-110 in one module, batch 37,
-//           1.29x against the per-layer kernels, batch 1 1.41x).
+//           largest over the blocks, exceed LDS: large images, and deep networks in one module from 32x32 on (ResNet-110: its
+//           table of scales and shifts alone is 32 KB). There too nothing got slower: ResNet-110 in one module, batch 37,
+//           1.29x against the per-layer kernels, batch 1 1.41x. As whole images ResNet-20 in one module takes 57 us
+//           at batch 256 and 54 at batch 1, 130 and 85 in strips).
 //
 // Buffers: three LDS regions of NHWC pixels with a zero border (row and column -1 and H / W); pixels are an
 // odd multiple of 32 bytes apart and rows continue that where a block of 16 pixels spans two, so that
@@ -36,6 +36,7 @@
 // rounded to the storage type, sums are fp32.
 #include "ddg_device.h"
 #include "ddg_kernels.h"
+#include <type_traits>
 
 namespace ddg {
 
@@ -62,10 +63,11 @@ __device__ __forceinline__ unsigned char* lds() {
   return smem;
 }
 
-// bytes of a pixel of ch channels (of esz bytes), and of a buffer row of W pixels and their border
-__host__ __device__ constexpr int pix_bytes_of(int ch, int esz) { return ch * esz <= 32 ? (ch * esz <= 16 ? 16 : 32) : ch * esz + 32; }
+// bytes of a pixel of ch channels (of esz bytes), and of a buffer row of W pixels and their border (fp32, where the matrix
+// instructions hide the reads: an odd multiple of 16, whose conflicts cost less than those of the stores with 32, 1-3 %)
+__host__ __device__ constexpr int pix_bytes_of(int ch, int esz) { return ch * esz <= 16 ? 16 : esz == 4 ? ch * 4 + 16 : ch == 16 ? 32 : ch * 2 + 32; }
 template <typename T> __host__ __device__ constexpr int pix_bytes(int ch) { return pix_bytes_of(ch, (int)sizeof(T)); }
-__host__ __device__ constexpr int row_bytes(int W, int pix) { return W % 16 == 0 ? (W + 2) * pix : W * pix + (2 * pix + 255) / 256 * 256; }
+__host__ __device__ constexpr int row_bytes(int W, int pix) { return W % 16 == 0 || pix % 32 != 0 ? (W + 2) * pix : W * pix + (2 * pix + 255) / 256 * 256; }
 
 struct Args {
   const EvalBlockDesc* blocks; int nb;   // the blocks this launch runs
@@ -211,6 +213,14 @@ template <> struct Down<bf16_t, 32> { typedef Conv<bf16_t, 32, 64, 3, 2, 1, 1, 2
 template <> struct Down<float, 16> { typedef Conv<float, 16, 32, 3, 2, 1, 1, 1> type; };
 template <> struct Down<float, 32> { typedef Conv<float, 32, 64, 3, 2, 1, 1, 1> type; };
 
+// The thread's index, as a value the compiler does not know: the lane-dependent addresses of a stage are then computed where the
+// stage begins. Otherwise those of all stages are hoisted to the start of the kernel, and spilled.
+template <typename T> __device__ __forceinline__ int own_tid() {
+  int t = threadIdx.x;
+  if (sizeof(T) == 2) asm volatile("" : "+v"(t));
+  return t;
+}
+
 // what a workgroup holds between blocks
 struct Bufs {
   int x, o, y;     // LDS offsets
@@ -240,6 +250,142 @@ __device__ __forceinline__ void store_relu(int p, const float (&v)[4]) {
   Store<T>::store4(reinterpret_cast<T*>(lds() + p), fmaxf(v[0], 0.f), fmaxf(v[1], 0.f), fmaxf(v[2], 0.f), fmaxf(v[3], 0.f));
 }
 
+// Lane l of an accumulator pair (two pixel blocks, rounded to bf16) holds channels 4*(l/16) .. +3 of pixel l%16 of either
+// block. Swapping rows of 16 lanes gives every lane 8 channels of one pixel: channels 8*(l/32) .. +7, pixel l%16 of the
+// first block (l/16 even) or the second (odd), so that LDS sees 16-byte accesses instead of twice as many of 8.
+__device__ __forceinline__ uint4 pair_rows(const f32x4_t& a, const f32x4_t& b) {
+  const auto lo = __builtin_amdgcn_permlane16_swap(Store<bf16_t>::pack2(a[0], a[1]), Store<bf16_t>::pack2(b[0], b[1]), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(Store<bf16_t>::pack2(a[2], a[3]), Store<bf16_t>::pack2(b[2], b[3]), false, false);
+  return make_uint4(lo[0], hi[0], lo[1], hi[1]);
+}
+
+// Identity blocks on whole images of the usual size, 512 / C pixels wide and high (bf16). A wave owns NB pixel blocks
+// below each other (a block is 16 pixels: half a row, a row, or two rows of 8) and walks down the input rows: what it reads
+// of a row serves every output row that the row is a tap of, 27 / 18 / 27 fragment reads a layer instead of 40 / 36 / 36 with
+// a tap at a time, which is most of the LDS time that bounds a layer. All addresses are one per-lane register and an
+// instruction immediate. Fragments are requested D rows ahead, and finished pairs of blocks are normalised and stored
+// between the matrix instructions of the next row. Eight waves:
+//   16 channels: half a row x 8 rows. A k-step (32) is two taps: columns -1 and 0 of a row; column 1 of a row and the
+//                next; column 1 of the last row alone (the other lanes read border and multiply zero weights);
+//   32 channels: one channel block x 4 rows; a k-step is a tap;
+//   64 channels: one channel block x half of the input channels, all four blocks; the halves meet in LDS.
+template <int C>
+__device__ __forceinline__ void identity_square(const EvalConvDesc* cv, int tab, int count, Bufs& B, int red, int& flip) {
+  typedef bf16_t T;
+  typedef typename Same<T, C>::type K;
+  typedef Mma<T>::frag_t frag_t;
+  constexpr int PIX = K::PIX, W = 512 / C, RB = row_bytes(W, PIX), OCB = C / 16;
+  constexpr int BLK = C == 64 ? 2 : 1, NB = C == 16 ? 8 : 4, NT = NB * BLK + 3 - BLK;   // rows of a block, blocks of a wave, row positions it reads
+  constexpr int NW = C == 16 ? 5 : 9, D = 3, F = C == 64 ? 2 : NB;                     // weight fragments; blocks a wave finishes
+  const int tid = own_tid<T>(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, lg = lane >> 4;
+  const int cb = C == 16 ? 0 : C == 32 ? wave & 1 : wave & 3, half = C == 64 ? wave >> 2 : 0;      // channel block; half of the contraction
+  const int row0 = C == 64 ? 0 : (wave >> 1) * NB;
+  const int base = C == 16 ? row0 * RB + ((wave & 1) * 16 + l16) * PIX : C == 32 ? row0 * RB + l16 * PIX : (l16 >> 3) * RB + (l16 & 7) * PIX;
+  // fragment k of row position t at ka[k] + t * RB
+  int ka[3];
+  if (C == 16) {
+    ka[0] = base + (lg >> 1) * PIX + (lg & 1) * 16;
+    ka[1] = base + 2 * PIX + (lg >> 1) * RB + (lg & 1) * 16;
+    ka[2] = lg < 2 ? base + 2 * PIX + lg * 16 : 0;           // (column -1 of every row is border)
+  } else {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) ka[k] = base + k * PIX + half * 64 + lg * 16;
+  }
+  const int c0 = cb * 16 + (lane >> 5) * 8;                  // this lane's 8 channels, and where it finishes a pair of blocks
+  const int da = base + RB + PIX + c0 * (int)sizeof(T) + (lg & 1) * BLK * RB + (C == 64 ? half * 2 * BLK * RB : 0);
+  // Weights are requested a layer ahead, their address (from the table in memory) two.
+  struct Wts { frag_t w[NW]; } w1, w2;
+  int wo[NW];                                                // element offsets in the packed operand [k-step][channel block][lane][8]
+#pragma unroll
+  for (int k = 0; k < NW; ++k) {
+    const int tap = k < 3 ? k * 3 + (lg >> 1) : k == 3 ? (lg >> 1) * 3 + 2 : 8 + (lg >> 1);        // (16 channels; tap 9: zeros)
+    wo[k] = C == 16 ? ((tap >> 1) * 64 + ((tap & 1) * 2 + (lg & 1)) * 16 + l16) * 8 : (((C == 64 ? k * 2 + half : k) * OCB + cb) * 64 + lane) * 8;
+  }
+  uint64_t wp = reinterpret_cast<uint64_t>(cv[0].w);
+  auto load = [&](Wts& r, int next) __attribute__((always_inline)) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)wp), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(wp >> 32));
+    const uint64_t u = (uint64_t)hi << 32 | lo;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) r.w[k] = load16<frag_t>(reinterpret_cast<const T*>(u) + wo[k]);
+    if (next < 2 * count) wp = reinterpret_cast<uint64_t>(cv[next].w);
+  };
+  int st = tab + (cv[0].toff + c0) * 4;                      // scale and shift of the layer's channels, 2 * C floats a layer
+  load(w1, 1);
+  // one layer: dst = relu(bn(conv(src)) [+ dst])
+  auto layer = [&](int src, const Wts& wt, int dst, auto add) __attribute__((always_inline)) {
+    constexpr bool ADD = decltype(add)::value;
+    f32x4_t acc[NB];
+    frag_t x[D][3];
+    uint4 r[F / 2];
+    auto request = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        if (C != 16 || k == 0 || (k == 1 && t < NB) || (k == 2 && t >= 2)) x[t % D][k] = *reinterpret_cast<const frag_t*>(lds() + src + ka[k] + t * RB);
+    };
+#pragma unroll
+    for (int t = 0; t < D; ++t) request(t);
+    float sc[8], sh[8];
+    Store<float>::load4(reinterpret_cast<const float*>(lds() + st), *reinterpret_cast<float(*)[4]>(&sc[0]));
+    Store<float>::load4(reinterpret_cast<const float*>(lds() + st + 16), *reinterpret_cast<float(*)[4]>(&sc[4]));
+    Store<float>::load4(reinterpret_cast<const float*>(lds() + st + 4 * C), *reinterpret_cast<float(*)[4]>(&sh[0]));
+    Store<float>::load4(reinterpret_cast<const float*>(lds() + st + 4 * C + 16), *reinterpret_cast<float(*)[4]>(&sh[4]));
+    st += 8 * C;
+#pragma unroll
+    for (int i = 0; i < F / 2; ++i)
+      if (ADD) r[i] = *reinterpret_cast<const uint4*>(lds() + dst + da + i * 2 * BLK * RB);
+    auto finish = [&](int i) __attribute__((always_inline)) {   // blocks 2 * i and 2 * i + 1
+      float v[8], q[8];
+      Store<T>::unpack_vec(pair_rows(acc[2 * i], acc[2 * i + 1]), v);
+      if (ADD) Store<T>::unpack_vec(r[i], q);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        v[e] = v[e] * sc[e] + sh[e];
+        if (ADD) v[e] += q[e];
+        v[e] = fmaxf(v[e], 0.f);
+      }
+      Store<T>::store_vec(reinterpret_cast<T*>(lds() + dst + da + i * 2 * BLK * RB), v);
+    };
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      __builtin_amdgcn_sched_barrier(0);
+      // the blocks this row position is tap row dy of
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int dy = 0; dy < 3; ++dy) {
+          const int b = (t - dy) / BLK;
+          if (t < dy || (t - dy) % BLK != 0 || b >= NB) continue;
+          if (C == 16 && ((k == 1 && dy != 0) || (k == 2 && dy != 2))) continue;
+          acc[b] = Mma<T>::mma(wt.w[C == 16 ? (k == 0 ? dy : 2 + k) : dy * 3 + k], x[t % D][k], acc[b]);
+        }
+      if (t + D < NT) request(t + D);
+      const int last = t - 1 - 2;      // the position before completed block last / BLK
+      if (C != 64 && last >= 0 && last % 2 == 1) {
+        finish(last / 2);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // a matrix instruction,
+          __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);   // five vector instructions of the pair before
+        }
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (C == 64) K::exchange(acc, red, flip, wave, lane);
+    finish(F / 2 - 1);
+  };
+  for (int i = 0; i < count; ++i) {
+    load(w2, 2 * i + 2);
+    layer(B.x, w1, B.o, std::false_type{});
+    __syncthreads();
+    if (i + 1 < count) load(w1, 2 * i + 3);
+    layer(B.o, w2, B.x, std::true_type{});
+    __syncthreads();
+  }
+}
+
 // Identity blocks on whole images whose pixel blocks fit G groups per wave: every address of a layer
 // is the same for all layers of the run (both buffers start at image row -1), so a lane computes its
 // pixels' offsets once. Lanes past the last pixel write to `dump`.
@@ -247,7 +393,7 @@ template <typename T, int C, int G>
 __device__ __forceinline__ void identity_images(const EvalConvDesc* cv, int tab, int count, Bufs& B, int red, int dump, int& flip) {
   typedef typename Same<T, C>::type K;
   constexpr int PIX = K::PIX, U = K::U_, NCB = K::NCB_, F = K::KS_ == 1 ? U : U / 2;   // F: pixel blocks a wave finishes per group
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = own_tid<T>(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int W = B.W, RB = row_bytes(W, PIX), npx = B.H * W;
   int ka[K::KPW];
   K::addresses(ka, wave, lane, RB);
@@ -320,7 +466,7 @@ template <typename T, int C>
 __device__ __forceinline__ void identity_run(const EvalConvDesc* cv, int tab, int count, Bufs& B, int lo, int hi, int red, int& flip) {
   typedef typename Same<T, C>::type K;
   constexpr int PIX = K::PIX;
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = own_tid<T>(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int W = B.W, RB = row_bytes(W, PIX);
   const int olo = lo > 0 ? lo - 1 : 0, ohi = hi < B.H ? hi + 1 : B.H;
   const int orow0 = lo - 1;
@@ -359,7 +505,7 @@ __device__ __forceinline__ void down_block(const EvalConvDesc* cv, int tab, Bufs
   typedef typename Down<T, C>::type K1;
   typedef typename Same<T, 2 * C>::type K2;
   typedef Conv<T, C, 2 * C, 1, 2, K2::NCB_, 1, 1> KP;    // (only its weight layout: same channel blocks as K2)
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = own_tid<T>(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int RB = row_bytes(B.W, K1::PIX), RBo = row_bytes(Wo, K2::PIX);
   const int olo = lo > 0 ? lo - 1 : 0, ohi = hi < Ho ? hi + 1 : Ho;
   const int orow0 = lo - 1;
@@ -552,15 +698,18 @@ __global__ __launch_bounds__(NT) void eval_blocks_kernel(Args a) {
       while (bi + cnt < a.nb && a.blocks[bi + cnt].kind == EVAL_IDENTITY) ++cnt;
       const int npx = B.H * B.W;
       const EvalConvDesc* cv0 = a.convs + (a.blocks[bi].conv0 - a.blocks[0].conv0);
-      const bool whole = a.strips == 1 && WHOLE;
+      const bool whole = a.strips == 1 && WHOLE, square = sizeof(T) == 2 && B.W == 512 / C && B.H == B.W;
       if (C == 16) {
-        if (whole && npx <= 1024) identity_images<T, 16, WHOLE ? 2 : 1>(cv0, tab, cnt, B, red, (int)a.dump_off, flip);
+        if (whole && square) identity_square<16>(cv0, tab, cnt, B, red, flip);
+        else if (whole && npx <= 1024) identity_images<T, 16, WHOLE ? 2 : 1>(cv0, tab, cnt, B, red, (int)a.dump_off, flip);
         else identity_run<T, 16>(cv0, tab, cnt, B, lo, hi, red, flip);
       } else if (C == 32) {
-        if (whole && npx <= 256) identity_images<T, 32, 1>(cv0, tab, cnt, B, red, (int)a.dump_off, flip);
+        if (whole && square) identity_square<32>(cv0, tab, cnt, B, red, flip);
+        else if (whole && npx <= 256) identity_images<T, 32, 1>(cv0, tab, cnt, B, red, (int)a.dump_off, flip);
         else identity_run<T, 32>(cv0, tab, cnt, B, lo, hi, red, flip);
       } else {
-        if (whole && npx <= 64) identity_images<T, 64, 1>(cv0, tab, cnt, B, red, (int)a.dump_off, flip);
+        if (whole && square) identity_square<64>(cv0, tab, cnt, B, red, flip);
+        else if (whole && npx <= 64) identity_images<T, 64, 1>(cv0, tab, cnt, B, red, (int)a.dump_off, flip);
         else identity_run<T, 64>(cv0, tab, cnt, B, lo, hi, red, flip);
       }
       bi += cnt;
