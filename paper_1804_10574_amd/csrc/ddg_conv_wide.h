@@ -28,21 +28,6 @@ struct ConvWideArgs {
   int M, H, W, HW, IC, OC, R;
 };
 
-// 16-byte loads with a uniform base, a 32-bit lane offset and a uniform offset (bytes): one address
-// register whatever is loaded. Tensors stay below 4 GiB (the launchers check 2^31 elements).
-typedef __amdgpu_buffer_rsrc_t wide_rsrc_t;
-__device__ __forceinline__ wide_rsrc_t wide_rsrc(const void* p, size_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)(unsigned)bytes, 0x00027000);
-}
-typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uint4 wide_load(wide_rsrc_t r, unsigned lane_off, unsigned uniform_off) {
-  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, uniform_off, 0));
-}
-
-__device__ __forceinline__ void wide_store(wide_rsrc_t r, uint4 v, unsigned lane_off) {   // (past the end: dropped)
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), r, lane_off, 0, 0);
-}
-
 // relu(v*sc + sh) of eight bf16 values, rounded back to bf16
 __device__ __forceinline__ uint4 wide_act(uint4 v, const float* sc, const float* sh) {
   float f[8];

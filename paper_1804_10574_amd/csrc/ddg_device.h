@@ -6,6 +6,17 @@
 
 namespace ddg {
 
+// t / d for tiles t and tiles per image d, by a multiplication where that is exact (a division costs some 25 scalar
+// instructions in a chain, twice per tile)
+struct ImgOf {
+  int d; uint32_t magic;
+  static ImgOf make(int d, long tiles) {
+    const uint64_t m = ((1ull << 32) + d - 1) / d;                   // t * m >> 32 == t / d while t * (m * d - 2^32) < 2^32
+    return ImgOf{d, d > 1 && (uint64_t)tiles * (m * d - (1ull << 32)) < (1ull << 32) ? (uint32_t)m : 0u};
+  }
+  __device__ __forceinline__ int of(int t) const { return d == 1 ? t : magic ? (int)__umulhi((uint32_t)t, magic) : t / d; }
+};
+
 struct bf16_t { uint16_t v; };
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
@@ -85,6 +96,38 @@ template <> struct Store<bf16_t> {
     o[2] = __uint_as_float(v.y << 16); o[3] = __uint_as_float(v.y & 0xffff0000u);
   }
 };
+
+// Sum over the 16 lanes of a row, in every lane: xor butterflies 1, 2, 4, 8 as data-parallel-primitive operands of the additions
+// (4 steps of a few cycles; through __shfl_xor, an LDS operation each, the eight sums of a convolution's epilogue took 1.9k
+// cycles, as long as its matrix instructions). The mirrored rows stand for xor 4 and 8: their lanes hold the same sums.
+template <int CTRL> __device__ __forceinline__ float dpp_move(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float row_sum16(float v) {
+  v += dpp_move<0xB1>(v);     // quad_perm 1,0,3,2
+  v += dpp_move<0x4E>(v);     // quad_perm 2,3,0,1
+  v += dpp_move<0x141>(v);    // row_half_mirror
+  v += dpp_move<0x140>(v);    // row_mirror
+  return v;
+}
+
+// 16-byte loads with a uniform base, a 32-bit lane offset and a uniform offset (bytes): one address
+// register whatever is loaded, and none of them conditional: a lane that has nothing to load gives an offset past the end (NOWHERE) and gets
+// zeros, a store there is dropped. (A conditional load is a branch, and where branches meet the compiler waits for all loads in
+// flight.) Tensors, or what a resource covers of one, stay below 4 GiB.
+typedef __amdgpu_buffer_rsrc_t wide_rsrc_t;
+__device__ __forceinline__ wide_rsrc_t wide_rsrc(const void* p, size_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)(unsigned)bytes, 0x00027000);
+}
+typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint4 wide_load(wide_rsrc_t r, unsigned lane_off, unsigned uniform_off) {
+  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, uniform_off, 0));
+}
+
+__device__ __forceinline__ void wide_store(wide_rsrc_t r, uint4 v, unsigned lane_off) {   // (past the end: dropped)
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), r, lane_off, 0, 0);
+}
+constexpr unsigned NOWHERE = 0xfffffff0u;
 
 // MFMA atoms, 16x16 output tile per wave. Operand X (first) supplies rows, operand Y
 // (second) supplies columns; lane l feeds row/column l%16 with the KV consecutive

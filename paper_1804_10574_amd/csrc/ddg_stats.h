@@ -18,85 +18,123 @@ constexpr int STATS_CMAX = 64;
 // repeats the last one and counts as zero) and adds its rows in order (fp32, like the rows
 // themselves). The NSL row slices of a column are then combined in a fixed order in
 // fp64 in two short steps (four values per thread, then 256/(2C) per column), all unrolled.
-// This sits in the prologue of nearly every training kernel, where latency is all that counts: the
-// per-channel parameters are requested before the rows (by the callers below), and the fp64 part
+// This sits in the prologue of nearly every training kernel, where latency is all that counts: the rows and the
+// per-channel parameters are requested (request()) before anything else a kernel loads and added up (reduce()) when its other
+// loads are on their way; loads return in order, so rows requested behind a tile would wait for it. The fp64 part
 // multiplies by 1/count and takes one rsqrt instead of two divisions, a square root and a division.
-template <int C, typename F>
-__device__ __forceinline__ void reduce_stat_rows(const float* __restrict__ partial, int rows, F f) {
+template <int C>
+struct StatRows {
   static_assert(C == 16 || C == 32 || C == 64, "channel count");
-  constexpr int NCOL4 = C / 2;            // float4 groups per row (2*C/4)
-  constexpr int NSL = 256 / NCOL4;        // row slices: 32, 16, 8
-  constexpr int G = 256 / (2 * C);        // second-step groups per column: 8, 4, 2 (NSL == 4*G)
-  constexpr int U = C == 64 ? 12 : 8;     // loads in flight: all rows of the usual launches (256, 128, 96)
-  __shared__ float4 sh[256];
-  __shared__ double sh2[256];
-  const int tid = threadIdx.x;
-  const int c4 = tid % NCOL4, slice = tid / NCOL4;
-  const float4* __restrict__ p4 = reinterpret_cast<const float4*>(partial);
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int r0 = slice; r0 < rows; r0 += NSL * U) {
-    float4 v[U];
+  static constexpr int NCOL4 = C / 2;            // float4 groups per row (2*C/4)
+  static constexpr int NSL = 256 / NCOL4;        // row slices: 32, 16, 8
+  static constexpr int G = 256 / (2 * C);        // second-step groups per column: 8, 4, 2 (NSL == 4*G)
+  static constexpr int U = C == 64 ? 12 : 8;     // loads in flight: all rows of the usual launches (256, 128, 96)
+  float4 v[U];
+
+  __device__ __forceinline__ void load(const float* __restrict__ partial, int rows, int r0) {
+    const float4* __restrict__ p4 = reinterpret_cast<const float4*>(partial) + threadIdx.x % NCOL4;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int rr = r0 + u * NSL;
-      v[u] = p4[(rr < rows ? rr : rows - 1) * NCOL4 + c4];
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const bool in = r0 + u * NSL < rows;
-      acc.x += in ? v[u].x : 0.f; acc.y += in ? v[u].y : 0.f; acc.z += in ? v[u].z : 0.f; acc.w += in ? v[u].w : 0.f;
+      v[u] = p4[(unsigned)(rr < rows ? rr : rows - 1) * NCOL4];
     }
   }
-  sh[tid] = acc;
-  __syncthreads();
-  {
-    // thread (column col of 2C, group g): slices g*4 .. g*4+3
-    const float* shf = reinterpret_cast<const float*>(sh);
-    const int col = tid % (2 * C), g = tid / (2 * C);
-    double t = 0.0;
+  __device__ __forceinline__ void request(const float* __restrict__ partial, int rows) { load(partial, rows, threadIdx.x / NCOL4); }
+
+  template <typename F>
+  __device__ __forceinline__ void reduce(const float* __restrict__ partial, int rows, F f) {
+    __shared__ float4 sh[256];
+    __shared__ double sh2[256];
+    const int tid = threadIdx.x;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int r0 = tid / NCOL4;;) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) t += (double)shf[((g * 4 + k) * NCOL4) * 4 + col];
-    sh2[g * (2 * C) + col] = t;
-  }
-  __syncthreads();
-  if (tid < C) {
-    double t1 = 0.0, t2 = 0.0;
+      for (int u = 0; u < U; ++u) {
+        const bool in = r0 + u * NSL < rows;
+        acc.x += in ? v[u].x : 0.f; acc.y += in ? v[u].y : 0.f; acc.z += in ? v[u].z : 0.f; acc.w += in ? v[u].w : 0.f;
+      }
+      r0 += NSL * U;
+      if (r0 >= rows) break;
+      load(partial, rows, r0);
+    }
+    sh[tid] = acc;
+    __syncthreads();
+    {
+      // thread (column col of 2C, group g): slices g*4 .. g*4+3
+      const float* shf = reinterpret_cast<const float*>(sh);
+      const int col = tid % (2 * C), g = tid / (2 * C);
+      double t = 0.0;
 #pragma unroll
-    for (int g = 0; g < G; ++g) { t1 += sh2[g * (2 * C) + tid]; t2 += sh2[g * (2 * C) + C + tid]; }
-    f(tid, t1, t2);
+      for (int k = 0; k < 4; ++k) t += (double)shf[((g * 4 + k) * NCOL4) * 4 + col];
+      sh2[g * (2 * C) + col] = t;
+    }
+    __syncthreads();
+    if (tid < C) {
+      double t1 = 0.0, t2 = 0.0;
+#pragma unroll
+      for (int g = 0; g < G; ++g) { t1 += sh2[g * (2 * C) + tid]; t2 += sh2[g * (2 * C) + C + tid]; }
+      f(tid, t1, t2);
+    }
+    __syncthreads();
   }
-  __syncthreads();
-}
+};
 
 // Forward statistics -> scale = gamma*invstd, shift = beta - mean*scale in LDS (s_scale, s_shift);
 // workgroup 0 (write != 0) also stores mean, invstd, scale, shift.
 template <int C>
+struct BnFwdRows {
+  StatRows<C> r;
+  float gamma, beta;
+  __device__ __forceinline__ void request(const BnRows& p) {
+    r.request(p.partial, p.rows);
+    const int tc = threadIdx.x < C ? threadIdx.x : 0;
+    gamma = p.gamma[tc]; beta = p.beta[tc];
+  }
+  __device__ __forceinline__ void finish(const BnRows& p, float* s_scale, float* s_shift, bool write) {
+    r.reduce(p.partial, p.rows, [&](int c, double t1, double t2) {
+      const double mu = t1 * p.inv_count;
+      double var = t2 * p.inv_count - mu * mu;
+      if (var < 0.0) var = 0.0;
+      const float is = (float)rsqrt(var + (double)p.eps);
+      const float sc = gamma * is;
+      const float sh = beta - (float)mu * sc;
+      s_scale[c] = sc; s_shift[c] = sh;
+      if (write) { p.mean[c] = (float)mu; p.invstd[c] = is; p.scale[c] = sc; p.shift[c] = sh; }
+    });
+  }
+};
+template <int C>
 __device__ __forceinline__ void bn_fwd_from_rows(const BnRows& p, float* s_scale, float* s_shift, bool write) {
-  const int tc = threadIdx.x < C ? threadIdx.x : 0;
-  const float gamma = p.gamma[tc], beta = p.beta[tc];
-  reduce_stat_rows<C>(p.partial, p.rows, [&](int c, double t1, double t2) {
-    const double mu = t1 * p.inv_count;
-    double var = t2 * p.inv_count - mu * mu;
-    if (var < 0.0) var = 0.0;
-    const float is = (float)rsqrt(var + (double)p.eps);
-    const float sc = gamma * is;
-    const float sh = beta - (float)mu * sc;
-    s_scale[c] = sc; s_shift[c] = sh;
-    if (write) { p.mean[c] = (float)mu; p.invstd[c] = is; p.scale[c] = sc; p.shift[c] = sh; }
-  });
+  BnFwdRows<C> r;
+  r.request(p);
+  r.finish(p, s_scale, s_shift, write);
 }
 
 // Backward sums (sum g, sum g*xhat) -> coefficients of dz = A*g + B*z + C0 in LDS (s_coef[3][C]);
 // workgroup 0 also stores dgamma, dbeta.
 template <int C>
+struct BnBwdFromRows {
+  StatRows<C> r;
+  float gamma, invstd, mean;
+  __device__ __forceinline__ void request(const BnBwdRows& p) {
+    r.request(p.partial, p.rows);
+    const int tc = threadIdx.x < C ? threadIdx.x : 0;
+    gamma = p.gamma[tc]; invstd = p.invstd[tc]; mean = p.mean[tc];
+  }
+  __device__ __forceinline__ void finish(const BnBwdRows& p, float* s_coef, bool write) {
+    r.reduce(p.partial, p.rows, [&](int c, double db, double dg) {
+      const double g = gamma, is = invstd, mu = mean;
+      const double A = g * is, B = -A * is * (dg * p.inv_count), C0 = -A * (db * p.inv_count) - B * mu;
+      s_coef[c] = (float)A; s_coef[C + c] = (float)B; s_coef[2 * C + c] = (float)C0;
+      if (write) { p.dgamma[c] = (float)dg; p.dbeta[c] = (float)db; }
+    });
+  }
+};
+template <int C>
 __device__ __forceinline__ void bn_bwd_from_rows(const BnBwdRows& p, float* s_coef, bool write) {
-  const int tc = threadIdx.x < C ? threadIdx.x : 0;
-  const double g = p.gamma[tc], is = p.invstd[tc], mu = p.mean[tc];
-  reduce_stat_rows<C>(p.partial, p.rows, [&](int c, double db, double dg) {
-    const double A = g * is, B = -A * is * (dg * p.inv_count), C0 = -A * (db * p.inv_count) - B * mu;
-    s_coef[c] = (float)A; s_coef[C + c] = (float)B; s_coef[2 * C + c] = (float)C0;
-    if (write) { p.dgamma[c] = (float)dg; p.dbeta[c] = (float)db; }
-  });
+  BnBwdFromRows<C> r;
+  r.request(p);
+  r.finish(p, s_coef, write);
 }
 
 // Run-time channel count (16, 32 or 64; the host checks): one of the three instances.

@@ -181,12 +181,7 @@ __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, bool second, i
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        float s1 = ssum[nb][j], s2 = ssq[nb][j];
-#pragma unroll
-        for (int o = 1; o < 16; o <<= 1) {
-          s1 += __shfl_xor(s1, o, 64);
-          s2 += __shfl_xor(s2, o, 64);
-        }
+        const float s1 = row_sum16(ssum[nb][j]), s2 = row_sum16(ssq[nb][j]);
         if (l16 == 0) {
           red[wave][0][nb * 16 + lg * 4 + j] = s1;
           red[wave][1][nb * 16 + lg * 4 + j] = s2;

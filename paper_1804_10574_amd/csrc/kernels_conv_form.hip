@@ -31,7 +31,6 @@ constexpr int opitch(int OC) { return OC * 2 + 16; }
 constexpr int max3(int a, int b, int c) { return a > b ? (a > c ? a : c) : (b > c ? b : c); }
 // the table of scales and shifts; then the chunks, later the finished tile, later the sums per row class
 constexpr int lds_bytes(int OC, int IC) { return IC * 8 + max3(2 * BUF, BM * opitch(OC), 2 * OC * (4096 / OC) * 4); }
-constexpr unsigned NOWHERE = 0xfffffff0u;                      // past the end of any tensor: loads give zeros, stores are dropped
 }
 
 template <int OC>

@@ -43,7 +43,6 @@ constexpr int opitch(int stats) { return stats == 1 ? 128 * 2 + 16 : 128 * 4 + 1
 constexpr int RED = 32 * 128 * 4;                              // where sums of the 32 pixel classes meet
 constexpr int lds_bytes(int K, int stats) { return 2 * BM * (pitch(K) + opitch(stats)) + (stats ? RED : 0); }
 constexpr int CHAIN = 8;                                       // tiles whose values a thread adds in fp32 (a power of two)
-constexpr unsigned NOWHERE = 0xfffffff0u;                      // past the end of any tensor: the load gives zeros
 }
 
 template <int STATS, bool XFORM, int K>

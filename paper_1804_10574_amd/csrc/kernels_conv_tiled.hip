@@ -42,7 +42,8 @@ struct ConvTiledArgs {
   BnBwdRows brows; bf16_t* dz_out;
   int N, H;                // N counts the images of all groups
   int tiles;               // N * H/8
-  // groups > 1: the batch is `groups` independent minibatches laid end to end (batch-norm
+  ImgOf img;               // tile -> image
+  // groups 2: the batch is two independent minibatches laid end to end (batch-norm
   // statistics are per minibatch). A workgroup works on one group only: workgroups
   // [g*grid/groups, (g+1)*grid/groups) take group g, write that group's statistics rows
   // (rows are indexed by workgroup), and use that group's input transform: in_rows.partial and
@@ -59,7 +60,7 @@ struct ConvTiledCfg {
   // bytes apart do that; where a block of 16 pixels spans two rows (8 wide), the rows have to be a multiple of 256 apart too.
   static constexpr int PIX = C == 16 ? 32 : C * 2 + 32;
   static constexpr int ROWB = W == 8 ? (WC * PIX + 255) / 256 * 256 : WC * PIX;
-  static constexpr int TILE_BYTES = ROWS * ROWB;
+  static constexpr int TILE_BYTES = ROWS * ROWB, LDS_BYTES = TILE_BYTES + 16;
   static constexpr int CH = C / 8;                       // 16-byte chunks per pixel
   static constexpr int NCHUNK = ROWS * WC * CH;          // chunks per tile (halo columns included)
   static constexpr int PER_THREAD = (NCHUNK + 255) / 256;
@@ -76,7 +77,7 @@ struct ConvTiledCfg {
 enum { XF_PLAIN = 0, XF_RES = 1, XF_APPLY = 2, XF_APPLY_MASK = 3 };
 
 constexpr int conv_tiled_waves(int C, int MODE, int XF) {
-  return C == 64 ? (XF != XF_PLAIN ? 1 : 2)
+  return C == 64 ? (MODE == 2 && XF >= XF_APPLY ? 1 : 2)
                  : (((C == 32 && (XF != XF_PLAIN || MODE == 2)) || (C == 16 && XF >= XF_APPLY && MODE == 2)) ? 2 : 3);
 }
 
@@ -103,57 +104,83 @@ __device__ __forceinline__ void conv3x3_tiled_body(const ConvTiledArgs& a, unsig
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l16 = lane & 15, lg = lane >> 4;
   const int pgrp = wave % PG, cb = wave / PG;
-  const int tiles_per_img = a.H / TH;
-  // this workgroup's group, its index among the group's workgroups, the group's tile range
-  const int g1 = gdim / a.groups;
-  const int grp = bidx / g1, bl = bidx - grp * g1;
-  const int tiles_g = a.tiles / a.groups, t_end = (grp + 1) * tiles_g;
+  // this workgroup's group (one of at most two), its index among the group's workgroups, the group's tile range
+  const int g1 = gdim >> (a.groups - 1);
+  const int grp = bidx >= g1 ? 1 : 0, bl = bidx - grp * g1;
+  const int tiles_g = a.tiles >> (a.groups - 1), t_end = (grp + 1) * tiles_g;
+
+  // what the on-load transform waits for is requested before everything else
+  BnFwdRows<C> fwd;
+  BnBwdFromRows<C> bwd;
+  BnRows in_rows = a.in_rows;
+  float bms = 1.f, bmh = 0.f;
+  const int vo = grp * a.vec_stride;
+  if (APPLY) {
+    bwd.request(a.brows);
+    if (a.bmscale && tid < C) { bms = a.bmscale[tid]; bmh = a.bmshift[tid]; }
+  } else if (in_rows.partial) {
+    in_rows.partial += (size_t)grp * in_rows.rows * 2 * C;
+    in_rows.mean += vo; in_rows.invstd += vo; in_rows.scale += vo; in_rows.shift += vo;
+    fwd.request(in_rows);
+  } else if (a.scale && tid < C) {
+    bms = a.scale[vo + tid]; bmh = a.shift[vo + tid];
+  }
 
   // ---- staging map (the same for every tile): chunk v = tid + i*256 -> halo pixel, 8 channels
   const int my_ch = tid % CH;
-  int goff[PT];      // element offset of the chunk relative to the tile's first pixel (row r0, column 0)
-  unsigned srows = 0;  // 4 bits per chunk: halo row 0..9 of the chunk + 1; 0: no chunk, or a pad column (stays zero)
-  int loff[PT];      // LDS byte offset
+  unsigned goff[PT];   // byte offset of the chunk from column 0 of the tile's first halo row
+  unsigned out = 0;    // 3 bits per chunk: in the first / the last halo row, in a pad column (or no chunk)
+  unsigned own = 0;    // bit i: chunk i lies in the tile's own rows, which this workgroup stores
+  int loff[PT];        // LDS byte offset (no chunk: behind the tile)
 #pragma unroll
   for (int i = 0; i < PT; ++i) {
     const int v = tid + i * 256;
     const int px = v / CH;
     const int rr = px / WC, cc = px - rr * WC;
     const bool col_ok = v < NCHUNK && cc >= 1 && cc <= W;
-    srows |= (col_ok ? (unsigned)(rr + 1) : 0u) << (4 * i);
-    goff[i] = ((rr - 1) * W + (cc - 1)) * C + my_ch * 8;
-    loff[i] = v < NCHUNK ? rr * ROWB + cc * PIX + my_ch * 16 : -1;
+    out |= ((rr == 0 ? 1u : 0u) | (rr == TH + 1 ? 2u : 0u) | (col_ok ? 0u : 4u)) << (3 * i);
+    own |= (col_ok && rr >= 1 && rr <= TH ? 1u : 0u) << i;
+    goff[i] = (unsigned)((rr * W + cc - 1) * C + my_ch * 8) * 2;
+    loff[i] = v < NCHUNK ? rr * ROWB + cc * PIX + my_ch * 16 : Cfg::TILE_BYTES;
   }
   uint4 stage[PT], stage2[(RES || APPLY) ? PT : 1], stage3[XF == XF_APPLY_MASK ? PT : 1];
-  unsigned inimg = 0;   // bit i: chunk i of the tile in flight lies inside the image
-  unsigned tile_base = 0;   // element offset of the staged tile's first pixel (the host checks 32 bits suffice)
-  auto issue_loads = [&](int t) {
-    const int n = t / tiles_per_img, r0 = (t - n * tiles_per_img) * TH;
-    const unsigned tb = (unsigned)((n * a.H + r0) * W) * C;
-    tile_base = tb;
-    inimg = 0;
+  // element offset of column 0 of tile t's first halo row (it may lie before the tensor, where nothing is loaded), and which
+  // chunks of it lie outside the image
+  auto tile_at = [&](int t, unsigned& outside) {
+    const int n = a.img.of(t), r0 = (t - n * a.img.d) * TH;
+    outside = 4u | (r0 == 0 ? 1u : 0u) | (r0 + TH == a.H ? 2u : 0u);
+    return ((ptrdiff_t)(n * a.H + r0) - 1) * (W * C);
+  };
+  auto resource = [&](const bf16_t* p, ptrdiff_t at, bool any = true) { return wide_rsrc(p + at, any ? (TH + 2) * W * C * 2 : 0); };
+  auto issue_loads = [&](int t) {     // (a tile past the last: loads that fetch nothing, so that their number is the same)
+    unsigned outside;
+    const ptrdiff_t at = tile_at(t, outside);
+    const bool any = t < t_end;
+    const wide_rsrc_t r1 = resource(a.in, at, any);
+    const wide_rsrc_t r2 = resource(RES ? a.res : APPLY ? a.bz : a.in, at, any), r3 = resource(XF == XF_APPLY_MASK ? a.bmask : a.in, at, any);
 #pragma unroll
     for (int i = 0; i < PT; ++i) {
-      stage[i] = make_uint4(0, 0, 0, 0);
-      const int sr = (int)((srows >> (4 * i)) & 15u) - 1;   // halo row, -1: nothing to load
-      const int ih = r0 - 1 + sr;
-      if (sr >= 0 && ih >= 0 && ih < a.H) {
-        inimg |= 1u << i;
-        stage[i] = *reinterpret_cast<const uint4*>(a.in + tb + goff[i]);
-        if (RES) stage2[i] = *reinterpret_cast<const uint4*>(a.res + tb + goff[i]);
-        if (APPLY) stage2[i] = *reinterpret_cast<const uint4*>(a.bz + tb + goff[i]);
-        if (XF == XF_APPLY_MASK) stage3[i] = *reinterpret_cast<const uint4*>(a.bmask + tb + goff[i]);
-      }
+      const unsigned o = (out & (outside << (3 * i))) ? NOWHERE : goff[i];
+      stage[i] = __builtin_bit_cast(uint4, wide_load(r1, o, 0));
+      if (RES || APPLY) stage2[i] = __builtin_bit_cast(uint4, wide_load(r2, o, 0));
+      if (XF == XF_APPLY_MASK) stage3[i] = __builtin_bit_cast(uint4, wide_load(r3, o, 0));
     }
   };
-  int t = grp * tiles_g + bl;
-  if (t < t_end) issue_loads(t);
-
-  // ---- this wave's weights: KSTEPS fragments of its output-channel block
+  // ---- this wave's weights: KSTEPS fragments of its output-channel block (before the tile: with the tile they have arrived too,
+  // so the loop never waits for them)
   uint4 wf[KSTEPS];
 #pragma unroll
   for (int ks = 0; ks < KSTEPS; ++ks)
     wf[ks] = *reinterpret_cast<const uint4*>(a.wpack + ((size_t)(ks * COB + cb) * 64 + lane) * 8);
+
+  int t = grp * tiles_g + bl;
+  issue_loads(t);
+
+  float below[4] = {0.f, 1.f, 1.f, 0.f};   // mode 2: constants of the BN below (mean, invstd, mask scale, mask shift)
+  if (MODE == 2 && tid < C) {
+    below[0] = a.st.zmean[tid]; below[1] = a.st.zinvstd[tid];
+    if (a.st.mscale) { below[2] = a.st.mscale[tid]; below[3] = a.st.mshift[tid]; }
+  }
 
   // ---- LDS fragment addresses: lane part + k-step part in a register, pixel block as immediate
   // pixel of block i, lane l16: pt = (pgrp*4 + i)*16 + l16; its row/column split is additive in i
@@ -178,82 +205,64 @@ __device__ __forceinline__ void conv3x3_tiled_body(const ConvTiledArgs& a, unsig
   // XF_APPLY: A, B, C0 of the formula, then the mask's scale and shift
   __shared__ __align__(16) float s_coef[APPLY ? 5 * C : 4];
   if (APPLY) {
-    if (tid < C) {
-      s_coef[3 * C + tid] = a.bmscale ? a.bmscale[tid] : 1.f;
-      s_coef[4 * C + tid] = a.bmscale ? a.bmshift[tid] : 0.f;
-    }
-    bn_bwd_from_rows<C>(a.brows, s_coef, bidx == 0);   // ends with a barrier
-  } else if (a.in_rows.partial) {
-    BnRows r = a.in_rows;
-    r.partial += (size_t)grp * r.rows * 2 * C;
-    const int vo = grp * a.vec_stride;
-    r.mean += vo; r.invstd += vo; r.scale += vo; r.shift += vo;
-    bn_fwd_from_rows<C>(r, s_sc, s_sh, bl == 0);
+    if (tid < C) { s_coef[3 * C + tid] = bms; s_coef[4 * C + tid] = bmh; }
+    bwd.finish(a.brows, s_coef, bidx == 0);   // ends with a barrier
+  } else if (in_rows.partial) {
+    fwd.finish(in_rows, s_sc, s_sh, bl == 0);
   } else if (a.scale) {
-    const int vo = grp * a.vec_stride;
-    if (tid < C) { s_sc[tid] = a.scale[vo + tid]; s_sh[tid] = a.shift[vo + tid]; }
+    if (tid < C) { s_sc[tid] = bms; s_sh[tid] = bmh; }
     __syncthreads();
   }
-  auto write_stage = [&]() {
-    const unsigned stage_base = tile_base;   // of the tile held in the registers
+  auto write_stage = [&](int t) {
+    unsigned outside;
+    const ptrdiff_t at = tile_at(t, outside);
+    auto ld8 = [&](const float* p, float (&d)[8]) {
+      *reinterpret_cast<float4*>(&d[0]) = *reinterpret_cast<const float4*>(p + my_ch * 8);
+      *reinterpret_cast<float4*>(&d[4]) = *reinterpret_cast<const float4*>(p + my_ch * 8 + 4);
+    };
+    float k0[8], k1[8], k2[8], m0[8], m1[8];      // this thread's channels: A, B, C0, the mask's scale and shift; or scale and shift
+    wide_rsrc_t ro;
+    if (APPLY) {
+      ld8(&s_coef[0], k0); ld8(&s_coef[C], k1); ld8(&s_coef[2 * C], k2);
+      if (C != 64) { ld8(&s_coef[3 * C], m0); ld8(&s_coef[4 * C], m1); }   // (64 channels: no registers for these)
+      ro = resource(a.dz_out, at);
+    } else if (xform) {
+      ld8(s_sc, k0); ld8(s_sh, k1);
+      if (RES) ro = a.y_out ? resource(a.y_out, at) : wide_rsrc(nullptr, 0);
+    }
 #pragma unroll
     for (int i = 0; i < PT; ++i) {
-      if (loff[i] >= 0) {
-        uint4 q = stage[i];
-        if (APPLY && ((inimg >> i) & 1u)) {
-          auto ld8 = [&](const float* p, float (&d)[8]) {
-            *reinterpret_cast<float4*>(&d[0]) = *reinterpret_cast<const float4*>(p + my_ch * 8);
-            *reinterpret_cast<float4*>(&d[4]) = *reinterpret_cast<const float4*>(p + my_ch * 8 + 4);
-          };
-          float g[8], zz[8], k0[8], k1[8];
-          Store<bf16_t>::unpack_vec(q, g);
+      uint4 q = stage[i];
+      if (APPLY || xform) {
+        float g[8], zz[8];
+        Store<bf16_t>::unpack_vec(q, g);
+        if (APPLY) {
           Store<bf16_t>::unpack_vec(stage2[i], zz);
           if (a.bmask) {
             float mk[8];
             Store<bf16_t>::unpack_vec(XF == XF_APPLY_MASK ? stage3[i] : stage2[i], mk);
-            ld8(&s_coef[3 * C], k0); ld8(&s_coef[4 * C], k1);
+            if (C == 64) { ld8(&s_coef[3 * C], m0); ld8(&s_coef[4 * C], m1); }
 #pragma unroll
-            for (int j = 0; j < 8; ++j) g[j] = (mk[j] * k0[j] + k1[j]) > 0.f ? g[j] : 0.f;
-          }
-          ld8(&s_coef[C], k0); ld8(&s_coef[2 * C], k1);
-#pragma unroll
-          for (int j = 0; j < 8; ++j) zz[j] = k0[j] * zz[j] + k1[j];
-          ld8(&s_coef[0], k0);
-#pragma unroll
-          for (int j = 0; j < 8; ++j) g[j] = k0[j] * g[j] + zz[j];
-          q.x = Store<bf16_t>::pack2(g[0], g[1]); q.y = Store<bf16_t>::pack2(g[2], g[3]);
-          q.z = Store<bf16_t>::pack2(g[4], g[5]); q.w = Store<bf16_t>::pack2(g[6], g[7]);
-          const unsigned sr1 = (srows >> (4 * i)) & 15u;   // halo row + 1
-          if (sr1 >= 2 && sr1 <= TH + 1)
-            *reinterpret_cast<uint4*>(a.dz_out + stage_base + goff[i]) = q;
-        }
-        if (xform && ((inimg >> i) & 1u)) {
-          float f[8], tsc[8], tsh[8];
-          *reinterpret_cast<float4*>(&tsc[0]) = *reinterpret_cast<const float4*>(&s_sc[my_ch * 8]);
-          *reinterpret_cast<float4*>(&tsc[4]) = *reinterpret_cast<const float4*>(&s_sc[my_ch * 8 + 4]);
-          *reinterpret_cast<float4*>(&tsh[0]) = *reinterpret_cast<const float4*>(&s_sh[my_ch * 8]);
-          *reinterpret_cast<float4*>(&tsh[4]) = *reinterpret_cast<const float4*>(&s_sh[my_ch * 8 + 4]);
-          Store<bf16_t>::unpack_vec(q, f);
-          if (RES) {
-            float r[8];
-            Store<bf16_t>::unpack_vec(stage2[i], r);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) f[j] = f[j] * tsc[j] + tsh[j] + r[j];
-          } else {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) f[j] = f[j] * tsc[j] + tsh[j];
+            for (int j = 0; j < 8; ++j) g[j] = (mk[j] * m0[j] + m1[j]) > 0.f ? g[j] : 0.f;
           }
 #pragma unroll
-          for (int j = 0; j < 8; ++j) f[j] = f[j] > 0.f ? f[j] : 0.f;
-          q.x = Store<bf16_t>::pack2(f[0], f[1]); q.y = Store<bf16_t>::pack2(f[2], f[3]);
-          q.z = Store<bf16_t>::pack2(f[4], f[5]); q.w = Store<bf16_t>::pack2(f[6], f[7]);
-          // the tile's own rows (halo rows 1..8) are this workgroup's to store
-          const unsigned sr1 = (srows >> (4 * i)) & 15u;   // halo row + 1
-          if (RES && a.y_out && sr1 >= 2 && sr1 <= TH + 1)
-            *reinterpret_cast<uint4*>(a.y_out + stage_base + goff[i]) = q;
+          for (int j = 0; j < 8; ++j) g[j] = k0[j] * g[j] + (k1[j] * zz[j] + k2[j]);
+        } else {
+          if (RES) Store<bf16_t>::unpack_vec(stage2[i], zz);
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            g[j] = g[j] * k0[j] + k1[j];
+            if (RES) g[j] += zz[j];
+            g[j] = g[j] > 0.f ? g[j] : 0.f;
+          }
         }
-        *reinterpret_cast<uint4*>(tile + loff[i]) = q;
+        // zero padding comes after the transform
+        const bool in = !(out & (outside << (3 * i)));
+        q.x = in ? Store<bf16_t>::pack2(g[0], g[1]) : 0u; q.y = in ? Store<bf16_t>::pack2(g[2], g[3]) : 0u;
+        q.z = in ? Store<bf16_t>::pack2(g[4], g[5]) : 0u; q.w = in ? Store<bf16_t>::pack2(g[6], g[7]) : 0u;
+        if (APPLY || RES) wide_store(ro, q, (own >> i) & 1u ? goff[i] : NOWHERE);
       }
+      *reinterpret_cast<uint4*>(tile + loff[i]) = q;
     }
   };
 
@@ -264,29 +273,28 @@ __device__ __forceinline__ void conv3x3_tiled_body(const ConvTiledArgs& a, unsig
   const bf16_t* st_mask = reinterpret_cast<const bf16_t*>(a.st.mask);
   const bf16_t* st_z = reinterpret_cast<const bf16_t*>(a.st.z);
   const bool two_tensors = MODE == 2 && st_z != st_mask;
+  const bool add = MODE != 1 && a.add_g != nullptr;   // (a shortcut gradient is added to gradients only)
   if (MODE == 2) {
-    if (tid < C) {
-      s_below[tid] = a.st.zmean[tid]; s_below[C + tid] = a.st.zinvstd[tid];
-      s_below[2 * C + tid] = a.st.mscale ? a.st.mscale[tid] : 1.f;
-      s_below[3 * C + tid] = a.st.mscale ? a.st.mshift[tid] : 0.f;
-    }
+    if (tid < C) { s_below[tid] = below[0]; s_below[C + tid] = below[1]; s_below[2 * C + tid] = below[2]; s_below[3 * C + tid] = below[3]; }
     // (made visible by the barriers of the tile loop before any epilogue runs)
   }
+  // (the weights' wait, which comes before the first tile's: inside the loop it would be one for all loads in flight, every time)
+#pragma unroll
+  for (int ks = 0; ks < KSTEPS; ++ks) asm volatile("" : "+v"(wf[ks].x), "+v"(wf[ks].y), "+v"(wf[ks].z), "+v"(wf[ks].w));
   // output element offset of (block 0, this lane) inside a tile; block i adds i*16*C
   const int out_lane = ptl * C + cb * 16 + lg * 4;
 
   for (; t < t_end; t += g1) {
     __syncthreads();            // the previous tile has been consumed
-    write_stage();
+    write_stage(t);
     __syncthreads();
-    const int tn = t + g1;
-    if (tn < t_end) issue_loads(tn);   // in flight during the MFMA phase
+    issue_loads(t + g1);               // in flight during the MFMA phase
 
     // what the epilogue reads, requested now
-    const int n = t / tiles_per_img, r0 = (t - n * tiles_per_img) * TH;
+    const int n = a.img.of(t), r0 = (t - n * a.img.d) * TH;
     const unsigned obase = (unsigned)((n * a.H + r0) * W) * C + out_lane;
     uint2 eg[4], em[4], ek[4], ez[4];
-    if (a.add_g) {
+    if (add) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         eg[i] = *reinterpret_cast<const uint2*>(a.add_g + obase + i * 16 * C);
@@ -322,7 +330,7 @@ __device__ __forceinline__ void conv3x3_tiled_body(const ConvTiledArgs& a, unsig
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       float v[4] = {acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
-      if (a.add_g) {
+      if (add) {
         float g[4] = {lo(eg[i].x), hi(eg[i].x), lo(eg[i].y), hi(eg[i].y)};
         if (a.add_mask) {
           const float mk[4] = {lo(em[i].x), hi(em[i].x), lo(em[i].y), hi(em[i].y)};
@@ -377,12 +385,7 @@ __device__ __forceinline__ void conv3x3_tiled_body(const ConvTiledArgs& a, unsig
     __shared__ float red[4][2][16];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      float s1 = ssum[j], s2 = ssq[j];
-#pragma unroll
-      for (int o = 1; o < 16; o <<= 1) {
-        s1 += __shfl_xor(s1, o, 64);
-        s2 += __shfl_xor(s2, o, 64);
-      }
+      const float s1 = row_sum16(ssum[j]), s2 = row_sum16(ssq[j]);
       if (l16 == 0) { red[wave][0][lg * 4 + j] = s1; red[wave][1][lg * 4 + j] = s2; }
     }
     __syncthreads();
@@ -474,7 +477,7 @@ static hipError_t conv_tiled_launch_t(const ConvTiledArgs& a, int grid, hipStrea
     using WCfg = WgradTiledCfg<C, C, W>;
     if (!wa || !a.bz || a.st.mode != 2 || a.scale || a.in_rows.partial || !a.brows.partial || !a.dz_out || C == 16 || ride->C != C || ride->grid < 1)
       return hipErrorInvalidValue;
-    constexpr int lds = Cfg::TILE_BYTES > WCfg::LDS ? Cfg::TILE_BYTES : WCfg::LDS;
+    constexpr int lds = Cfg::LDS_BYTES > WCfg::LDS ? Cfg::LDS_BYTES : WCfg::LDS;
     if constexpr (C != 16) {
       const int wgb = wg_rows * WCfg::OT;
       const dim3 g(grid + wgb + ride->grid);
@@ -487,7 +490,7 @@ static hipError_t conv_tiled_launch_t(const ConvTiledArgs& a, int grid, hipStrea
     using WCfg = WgradTiledCfg<C, C, W>;
     if (!a.bz || a.st.mode == 1 || a.scale || a.in_rows.partial || !a.brows.partial || !a.dz_out || wg_rows < 1)
       return hipErrorInvalidValue;
-    constexpr int lds = Cfg::TILE_BYTES > WCfg::LDS ? Cfg::TILE_BYTES : WCfg::LDS;
+    constexpr int lds = Cfg::LDS_BYTES > WCfg::LDS ? Cfg::LDS_BYTES : WCfg::LDS;
     static_assert(lds <= 48 * 1024, "dynamic LDS within the default limit");
     const bool own_mask = a.bmask && a.bmask != a.bz;
     const dim3 g(grid + wg_rows * WCfg::OT);
@@ -502,21 +505,21 @@ static hipError_t conv_tiled_launch_t(const ConvTiledArgs& a, int grid, hipStrea
   }
   if (a.res) {
     if (a.st.mode != 1 || !(a.scale || a.in_rows.partial)) return hipErrorInvalidValue;
-    DDG_LAUNCH((conv3x3_tiled_kernel<C, W, 1, XF_RES>), dim3(grid), dim3(256), Cfg::TILE_BYTES, s, a);
+    DDG_LAUNCH((conv3x3_tiled_kernel<C, W, 1, XF_RES>), dim3(grid), dim3(256), Cfg::LDS_BYTES, s, a);
   } else if (a.bz) {
     // input-gradient kernel that applies the batch-norm backward formula to its input
     if (a.st.mode == 1 || a.scale || a.in_rows.partial || !a.brows.partial || !a.dz_out) return hipErrorInvalidValue;
     const bool own_mask = a.bmask && a.bmask != a.bz;
     if (a.st.mode == 2) {
-      if (own_mask) DDG_LAUNCH((conv3x3_tiled_kernel<C, W, 2, XF_APPLY_MASK>), dim3(grid), dim3(256), Cfg::TILE_BYTES, s, a);
-      else DDG_LAUNCH((conv3x3_tiled_kernel<C, W, 2, XF_APPLY>), dim3(grid), dim3(256), Cfg::TILE_BYTES, s, a);
+      if (own_mask) DDG_LAUNCH((conv3x3_tiled_kernel<C, W, 2, XF_APPLY_MASK>), dim3(grid), dim3(256), Cfg::LDS_BYTES, s, a);
+      else DDG_LAUNCH((conv3x3_tiled_kernel<C, W, 2, XF_APPLY>), dim3(grid), dim3(256), Cfg::LDS_BYTES, s, a);
     } else {
-      if (own_mask) DDG_LAUNCH((conv3x3_tiled_kernel<C, W, 0, XF_APPLY_MASK>), dim3(grid), dim3(256), Cfg::TILE_BYTES, s, a);
-      else DDG_LAUNCH((conv3x3_tiled_kernel<C, W, 0, XF_APPLY>), dim3(grid), dim3(256), Cfg::TILE_BYTES, s, a);
+      if (own_mask) DDG_LAUNCH((conv3x3_tiled_kernel<C, W, 0, XF_APPLY_MASK>), dim3(grid), dim3(256), Cfg::LDS_BYTES, s, a);
+      else DDG_LAUNCH((conv3x3_tiled_kernel<C, W, 0, XF_APPLY>), dim3(grid), dim3(256), Cfg::LDS_BYTES, s, a);
     }
-  } else if (a.st.mode == 1) DDG_LAUNCH((conv3x3_tiled_kernel<C, W, 1>), dim3(grid), dim3(256), Cfg::TILE_BYTES, s, a);
-  else if (a.st.mode == 2) DDG_LAUNCH((conv3x3_tiled_kernel<C, W, 2>), dim3(grid), dim3(256), Cfg::TILE_BYTES, s, a);
-  else DDG_LAUNCH((conv3x3_tiled_kernel<C, W, 0>), dim3(grid), dim3(256), Cfg::TILE_BYTES, s, a);
+  } else if (a.st.mode == 1) DDG_LAUNCH((conv3x3_tiled_kernel<C, W, 1>), dim3(grid), dim3(256), Cfg::LDS_BYTES, s, a);
+  else if (a.st.mode == 2) DDG_LAUNCH((conv3x3_tiled_kernel<C, W, 2>), dim3(grid), dim3(256), Cfg::LDS_BYTES, s, a);
+  else DDG_LAUNCH((conv3x3_tiled_kernel<C, W, 0>), dim3(grid), dim3(256), Cfg::LDS_BYTES, s, a);
   return hipGetLastError();
 }
 
@@ -526,7 +529,7 @@ hipError_t conv_tiled_launch(const void* in, const float* scale, const float* sh
                              const void* res, void* y_out, int groups, int vec_stride, const WgradFuse* apply,
                              const WgradPair* pair, const BnReduceRide* ride) {
   if (groups < 1 || N % groups != 0 || grid % groups != 0) return hipErrorInvalidValue;
-  if (groups > 1 && (st.mode != 1 || add_g)) return hipErrorInvalidValue;   // forward only
+  if (groups > 2 || (groups > 1 && st.mode != 1) || (st.mode == 1 && add_g)) return hipErrorInvalidValue;   // two groups: forward only
   ConvTiledArgs a{};
   if (apply) {
     if (groups != 1 || res || !apply->rows) return hipErrorInvalidValue;
@@ -539,7 +542,7 @@ hipError_t conv_tiled_launch(const void* in, const float* scale, const float* sh
   a.res = (const bf16_t*)res; a.y_out = (bf16_t*)y_out;
   if (in_rows) a.in_rows = *in_rows; else a.in_rows = BnRows{};
   a.out = (bf16_t*)out; a.st = st; a.add_g = (const bf16_t*)add_g;
-  a.add_mask = (const bf16_t*)add_mask; a.N = N; a.H = H; a.tiles = N * (H / 8);
+  a.add_mask = (const bf16_t*)add_mask; a.N = N; a.H = H; a.tiles = N * (H / 8); a.img = ImgOf::make(H / 8, a.tiles);
   if ((size_t)N * H * W * C >= ((size_t)1 << 31)) return hipErrorInvalidValue;   // 32-bit element offsets inside
   WgradTiledArgs wa{};
   if (pair) {

@@ -4,7 +4,7 @@
 // fp32 matrix instruction mfma_f32_16x16x4_f32 (one element per lane and operand, k = 4).
 //
 // Forward / input gradient: a workgroup stages the (8+2) x (W+2) halo tile of its input once in
-// LDS (NHWC, each pixel padded by 16 bytes); while staging the input can be turned into the
+// LDS (NHWC); while staging the input can be turned into the
 // tensor it stands for: relu(x*scale+shift) (batch norm + ReLU of the layer before, the vectors
 // final or derived from that layer's partial statistics rows), relu(x*scale+shift + res) (the
 // output of the residual block before, which the kernel also stores), or the batch-norm backward
@@ -36,6 +36,7 @@ struct ConvTiledF32Args {
   const float* add_g; const float* add_mask;
   const float* bz; const float* bmask; const float* bmscale; const float* bmshift; BnBwdRows brows; float* dz_out;
   int N, H, tiles, groups, vec_stride;
+  ImgOf img;
 };
 
 struct WgradTiledF32Args {
@@ -52,8 +53,9 @@ struct ConvTiledF32Cfg {
   // 64 channels: tiles of 4 rows, so that a minibatch of 128 8x8 maps has a tile for every
   // compute unit (the fp32 matrix instruction makes these layers compute-bound)
   static constexpr int TH = C == 64 ? 4 : 8, ROWS = TH + 2, WC = W + 2;
-  static constexpr int PIX = C * 4 + 16;                 // bytes per staged pixel
-  static constexpr int TILE_BYTES = ROWS * WC * PIX;
+  static constexpr int PIX = C * 4 + 32;                 // bytes per staged pixel and row: fragment reads without
+  static constexpr int ROWB = W == 8 ? (WC * PIX + 255) / 256 * 256 : WC * PIX;   // bank conflicts, as in the bf16 kernels
+  static constexpr int TILE_BYTES = ROWS * ROWB, LDS_BYTES = TILE_BYTES + 16;
   static constexpr int CH = C / 4;                       // 16-byte chunks per pixel
   static constexpr int NCHUNK = ROWS * WC * CH;
   static constexpr int PER_THREAD = (NCHUNK + 255) / 256;
@@ -72,58 +74,76 @@ template <int C, int W, int MODE, int XF>
 __device__ __forceinline__ void conv3x3_tiled_f32_body(const ConvTiledF32Args& a, unsigned char* tile, int bidx, int gdim) {
   using Cfg = ConvTiledF32Cfg<C, W>;
   constexpr bool RES = XF == XF32_RES, APPLY = XF == XF32_APPLY || XF == XF32_APPLY_MASK;
-  constexpr int TH = Cfg::TH, WC = Cfg::WC, PIX = Cfg::PIX, CH = Cfg::CH, NCHUNK = Cfg::NCHUNK;
+  constexpr int TH = Cfg::TH, WC = Cfg::WC, PIX = Cfg::PIX, ROWB = Cfg::ROWB, CH = Cfg::CH, NCHUNK = Cfg::NCHUNK;
   constexpr int PT = Cfg::PER_THREAD, KSTEPS = Cfg::KSTEPS, PG = Cfg::PG, COB = Cfg::COB, NB = Cfg::NB;
-  static_assert(PT <= 8, "four bits per chunk in one word");
+  static_assert(PT <= 10, "three bits per chunk in one word");
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l16 = lane & 15, lg = lane >> 4;
   const int pgrp = wave % PG, cb = wave / PG;
-  const int tiles_per_img = a.H / TH;
-  const int g1 = gdim / a.groups;
-  const int grp = bidx / g1, bl = bidx - grp * g1;
-  const int tiles_g = a.tiles / a.groups, t_end = (grp + 1) * tiles_g;
+  // this workgroup's group (one of at most two), its index among the group's workgroups, the group's tile range
+  const int g1 = gdim >> (a.groups - 1);
+  const int grp = bidx >= g1 ? 1 : 0, bl = bidx - grp * g1;
+  const int tiles_g = a.tiles >> (a.groups - 1), t_end = (grp + 1) * tiles_g;
+
+  // what the on-load transform waits for is requested before everything else
+  BnFwdRows<C> fwd;
+  BnBwdFromRows<C> bwd;
+  BnRows in_rows = a.in_rows;
+  float bms = 1.f, bmh = 0.f;
+  const int vo = grp * a.vec_stride;
+  if (APPLY) {
+    bwd.request(a.brows);
+    if (a.bmscale && tid < C) { bms = a.bmscale[tid]; bmh = a.bmshift[tid]; }
+  } else if (in_rows.partial) {
+    in_rows.partial += (size_t)grp * in_rows.rows * 2 * C;
+    in_rows.mean += vo; in_rows.invstd += vo; in_rows.scale += vo; in_rows.shift += vo;
+    fwd.request(in_rows);
+  } else if (a.scale && tid < C) {
+    bms = a.scale[vo + tid]; bmh = a.shift[vo + tid];
+  }
 
   // ---- staging map (the same for every tile): chunk v = tid + i*256 -> halo pixel, 4 channels
   const int my_ch = tid % CH;
-  int goff[PT], loff[PT];
-  unsigned srows = 0;    // 4 bits per chunk: halo row + 1; 0: no chunk, or a pad column (stays zero)
+  unsigned goff[PT];   // byte offset of the chunk from column 0 of the tile's first halo row
+  unsigned out = 0;    // 3 bits per chunk: in the first / the last halo row, in a pad column (or no chunk)
+  unsigned own = 0;    // bit i: chunk i lies in the tile's own rows, which this workgroup stores
+  int loff[PT];        // LDS byte offset (no chunk: behind the tile)
 #pragma unroll
   for (int i = 0; i < PT; ++i) {
     const int v = tid + i * 256;
     const int px = v / CH;
     const int rr = px / WC, cc = px - rr * WC;
     const bool col_ok = v < NCHUNK && cc >= 1 && cc <= W;
-    srows |= (col_ok ? (unsigned)(rr + 1) : 0u) << (4 * i);
-    goff[i] = ((rr - 1) * W + (cc - 1)) * C + my_ch * 4;
-    loff[i] = v < NCHUNK ? px * PIX + my_ch * 16 : -1;
+    out |= ((rr == 0 ? 1u : 0u) | (rr == TH + 1 ? 2u : 0u) | (col_ok ? 0u : 4u)) << (3 * i);
+    own |= (col_ok && rr >= 1 && rr <= TH ? 1u : 0u) << i;
+    goff[i] = (unsigned)((rr * W + cc - 1) * C + my_ch * 4) * 4;
+    loff[i] = v < NCHUNK ? rr * ROWB + cc * PIX + my_ch * 16 : Cfg::TILE_BYTES;
   }
   float4 stage[PT], stage2[(RES || APPLY) ? PT : 1], stage3[XF == XF32_APPLY_MASK ? PT : 1];
-  unsigned inimg = 0;       // bit i: chunk i of the tile in flight lies inside the image
-  unsigned tile_base = 0;   // element offset of the staged tile's first pixel (32 bits: the host checks)
-  auto issue_loads = [&](int t) {
-    const int n = t / tiles_per_img, r0 = (t - n * tiles_per_img) * TH;
-    const unsigned tb = (unsigned)((n * a.H + r0) * W) * C;
-    tile_base = tb;
-    inimg = 0;
+  // element offset of column 0 of tile t's first halo row (it may lie before the tensor, where nothing is loaded), and which
+  // chunks of it lie outside the image
+  auto tile_at = [&](int t, unsigned& outside) {
+    const int n = a.img.of(t), r0 = (t - n * a.img.d) * TH;
+    outside = 4u | (r0 == 0 ? 1u : 0u) | (r0 + TH == a.H ? 2u : 0u);
+    return ((ptrdiff_t)(n * a.H + r0) - 1) * (W * C);
+  };
+  auto resource = [&](const float* p, ptrdiff_t at, bool any = true) { return wide_rsrc(p + at, any ? (TH + 2) * W * C * 4 : 0); };
+  auto issue_loads = [&](int t) {     // (a tile past the last: loads that fetch nothing, so that their number is the same)
+    unsigned outside;
+    const ptrdiff_t at = tile_at(t, outside);
+    const bool any = t < t_end;
+    const wide_rsrc_t r1 = resource(a.in, at, any);
+    const wide_rsrc_t r2 = resource(RES ? a.res : APPLY ? a.bz : a.in, at, any), r3 = resource(XF == XF32_APPLY_MASK ? a.bmask : a.in, at, any);
 #pragma unroll
     for (int i = 0; i < PT; ++i) {
-      stage[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-      const int sr = (int)((srows >> (4 * i)) & 15u) - 1;
-      const int ih = r0 - 1 + sr;
-      if (sr >= 0 && ih >= 0 && ih < a.H) {
-        inimg |= 1u << i;
-        stage[i] = *reinterpret_cast<const float4*>(a.in + tb + goff[i]);
-        if (RES) stage2[i] = *reinterpret_cast<const float4*>(a.res + tb + goff[i]);
-        if (APPLY) stage2[i] = *reinterpret_cast<const float4*>(a.bz + tb + goff[i]);
-        if (XF == XF32_APPLY_MASK) stage3[i] = *reinterpret_cast<const float4*>(a.bmask + tb + goff[i]);
-      }
+      const unsigned o = (out & (outside << (3 * i))) ? NOWHERE : goff[i];
+      stage[i] = __builtin_bit_cast(float4, wide_load(r1, o, 0));
+      if (RES || APPLY) stage2[i] = __builtin_bit_cast(float4, wide_load(r2, o, 0));
+      if (XF == XF32_APPLY_MASK) stage3[i] = __builtin_bit_cast(float4, wide_load(r3, o, 0));
     }
   };
-  int t = grp * tiles_g + bl;
-  if (t < t_end) issue_loads(t);
-
-  // ---- this wave's weights: KSTEPS fragments of its output-channel block
+  // ---- this wave's weights: KSTEPS fragments of its output-channel block (before the tile, as in the bf16 kernels)
   const float* wsrc = a.wpack + ((size_t)cb * 64 + lane) * 4;     // + ks * COB*64*4
   float4 wf[Cfg::WREG ? KSTEPS : 1];
   if (Cfg::WREG) {
@@ -131,8 +151,18 @@ __device__ __forceinline__ void conv3x3_tiled_f32_body(const ConvTiledF32Args& a
     for (int ks = 0; ks < KSTEPS; ++ks) wf[ks] = *reinterpret_cast<const float4*>(wsrc + (size_t)ks * COB * 64 * 4);
   }
 
+  int t = grp * tiles_g + bl;
+  issue_loads(t);
+
+  float below[4] = {0.f, 1.f, 1.f, 0.f};   // mode 2: constants of the BN below (mean, invstd, mask scale, mask shift)
+  if (MODE == 2 && tid < C) {
+    below[0] = a.st.zmean[tid]; below[1] = a.st.zinvstd[tid];
+    if (a.st.mscale) { below[2] = a.st.mscale[tid]; below[3] = a.st.mshift[tid]; }
+  }
+
+
   const int ptl = pgrp * (NB * 16) + l16;
-  const int lane_base = ((ptl / W) * WC + (ptl % W)) * PIX + lg * 16;
+  const int lane_base = (ptl / W) * ROWB + (ptl % W) * PIX + lg * 16;
   const int out_lane = ptl * C + cb * 16 + lg * 4;
 
   // ---- per-channel vectors of the on-load transform, in LDS (derived while the first loads fly)
@@ -140,59 +170,54 @@ __device__ __forceinline__ void conv3x3_tiled_f32_body(const ConvTiledF32Args& a
   __shared__ __align__(16) float s_sc[APPLY ? 4 : C], s_sh[APPLY ? 4 : C];
   __shared__ __align__(16) float s_coef[APPLY ? 5 * C : 4];   // A, B, C0, mask scale, mask shift
   if (APPLY) {
-    if (tid < C) {
-      s_coef[3 * C + tid] = a.bmscale ? a.bmscale[tid] : 1.f;
-      s_coef[4 * C + tid] = a.bmscale ? a.bmshift[tid] : 0.f;
-    }
-    bn_bwd_from_rows<C>(a.brows, s_coef, bidx == 0);   // ends with a barrier
-  } else if (a.in_rows.partial) {
-    BnRows r = a.in_rows;
-    r.partial += (size_t)grp * r.rows * 2 * C;
-    const int vo = grp * a.vec_stride;
-    r.mean += vo; r.invstd += vo; r.scale += vo; r.shift += vo;
-    bn_fwd_from_rows<C>(r, s_sc, s_sh, bl == 0);
+    if (tid < C) { s_coef[3 * C + tid] = bms; s_coef[4 * C + tid] = bmh; }
+    bwd.finish(a.brows, s_coef, bidx == 0);   // ends with a barrier
+  } else if (in_rows.partial) {
+    fwd.finish(in_rows, s_sc, s_sh, bl == 0);
   } else if (a.scale) {
-    const int vo = grp * a.vec_stride;
-    if (tid < C) { s_sc[tid] = a.scale[vo + tid]; s_sh[tid] = a.shift[vo + tid]; }
+    if (tid < C) { s_sc[tid] = bms; s_sh[tid] = bmh; }
     __syncthreads();
   }
-  auto write_stage = [&]() {
-    const unsigned stage_base = tile_base;
+  auto write_stage = [&](int t) {
+    unsigned outside;
+    const ptrdiff_t at = tile_at(t, outside);
+    auto ld4 = [&](const float* p) { return *reinterpret_cast<const float4*>(p + my_ch * 4); };
+    float4 k0, k1, k2, m0, m1;      // this thread's channels: A, B, C0, the mask's scale and shift; or scale and shift
+    wide_rsrc_t ro;
+    if (APPLY) {
+      k0 = ld4(&s_coef[0]); k1 = ld4(&s_coef[C]); k2 = ld4(&s_coef[2 * C]); m0 = ld4(&s_coef[3 * C]); m1 = ld4(&s_coef[4 * C]);
+      ro = resource(a.dz_out, at);
+    } else if (xform) {
+      k0 = ld4(s_sc); k1 = ld4(s_sh);
+      if (RES) ro = a.y_out ? resource(a.y_out, at) : wide_rsrc(nullptr, 0);
+    }
 #pragma unroll
     for (int i = 0; i < PT; ++i) {
-      if (loff[i] >= 0) {
-        float4 q = stage[i];
-        const unsigned sr1 = (srows >> (4 * i)) & 15u;   // halo row + 1
-        const bool own_row = sr1 >= 2 && sr1 <= TH + 1;  // the tile's own rows are this workgroup's to store
-        if (APPLY && ((inimg >> i) & 1u)) {
+      float4 q = stage[i];
+      if (APPLY || xform) {
+        if (APPLY) {
           const float4 zz = stage2[i];
           if (a.bmask) {
             const float4 mk = XF == XF32_APPLY_MASK ? stage3[i] : stage2[i];
-            const float4 ms = *reinterpret_cast<const float4*>(&s_coef[3 * C + my_ch * 4]);
-            const float4 mh = *reinterpret_cast<const float4*>(&s_coef[4 * C + my_ch * 4]);
-            q.x = (mk.x * ms.x + mh.x) > 0.f ? q.x : 0.f; q.y = (mk.y * ms.y + mh.y) > 0.f ? q.y : 0.f;
-            q.z = (mk.z * ms.z + mh.z) > 0.f ? q.z : 0.f; q.w = (mk.w * ms.w + mh.w) > 0.f ? q.w : 0.f;
+            q.x = (mk.x * m0.x + m1.x) > 0.f ? q.x : 0.f; q.y = (mk.y * m0.y + m1.y) > 0.f ? q.y : 0.f;
+            q.z = (mk.z * m0.z + m1.z) > 0.f ? q.z : 0.f; q.w = (mk.w * m0.w + m1.w) > 0.f ? q.w : 0.f;
           }
-          const float4 cA = *reinterpret_cast<const float4*>(&s_coef[my_ch * 4]);
-          const float4 cB = *reinterpret_cast<const float4*>(&s_coef[C + my_ch * 4]);
-          const float4 cC = *reinterpret_cast<const float4*>(&s_coef[2 * C + my_ch * 4]);
-          q.x = cA.x * q.x + (cB.x * zz.x + cC.x); q.y = cA.y * q.y + (cB.y * zz.y + cC.y);
-          q.z = cA.z * q.z + (cB.z * zz.z + cC.z); q.w = cA.w * q.w + (cB.w * zz.w + cC.w);
-          if (own_row) *reinterpret_cast<float4*>(a.dz_out + stage_base + goff[i]) = q;
-        }
-        if (xform && ((inimg >> i) & 1u)) {
-          const float4 sc = *reinterpret_cast<const float4*>(&s_sc[my_ch * 4]);
-          const float4 sh = *reinterpret_cast<const float4*>(&s_sh[my_ch * 4]);
-          q.x = q.x * sc.x + sh.x; q.y = q.y * sc.y + sh.y; q.z = q.z * sc.z + sh.z; q.w = q.w * sc.w + sh.w;
+          q.x = k0.x * q.x + (k1.x * zz.x + k2.x); q.y = k0.y * q.y + (k1.y * zz.y + k2.y);
+          q.z = k0.z * q.z + (k1.z * zz.z + k2.z); q.w = k0.w * q.w + (k1.w * zz.w + k2.w);
+        } else {
+          q.x = q.x * k0.x + k1.x; q.y = q.y * k0.y + k1.y; q.z = q.z * k0.z + k1.z; q.w = q.w * k0.w + k1.w;
           if (RES) {
             const float4 r = stage2[i];
             q.x += r.x; q.y += r.y; q.z += r.z; q.w += r.w;
           }
           q.x = q.x > 0.f ? q.x : 0.f; q.y = q.y > 0.f ? q.y : 0.f; q.z = q.z > 0.f ? q.z : 0.f; q.w = q.w > 0.f ? q.w : 0.f;
-          if (RES && a.y_out && own_row) *reinterpret_cast<float4*>(a.y_out + stage_base + goff[i]) = q;
         }
-        *reinterpret_cast<float4*>(tile + loff[i]) = q;
+        // zero padding comes after the transform
+        const bool in = !(out & (outside << (3 * i)));
+        q.x = in ? q.x : 0.f; q.y = in ? q.y : 0.f; q.z = in ? q.z : 0.f; q.w = in ? q.w : 0.f;
+        if (APPLY || RES) wide_store(ro, __builtin_bit_cast(uint4, q), (own >> i) & 1u ? goff[i] : NOWHERE);
       }
+      *reinterpret_cast<float4*>(tile + loff[i]) = q;
     }
   };
 
@@ -201,28 +226,33 @@ __device__ __forceinline__ void conv3x3_tiled_f32_body(const ConvTiledF32Args& a
   __shared__ __align__(16) float s_below[MODE == 2 ? 4 * C : 4];
   const float* st_mask = reinterpret_cast<const float*>(a.st.mask);
   const float* st_z = reinterpret_cast<const float*>(a.st.z);
-  const bool two_tensors = MODE == 2 && st_z != st_mask;
+  const bool add = MODE != 1 && a.add_g != nullptr;   // (a shortcut gradient is added to gradients only)
   if (MODE == 2) {
-    if (tid < C) {
-      s_below[tid] = a.st.zmean[tid]; s_below[C + tid] = a.st.zinvstd[tid];
-      s_below[2 * C + tid] = a.st.mscale ? a.st.mscale[tid] : 1.f;
-      s_below[3 * C + tid] = a.st.mscale ? a.st.mshift[tid] : 0.f;
-    }
+    if (tid < C) { s_below[tid] = below[0]; s_below[C + tid] = below[1]; s_below[2 * C + tid] = below[2]; s_below[3 * C + tid] = below[3]; }
     // (made visible by the barriers of the tile loop before any epilogue runs)
   }
 
+  if (Cfg::WREG) {   // (the weights' wait, before the loop)
+#pragma unroll
+    for (int ks = 0; ks < KSTEPS; ++ks) asm volatile("" : "+v"(wf[ks].x), "+v"(wf[ks].y), "+v"(wf[ks].z), "+v"(wf[ks].w));
+  }
   for (; t < t_end; t += g1) {
     __syncthreads();            // the previous tile has been consumed
-    write_stage();
+    write_stage(t);
     __syncthreads();
-    const int tn = t + g1;
-    if (tn < t_end) issue_loads(tn);   // in flight during the matrix phase
-
-    const int n = t / tiles_per_img, r0 = (t - n * tiles_per_img) * TH;
+    const int n = a.img.of(t), r0 = (t - n * a.img.d) * TH;
     const unsigned obase = (unsigned)((n * a.H + r0) * W) * C + out_lane;
+    // 64 channels: the weight fragments do not fit the registers; they come from the packed
+    // operand (L1/L2 resident) through a ring of four, requested three to four k-steps ahead
+    float4 wq[Cfg::WREG ? 1 : 4];
+    if (!Cfg::WREG) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) wq[j] = *reinterpret_cast<const float4*>(wsrc + (size_t)j * COB * 64 * 4);
+    }
+    issue_loads(t + g1);               // in flight during the matrix phase
     // what the epilogue reads, requested now
     float4 eg[NB], em[NB], ek[NB], ez[NB];
-    if (a.add_g) {
+    if (add) {
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
         eg[i] = *reinterpret_cast<const float4*>(a.add_g + obase + i * 16 * C);
@@ -233,30 +263,23 @@ __device__ __forceinline__ void conv3x3_tiled_f32_body(const ConvTiledF32Args& a
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
         ek[i] = *reinterpret_cast<const float4*>(st_mask + obase + i * 16 * C);
-        if (two_tensors) ez[i] = *reinterpret_cast<const float4*>(st_z + obase + i * 16 * C);
+        ez[i] = *reinterpret_cast<const float4*>(st_z + obase + i * 16 * C);   // (often the same tensor, and then in L1)
       }
     }
 
     f32x4_t acc[NB];
 #pragma unroll
     for (int i = 0; i < NB; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    // 64 channels: the weight fragments do not fit the registers; they come from the packed
-    // operand (L1/L2 resident) through a ring of four, requested three to four k-steps ahead
-    float4 wq[Cfg::WREG ? 1 : 4];
-    if (!Cfg::WREG) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) wq[j] = *reinterpret_cast<const float4*>(wsrc + (size_t)j * COB * 64 * 4);
-    }
 #pragma unroll
     for (int ks = 0; ks < KSTEPS; ++ks) {
       // k-values ks*16 + lg*4 .. +3: tap k/C, channels k%C (a fragment never straddles taps)
       const int kidx = ks * 16;
       const int tap = kidx / C, c0 = kidx % C;
-      const unsigned char* kp = tile + lane_base + ((tap / 3) * WC + (tap % 3)) * PIX + c0 * 4;
+      const unsigned char* kp = tile + lane_base + (tap / 3) * ROWB + (tap % 3) * PIX + c0 * 4;
       const float4 w4 = Cfg::WREG ? wf[Cfg::WREG ? ks : 0] : wq[Cfg::WREG ? 0 : (ks & 3)];
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
-        const int blk = (((i * 16) / W) * WC + (i * 16) % W) * PIX;   // constant after unrolling
+        const int blk = ((i * 16) / W) * ROWB + ((i * 16) % W) * PIX;   // constant after unrolling
         const float4 af = *reinterpret_cast<const float4*>(kp + blk);
         acc[i] = Mma<float>::mma(w4, af, acc[i]);
       }
@@ -274,7 +297,7 @@ __device__ __forceinline__ void conv3x3_tiled_f32_body(const ConvTiledF32Args& a
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
       float v[4] = {acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
-      if (a.add_g) {
+      if (add) {
         float g[4] = {eg[i].x, eg[i].y, eg[i].z, eg[i].w};
         if (a.add_mask) {
           const float mk[4] = {em[i].x, em[i].y, em[i].z, em[i].w};
@@ -293,8 +316,7 @@ __device__ __forceinline__ void conv3x3_tiled_f32_body(const ConvTiledF32Args& a
         const float4 bis = *reinterpret_cast<const float4*>(&s_below[C + cq]);
         const float4 bms = *reinterpret_cast<const float4*>(&s_below[2 * C + cq]);
         const float4 bmh = *reinterpret_cast<const float4*>(&s_below[3 * C + cq]);
-        const float zz[4] = {two_tensors ? ez[i].x : mk[0], two_tensors ? ez[i].y : mk[1],
-                             two_tensors ? ez[i].z : mk[2], two_tensors ? ez[i].w : mk[3]};
+        const float zz[4] = {ez[i].x, ez[i].y, ez[i].z, ez[i].w};
         const float mu4[4] = {bmu.x, bmu.y, bmu.z, bmu.w}, is4[4] = {bis.x, bis.y, bis.z, bis.w};
         const float ms4[4] = {bms.x, bms.y, bms.z, bms.w}, mh4[4] = {bmh.x, bmh.y, bmh.z, bmh.w};
 #pragma unroll
@@ -319,12 +341,7 @@ __device__ __forceinline__ void conv3x3_tiled_f32_body(const ConvTiledF32Args& a
     __shared__ float red[4][2][16];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      float s1 = ssum[j], s2 = ssq[j];
-#pragma unroll
-      for (int o = 1; o < 16; o <<= 1) {
-        s1 += __shfl_xor(s1, o, 64);
-        s2 += __shfl_xor(s2, o, 64);
-      }
+      const float s1 = row_sum16(ssum[j]), s2 = row_sum16(ssq[j]);
       if (l16 == 0) { red[wave][0][lg * 4 + j] = s1; red[wave][1][lg * 4 + j] = s2; }
     }
     __syncthreads();
@@ -596,7 +613,7 @@ static hipError_t conv_tiled_f32_launch_t(const ConvTiledF32Args& a, int grid, h
     using WCfg = WgradTiledF32Cfg<C, W>;
     if (!wa || !a.bz || a.st.mode != 2 || a.scale || a.in_rows.partial || !a.brows.partial || !a.dz_out || C == 16 || ride->C != C || ride->grid < 1)
       return hipErrorInvalidValue;
-    constexpr int lds = Cfg::TILE_BYTES > WCfg::LDS ? Cfg::TILE_BYTES : WCfg::LDS;
+    constexpr int lds = Cfg::LDS_BYTES > WCfg::LDS ? Cfg::LDS_BYTES : WCfg::LDS;
     if constexpr (C != 16) {
       const dim3 g(grid + wg_rows + ride->grid);
       if (a.bmask && a.bmask != a.bz) DDG_LAUNCH((bwd_down_f32_kernel<C, W, XF32_APPLY_MASK>), g, dim3(256), lds, s, a, *wa, *ride, grid, wg_rows);
@@ -609,7 +626,7 @@ static hipError_t conv_tiled_f32_launch_t(const ConvTiledF32Args& a, int grid, h
     using WCfg = WgradTiledF32Cfg<C, W>;
     if (!a.bz || a.st.mode == 1 || a.scale || a.in_rows.partial || !a.brows.partial || !a.dz_out || wg_rows < 1)
       return hipErrorInvalidValue;
-    constexpr int lds = Cfg::TILE_BYTES > WCfg::LDS ? Cfg::TILE_BYTES : WCfg::LDS;
+    constexpr int lds = Cfg::LDS_BYTES > WCfg::LDS ? Cfg::LDS_BYTES : WCfg::LDS;
     static_assert(lds <= 48 * 1024, "dynamic LDS within the default limit");
     const bool own_mask = a.bmask && a.bmask != a.bz;
     const dim3 g(grid + wg_rows);
@@ -624,20 +641,20 @@ static hipError_t conv_tiled_f32_launch_t(const ConvTiledF32Args& a, int grid, h
   }
   if (a.res) {
     if (a.st.mode != 1 || !(a.scale || a.in_rows.partial)) return hipErrorInvalidValue;
-    DDG_LAUNCH((conv3x3_tiled_f32_kernel<C, W, 1, XF32_RES>), dim3(grid), dim3(256), Cfg::TILE_BYTES, s, a);
+    DDG_LAUNCH((conv3x3_tiled_f32_kernel<C, W, 1, XF32_RES>), dim3(grid), dim3(256), Cfg::LDS_BYTES, s, a);
   } else if (a.bz) {
     if (a.st.mode == 1 || a.scale || a.in_rows.partial || !a.brows.partial || !a.dz_out) return hipErrorInvalidValue;
     const bool own_mask = a.bmask && a.bmask != a.bz;
     if (a.st.mode == 2) {
-      if (own_mask) DDG_LAUNCH((conv3x3_tiled_f32_kernel<C, W, 2, XF32_APPLY_MASK>), dim3(grid), dim3(256), Cfg::TILE_BYTES, s, a);
-      else DDG_LAUNCH((conv3x3_tiled_f32_kernel<C, W, 2, XF32_APPLY>), dim3(grid), dim3(256), Cfg::TILE_BYTES, s, a);
+      if (own_mask) DDG_LAUNCH((conv3x3_tiled_f32_kernel<C, W, 2, XF32_APPLY_MASK>), dim3(grid), dim3(256), Cfg::LDS_BYTES, s, a);
+      else DDG_LAUNCH((conv3x3_tiled_f32_kernel<C, W, 2, XF32_APPLY>), dim3(grid), dim3(256), Cfg::LDS_BYTES, s, a);
     } else {
-      if (own_mask) DDG_LAUNCH((conv3x3_tiled_f32_kernel<C, W, 0, XF32_APPLY_MASK>), dim3(grid), dim3(256), Cfg::TILE_BYTES, s, a);
-      else DDG_LAUNCH((conv3x3_tiled_f32_kernel<C, W, 0, XF32_APPLY>), dim3(grid), dim3(256), Cfg::TILE_BYTES, s, a);
+      if (own_mask) DDG_LAUNCH((conv3x3_tiled_f32_kernel<C, W, 0, XF32_APPLY_MASK>), dim3(grid), dim3(256), Cfg::LDS_BYTES, s, a);
+      else DDG_LAUNCH((conv3x3_tiled_f32_kernel<C, W, 0, XF32_APPLY>), dim3(grid), dim3(256), Cfg::LDS_BYTES, s, a);
     }
-  } else if (a.st.mode == 1) DDG_LAUNCH((conv3x3_tiled_f32_kernel<C, W, 1, XF32_PLAIN>), dim3(grid), dim3(256), Cfg::TILE_BYTES, s, a);
-  else if (a.st.mode == 2) DDG_LAUNCH((conv3x3_tiled_f32_kernel<C, W, 2, XF32_PLAIN>), dim3(grid), dim3(256), Cfg::TILE_BYTES, s, a);
-  else DDG_LAUNCH((conv3x3_tiled_f32_kernel<C, W, 0, XF32_PLAIN>), dim3(grid), dim3(256), Cfg::TILE_BYTES, s, a);
+  } else if (a.st.mode == 1) DDG_LAUNCH((conv3x3_tiled_f32_kernel<C, W, 1, XF32_PLAIN>), dim3(grid), dim3(256), Cfg::LDS_BYTES, s, a);
+  else if (a.st.mode == 2) DDG_LAUNCH((conv3x3_tiled_f32_kernel<C, W, 2, XF32_PLAIN>), dim3(grid), dim3(256), Cfg::LDS_BYTES, s, a);
+  else DDG_LAUNCH((conv3x3_tiled_f32_kernel<C, W, 0, XF32_PLAIN>), dim3(grid), dim3(256), Cfg::LDS_BYTES, s, a);
   return hipGetLastError();
 }
 
@@ -648,7 +665,7 @@ hipError_t conv_tiled_f32_launch(const void* in, const float* scale, const float
                                  const void* res, void* y_out, int groups, int vec_stride, const WgradFuse* apply,
                                  const WgradPair* pair, const BnReduceRide* ride) {
   if (groups < 1 || N % groups != 0 || grid % groups != 0) return hipErrorInvalidValue;
-  if (groups > 1 && (st.mode != 1 || add_g)) return hipErrorInvalidValue;   // forward only
+  if (groups > 2 || (groups > 1 && st.mode != 1) || (st.mode == 1 && add_g)) return hipErrorInvalidValue;   // two groups: forward only
   if ((size_t)N * H * W * C >= ((size_t)1 << 31)) return hipErrorInvalidValue;   // 32-bit element offsets inside
   ConvTiledF32Args a{};
   if (apply) {
@@ -662,7 +679,7 @@ hipError_t conv_tiled_f32_launch(const void* in, const float* scale, const float
   a.res = (const float*)res; a.y_out = (float*)y_out;
   if (in_rows) a.in_rows = *in_rows; else a.in_rows = BnRows{};
   a.out = (float*)out; a.st = st; a.add_g = (const float*)add_g; a.add_mask = (const float*)add_mask;
-  a.N = N; a.H = H; a.tiles = N * (H / (C == 64 ? 4 : 8));
+  a.N = N; a.H = H; a.tiles = N * (H / (C == 64 ? 4 : 8)); a.img = ImgOf::make(H / (C == 64 ? 4 : 8), a.tiles);
   WgradTiledF32Args wa{};
   if (pair) {
     const int wtiles = N * (H / (C == 64 ? 4 : 8));

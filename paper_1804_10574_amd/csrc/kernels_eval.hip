@@ -51,7 +51,6 @@ constexpr int DUMP_BYTES = 64 * 16;               // where lanes without a pixel
 // the LDS regions change roles at run time: without help it makes flat accesses of both kinds, which
 // wait for both memories. Pointers from the table are cast to the global address space, LDS is
 // addressed by byte offsets from its start.
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 #define EV_GLOBAL __attribute__((address_space(1)))
 template <typename V> __device__ __forceinline__ V load16(const void* p) {
   static_assert(sizeof(V) == 16, "16-byte vectors");

@@ -55,7 +55,6 @@ constexpr int BUF = 2 * OPB;
 constexpr int LDS = 2 * BUF;               // 73728
 constexpr int PLACES = 512;                // workgroups that run at the same time: two per compute unit
 constexpr int SLICE_MAX = 49;              // steps of a slice, unless its layer alone fills the chip
-constexpr unsigned NOWHERE = 0xfffffff0u;  // past the end of any tensor: the load gives zeros
 }
 
 typedef short wtr4_t __attribute__((ext_vector_type(4)));
