@@ -15,7 +15,7 @@ constexpr int STATS_CMAX = 64;
 // 256 threads, C a compile-time constant in {16, 32, 64}. f(c, t1, t2) runs once per channel (in
 // thread c) with the two column sums. A row is 2*C floats; a thread owns one 16-byte column
 // group and every NSL-th row, keeps its loads in flight together (unconditional: a row past the end
-// repeats the last one and counts as zero) and adds its rows in order (fp32, like the rows
+// reads as zeros) and adds its rows in order (fp32, like the rows
 // themselves). The NSL row slices of a column are then combined in a fixed order in
 // fp64 in two short steps (four values per thread, then 256/(2C) per column), all unrolled.
 // This sits in the prologue of nearly every training kernel, where latency is all that counts: the rows and the
@@ -32,11 +32,10 @@ struct StatRows {
   float4 v[U];
 
   __device__ __forceinline__ void load(const float* __restrict__ partial, int rows, int r0) {
-    const float4* __restrict__ p4 = reinterpret_cast<const float4*>(partial) + threadIdx.x % NCOL4;
+    const wide_rsrc_t res = wide_rsrc(partial, (size_t)rows * (NCOL4 * 16));
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int rr = r0 + u * NSL;
-      v[u] = p4[(unsigned)(rr < rows ? rr : rows - 1) * NCOL4];
+      v[u] = __builtin_bit_cast(float4, wide_load(res, (unsigned)((r0 + u * NSL) * NCOL4 + threadIdx.x % NCOL4) * 16, 0));
     }
   }
   __device__ __forceinline__ void request(const float* __restrict__ partial, int rows) { load(partial, rows, threadIdx.x / NCOL4); }
@@ -50,8 +49,7 @@ struct StatRows {
     for (int r0 = tid / NCOL4;;) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const bool in = r0 + u * NSL < rows;
-        acc.x += in ? v[u].x : 0.f; acc.y += in ? v[u].y : 0.f; acc.z += in ? v[u].z : 0.f; acc.w += in ? v[u].w : 0.f;
+        acc.x += v[u].x; acc.y += v[u].y; acc.z += v[u].z; acc.w += v[u].w;
       }
       r0 += NSL * U;
       if (r0 >= rows) break;

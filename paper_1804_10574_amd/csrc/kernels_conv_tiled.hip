@@ -253,7 +253,7 @@ __device__ __forceinline__ void conv3x3_tiled_body(const ConvTiledArgs& a, unsig
           for (int j = 0; j < 8; ++j) {
             g[j] = g[j] * k0[j] + k1[j];
             if (RES) g[j] += zz[j];
-            g[j] = g[j] > 0.f ? g[j] : 0.f;
+            g[j] = fmaxf(g[j], 0.f);
           }
         }
         // zero padding comes after the transform

@@ -210,7 +210,7 @@ __device__ __forceinline__ void conv3x3_tiled_f32_body(const ConvTiledF32Args& a
             const float4 r = stage2[i];
             q.x += r.x; q.y += r.y; q.z += r.z; q.w += r.w;
           }
-          q.x = q.x > 0.f ? q.x : 0.f; q.y = q.y > 0.f ? q.y : 0.f; q.z = q.z > 0.f ? q.z : 0.f; q.w = q.w > 0.f ? q.w : 0.f;
+          q.x = fmaxf(q.x, 0.f); q.y = fmaxf(q.y, 0.f); q.z = fmaxf(q.z, 0.f); q.w = fmaxf(q.w, 0.f);
         }
         // zero padding comes after the transform
         const bool in = !(out & (outside << (3 * i)));
