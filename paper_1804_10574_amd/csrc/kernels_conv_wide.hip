@@ -6,8 +6,8 @@
 // 128 channels of one tap, one barrier per chunk.
 //
 //   pixel operand:  64 rows x one chunk of channels, through registers into one of two LDS
-//                   buffers (rows padded by 16 bytes, so the 16 rows of a fragment read fall
-//                   into distinct bank groups); a 3x3 tap is a shifted pixel row, out-of-image
+//                   buffers (rows padded by 32 bytes, an odd multiple of 32 apart: a fragment read takes 4.6
+//                   cycles, at an odd multiple of 16 it took 8.3); a 3x3 tap is a shifted pixel row, out-of-image
 //                   rows are zero: no im2col matrix.
 //   weight operand: the packed operand of the generic kernel is already fragment-ordered
 //                   ([k-step][16-channel block][lane][8]), so a wave loads the fragments it
@@ -32,7 +32,7 @@ namespace ddg {
 namespace wide {
 constexpr int BM = 64, BN = 128;
 constexpr int OROW = BN * 4 + 16;                 // bytes per pixel row of the epilogue's fp32 tile
-constexpr int prow_bytes(int BK) { return BK * 2 + 16; }          // bytes per staged pixel row
+constexpr int prow_bytes(int BK) { return BK * 2 + 32; }          // bytes per staged pixel row
 constexpr int pix_bytes(int BK) { return BM * prow_bytes(BK); }   // one pixel buffer
 // dynamic LDS: the two pixel buffers, later reused by the epilogue's fp32 tile and statistics scratch
 constexpr int lds_bytes(int BK) { return 2 * pix_bytes(BK) > BM * OROW ? 2 * pix_bytes(BK) : BM * OROW; }

@@ -6,7 +6,7 @@
 // A GEMM whose contraction index, the pixel, is the slow index of both NHWC operands. A
 // workgroup owns a 128 (co) x 128 (ci) tile of one tap and a slice of the pixels; it stages
 // 64 pixels of both operands per step exactly as they lie in memory ([pixel][128 channels],
-// row stride 288 bytes) and takes MFMA fragments out of LDS with the transposing read of
+// the 64-byte quarters of a row turned by the pixel modulo 4) and takes MFMA fragments out of LDS with the transposing read of
 // gfx950 (ds_read_b64_tr_b16: a lane ends up with 8 consecutive pixels of one channel). A tap
 // is a shifted pixel row; where the neighbour lies outside the image both rows are zero, which the
 // buffer loads give without an instruction (an offset past the tensor's end).
@@ -26,10 +26,16 @@
 // one 2.7 more; every third one would save 0.7 but is 6.9e-8, more than slices of 2 or 3 steps had at 2548 pixels.
 //
 // Four waves as 2 (co) x 2 (ci), 64 x 64 each = four accumulators of mfma_f32_32x32x16_bf16 (16x16x32 runs at little more
-// than half the rate) and their sums, 231 registers; 72 KB of LDS: two workgroups a compute unit, one of which multiplies
+// than half the rate) and their sums, 256 registers; 64 KB of LDS: two workgroups a compute unit, one of which multiplies
 // while the other waits for its rows. Eight waves, which halve the pixels of a step between them, have room for one set of
-// accumulators only (21.9 us a block). What bounds it: the LDS port (transposing reads of 64 KB a step at about
-// 64 bytes a clock, stores of 32 KB), and the vector instructions that fold beside the matrix instructions.
+// accumulators only (21.9 us a block, before what follows).
+//
+// Rows of 288 bytes made a transposing read 4.4 cycles of the LDS port instead of 2.6; turned rows of 256 do not. A load was
+// requested one contraction before its use; now, between the matrix instructions of the step before, a whole step. Kernel
+// size and activation are constants in the loop, the slice's end is the resource's end. A launch of 512 workgroups (23
+// blocks at 14x14, batch 32): 90.1 us; LDS rows 86.8, a step ahead 84.0, constants 81.7, the same bits. What bounds it:
+// vector instructions, 62 % of the cycles (112 a step fold, 112 form the activation, 40 find the neighbours of 3x3 layers);
+// matrix instructions are 28 %, and the two add up to nearly all of the time.
 #include "ddg_conv_wide.h"
 #include <algorithm>
 #include <cstdlib>
@@ -49,10 +55,10 @@ struct WgwArgs { WgwLayer l[WGRAD_WIDE_LAYERS]; int n, by_xcd; };
 
 namespace wgw {
 constexpr int BP = 64;                     // pixels per step
-constexpr int ROW = 256 + 32;              // bytes per staged pixel (128 channels), 32 modulo 128
-constexpr int OPB = BP * ROW;              // one operand, one buffer: 18432
+constexpr int ROW = 256;                   // bytes per staged pixel (128 channels)
+constexpr int OPB = BP * ROW;              // one operand, one buffer: 16384
 constexpr int BUF = 2 * OPB;
-constexpr int LDS = 2 * BUF;               // 73728
+constexpr int LDS = 2 * BUF;               // 65536
 constexpr int PLACES = 512;                // workgroups that run at the same time: two per compute unit
 constexpr int SLICE_MAX = 49;              // steps of a slice, unless its layer alone fills the chip
 }
@@ -67,7 +73,7 @@ __device__ __forceinline__ bf16x8_t wide_frag_tr(const unsigned char* p) {
   return __builtin_bit_cast(bf16x8_t, make_uint4(l.x, l.y, h.x, h.y));
 }
 
-// A thread's share of one step on its way to LDS: rows prow, prow + 16, .. of dz and x.
+// A thread's share of one step on its way to LDS: rows prow, prow + 16, .. (unit q: row prow + 16*q) of dz and x.
 struct WgwSet { uint4 z[4], x[4]; };
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void wgrad_wide_kernel(WgwArgs args) {
@@ -102,9 +108,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
   // staging map: 16-byte unit tid + q*256 of a 64 x 128 tile = pixel (tid>>4) + 16*q, chunk tid&15
   const int ch = tid & 15, prow = tid >> 4;
+  // Resources cover the rows of the slice, those of x shifted by the tap (49 steps, so offsets stay small whatever the tensor's
+  // size): rows past the slice cost no instruction, rows outside the image get an offset past the end.
   const unsigned zst = a.Cout * 2, xst = a.Cin * 2;
-  const wide_rsrc_t rz = wide_rsrc(a.dz, (size_t)a.M * zst), rx = wide_rsrc(a.x, (size_t)a.M * xst);
-  const int dh = (16 / a.W) % a.H, dw = 16 % a.W;    // 16 pixels further
+  const int first = s0 * BP, rows = m_end - first;
+  const wide_rsrc_t rz = wide_rsrc(a.dz + (size_t)first * a.Cout, (size_t)rows * zst);
+  const wide_rsrc_t rx = wide_rsrc(a.x + ((ptrdiff_t)first + dr * a.W + ds) * a.Cin, (size_t)rows * xst);
+  // the neighbour of pixel `rem` of the image, in column w, is inside it where rem - lo < span and w != edge
+  const unsigned HW = a.H * a.W, lo = dr < 0 ? a.W : 0, span = HW - (dr != 0 ? a.W : 0);
+  const unsigned edge = ds < 0 ? 0u : ds > 0 ? a.W - 1u : ~0u;
+  const unsigned drem = 16 % HW, dw = 16 % (unsigned)a.W;        // 16 pixels further
   // per-channel constants of this thread's 8 input channels (the same in every step)
   const bool xform = a.scale != nullptr;
   float tsc[8], tsh[8];
@@ -114,23 +127,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int e = 0; e < 8; ++e) { tsc[e] = a.scale[ci0 + ch * 8 + e]; tsh[e] = a.shift[ci0 + ch * 8 + e]; }
   }
-  // (a row that does not exist is relu(shift) after the transform; its dz row is zero)
-  auto stash = [&](WgwSet r, int bufo) __attribute__((always_inline)) {
-    unsigned char* Z = smem + bufo + prow * ROW + ch * 16;
-    unsigned char* X = Z + OPB;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      *reinterpret_cast<uint4*>(Z + q * 16 * ROW) = r.z[q];
-      if (xform) r.x[q] = wide_act(r.x[q], tsc, tsh);
-      *reinterpret_cast<uint4*>(X + q * 16 * ROW) = r.x[q];
-    }
-  };
   // fragment address of (k-step 0, block 0): a group of 16 lanes takes 16 channels (groups 0, 2 the first, 1, 3 the
   // second half of a block) of 8 pixels (groups 0, 1 the first, 2, 3 the second eight); within it lane s points at
-  // channels 4*(s%4).. of pixel s/4, the second read is 4 pixels further
-  const int frag = (half * 8 + (l16 >> 2)) * ROW + ((lane >> 4) & 1) * 32 + (l16 & 3) * 8;
-  const int zoff = frag + wa * 128;   // + i*64 (channel block)
-  const int xoff = OPB + frag + wb * 128;
+  // channels 4*(s%4).. of pixel s/4, the second read is 4 pixels further. All pixels of a lane are s/4 modulo 4
+  const int frag = (half * 8 + (l16 >> 2)) * ROW + ((lane >> 4) & 1) * 32 + (l16 & 3) * 8, turn = (l16 >> 2) * 64;
+  const int zoff = frag + (wa * 128 ^ turn);         // ^ i*64 (channel block)
+  const int xoff = OPB + frag + (wb * 128 ^ turn);
 
   f32x16_t acc[2][2], sum[2][2];                     // [co block][ci block]: rows = ci, columns = co
 #pragma unroll
@@ -142,28 +144,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int period = s1 - s0 <= 8 ? 1 : 2;
 
   // One pass over the slice. HOW 0: acc takes all; 1: acc takes the first half of every step, sum the second; 2: acc takes all
-  // and is folded into sum every `period` steps.
-  auto run = [&](auto how) __attribute__((always_inline)) {
+  // and is folded into sum every `period` steps. taps3, act: r3 and xform, as constants where the time goes (a
+  // branch per unit would end the block that the scheduler interleaves).
+  auto run = [&](auto how, auto taps3, auto act) __attribute__((always_inline)) {
     constexpr int HOW = decltype(how)::value;
-    // pixel, image row and column, and byte offsets of the thread's row that is requested next
-    int m0 = s0 * BP + prow, h, w;
-    unsigned zo = (unsigned)m0 * zst + (co0 + ch * 8) * 2, xo = (unsigned)(m0 + dr * a.W + ds) * xst + (ci0 + ch * 8) * 2;
-    {
-      const int r = m0 % (a.H * a.W);
-      h = r / a.W; w = r - h * a.W;
-    }
-    auto issue = [&](WgwSet& r) __attribute__((always_inline)) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        bool in = m0 + 16 * q < m_end;
-        if (r3) {
-          in = in && (unsigned)(h + dr) < (unsigned)a.H && (unsigned)(w + ds) < (unsigned)a.W;
-          w += dw; h += dh; if (w >= a.W) { w -= a.W; ++h; } if (h >= a.H) h -= a.H;
-        }
-        r.z[q] = wide_load(rz, in ? zo + 16 * q * zst : NOWHERE, 0);
-        r.x[q] = wide_load(rx, in ? xo + 16 * q * xst : NOWHERE, 0);
+    // image pixel and column, and byte offsets of the thread's unit that is requested next
+    unsigned rem = (unsigned)(first + prow) % HW, w = rem % (unsigned)a.W;
+    unsigned zo = prow * zst + (co0 + ch * 8) * 2, xo = prow * xst + (ci0 + ch * 8) * 2;
+    WgwSet r;
+    auto issue = [&](int q) __attribute__((always_inline)) {   // the units in turn
+      if (taps3) {
+        const bool in = (rem - lo < span) & (w != edge);
+        r.z[q] = wide_load(rz, in ? zo : NOWHERE, 0);
+        r.x[q] = wide_load(rx, in ? xo : NOWHERE, 0);
+        const unsigned r1 = rem + drem, w1 = w + dw, r2 = r1 - HW, w2 = w1 - a.W;    // (wrapped around zero unless past the end)
+        rem = r1 < r2 ? r1 : r2; w = w1 < w2 ? w1 : w2;
+      } else {
+        r.z[q] = wide_load(rz, zo, 0);
+        r.x[q] = wide_load(rx, xo, 0);
       }
-      m0 += BP; zo += BP * zst; xo += BP * xst;
+      zo += 16 * zst; xo += 16 * xst;
+    };
+    // (a row that does not exist is relu(shift) after the transform; its dz row is zero)
+    auto stash = [&](int q, int bufo) __attribute__((always_inline)) {
+      unsigned char* Z = smem + bufo + q * 16 * ROW + prow * ROW + (ch * 16 ^ (prow & 3) * 64);
+      *reinterpret_cast<uint4*>(Z) = r.z[q];
+      *reinterpret_cast<uint4*>(Z + OPB) = act ? wide_act(r.x[q], tsc, tsh) : r.x[q];
     };
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -184,15 +190,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             sum[i][j][e] = s;
           }
     };
-    auto contract = [&](int bufo) __attribute__((always_inline)) {
+    // Step `s` out of the buffer at bufo. Beside the matrix instructions of 16 pixels, a unit of the next step goes from its
+    // registers to the other buffer (free since the barrier that ended the step before) and the unit of the step after
+    // that is requested into them: a load has a whole step to arrive.
+    auto step = [&](int bufo) __attribute__((always_inline)) {
       const unsigned char* B = smem + bufo;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         bf16x8_t zf[2], xf[2];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) zf[i] = wide_frag_tr(B + zoff + i * 64 + k * 16 * ROW);
+        for (int i = 0; i < 2; ++i) zf[i] = wide_frag_tr(B + (zoff ^ i * 64) + k * 16 * ROW);
 #pragma unroll
-        for (int j = 0; j < 2; ++j) xf[j] = wide_frag_tr(B + xoff + j * 64 + k * 16 * ROW);
+        for (int j = 0; j < 2; ++j) xf[j] = wide_frag_tr(B + (xoff ^ j * 64) + k * 16 * ROW);
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -200,26 +209,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             f32x16_t& c = HOW == 1 && k >= 2 ? sum[i][j] : acc[i][j];
             c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[j], zf[i], c, 0, 0, 0);
           }
+        stash(k, BUF - bufo);
+        issue(k);
+        __builtin_amdgcn_sched_barrier(0);
       }
     };
     // (the host gives every slice at least one step; the step requested last is stored and never multiplied)
-    WgwSet ra;
-    issue(ra);
-    stash(ra, 0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) issue(q);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) { stash(q, 0); issue(q); }
     __syncthreads();
     for (int s = s0; s < s1; ++s) {
-      const int bufo = (s - s0) & 1 ? BUF : 0;
-      issue(ra);
-      __builtin_amdgcn_sched_barrier(0);
-      contract(bufo);
-      __builtin_amdgcn_sched_barrier(0);
-      stash(ra, BUF - bufo);
+      step((s - s0) & 1 ? BUF : 0);
       if (HOW == 2 && ((s - s0) & (period - 1)) == period - 1) fold();
       __syncthreads();
     }
   };
-  if (s1 - s0 <= 2) run(std::integral_constant<int, 1>{});
-  else run(std::integral_constant<int, 2>{});
+  using std::integral_constant;
+  using std::bool_constant;
+  if (s1 - s0 <= 2) run(integral_constant<int, 1>{}, r3, xform);
+  else if (r3 && xform) run(integral_constant<int, 2>{}, bool_constant<true>{}, bool_constant<true>{});
+  else if (r3) run(integral_constant<int, 2>{}, bool_constant<true>{}, bool_constant<false>{});
+  else if (xform) run(integral_constant<int, 2>{}, bool_constant<false>{}, bool_constant<true>{});
+  else run(integral_constant<int, 2>{}, bool_constant<false>{}, bool_constant<false>{});
   // Folding an infinity leaves no number in acc. If any element of the tile ends as none, the slice is added up plainly,
   // which supplies those elements: infinities come out as infinities.
   int bad = 0;
@@ -233,7 +246,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         bad |= sum[i][j][e] == sum[i][j][e] ? 0 : 1;
       }
   if (s1 - s0 > 2 && __syncthreads_or(bad)) {
-    run(std::integral_constant<int, 0>{});
+    run(integral_constant<int, 0>{}, r3, xform);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
