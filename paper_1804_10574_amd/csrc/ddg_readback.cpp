@@ -1,10 +1,12 @@
 // Device -> host copies of a module's state (weights, velocity, gradients, stored inputs).
 //
 // A large copy into fresh pageable memory moves about 10 GB/s here: the runtime stages it in 1 MiB pieces, and its
-// one thread takes the page faults of the destination between two pieces. From RING_MIN on the pieces land in a
+// one thread takes the page faults of the destination between two pieces. From RING_MIN on pieces land in a
 // small ring of pinned slots instead while threads of this process copy earlier pieces out: 102 MB (23
-// bottleneck blocks) 9.8 -> 3.6 ms, 27 MB 1.6 -> 1.0 ms; at 1.7 MB the two are even (0.10 ms), below the
-// runtime's way is shorter (0.04 MB: 22 against 38 us), and it needs no pinned memory.
+// bottleneck blocks) 9.8 -> 3.6 ms in pieces of 1 MiB; at 1.7 MB the two are even (0.10 ms), below the
+// runtime's way is shorter (0.04 MB: 22 against 38 us), and it needs no pinned memory. A piece costs the queue about 12 us
+// beside its transfer (102 MB in pieces of 0.5 / 1 / 2 / 4 MiB: 4.8 / 3.4 / 2.8 / 2.6 ms; the link alone 1.85), so pieces are
+// large and the threads share each of them.
 //
 // The callers are C functions, so no exception leaves this file: without host memory for the bookkeeping the copy is
 // the runtime's, without threads the caller copies the pieces out itself.
@@ -21,28 +23,32 @@ namespace ddg {
 
 namespace {
 
-constexpr size_t PIECE = (size_t)1 << 20, RING_MIN = (size_t)8 << 20;
+constexpr size_t PIECE = Readback::PIECE, RING_MIN = (size_t)8 << 20;
+constexpr size_t SHARE = (size_t)512 << 10, SHARES = PIECE / SHARE;   // what a thread copies out at a time
 constexpr int SLOTS = Readback::SLOTS;
 constexpr int WORKERS = 7;            // beside the calling thread
 
 struct Job {
-  char* dst; const char* ring; size_t bytes, pieces;
-  std::atomic<size_t> landed{0}, ticket{0};
+  char* dst; const char* ring; size_t bytes, pieces, shares;
+  std::atomic<size_t> landed{0}, ticket{0};     // pieces, shares
   std::atomic<bool> stop{false};
-  std::unique_ptr<std::atomic<char>[]> done;   // null: no memory for it
-  Job(char* d, const char* r, size_t b, size_t n) : dst(d), ring(r), bytes(b), pieces(n), done(new (std::nothrow) std::atomic<char>[n]) {
-    if (done) for (size_t i = 0; i < n; ++i) done[i].store(0, std::memory_order_relaxed);
+  std::unique_ptr<std::atomic<int>[]> left;    // shares of a piece not yet copied out; null: no memory for it
+  Job(char* d, const char* r, size_t b, size_t n)
+      : dst(d), ring(r), bytes(b), pieces(n), shares((b + SHARE - 1) / SHARE), left(new (std::nothrow) std::atomic<int>[n]) {
+    if (left) for (size_t i = 0; i < n; ++i) left[i].store((int)std::min(SHARES, shares - i * SHARES), std::memory_order_relaxed);
   }
   size_t len(size_t i) const { return std::min(PIECE, bytes - i * PIECE); }
-  void copy_out(size_t i) {
-    memcpy(dst + i * PIECE, ring + (i % SLOTS) * PIECE, len(i));
-    done[i].store(1, std::memory_order_release);
+  void copy_out(size_t share) {
+    const size_t piece = share / SHARES;
+    memcpy(dst + share * SHARE, ring + (piece % SLOTS) * PIECE + (share % SHARES) * SHARE, std::min(SHARE, bytes - share * SHARE));
+    left[piece].fetch_sub(1, std::memory_order_release);
   }
-  void work() {   // until every piece has an owner, or stop
+  bool emptied(size_t piece) const { return left[piece].load(std::memory_order_acquire) == 0; }
+  void work() {   // until every share has an owner, or stop
     for (;;) {
       const size_t i = ticket.fetch_add(1, std::memory_order_relaxed);
-      if (i >= pieces) return;
-      while (landed.load(std::memory_order_acquire) <= i) {
+      if (i >= shares) return;
+      while (landed.load(std::memory_order_acquire) <= i / SHARES) {
         if (stop.load(std::memory_order_relaxed)) return;
         std::this_thread::yield();
       }
@@ -55,7 +61,7 @@ struct Job {
 hipError_t through_ring(Readback& rb, char* dst, const char* src, size_t bytes, hipStream_t s) {
   const size_t pieces = (bytes + PIECE - 1) / PIECE;
   Job job(dst, (const char*)rb.ring, bytes, pieces);
-  if (!job.done) return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
+  if (!job.left) return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
   std::thread team[WORKERS];
   const unsigned hw = std::thread::hardware_concurrency();
   const size_t want = std::min<size_t>(WORKERS, hw > 1 ? hw - 1 : 0);
@@ -67,7 +73,7 @@ hipError_t through_ring(Readback& rb, char* dst, const char* src, size_t bytes, 
   size_t sent = 0, landed = 0;
   while (landed < pieces && err == hipSuccess) {
     while (sent < pieces && err == hipSuccess &&
-           (sent < (size_t)SLOTS || job.done[sent - SLOTS].load(std::memory_order_acquire))) {
+           (sent < (size_t)SLOTS || job.emptied(sent - SLOTS))) {
       err = hipMemcpyAsync((char*)rb.ring + (sent % SLOTS) * PIECE, src + sent * PIECE, job.len(sent), hipMemcpyDeviceToHost, s);
       if (err == hipSuccess) err = hipEventRecord(rb.ev[sent % SLOTS], s);
       if (err == hipSuccess) ++sent;
@@ -76,7 +82,8 @@ hipError_t through_ring(Readback& rb, char* dst, const char* src, size_t bytes, 
     if (landed == sent) { std::this_thread::yield(); continue; }   // the ring is full of pieces being copied out
     err = hipEventSynchronize(rb.ev[landed % SLOTS]);
     if (err != hipSuccess) break;
-    if (workers == 0) job.copy_out(landed);
+    if (workers == 0)
+      for (size_t i = landed * SHARES; i < std::min((landed + 1) * SHARES, job.shares); ++i) job.copy_out(i);
     job.landed.store(++landed, std::memory_order_release);
   }
   if (err != hipSuccess) { job.stop.store(true); (void)hipStreamSynchronize(s); }
