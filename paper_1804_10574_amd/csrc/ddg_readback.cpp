@@ -5,8 +5,8 @@
 // small ring of pinned slots instead while threads of this process copy earlier pieces out: 102 MB (23
 // bottleneck blocks) 9.8 -> 3.6 ms in pieces of 1 MiB; at 1.7 MB the two are even (0.10 ms), below the
 // runtime's way is shorter (0.04 MB: 22 against 38 us), and it needs no pinned memory. A piece costs the queue about 12 us
-// beside its transfer (102 MB in pieces of 0.5 / 1 / 2 / 4 MiB: 4.8 / 3.4 / 2.8 / 2.6 ms; the link alone 1.85), so pieces are
-// large and the threads share each of them.
+// beside its transfer (102 MB in pieces of 0.5 / 1 / 2 / 4 MiB: 4.8 / 3.4 / 2.8 / 2.6 ms; the link alone 1.85), so pieces
+// are 2 MiB, eight of them as much pinned memory as a module should hold, and the threads share each.
 //
 // The callers are C functions, so no exception leaves this file: without host memory for the bookkeeping the copy is
 // the runtime's, without threads the caller copies the pieces out itself.

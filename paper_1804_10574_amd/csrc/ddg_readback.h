@@ -9,8 +9,8 @@
 namespace ddg {
 
 struct Readback {
-  static constexpr int SLOTS = 4;
-  static constexpr size_t PIECE = (size_t)4 << 20;
+  static constexpr int SLOTS = 8;
+  static constexpr size_t PIECE = (size_t)2 << 20;
   void* ring = nullptr;
   hipEvent_t ev[SLOTS] = {};
   std::mutex mu;
