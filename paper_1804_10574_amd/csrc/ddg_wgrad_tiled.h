@@ -50,7 +50,7 @@ struct WgradTiledCfg {
 };
 
 typedef short tr4_t __attribute__((ext_vector_type(4)));
-// 8-pixel fragment of one channel per lane: two transposing reads of 4 pixels each, half_stride bytes apart
+// 8-pixel fragment of one channel per lane: two transposing reads 4 pixels apart
 __device__ __forceinline__ uint4 lds_frag_tr(const unsigned char* p, int half_stride) {
   typedef tr4_t __attribute__((address_space(3))) * lds_ptr_t;
   const tr4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p));
@@ -134,15 +134,12 @@ __device__ __forceinline__ void wgrad_tiled_body(const WgradTiledArgs& a, unsign
   if (tile < a.tiles) issue(tile);
 
   // ---- fragment addresses: lane and k-step part in a register, tap / ci-block / half as immediates
-  // k-step q of this wave covers pixels p = (kpart + q*KSPLIT)*32 + lg*4 .. +3 and those 16 further on: the 32 lanes a transposing
-  // read serves together then take 8 neighbouring pixels, which lie in different banks at every pixel pitch used here (2 cycles a
-  // read instead of 4 with 8 consecutive pixels a lane)
+  // k-step q of this wave covers pixels p = (kpart + q*KSPLIT)*32 + lg*8 .. +7 of the tile
   const int sub = l16 >> 2, chq = (l16 & 3) * 8;     // pixel within a group of 4; byte offset of 4 channels
-  constexpr int XHALF = ((16 / W) * S * WC + (16 % W) * S) * PIXX;   // 16 output pixels further on
   int zaddr[KPW], xaddr[KPW];
 #pragma unroll
   for (int q = 0; q < KPW; ++q) {
-    const int p = (kpart + q * KSPLIT) * 32 + lg * 4;
+    const int p = (kpart + q * KSPLIT) * 32 + lg * 8;
     const int row = p / W, col = p % W;
     zaddr[q] = Cfg::LDS_X + (p + sub) * PIXZ + cb * 32 + chq;
     xaddr[q] = (row * S * WC + (col + sub) * S) * PIXX + chq;
@@ -231,7 +228,7 @@ __device__ __forceinline__ void wgrad_tiled_body(const WgradTiledArgs& a, unsign
     // ---- contraction over this wave's pixels of the tile ----
 #pragma unroll
     for (int q = 0; q < KPW; ++q) {
-      const uint4 zf = lds_frag_tr(smem + zaddr[q], 16 * PIXZ);
+      const uint4 zf = lds_frag_tr(smem + zaddr[q], 4 * PIXZ);
       const unsigned char* xp = xt + xaddr[q];
 #pragma unroll
       for (int b = 0; b < CIB; ++b)
@@ -239,7 +236,7 @@ __device__ __forceinline__ void wgrad_tiled_body(const WgradTiledArgs& a, unsign
         for (int r = 0; r < R; ++r)
 #pragma unroll
           for (int sx = 0; sx < R; ++sx) {
-            const uint4 xf = lds_frag_tr(xp + (r * WC + sx) * PIXX + b * 32, XHALF);
+            const uint4 xf = lds_frag_tr(xp + (r * WC + sx) * PIXX + b * 32, 4 * S * PIXX);
             acc[r * R + sx][b] = Mma<bf16_t>::mma(zf, xf, acc[r * R + sx][b]);
           }
     }
