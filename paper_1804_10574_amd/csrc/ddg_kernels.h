@@ -341,7 +341,7 @@ struct EvalConvDesc { const void* w; const float *gamma, *beta, *rmean, *rvar; f
 struct EvalBlockDesc { int kind, stride, conv0; };          // conv0: index of the block's first convolution
 struct EvalBlockShape { int kind, c, stride; };             // c: input channels
 struct EvalLaunch {        // blocks [first, first + count) of a module on H x W inputs
-  int first, count, conv0, nconv, H, W, TH, strips;
+  int first, count, conv0, nconv, H, W, TH, strips, gap;     // gap: bytes between pixels in LDS
   unsigned off1, off2, red_off, tab_off, dump_off; size_t lds;
 };
 struct EvalPlan { std::vector<EvalLaunch> launches; };

@@ -14,22 +14,29 @@
 //   whole images: all blocks of a module in one launch, one image per workgroup (bf16);
 //   strips: one residual block per launch, TH output rows per workgroup, the rows of the halo
 //           recomputed (fp32, whose matrix rate makes an image 10-18 us per layer on one unit, so
-//           that one image has to be spread over several; and bf16 modules whose buffers, each at its
-//           largest over the blocks, exceed LDS: large images, and deep networks in one module from 32x32 on (ResNet-110: its
-//           table of scales and shifts alone is 32 KB). There too nothing got slower: ResNet-110 in one module, batch 37,
-//           1.29x against the per-layer kernels, batch 1 1.41x. As whole images ResNet-20 in one module takes 57 us
-//           at batch 256 and 54 at batch 1, 130 and 85 in strips).
+//           that one image has to be spread over several; bf16 modules whose buffers, each at its largest over the blocks,
+//           exceed LDS: large images, and deep networks in one module from 32x32 on (ResNet-110: its table of scales and shifts
+//           alone is 32 KB)). Strips are no slower than
+//           the per-layer kernels either: ResNet-110 in one module, batch 37, 1.29x, batch 1 1.41x. As whole images
+//           ResNet-20 in one module takes 57 us at batch 256 and 54 at batch 1, 130 and 85 in strips.
 //
-// Buffers: three LDS regions of NHWC pixels with a zero border (row and column -1 and H / W); pixels are an
-// odd multiple of 32 bytes apart and rows continue that where a block of 16 pixels spans two, so that
-// fragment reads have no bank conflicts (4 cycles each; 8-12 with pixels an odd multiple of 16 bytes apart). An identity block reads x, writes o = relu(bn1(conv1 x)), then adds relu(bn2(conv2 o) + x)
+// Buffers: three LDS regions of NHWC pixels with a zero border (row and column -1 and H / W). An identity block reads x, writes
+// o = relu(bn1(conv1 x)), then adds relu(bn2(conv2 o) + x)
 // back into x in place (an output pixel needs x at that pixel only). A block between stages writes
 // its output to the third region, and the regions change roles.
 //
+// Pitch: bf16 pixels of 32 and 64 channels have GAP bytes between them, and there is a kernel for either GAP. 32: pixels are an
+// odd multiple of 32 bytes apart and rows continue that where a block of 16 pixels spans two, so that
+// fragment reads have no bank conflicts (4 cycles each; 8-12 with pixels an odd multiple of 16 bytes apart). 16: more fits,
+// larger images as a whole (three identity blocks of 32 channels to 29x29 instead of 26x26, of 64 to 18x18 instead of 17x17) and higher strips with
+// fewer halo rows. fp32, where the matrix instructions hide the reads: 16, whose conflicts cost less than those of the stores with 32, 1-3 %.
+//
 // Eight waves; a wave holds the weight fragments of one layer in registers (two sets: the next
 // layer's are requested before the current one is contracted) and walks over 16-pixel blocks:
-//   16 channels: every wave all channels, 8 pixel groups;  32 channels: one channel block and 4 pixel groups (both
-//   blocks in every wave would bring a layer's weights into the compute unit eight times, 147 KB at 64 bytes a cycle);
+//   16 channels: every wave all channels, 8 pixel groups;  32 channels: one channel block and 4 pixel groups (with both
+//   blocks in every wave a layer's weights enter the compute unit eight times, 147 KB at 64 bytes a cycle), but with GAP 16, which
+//   larger maps take, both and 8 groups: half the reads of LDS per matrix instruction (24x24, 3 blocks, 256 images:
+//   31 us instead of 39 with one block each and of 36 with GAP 32);
 //   64 channels: 4 channel blocks x 2 halves of the contraction (a layer's weights, 73 KB in bf16,
 //   then enter the compute unit once; the halves meet in LDS).
 // Rounding points are those of the per-layer kernels: the conv output and the activations are
@@ -62,10 +69,9 @@ __device__ __forceinline__ unsigned char* lds() {
   return smem;
 }
 
-// bytes of a pixel of ch channels (of esz bytes), and of a buffer row of W pixels and their border (fp32, where the matrix
-// instructions hide the reads: an odd multiple of 16, whose conflicts cost less than those of the stores with 32, 1-3 %)
-__host__ __device__ constexpr int pix_bytes_of(int ch, int esz) { return ch * esz <= 16 ? 16 : esz == 4 ? ch * 4 + 16 : ch == 16 ? 32 : ch * 2 + 32; }
-template <typename T> __host__ __device__ constexpr int pix_bytes(int ch) { return pix_bytes_of(ch, (int)sizeof(T)); }
+// bytes of a pixel of ch channels (of esz bytes; `gap`: as above), and of a buffer row of W pixels and their border
+__host__ __device__ constexpr int pix_bytes_of(int ch, int esz, int gap) { return ch * esz <= 16 ? 16 : esz == 4 ? ch * 4 + 16 : ch == 16 ? 32 : ch * 2 + gap; }
+template <typename T, int GAP> __host__ __device__ constexpr int pix_bytes(int ch) { return pix_bytes_of(ch, (int)sizeof(T), GAP); }
 __host__ __device__ constexpr int row_bytes(int W, int pix) { return W % 16 == 0 || pix % 32 != 0 ? (W + 2) * pix : W * pix + (2 * pix + 255) / 256 * 256; }
 
 struct Args {
@@ -79,10 +85,10 @@ struct Args {
 
 // One convolution layer shape: CIN -> COUT, R x R, stride S, NCB channel blocks and 1/KS of the
 // contraction per wave, U pixel blocks in flight.
-template <typename T, int CIN, int COUT, int R, int S, int NCB, int KS, int U>
+template <typename T, int GAP, int CIN, int COUT, int R, int S, int NCB, int KS, int U>
 struct Conv {
   typedef typename Mma<T>::frag_t frag_t;
-  static constexpr int KV = Mma<T>::KV, KSTEP = Mma<T>::KSTEP, PIX = pix_bytes<T>(CIN);
+  static constexpr int KV = Mma<T>::KV, KSTEP = Mma<T>::KSTEP, PIX = pix_bytes<T, GAP>(CIN);
   static constexpr int KSTEPS = (R * R * CIN + KSTEP - 1) / KSTEP, KPW = KSTEPS / KS;
   // Lanes of the last k-step past the last tap (16 channels in bf16, the stem) multiply zero weights; what they
   // read has to be zero as well, or an infinite activation becomes NaN in every channel: the buffer's first
@@ -199,18 +205,18 @@ struct Conv {
   }
 };
 
-template <typename T, int C> struct Same;       // 3x3, stride 1, C -> C
-template <> struct Same<bf16_t, 16> { typedef Conv<bf16_t, 16, 16, 3, 1, 1, 1, 4> type; };
-template <> struct Same<bf16_t, 32> { typedef Conv<bf16_t, 32, 32, 3, 1, 1, 1, 4> type; };
-template <> struct Same<bf16_t, 64> { typedef Conv<bf16_t, 64, 64, 3, 1, 1, 2, 4> type; };
-template <> struct Same<float, 16> { typedef Conv<float, 16, 16, 3, 1, 1, 1, 1> type; };
-template <> struct Same<float, 32> { typedef Conv<float, 32, 32, 3, 1, 1, 1, 1> type; };
-template <> struct Same<float, 64> { typedef Conv<float, 64, 64, 3, 1, 1, 2, 2> type; };
-template <typename T, int C> struct Down;       // 3x3, stride 2, C -> 2C
-template <> struct Down<bf16_t, 16> { typedef Conv<bf16_t, 16, 32, 3, 2, 2, 1, 2> type; };
-template <> struct Down<bf16_t, 32> { typedef Conv<bf16_t, 32, 64, 3, 2, 1, 1, 2> type; };
-template <> struct Down<float, 16> { typedef Conv<float, 16, 32, 3, 2, 1, 1, 1> type; };
-template <> struct Down<float, 32> { typedef Conv<float, 32, 64, 3, 2, 1, 1, 1> type; };
+template <typename T, int GAP, int C> struct Same;       // 3x3, stride 1, C -> C
+template <int GAP> struct Same<bf16_t, GAP, 16> { typedef Conv<bf16_t, GAP, 16, 16, 3, 1, 1, 1, 4> type; };
+template <int GAP> struct Same<bf16_t, GAP, 32> { typedef Conv<bf16_t, GAP, 32, 32, 3, 1, GAP == 32 ? 1 : 2, 1, GAP == 32 ? 4 : 2> type; };
+template <int GAP> struct Same<bf16_t, GAP, 64> { typedef Conv<bf16_t, GAP, 64, 64, 3, 1, 1, 2, 4> type; };
+template <int GAP> struct Same<float, GAP, 16> { typedef Conv<float, GAP, 16, 16, 3, 1, 1, 1, 1> type; };
+template <int GAP> struct Same<float, GAP, 32> { typedef Conv<float, GAP, 32, 32, 3, 1, 1, 1, 1> type; };
+template <int GAP> struct Same<float, GAP, 64> { typedef Conv<float, GAP, 64, 64, 3, 1, 1, 2, 2> type; };
+template <typename T, int GAP, int C> struct Down;       // 3x3, stride 2, C -> 2C
+template <int GAP> struct Down<bf16_t, GAP, 16> { typedef Conv<bf16_t, GAP, 16, 32, 3, 2, 2, 1, 2> type; };
+template <int GAP> struct Down<bf16_t, GAP, 32> { typedef Conv<bf16_t, GAP, 32, 64, 3, 2, 1, 1, 2> type; };
+template <int GAP> struct Down<float, GAP, 16> { typedef Conv<float, GAP, 16, 32, 3, 2, 1, 1, 1> type; };
+template <int GAP> struct Down<float, GAP, 32> { typedef Conv<float, GAP, 32, 64, 3, 2, 1, 1, 1> type; };
 
 // The thread's index, as a value the compiler does not know: the lane-dependent addresses of a stage are then computed where the
 // stage begins. Otherwise those of all stages are hoisted to the start of the kernel, and spilled.
@@ -268,10 +274,10 @@ __device__ __forceinline__ uint4 pair_rows(const f32x4_t& a, const f32x4_t& b) {
 //                next; column 1 of the last row alone (the other lanes read border and multiply zero weights);
 //   32 channels: one channel block x 4 rows; a k-step is a tap;
 //   64 channels: one channel block x half of the input channels, all four blocks; the halves meet in LDS.
-template <int C>
+template <int GAP, int C>
 __device__ __forceinline__ void identity_square(const EvalConvDesc* cv, int tab, int count, Bufs& B, int red, int& flip) {
   typedef bf16_t T;
-  typedef typename Same<T, C>::type K;
+  typedef typename Same<T, GAP, C>::type K;
   typedef Mma<T>::frag_t frag_t;
   constexpr int PIX = K::PIX, W = 512 / C, RB = row_bytes(W, PIX), OCB = C / 16;
   constexpr int BLK = C == 64 ? 2 : 1, NB = C == 16 ? 8 : 4, NT = NB * BLK + 3 - BLK;   // rows of a block, blocks of a wave, row positions it reads
@@ -388,9 +394,9 @@ __device__ __forceinline__ void identity_square(const EvalConvDesc* cv, int tab,
 // Identity blocks on whole images whose pixel blocks fit G groups per wave: every address of a layer
 // is the same for all layers of the run (both buffers start at image row -1), so a lane computes its
 // pixels' offsets once. Lanes past the last pixel write to `dump`.
-template <typename T, int C, int G>
+template <typename T, int GAP, int C, int G>
 __device__ __forceinline__ void identity_images(const EvalConvDesc* cv, int tab, int count, Bufs& B, int red, int dump, int& flip) {
-  typedef typename Same<T, C>::type K;
+  typedef typename Same<T, GAP, C>::type K;
   constexpr int PIX = K::PIX, U = K::U_, NCB = K::NCB_, F = K::KS_ == 1 ? U : U / 2;   // F: pixel blocks a wave finishes per group
   const int tid = own_tid<T>(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int W = B.W, RB = row_bytes(W, PIX), npx = B.H * W;
@@ -461,9 +467,9 @@ __device__ __forceinline__ void identity_images(const EvalConvDesc* cv, int tab,
 }
 
 // `count` identity blocks of C channels, output rows [lo, hi) (all rows when count > 1)
-template <typename T, int C>
+template <typename T, int GAP, int C>
 __device__ __forceinline__ void identity_run(const EvalConvDesc* cv, int tab, int count, Bufs& B, int lo, int hi, int red, int& flip) {
-  typedef typename Same<T, C>::type K;
+  typedef typename Same<T, GAP, C>::type K;
   constexpr int PIX = K::PIX;
   const int tid = own_tid<T>(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int W = B.W, RB = row_bytes(W, PIX);
@@ -499,11 +505,11 @@ __device__ __forceinline__ void identity_run(const EvalConvDesc* cv, int tab, in
 }
 
 // A block between stages: C -> 2C channels, stride 2, 1x1 projection on the shortcut
-template <typename T, int C>
+template <typename T, int GAP, int C>
 __device__ __forceinline__ void down_block(const EvalConvDesc* cv, int tab, Bufs& B, int lo, int hi, int Ho, int Wo, int red, int& flip) {
-  typedef typename Down<T, C>::type K1;
-  typedef typename Same<T, 2 * C>::type K2;
-  typedef Conv<T, C, 2 * C, 1, 2, K2::NCB_, 1, 1> KP;    // (only its weight layout: same channel blocks as K2)
+  typedef typename Down<T, GAP, C>::type K1;
+  typedef typename Same<T, GAP, 2 * C>::type K2;
+  typedef Conv<T, GAP, C, 2 * C, 1, 2, K2::NCB_, 1, 1> KP;    // (only its weight layout: same channel blocks as K2)
   const int tid = own_tid<T>(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int RB = row_bytes(B.W, K1::PIX), RBo = row_bytes(Wo, K2::PIX);
   const int olo = lo > 0 ? lo - 1 : 0, ohi = hi < Ho ? hi + 1 : Ho;
@@ -601,7 +607,7 @@ __device__ __forceinline__ void load_rows_stem(int buf, const T* img, int row0, 
 }
 
 // (the fp32 kernel runs strips; whole images only where an image is one strip)
-template <typename T, bool WHOLE>
+template <typename T, bool WHOLE, int GAP>
 __global__ __launch_bounds__(NT) void eval_blocks_kernel(Args a) {
   const int n = blockIdx.x / a.strips, st = blockIdx.x - n * a.strips;
   const int tid = threadIdx.x;
@@ -624,8 +630,8 @@ __global__ __launch_bounds__(NT) void eval_blocks_kernel(Args a) {
     if (b0.kind == EVAL_STEM) {
       load_rows_stem<T>(B.o, img, B.row0, rows, a.H, a.W, a.C);
     } else {
-      load_rows<T>(B.x, img, B.row0, rows, a.H, a.W, a.C, pix_bytes<T>(a.C));
-      if (b0.kind == EVAL_IDENTITY) zero<T>(B.o, (hi - lo + 2) * row_bytes(a.W, pix_bytes<T>(a.C)));
+      load_rows<T>(B.x, img, B.row0, rows, a.H, a.W, a.C, pix_bytes<T, GAP>(a.C));
+      if (b0.kind == EVAL_IDENTITY) zero<T>(B.o, (hi - lo + 2) * row_bytes(a.W, pix_bytes<T, GAP>(a.C)));
     }
   }
   // scale and shift of every batch norm of the launch, a wave per layer and four layers at a time
@@ -656,11 +662,11 @@ __global__ __launch_bounds__(NT) void eval_blocks_kernel(Args a) {
   }
   int bi = 0;
   if (b0.kind == EVAL_STEM) {
-    typedef Conv<T, Mma<T>::KV, 16, 3, 1, 1, 1, 2> K1;
-    typedef Conv<T, Mma<T>::KV, 16, 3, 2, 1, 1, 2> K2;
+    typedef Conv<T, GAP, Mma<T>::KV, 16, 3, 1, 1, 1, 2> K1;
+    typedef Conv<T, GAP, Mma<T>::KV, 16, 3, 2, 1, 1, 2> K2;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int Wo = (a.W - 1) / b0.stride + 1, srow0 = B.row0;
-    constexpr int PIX = pix_bytes<T>(16);
+    constexpr int PIX = pix_bytes<T, GAP>(16);
     B.row0 = lo - 1;
     const int RBo = row_bytes(Wo, PIX), RBi = row_bytes(a.W, K1::PIX);
     zero<T>(B.x, (hi - lo + 2) * RBo);
@@ -699,31 +705,31 @@ __global__ __launch_bounds__(NT) void eval_blocks_kernel(Args a) {
       const EvalConvDesc* cv0 = a.convs + (a.blocks[bi].conv0 - a.blocks[0].conv0);
       const bool whole = a.strips == 1 && WHOLE, square = sizeof(T) == 2 && B.W == 512 / C && B.H == B.W;
       if (C == 16) {
-        if (whole && square) identity_square<16>(cv0, tab, cnt, B, red, flip);
-        else if (whole && npx <= 1024) identity_images<T, 16, WHOLE ? 2 : 1>(cv0, tab, cnt, B, red, (int)a.dump_off, flip);
-        else identity_run<T, 16>(cv0, tab, cnt, B, lo, hi, red, flip);
+        if (whole && square) identity_square<GAP, 16>(cv0, tab, cnt, B, red, flip);
+        else if (whole && npx <= 1024) identity_images<T, GAP, 16, WHOLE ? 2 : 1>(cv0, tab, cnt, B, red, (int)a.dump_off, flip);
+        else identity_run<T, GAP, 16>(cv0, tab, cnt, B, lo, hi, red, flip);
       } else if (C == 32) {
-        if (whole && square) identity_square<32>(cv0, tab, cnt, B, red, flip);
-        else if (whole && npx <= 256) identity_images<T, 32, 1>(cv0, tab, cnt, B, red, (int)a.dump_off, flip);
-        else identity_run<T, 32>(cv0, tab, cnt, B, lo, hi, red, flip);
+        if (whole && square) identity_square<GAP, 32>(cv0, tab, cnt, B, red, flip);
+        else if (whole && npx <= 256) identity_images<T, GAP, 32, 1>(cv0, tab, cnt, B, red, (int)a.dump_off, flip);
+        else identity_run<T, GAP, 32>(cv0, tab, cnt, B, lo, hi, red, flip);
       } else {
-        if (whole && square) identity_square<64>(cv0, tab, cnt, B, red, flip);
-        else if (whole && npx <= 64) identity_images<T, 64, 1>(cv0, tab, cnt, B, red, (int)a.dump_off, flip);
-        else identity_run<T, 64>(cv0, tab, cnt, B, lo, hi, red, flip);
+        if (whole && square) identity_square<GAP, 64>(cv0, tab, cnt, B, red, flip);
+        else if (whole && npx <= 64) identity_images<T, GAP, 64, 1>(cv0, tab, cnt, B, red, (int)a.dump_off, flip);
+        else identity_run<T, GAP, 64>(cv0, tab, cnt, B, lo, hi, red, flip);
       }
       bi += cnt;
     } else {
       const int Ho = (B.H - 1) / 2 + 1, Wo = (B.W - 1) / 2 + 1;
       const EvalConvDesc* cv = a.convs + (a.blocks[bi].conv0 - a.blocks[0].conv0);
-      if (C == 16) down_block<T, 16>(cv, tab, B, lo, hi, Ho, Wo, red, flip);
-      else down_block<T, 32>(cv, tab, B, lo, hi, Ho, Wo, red, flip);
+      if (C == 16) down_block<T, GAP, 16>(cv, tab, B, lo, hi, Ho, Wo, red, flip);
+      else down_block<T, GAP, 32>(cv, tab, B, lo, hi, Ho, Wo, red, flip);
       C *= 2;
       ++bi;
     }
   }
   // the output rows of this workgroup
   constexpr int V = Store<T>::VEC;
-  const int ch = C / V, pix = pix_bytes<T>(C), RB = row_bytes(B.W, pix), per_row = B.W * ch, total = (hi - lo) * per_row;
+  const int ch = C / V, pix = pix_bytes<T, GAP>(C), RB = row_bytes(B.W, pix), per_row = B.W * ch, total = (hi - lo) * per_row;
   T* out = reinterpret_cast<T*>(a.out) + ((size_t)n * B.H + lo) * B.W * C;
   for (int i = tid; i < total; i += NT) {
     const int r = i / per_row, e = i - r * per_row, px = e / ch, k = e - px * ch;
@@ -735,9 +741,9 @@ __global__ __launch_bounds__(NT) void eval_blocks_kernel(Args a) {
 }  // namespace ev
 
 // LDS of a launch over `kinds`/`chans` (nb blocks) on H x W images with TH output rows per workgroup.
-static void eval_lds(const EvalBlockShape* b, int nb, int H, int W, int TH, int strips, int dtype, EvalLaunch* l) {
+static void eval_lds(const EvalBlockShape* b, int nb, int H, int W, int TH, int strips, int dtype, int gap, EvalLaunch* l) {
   const size_t esz = dtype_size(dtype);
-  auto row = [&](int w, int c) -> size_t { return ev::row_bytes(w, ev::pix_bytes_of(c, (int)esz)); };   // bytes of a row of w pixels
+  auto row = [&](int w, int c) -> size_t { return ev::row_bytes(w, ev::pix_bytes_of(c, (int)esz, gap)); };   // bytes of a row of w pixels
   size_t need[3] = {0, 0, 0};     // regions A, B, C
   int xi = 0, yi = 2;             // which region holds x, which is free
   auto want = [&](int region, size_t bytes) { if (bytes > need[region]) need[region] = bytes; };
@@ -772,6 +778,7 @@ static void eval_lds(const EvalBlockShape* b, int nb, int H, int W, int TH, int 
   l->tab_off = l->red_off + (exch ? ev::RED_BYTES : 0);
   l->dump_off = l->tab_off + (unsigned)tab;
   l->lds = l->dump_off + ev::DUMP_BYTES;
+  l->gap = gap;
 }
 
 bool eval_block_ok(int kind, int c) {
@@ -780,23 +787,58 @@ bool eval_block_ok(int kind, int c) {
   return kind == EVAL_DOWN && (c == 16 || c == 32);
 }
 
-// How a module's blocks are cut into launches. bf16: whole images, all blocks at once, if the
-// buffers fit LDS. Otherwise one block per launch in strips of the height that minimises
+// Estimated time of a bf16 launch of N images, us: 2 for the launch, 0.15 per MB in and out, and per round over 256 compute units
+// (registers: one workgroup per unit) 2, 1 per layer, 0.04 per KB of a workgroup's rows in and out, and for every 16 pixels of a
+// layer what `per` says, in whole groups of a workgroup's waves. Fitted to 1752 measured evaluations (maps 8 to 64 wide,
+// 1 to 256 images, one to three blocks, both pitches, whole images and strips): 7 % rms.
+static double eval_cost(const EvalBlockShape* b, const EvalLaunch& l, int N) {
+  const bool wide = l.gap == 32;
+  double layers = 0.0, matrix = 0.0;
+  int h = l.H, w = l.W, co = 0;
+  for (int i = 0; i < l.count; ++i) {
+    const int s = b[i].kind == EVAL_DOWN ? 2 : b[i].stride;
+    h = (h - 1) / s + 1; w = (w - 1) / s + 1;
+    co = b[i].kind == EVAL_STEM ? 16 : b[i].kind == EVAL_DOWN ? 2 * b[i].c : b[i].c;
+    const bool whole = l.strips == 1, square = whole && w == 512 / co && h == w && b[i].kind == EVAL_IDENTITY;
+    const double per = co == 16 ? (square ? 0.008 : 0.023) : co == 32 ? (!wide ? 0.050 : whole && h * w <= 256 ? 0.035 : 0.064)
+                                : square ? (wide ? 0.19 : 0.30) : wide ? 0.365 : 0.40;
+    const double each = co == 32 && !wide ? 1.5 : 1.0;     // (both channel blocks in every wave: twice the weights)
+    auto groups = [&](int r) { const int pb = (r * w + 15) / 16, g = co == 64 ? 4 : co == 32 ? 16 : 8; return (pb + g - 1) / g * g; };
+    const int th = whole ? h : l.TH, r1 = whole || th + 2 > h ? h : th + 2;
+    if (b[i].kind != EVAL_STEM) { layers += each; matrix += groups(r1) * per; }
+    layers += each; matrix += groups(th) * per;
+  }
+  const int s0 = b[0].kind == EVAL_DOWN ? 2 : b[0].stride, cin = b[0].kind == EVAL_STEM ? 3 : b[0].c;
+  const double in = 2.0 * l.H * l.W * cin * (l.strips > 1 ? 1.0 + 4.0 / (l.TH * s0) : 1.0), out = 2.0 * h * w * co;
+  const double rounds = (double)(((size_t)N * l.strips + 255) / 256);
+  return 2.0 + 0.15e-6 * N * (in + out) + rounds * (2.0 + layers + 0.04e-3 * (in + out) / l.strips + matrix);
+}
+
+// How a module's blocks are cut into launches: all blocks at once, whole images (bf16, if the buffers fit LDS), or one
+// block per launch in strips of the height that minimises
 //   rounds over 256 compute units x (2 us + the strip's matrix time, halo rows included)
-// (2 us: loads, barriers and epilogues of a block, measured on one image).
+// (2 us: loads, barriers and epilogues of a block, measured on one image). bf16: in the pitch that
+// eval_cost() finds shorter. us a call, strips of 32 / 16 bytes between pixels, whole images of 32 / 16 (-: does not fit):
+//   9 blocks of 32 channels, 28x28, 256 images  234 / 184 / - / 97     3 blocks, 24x24, 256 images  54 / 49 / 36 / 31
+//   3 blocks of 64 channels, 14x14, 256 images  65 / 73 / 51 / 59
 bool eval_plan(const EvalBlockShape* b, int nb, int N, int H, int W, int dtype, EvalPlan* out) {
   for (int i = 0; i < nb; ++i)
     if (!eval_block_ok(b[i].kind, b[i].c) || (i > 0 && b[i].kind == EVAL_STEM)) return false;
   if (nb < 1 || H * W >= 65536) return false;
   out->launches.clear();
   auto convs = [&](int lo, int hi) { int c = 0; for (int i = lo; i < hi; ++i) c += b[i].kind == EVAL_STEM ? 1 : b[i].kind == EVAL_IDENTITY ? 2 : 3; return c; };
-  if (dtype == BF16) {
+  EvalLaunch whole{};
+  double whole_t = 1e30;
+  for (int gap = 32; dtype == BF16 && gap >= 16; gap -= 16) {
     EvalLaunch l{};
     l.first = 0; l.count = nb; l.H = H; l.W = W; l.TH = H; l.strips = 1;
-    eval_lds(b, nb, H, W, H, 1, dtype, &l);
+    eval_lds(b, nb, H, W, H, 1, dtype, gap, &l);
     l.conv0 = 0; l.nconv = convs(0, nb);
-    if (l.lds <= ev::LDS_MAX) { out->launches.push_back(l); return true; }
+    if (l.lds > ev::LDS_MAX) continue;
+    const double t = eval_cost(b, l, N);
+    if (t < whole_t) { whole_t = t; whole = l; }
   }
+  if (whole.count) { out->launches.push_back(whole); return true; }
   // matrix-core FLOP per second of one compute unit
   const double rate = dtype == BF16 ? 4.0e12 : 0.5e12;
   int h = H, w = W;
@@ -805,25 +847,32 @@ bool eval_plan(const EvalBlockShape* b, int nb, int N, int H, int W, int dtype, 
     const int ho = (h - 1) / s + 1, wo = (w - 1) / s + 1;
     const int co = b[i].kind == EVAL_STEM ? 16 : (b[i].kind == EVAL_DOWN ? 2 * b[i].c : b[i].c);
     const double f2 = 2.0 * 9 * co * co, f1 = b[i].kind == EVAL_STEM ? 0.0 : 2.0 * 9 * co * b[i].c;
-    EvalLaunch best{};
-    double best_t = 1e30;
-    for (int th = 1; th <= ho; ++th) {
-      if (th > 8 && th < ho && th % 4 != 0) continue;
-      EvalLaunch l{};
-      l.first = i; l.count = 1; l.H = h; l.W = w; l.TH = th; l.strips = (ho + th - 1) / th;
-      eval_lds(b + i, 1, h, w, th, l.strips, dtype, &l);
-      if (l.lds > ev::LDS_MAX) continue;
-      // 16-pixel blocks, walked in groups of a workgroup's 8 waves (64 channels: 4 blocks together)
-      auto blocks = [&](int r) { const int pb = (r * wo + 15) / 16, g = co == 16 ? 8 : co == 32 ? 4 : dtype == BF16 ? 4 : 1; return (pb + g - 1) / g * g; };
-      const int r1 = th + 2 < ho ? th + 2 : ho;
-      const double flop = 16.0 * (blocks(r1) * f1 + blocks(th) * f2);   // whole groups of pixel blocks
-      const double rounds = ((size_t)N * l.strips + 255) / 256;   // (registers: one workgroup per compute unit)
-      const double t = rounds * (2e-6 + flop / rate);
-      if (t < best_t) { best_t = t; best = l; }
+    EvalLaunch pick{};
+    double pick_t = 1e30;
+    for (int gap = dtype == BF16 ? 32 : 16; gap >= 16; gap -= 16) {
+      EvalLaunch best{};
+      double best_t = 1e30;
+      for (int th = 1; th <= ho; ++th) {
+        if (th > 8 && th < ho && th % 4 != 0) continue;
+        EvalLaunch l{};
+        l.first = i; l.count = 1; l.H = h; l.W = w; l.TH = th; l.strips = (ho + th - 1) / th;
+        eval_lds(b + i, 1, h, w, th, l.strips, dtype, gap, &l);
+        if (l.lds > ev::LDS_MAX) continue;
+        // 16-pixel blocks, walked in groups of a workgroup's 8 waves (64 channels: 4 blocks together)
+        auto blocks = [&](int r) { const int pb = (r * wo + 15) / 16, g = co == 16 ? 8 : co == 32 ? 4 : dtype == BF16 ? 4 : 1; return (pb + g - 1) / g * g; };
+        const int r1 = th + 2 < ho ? th + 2 : ho;
+        const double flop = 16.0 * (blocks(r1) * f1 + blocks(th) * f2);   // whole groups of pixel blocks
+        const double rounds = ((size_t)N * l.strips + 255) / 256;
+        const double t = rounds * (2e-6 + flop / rate);
+        if (t < best_t) { best_t = t; best = l; }
+      }
+      if (best_t >= 1e30) continue;
+      const double t = dtype == BF16 ? eval_cost(b + i, best, N) : best_t;
+      if (t < pick_t) { pick_t = t; pick = best; }
     }
-    if (best_t >= 1e30) return false;
-    best.conv0 = convs(0, i); best.nconv = convs(i, i + 1);
-    out->launches.push_back(best);
+    if (pick_t >= 1e30) return false;
+    pick.conv0 = convs(0, i); pick.nconv = convs(i, i + 1);
+    out->launches.push_back(pick);
     h = ho; w = wo;
   }
   return true;
@@ -836,17 +885,16 @@ hipError_t eval_blocks_launch(const EvalBlockDesc* dev_blocks, const EvalConvDes
   a.blocks = dev_blocks + l.first; a.nb = l.count; a.in = in; a.out = out; a.N = N; a.H = l.H; a.W = l.W; a.C = C;
   a.TH = l.TH; a.strips = l.strips; a.off1 = l.off1; a.off2 = l.off2; a.red_off = l.red_off;
   a.convs = dev_convs + l.conv0; a.nconv = l.nconv; a.tab_off = l.tab_off; a.dump_off = l.dump_off;
-  const void* f = dtype == BF16 ? reinterpret_cast<const void*>(&ev::eval_blocks_kernel<bf16_t, true>)
-                                : reinterpret_cast<const void*>(&ev::eval_blocks_kernel<float, false>);
-  static bool attr_set[2] = {false, false};
-  if (!attr_set[dtype == BF16]) {
-    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ev::LDS_MAX);
+  typedef void (*Kernel)(ev::Args);
+  static const Kernel kernels[3] = {ev::eval_blocks_kernel<float, false, 16>, ev::eval_blocks_kernel<bf16_t, true, 16>, ev::eval_blocks_kernel<bf16_t, true, 32>};
+  const int which = dtype != BF16 ? 0 : l.gap == 16 ? 1 : 2;
+  static bool attr_set[3] = {false, false, false};
+  if (!attr_set[which]) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernels[which]), hipFuncAttributeMaxDynamicSharedMemorySize, (int)ev::LDS_MAX);
     if (e != hipSuccess) return e;
-    attr_set[dtype == BF16] = true;
+    attr_set[which] = true;
   }
-  const dim3 grid((unsigned)(N * l.strips));
-  if (dtype == BF16) DDG_LAUNCH((ev::eval_blocks_kernel<bf16_t, true>), grid, dim3(ev::NT), l.lds, s, a);
-  else DDG_LAUNCH((ev::eval_blocks_kernel<float, false>), grid, dim3(ev::NT), l.lds, s, a);
+  DDG_LAUNCH(kernels[which], dim3((unsigned)(N * l.strips)), dim3(ev::NT), l.lds, s, a);
   return hipGetLastError();
 }
 
