@@ -344,7 +344,7 @@ struct EvalLaunch {        // blocks [first, first + count) of a module on H x W
   int first, count, conv0, nconv, H, W, TH, strips, gap;     // gap: bytes between pixels in LDS
   unsigned off1, off2, red_off, tab_off, dump_off; size_t lds;
 };
-struct EvalPlan { std::vector<EvalLaunch> launches; };
+struct EvalPlan { std::vector<EvalLaunch> launches; EvalLaunch whole; };   // whole: all blocks in one launch, an image a workgroup (bf16; count 0: does not fit)
 bool eval_block_ok(int kind, int c);
 bool eval_plan(const EvalBlockShape* b, int nb, int N, int H, int W, int dtype, EvalPlan* out);   // false: not covered
 hipError_t eval_blocks_launch(const EvalBlockDesc* dev_blocks, const EvalConvDesc* dev_convs, const EvalLaunch& l, const void* in,

@@ -15,6 +15,7 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <utility>
 #include <vector>
 
 using namespace ddg;
@@ -1913,29 +1914,33 @@ ddg_status ddg_set_running(ddg_module* m, const float* host_src) {
 // The evaluation forward through `blocks` (the module's own forward buffers, or a view of them
 // whose buffers lie elsewhere); hs: the head's per-sample scratch.
 struct HeadScratch { float* pooled; float* dlogits; float* loss_n; };
-// May the many-layer kernel write h_out? Not if a workgroup's output can lie in what another one has still to read: one
-// launch from h_in to h_out with the two overlapping, unless every workgroup takes one image to its own place. The
-// per-layer kernels write h_out in their last launch, which reads h_in pixel by pixel at most.
-static bool eval_fused_ok(const ddg_module* m, const void* h_in, const void* h_out) {
-  if (m->eval.launches.empty()) return false;
-  if (m->d.num_classes > 0 || m->eval.launches.size() > 1) return true;
+// The launches of the many-layer kernel from h_in to h_out; none if it may not write h_out: a workgroup's output must not lie in what
+// another one has still to read, so one launch whose input and output overlap has to take every image to its own place,
+// a whole image per workgroup. The per-layer kernels write h_out in their last launch, which reads h_in pixel by pixel at most.
+static std::pair<const EvalLaunch*, size_t> eval_launches(const ddg_module* m, const void* h_in, const void* h_out) {
+  const std::vector<EvalLaunch>& l = m->eval.launches;
+  if (l.empty() || m->d.num_classes > 0 || l.size() > 1) return {l.data(), l.size()};
   const char *a = (const char*)h_in, *b = (const char*)h_out;
   const bool apart = a + m->in_elems * m->esz <= b || b + m->out_elems * m->esz <= a;
-  return apart || (a == b && m->in_elems == m->out_elems && m->eval.launches[0].strips == 1);
+  if (apart || (a == b && m->in_elems == m->out_elems && l[0].strips == 1)) return {l.data(), 1};
+  if (a == b && m->in_elems == m->out_elems && m->eval.whole.count) return {&m->eval.whole, 1};
+  return {nullptr, 0};
 }
 static ddg_status eval_forward(ddg_module* m, std::vector<Blk>& blocks, const HeadScratch& hs, const void* h_in,
                                void* h_out, const int32_t* labels, float* loss_out, float* logits_out) {
-  const bool head = m->d.num_classes > 0, fused = eval_fused_ok(m, h_in, h_out);
+  const auto launches = eval_launches(m, h_in, h_out);
+  const bool head = m->d.num_classes > 0, fused = launches.second > 0;
   m->stream = m->eval_elsewhere ? m->estream : m->bstream;
   if (m->n_run && !fused) DDG_TRY(eval_vectors_launch(m->run_descs[0], m->n_run, m->run_max_c, m->stream));
   const int nres = (int)blocks.size() - (head ? 1 : 0);
   if (fused) {
     const void* in = h_in;
-    for (const EvalLaunch& l : m->eval.launches) {
+    for (size_t i = 0; i < launches.second; ++i) {
+      const EvalLaunch& l = launches.first[i];
       const int last = l.first + l.count - 1;
       void* out = last == nres - 1 && !head ? h_out : blocks[last].y;
       double flops = 0.0, bytes = ((double)blocks[l.first].u[0].in_elems() + blocks[last].y_elems) * m->esz;
-      for (int i = l.first; i <= last; ++i) for (const Unit& u : blocks[i].u) { flops += conv_flops(u); bytes += wbytes(m, u); }
+      for (int k = l.first; k <= last; ++k) for (const Unit& u : blocks[k].u) { flops += conv_flops(u); bytes += wbytes(m, u); }
       Launch L(m, PK_EVAL, bytes, flops);
       DDG_TRY(eval_blocks_launch(m->eval_descs, m->eval_convs, l, in, out, m->d.batch, blocks[l.first].u[0].cin, m->d.compute, m->stream));
       in = out;

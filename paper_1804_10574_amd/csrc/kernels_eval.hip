@@ -16,7 +16,7 @@
 //           recomputed (fp32, whose matrix rate makes an image 10-18 us per layer on one unit, so
 //           that one image has to be spread over several; bf16 modules whose buffers, each at its largest over the blocks,
 //           exceed LDS: large images, and deep networks in one module from 32x32 on (ResNet-110: its table of scales and shifts
-//           alone is 32 KB)). Strips are no slower than
+//           alone is 32 KB); and bf16 where a few large images would leave most compute units idle). Strips are no slower than
 //           the per-layer kernels either: ResNet-110 in one module, batch 37, 1.29x, batch 1 1.41x. As whole images
 //           ResNet-20 in one module takes 57 us at batch 256 and 54 at batch 1, 130 and 85 in strips.
 //
@@ -817,18 +817,19 @@ static double eval_cost(const EvalBlockShape* b, const EvalLaunch& l, int N) {
 // How a module's blocks are cut into launches: all blocks at once, whole images (bf16, if the buffers fit LDS), or one
 // block per launch in strips of the height that minimises
 //   rounds over 256 compute units x (2 us + the strip's matrix time, halo rows included)
-// (2 us: loads, barriers and epilogues of a block, measured on one image). bf16: in the pitch that
-// eval_cost() finds shorter. us a call, strips of 32 / 16 bytes between pixels, whole images of 32 / 16 (-: does not fit):
+// (2 us: loads, barriers and epilogues of a block, measured on one image). bf16: in either of two pitches, whichever of the four
+// eval_cost() finds shortest. us a call, strips of 32 / 16 bytes between pixels, whole images of 32 / 16 (-: does not fit):
 //   9 blocks of 32 channels, 28x28, 256 images  234 / 184 / - / 97     3 blocks, 24x24, 256 images  54 / 49 / 36 / 31
-//   3 blocks of 64 channels, 14x14, 256 images  65 / 73 / 51 / 59
+//   3 blocks of 64 channels, 14x14, 256 images  65 / 73 / 51 / 59      3 blocks, 14x14, 37 images  34 / 35 / 44 / 53
+//   1 block of 16 channels, 48x48: 8 images 7 in strips, 18 whole; 256 images 24, 24      3 blocks, 256 images 72, 46
 bool eval_plan(const EvalBlockShape* b, int nb, int N, int H, int W, int dtype, EvalPlan* out) {
   for (int i = 0; i < nb; ++i)
     if (!eval_block_ok(b[i].kind, b[i].c) || (i > 0 && b[i].kind == EVAL_STEM)) return false;
   if (nb < 1 || H * W >= 65536) return false;
   out->launches.clear();
+  out->whole = EvalLaunch{};
   auto convs = [&](int lo, int hi) { int c = 0; for (int i = lo; i < hi; ++i) c += b[i].kind == EVAL_STEM ? 1 : b[i].kind == EVAL_IDENTITY ? 2 : 3; return c; };
-  EvalLaunch whole{};
-  double whole_t = 1e30;
+  double whole_t = 1e30, strips_t = 0.0;
   for (int gap = 32; dtype == BF16 && gap >= 16; gap -= 16) {
     EvalLaunch l{};
     l.first = 0; l.count = nb; l.H = H; l.W = W; l.TH = H; l.strips = 1;
@@ -836,9 +837,8 @@ bool eval_plan(const EvalBlockShape* b, int nb, int N, int H, int W, int dtype, 
     l.conv0 = 0; l.nconv = convs(0, nb);
     if (l.lds > ev::LDS_MAX) continue;
     const double t = eval_cost(b, l, N);
-    if (t < whole_t) { whole_t = t; whole = l; }
+    if (t < whole_t) { whole_t = t; out->whole = l; }
   }
-  if (whole.count) { out->launches.push_back(whole); return true; }
   // matrix-core FLOP per second of one compute unit
   const double rate = dtype == BF16 ? 4.0e12 : 0.5e12;
   int h = H, w = W;
@@ -870,12 +870,14 @@ bool eval_plan(const EvalBlockShape* b, int nb, int N, int H, int W, int dtype, 
       const double t = dtype == BF16 ? eval_cost(b + i, best, N) : best_t;
       if (t < pick_t) { pick_t = t; pick = best; }
     }
-    if (pick_t >= 1e30) return false;
+    if (pick_t >= 1e30) { strips_t = 1e30; break; }
     pick.conv0 = convs(0, i); pick.nconv = convs(i, i + 1);
     out->launches.push_back(pick);
+    strips_t += pick_t;
     h = ho; w = wo;
   }
-  return true;
+  if (out->whole.count && whole_t <= strips_t) out->launches.assign(1, out->whole);
+  return out->whole.count || strips_t < 1e30;
 }
 
 hipError_t eval_blocks_launch(const EvalBlockDesc* dev_blocks, const EvalConvDesc* dev_convs, const EvalLaunch& l, const void* in, void* out, int N, int C,

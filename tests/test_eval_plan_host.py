@@ -1,5 +1,5 @@
-"""How evaluation is cut into launches, on the host: whole images where a launch a block takes several times as long, and the
-pitch that was measured to be the shorter one."""
+"""How evaluation is cut into launches, on the host: whole images where a launch a block takes several times as long, strips of
+rows where a few images would leave most compute units idle, and the pitch that was measured to be the shorter one."""
 import pytest
 
 from tests.eval_plan import DOWN, IDENT, STEM, launches
@@ -17,6 +17,14 @@ def test_images_that_only_the_narrow_pitch_fits_are_one_launch(blocks, hw):
 @pytest.mark.parametrize("c,hw,gap", [(32, 16, 32), (64, 8, 32), (64, 16, 32), (32, 24, 16), (32, 38, 16), (64, 24, 16), (64, 20, 32)])
 def test_pitch_by_measured_time(c, hw, gap):
     assert {l[2] for l in launches([(IDENT, c, 1)] * 3, 256, hw)} == {gap}
+
+
+# (blocks of 16 channels, height = width, images, whole images)
+@pytest.mark.parametrize("blocks,hw,n,whole", [(1, 40, 1, False), (1, 44, 37, False), (3, 48, 8, False), (5, 48, 8, False), (3, 48, 256, True), (9, 40, 100, True)])
+def test_a_few_large_images_are_spread_over_the_compute_units(blocks, hw, n, whole):
+    plan = launches([(IDENT, 16, 1)] * blocks, n, hw)
+    assert [l[0] for l in plan] == ([blocks] if whole else [1] * blocks)
+    assert all((l[1] == 1) == whole for l in plan)
 
 
 @pytest.mark.parametrize("bf16", [True, False])

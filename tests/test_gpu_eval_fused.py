@@ -1,23 +1,26 @@
 """The evaluation kernel that keeps activations in LDS across layers, against the oracle: both
-operand types (bf16: whole images; fp32: strips of rows), pixel counts that fill no 16-pixel block,
-odd heights under stride 2, one and several images, an image too large for LDS in bf16 (strips), a
-module whose stages together are, a module that starts with a block between stages, and every channel
-count as first and last. The launches that ran are counted: no other convolution kernel may have."""
+operand types (bf16: whole images, or strips of rows; fp32: strips), pixel counts that fill no 16-pixel block,
+odd heights under stride 2, one and several images, one large image (strips in bf16 too), a
+module whose stages together exceed LDS, a module that starts with a block between stages, and every channel
+count as first and last. The launches that ran are counted, and no other convolution kernel may have."""
 import numpy as np
 import pytest
 
 import workloads as wk
+from tests.eval_plan import launches, shapes
 from workloads.configs import custom_cifar
 
 pytestmark = pytest.mark.gpu
 
-# (units, cuts, batch, image size): what the size is there for
+# (units, cuts, batch, image size): what the size is there for. bf16: the modules are one launch each but where it says strips
 CASES = [(1, [2, 3], 1, 32),        # one image; modules that start with a block between stages
          (1, [], 3, 10),            # 100 / 25 / 9 pixels: ragged everywhere, odd sizes under stride 2
          (2, [3, 5], 2, 24),        # 576 / 144 / 36 pixels
          (3, [4, 7], 2, 28),        # runs of identity blocks at 16, 32 and 64 channels
-         (1, [1, 2], 1, 44),        # bf16: two 16-channel buffers do not fit LDS
-         (1, [], 2, 32)]            # bf16: the buffers of all three stages together do not (strips, one block per launch)
+         (1, [1, 2], 1, 44),        # one large image: strips of a row or two
+         (1, [], 2, 32),            # a whole network
+         (2, [], 2, 40), (1, [], 20, 56)]   # networks whose buffers exceed LDS: strips of a row or two, and of several
+STRIPS = {(1, 1, 44), (2, 2, 40), (1, 20, 56)}     # (units, batch, image size)
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
@@ -53,8 +56,15 @@ def test_fused_evaluation_matches_the_oracle(dtype, units, cuts, batch, hw):
         m.profile_enable(True)
     pipe.forward_eval(xd, yd, loss, logits)
     for m in wl.modules:
-        ran = {kind for kind, v in mods[m.k].profile_read().items() if v[0]}
-        assert ran == ({"eval_blocks"} if len(m.blocks) > (m.k == K) else set()), (m.k, ran)
+        ran = {kind: v[0] for kind, v in mods[m.k].profile_read().items() if v[0]}
+        body = shapes([b.as_tuple() for b in m.blocks])
+        plan = launches(body, batch, m.in_h, dtype == "bf16") if body else []
+        assert ran == ({"eval_blocks": len(plan)} if body else {}), (m.k, ran)
+        if dtype == "bf16":
+            if (units, batch, hw) in STRIPS:
+                assert len(plan) == len(body) and all(l[1] > 1 for l in plan)
+            else:
+                assert len(plan) <= 1
     h = H.from_dev_nhwc(xd) if dtype == "bf16" else x
     for k in range(1, K):
         h = oracle.forward_eval(k, h)

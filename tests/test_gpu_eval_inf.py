@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 import workloads as wk
+from tests.eval_plan import launches, shapes
 
 pytestmark = pytest.mark.gpu
 
@@ -28,19 +29,23 @@ def reached(mask, block):
     return (conv(conv(m, stride), 1) | m[:, ::stride, ::stride]).numpy()
 
 
-# 10: whole images in bf16, 33: more pixels than a wave's registers hold, 44: strips in bf16 (16 channels); fp32: strips
-@pytest.mark.parametrize("hw", [10, 33, 44])
+# bf16: 256 images: whole (33: more pixels than a wave's registers hold; 32 channels of it exceed LDS); 64: strips of several rows;
+# two: strips of a row or two, and whole images where the map is small; fp32: strips
+@pytest.mark.parametrize("hw,N", [(10, 2), (33, 2), (44, 2), (44, 64), (52, 64), (10, 256), (33, 256)])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("which", sorted(BLOCKS))
-def test_an_infinity_reaches_what_it_should(which, dtype, hw):
+def test_an_infinity_reaches_what_it_should(which, dtype, hw, N):
     import torch
     if not torch.cuda.is_available():
         pytest.skip("needs a GPU")
     import paper_1804_10574_amd as ddg
     from paper_1804_10574_amd.ddg import make_desc
-    print(f"case infinity {which} {dtype} hw={hw}", flush=True)
+    print(f"case infinity {which} {dtype} hw={hw} N={N}", flush=True)
     block = BLOCKS[which]
-    cin, cout, stride, N = block[1], block[3], block[4], 2
+    cin, cout, stride = block[1], block[3], block[4]
+    strips = launches(shapes([block]), N, hw, dtype == "bf16")[0][1]
+    if dtype == "bf16" and (N > 2 or hw > 10):
+        assert (strips == 1) == (N == 256 and (which, hw) != ("identity32", 33))
     ho = (hw - 1) // stride + 1
     mod = ddg.Module(make_desc(2, 1, N, (cin, hw, hw), [block], 0, ddg.DDG_BF16 if dtype == "bf16" else ddg.DDG_F32, 0.9, 0.0, 1e-5))
     theta = np.abs(wk.normal(31, 1, mod.param_count()) * 0.05).astype(np.float32) + np.float32(0.01)
