@@ -1,5 +1,5 @@
 // Device -> host copies, large ones through a ring of pinned slots (ddg_readback.cpp). One per module: SLOTS * PIECE
-// bytes of pinned memory (16 MiB), allocated at the first large copy and given back with the module. Calls from
+// bytes of pinned memory (8 MiB), allocated at the first large copy and given back with the module. Calls from
 // several threads take turns.
 #pragma once
 #include <hip/hip_runtime_api.h>
@@ -10,7 +10,7 @@ namespace ddg {
 
 struct Readback {
   static constexpr int SLOTS = 8;
-  static constexpr size_t PIECE = (size_t)2 << 20;
+  static constexpr size_t PIECE = (size_t)1 << 20;
   void* ring = nullptr;
   hipEvent_t ev[SLOTS] = {};
   std::mutex mu;

@@ -87,16 +87,41 @@ int main() {
 """
 
 
-def test_a_copy_comes_back_whole_whatever_is_missing(tmp_path):
+# the first copy of a module pays for the pinned memory: 8 MiB of it, whatever is copied
+PINNED = HARNESS[:HARNESS.index("int main")].replace("*p = no_pinned", "pinned += n; *p = no_pinned").replace("static bool no_pinned", "static size_t pinned = 0; static bool no_pinned") + r"""
+int main() {
+  const size_t MiB = (size_t)1 << 20, most = 40 * MiB + 5;
+  src = (char*)malloc(most); dst = (char*)malloc(most);
+  for (size_t i = 0; i < most; ++i) src[i] = (char)(i * 2654435761u >> 13);
+  for (size_t n : {8 * MiB, 9 * MiB + 1, 19 * MiB, 26 * MiB + 300000, most}) {
+    pinned = 0;
+    if (!copies(n) || plain) return printf("%zu bytes: not copied through the ring\n", n), 1;
+    if (pinned == 0 || pinned > 8 * MiB) return printf("%zu bytes: %zu pinned\n", n, pinned), 1;
+  }
+  printf("all copies whole\n");
+  return 0;
+}
+"""
+
+
+def run(tmp_path, harness):
     gxx = shutil.which("g++")
     inc = "/opt/rocm/include"
     if not gxx or not os.path.isdir(inc):
         pytest.skip("needs g++ and the HIP headers")
     main = tmp_path / "main.cpp"
-    main.write_text(HARNESS)
+    main.write_text(harness)
     exe = tmp_path / "readback"
     subprocess.run([gxx, "-std=c++17", "-O1", "-pthread", "-D__HIP_PLATFORM_AMD__", "-I", inc, "-I", CSRC, str(main),
                     os.path.join(CSRC, "ddg_readback.cpp"), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, (r.stdout[-200:], r.stderr[-200:])
     assert "all copies whole" in r.stdout
+
+
+def test_a_copy_comes_back_whole_whatever_is_missing(tmp_path):
+    run(tmp_path, HARNESS)
+
+
+def test_a_first_copy_pins_no_more_than_8_mib(tmp_path):
+    run(tmp_path, PINNED)
