@@ -266,7 +266,7 @@ __device__ __forceinline__ uint4 pair_rows(const f32x4_t& a, const f32x4_t& b) {
 
 // Identity blocks on whole images of the usual size, 512 / C pixels wide and high (bf16). A wave owns NB pixel blocks
 // below each other (a block is 16 pixels: half a row, a row, or two rows of 8) and walks down the input rows: what it reads
-// of a row serves every output row that the row is a tap of, 27 / 18 / 27 fragment reads a layer instead of 40 / 36 / 36 with
+// of a row serves every output row that the row is a tap of, 26 / 18 / 27 fragment reads a layer instead of 40 / 36 / 36 with
 // a tap at a time, which is most of the LDS time that bounds a layer. All addresses are one per-lane register and an
 // instruction immediate. Fragments are requested D rows ahead, and finished pairs of blocks are normalised and stored
 // between the matrix instructions of the next row. Eight waves:
