@@ -789,8 +789,8 @@ bool eval_block_ok(int kind, int c) {
 
 // Estimated time of a bf16 launch of N images, us: 2 for the launch, 0.15 per MB in and out, and per round over 256 compute units
 // (registers: one workgroup per unit) 2, 1 per layer, 0.04 per KB of a workgroup's rows in and out, and for every 16 pixels of a
-// layer what `per` says, in whole groups of a workgroup's waves. Fitted to 1752 measured evaluations (maps 8 to 64 wide,
-// 1 to 256 images, one to three blocks, both pitches, whole images and strips): 7 % rms.
+// layer what `per` says, in whole groups of a workgroup's waves. Fitted to 1752 measured evaluations (maps 8 to 64 wide, 1 to 256 images,
+// one to three blocks, both pitches, whole images and strips), which it meets within 9 % rms.
 static double eval_cost(const EvalBlockShape* b, const EvalLaunch& l, int N) {
   const bool wide = l.gap == 32;
   double layers = 0.0, matrix = 0.0;
@@ -819,7 +819,7 @@ static double eval_cost(const EvalBlockShape* b, const EvalLaunch& l, int N) {
 //   rounds over 256 compute units x (2 us + the strip's matrix time, halo rows included)
 // (2 us: loads, barriers and epilogues of a block, measured on one image). bf16: in either of two pitches, whichever of the four
 // eval_cost() finds shortest. us a call, strips of 32 / 16 bytes between pixels, whole images of 32 / 16 (-: does not fit):
-//   9 blocks of 32 channels, 28x28, 256 images  234 / 184 / - / 97     3 blocks, 24x24, 256 images  54 / 49 / 36 / 31
+//   3 blocks of 32 channels, 28x28, 256 images  82 / 61 / - / 39       3 blocks, 24x24, 256 images  54 / 49 / 36 / 31
 //   3 blocks of 64 channels, 14x14, 256 images  65 / 73 / 51 / 59      3 blocks, 14x14, 37 images  34 / 35 / 44 / 53
 //   1 block of 16 channels, 48x48: 8 images 7 in strips, 18 whole; 256 images 24, 24      3 blocks, 256 images 72, 46
 bool eval_plan(const EvalBlockShape* b, int nb, int N, int H, int W, int dtype, EvalPlan* out) {
