@@ -347,8 +347,8 @@ struct EvalLaunch {        // blocks [first, first + count) of a module on H x W
 struct EvalPlan { std::vector<EvalLaunch> launches; EvalLaunch whole; };   // whole: all blocks in one launch, an image a workgroup (bf16; count 0: does not fit)
 bool eval_block_ok(int kind, int c);
 bool eval_plan(const EvalBlockShape* b, int nb, int N, int H, int W, int dtype, EvalPlan* out);   // false: not covered
-hipError_t eval_blocks_launch(const EvalBlockDesc* dev_blocks, const EvalConvDesc* dev_convs, const EvalLaunch& l, const void* in,
-                              void* out, int N, int C, int dtype, hipStream_t s);
+struct EvalTables { const EvalBlockDesc* dev_blocks; const EvalConvDesc* dev_convs; const EvalBlockDesc* blocks; const EvalConvDesc* convs; };   // on the device, and the same on the host
+hipError_t eval_blocks_launch(const EvalTables& t, const EvalLaunch& l, const void* in, void* out, int N, int C, int dtype, hipStream_t s);
 
 hipError_t set_scalar_launch(float* dst, float v, hipStream_t s);
 // Adam (Algorithm 2): pw[0], pw[1] hold beta1^n, beta2^n in device memory, so that a captured graph replays correctly; multiplied

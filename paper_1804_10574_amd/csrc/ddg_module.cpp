@@ -175,8 +175,8 @@ struct ddg_module {
   std::vector<RunDesc*> run_descs; RunDesc* run_descs_f = nullptr; int n_run = 0, run_max_c = 0;
   int32_t* zero_labels = nullptr;  // head modules: labels for an evaluation without labels
   EvalPlan eval;                   // launches of the many-layer evaluation kernel; empty: the per-layer kernels
-  EvalBlockDesc* eval_descs = nullptr;
-  EvalConvDesc* eval_convs = nullptr;
+  EvalBlockDesc* eval_descs = nullptr; std::vector<EvalBlockDesc> eval_descs_host;
+  EvalConvDesc* eval_convs = nullptr; std::vector<EvalConvDesc> eval_convs_host;
   bool eval_elsewhere = false; hipStream_t estream = nullptr;   // the pipeline runs every module's evaluation on one stream
   bool eval_mode = false;          // the forward helpers normalise with the evaluation vectors
   float* ws_stat = nullptr; size_t ws_stat_elems = 0;
@@ -1594,6 +1594,7 @@ ddg_status build_eval_plan(ddg_module* m) {
     return fail(DDG_ERR_DEVICE, "copying the layer tables failed");
   m->eval_descs = (EvalBlockDesc*)p;
   m->eval_convs = (EvalConvDesc*)q;
+  m->eval_descs_host = tab; m->eval_convs_host = convs;
   m->eval = plan;
   return DDG_OK;
 }
@@ -1942,7 +1943,7 @@ static ddg_status eval_forward(ddg_module* m, std::vector<Blk>& blocks, const He
       double flops = 0.0, bytes = ((double)blocks[l.first].u[0].in_elems() + blocks[last].y_elems) * m->esz;
       for (int k = l.first; k <= last; ++k) for (const Unit& u : blocks[k].u) { flops += conv_flops(u); bytes += wbytes(m, u); }
       Launch L(m, PK_EVAL, bytes, flops);
-      DDG_TRY(eval_blocks_launch(m->eval_descs, m->eval_convs, l, in, out, m->d.batch, blocks[l.first].u[0].cin, m->d.compute, m->stream));
+      DDG_TRY(eval_blocks_launch({m->eval_descs, m->eval_convs, m->eval_descs_host.data(), m->eval_convs_host.data()}, l, in, out, m->d.batch, blocks[l.first].u[0].cin, m->d.compute, m->stream));
       in = out;
     }
   } else if (nres > 0) {

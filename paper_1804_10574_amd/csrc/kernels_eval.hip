@@ -79,8 +79,16 @@ struct Args {
   const EvalConvDesc* convs; int nconv;  // and their convolutions
   const void* in; void* out;
   int N, H, W, C;          // input of the first block (C: real channels)
-  int TH, strips;          // output rows per workgroup; strips > 1 only with nb == 1
   unsigned off1, off2, red_off, tab_off, dump_off;   // LDS offsets: second and third region, exchange area, scale / shift table
+};
+// A launch of one block in strips of TH output rows. Its convolutions come with the arguments: from a table in memory a workgroup would
+// fetch the table, then the pointers, then what they point at.
+struct StripArgs {
+  EvalConvDesc conv[3];
+  const void* in; void* out;
+  int H, W, C, stride;     // input of the block (C: real channels)
+  int TH, strips;
+  unsigned off1, off2, red_off, tab_off;
 };
 
 // One convolution layer shape: CIN -> COUT, R x R, stride S, NCB channel blocks and 1/KS of the
@@ -105,20 +113,28 @@ struct Conv {
   __device__ static __forceinline__ int kh(int wave) { return KS == 1 ? 0 : (wave / CBG) % KS; }
   __device__ static __forceinline__ int pg(int wave) { return wave / (CBG * KS); }
 
-  // weights from memory, scale and shift ([COUT] each) from the LDS table
-  __device__ static __forceinline__ void load(const EvalConvDesc& d, int tab, Wts& r, int wave, int lane) {
+  // weights from memory
+  __device__ static __forceinline__ void load_weights(const EvalConvDesc& d, Wts& r, int wave, int lane) {
     const T* w = reinterpret_cast<const T*>(d.w);
+#pragma unroll
+    for (int b = 0; b < NCB; ++b)
+#pragma unroll
+      for (int ks = 0; ks < KPW; ++ks)
+        r.w[b][ks] = load16<frag_t>(w + ((size_t)((kh(wave) * KPW + ks) * OCB + cbg(wave) * NCB + b) * 64 + lane) * KV);
+  }
+  // scale and shift ([COUT] each) from the LDS table
+  __device__ static __forceinline__ void load_affine(const EvalConvDesc& d, int tab, Wts& r, int wave, int lane) {
     const float* sc = reinterpret_cast<const float*>(lds() + tab) + d.toff;
 #pragma unroll
     for (int b = 0; b < NCB; ++b) {
-      const int cb = cbg(wave) * NCB + b;
-#pragma unroll
-      for (int ks = 0; ks < KPW; ++ks)
-        r.w[b][ks] = load16<frag_t>(w + ((size_t)((kh(wave) * KPW + ks) * OCB + cb) * 64 + lane) * KV);
-      const int c = cb * 16 + (lane >> 4) * 4;
+      const int c = (cbg(wave) * NCB + b) * 16 + (lane >> 4) * 4;
       r.sc[b] = *reinterpret_cast<const float4*>(sc + c);
       r.sh[b] = *reinterpret_cast<const float4*>(sc + COUT + c);
     }
+  }
+  __device__ static __forceinline__ void load(const EvalConvDesc& d, int tab, Wts& r, int wave, int lane) {
+    load_weights(d, r, wave, lane);
+    load_affine(d, tab, r, wave, lane);
   }
   // per-lane LDS offset of k-step ks relative to the top left tap of an output pixel (RB: bytes of a
   // row of the source buffer)
@@ -466,9 +482,11 @@ __device__ __forceinline__ void identity_images(const EvalConvDesc* cv, int tab,
   }
 }
 
-// `count` identity blocks of C channels, output rows [lo, hi) (all rows when count > 1)
-template <typename T, int GAP, int C>
-__device__ __forceinline__ void identity_run(const EvalConvDesc* cv, int tab, int count, Bufs& B, int lo, int hi, int red, int& flip) {
+// `count` identity blocks of C channels, output rows [lo, hi) (all rows when count > 1). pre() is what has to be done before the
+// first contraction, with both layers' weights on their way; it is followed by a barrier. last(v, row, channel, pixel, valid) takes
+// four channels of an output pixel of the last block (of every block when count > 1).
+template <typename T, int GAP, int C, typename Pre, typename Last>
+__device__ __forceinline__ void identity_run(const EvalConvDesc* cv, int tab, int count, Bufs& B, int lo, int hi, int red, int& flip, Pre pre, Last last) {
   typedef typename Same<T, GAP, C>::type K;
   constexpr int PIX = K::PIX;
   const int tid = own_tid<T>(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -476,12 +494,17 @@ __device__ __forceinline__ void identity_run(const EvalConvDesc* cv, int tab, in
   const int olo = lo > 0 ? lo - 1 : 0, ohi = hi < B.H ? hi + 1 : B.H;
   const int orow0 = lo - 1;
   const int cq = K::cbg(wave) * K::NCB_ * 16 + (lane >> 4) * 4;
+  typename K::Wts w1, w2;
+  K::load_weights(cv[0], w1, wave, lane);
+  K::load_weights(cv[1], w2, wave, lane);
   int ka[K::KPW];
   K::addresses(ka, wave, lane, RB);
-  typename K::Wts w1, w2;
-  K::load(cv[0], tab, w1, wave, lane);
+  pre();
+  __syncthreads();
+  K::load_affine(cv[0], tab, w1, wave, lane);
   for (int i = 0; i < count; ++i) {
-    K::load(cv[2 * i + 1], tab, w2, wave, lane);
+    if (i > 0) K::load_weights(cv[2 * i + 1], w2, wave, lane);
+    K::load_affine(cv[2 * i + 1], tab, w2, wave, lane);
     K::pass(B.x, B.row0, RB, olo, ohi, W, ka, w1, red, flip, wave, lane,
             [&](const f32x4_t& acc, int b, int row, int col, bool ok) __attribute__((always_inline)) {
               float v[4];
@@ -498,15 +521,15 @@ __device__ __forceinline__ void identity_run(const EvalConvDesc* cv, int tab, in
               Store<T>::load4(reinterpret_cast<const T*>(lds() + p), r);
 #pragma unroll
               for (int e = 0; e < 4; ++e) v[e] += r[e];
-              if (ok) store_relu<T>(p, v);
+              last(v, cq + b * 16, row, col, p, ok);
             });
-    __syncthreads();
+    if (i + 1 < count) __syncthreads();
   }
 }
 
-// A block between stages: C -> 2C channels, stride 2, 1x1 projection on the shortcut
-template <typename T, int GAP, int C>
-__device__ __forceinline__ void down_block(const EvalConvDesc* cv, int tab, Bufs& B, int lo, int hi, int Ho, int Wo, int red, int& flip) {
+// A block between stages: C -> 2C channels, stride 2, 1x1 projection on the shortcut (pre, last: as above)
+template <typename T, int GAP, int C, typename Pre, typename Last>
+__device__ __forceinline__ void down_block(const EvalConvDesc* cv, int tab, const Bufs& B, int lo, int hi, int Ho, int Wo, int red, int& flip, Pre pre, Last last) {
   typedef typename Down<T, GAP, C>::type K1;
   typedef typename Same<T, GAP, 2 * C>::type K2;
   typedef Conv<T, GAP, C, 2 * C, 1, 2, K2::NCB_, 1, 1> KP;    // (only its weight layout: same channel blocks as K2)
@@ -514,17 +537,18 @@ __device__ __forceinline__ void down_block(const EvalConvDesc* cv, int tab, Bufs
   const int RB = row_bytes(B.W, K1::PIX), RBo = row_bytes(Wo, K2::PIX);
   const int olo = lo > 0 ? lo - 1 : 0, ohi = hi < Ho ? hi + 1 : Ho;
   const int orow0 = lo - 1;
-  zero<T>(B.o, (hi - lo + 2) * RBo);
-  zero<T>(B.y, (hi - lo + 2) * RBo);
   typename K1::Wts w1;
   typename K2::Wts w2;
-  K1::load(cv[0], tab, w1, wave, lane);
+  K1::load_weights(cv[0], w1, wave, lane);
+  K2::load_weights(cv[1], w2, wave, lane);
+  zero<T>(B.o, (hi - lo + 2) * RBo);
+  pre();
   __syncthreads();
+  K1::load_affine(cv[0], tab, w1, wave, lane);
   {
     int ka[K1::KPW];
     K1::addresses(ka, wave, lane, RB);
     const int cq = K1::cbg(wave) * K1::NCB_ * 16 + (lane >> 4) * 4;
-    K2::load(cv[1], tab, w2, wave, lane);
     K1::pass(B.x, B.row0, RB, olo, ohi, Wo, ka, w1, red, flip, wave, lane,
              [&](const f32x4_t& acc, int b, int row, int col, bool ok) __attribute__((always_inline)) {
                float v[4];
@@ -532,23 +556,24 @@ __device__ __forceinline__ void down_block(const EvalConvDesc* cv, int tab, Bufs
                if (ok) store_relu<T>(B.o + (row - orow0) * RBo + (col + 1) * K2::PIX + (cq + b * 16) * (int)sizeof(T), v);
              });
   }
+  // the projection: every wave the channel blocks it finishes, the whole contraction
+  const int cg = K2::cbg(wave), cq = cg * K2::NCB_ * 16 + (lane >> 4) * 4;
+  typename KP::frag_t wp[K2::NCB_][KP::KPW];
+  float4 psc[K2::NCB_], psh[K2::NCB_];
+#pragma unroll
+  for (int b = 0; b < K2::NCB_; ++b) {
+#pragma unroll
+    for (int ks = 0; ks < KP::KPW; ++ks)
+      wp[b][ks] = load16<typename KP::frag_t>(reinterpret_cast<const T*>(cv[2].w) +
+                                              ((size_t)(ks * KP::OCB + cg * K2::NCB_ + b) * 64 + lane) * KP::KV);
+    psc[b] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(lds() + tab) + cv[2].toff + cq + b * 16);
+    psh[b] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(lds() + tab) + cv[2].toff + 2 * C + cq + b * 16);
+  }
+  K2::load_affine(cv[1], tab, w2, wave, lane);
   __syncthreads();
   {
     int ka[K2::KPW], kp[KP::KPW];
     K2::addresses(ka, wave, lane, RBo);
-    const int cg = K2::cbg(wave), cq = cg * K2::NCB_ * 16 + (lane >> 4) * 4;
-    // the projection: every wave the channel blocks it finishes, the whole contraction
-    typename KP::frag_t wp[K2::NCB_][KP::KPW];
-    float4 psc[K2::NCB_], psh[K2::NCB_];
-#pragma unroll
-    for (int b = 0; b < K2::NCB_; ++b) {
-#pragma unroll
-      for (int ks = 0; ks < KP::KPW; ++ks)
-        wp[b][ks] = load16<typename KP::frag_t>(reinterpret_cast<const T*>(cv[2].w) +
-                                                ((size_t)(ks * KP::OCB + cg * K2::NCB_ + b) * 64 + lane) * KP::KV);
-      psc[b] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(lds() + tab) + cv[2].toff + cq + b * 16);
-      psh[b] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(lds() + tab) + cv[2].toff + 2 * C + cq + b * 16);
-    }
 #pragma unroll
     for (int ks = 0; ks < KP::KPW; ++ks) {
       const int k = (ks * 4 + (lane >> 4)) * KP::KV;
@@ -566,12 +591,9 @@ __device__ __forceinline__ void down_block(const EvalConvDesc* cv, int tab, Bufs
                affine<T>(pa, psc[b], psh[b], r);
 #pragma unroll
                for (int e = 0; e < 4; ++e) v[e] += r[e];
-               if (ok) store_relu<T>(B.y + (row - orow0) * RBo + (col + 1) * K2::PIX + (cq + b * 16) * (int)sizeof(T), v);
+               last(v, cq + b * 16, row, col, B.y + (row - orow0) * RBo + (col + 1) * K2::PIX + (cq + b * 16) * (int)sizeof(T), ok);
              });
   }
-  __syncthreads();
-  const int t = B.x; B.x = B.y; B.y = t;
-  B.row0 = orow0; B.H = Ho; B.W = Wo;
 }
 
 // rows [row0, row0 + rows) of an image with C channels into a buffer with a zero border
@@ -606,10 +628,10 @@ __device__ __forceinline__ void load_rows_stem(int buf, const T* img, int row0, 
   }
 }
 
-// (the fp32 kernel runs strips; whole images only where an image is one strip)
-template <typename T, bool WHOLE, int GAP>
+// the blocks of a launch, an image per workgroup
+template <typename T, int GAP>
 __global__ __launch_bounds__(NT) void eval_blocks_kernel(Args a) {
-  const int n = blockIdx.x / a.strips, st = blockIdx.x - n * a.strips;
+  const int n = blockIdx.x;
   const int tid = threadIdx.x;
   const int red = (int)a.red_off;
   int flip = 0;
@@ -618,20 +640,16 @@ __global__ __launch_bounds__(NT) void eval_blocks_kernel(Args a) {
   B.H = a.H; B.W = a.W;
   int C = a.C;
   const T* img = reinterpret_cast<const T*>(a.in) + (size_t)n * a.H * a.W * a.C;
-  // output rows of the (first) block, and the input rows they need
   const EvalBlockDesc& b0 = a.blocks[0];
-  const int st0 = b0.kind == EVAL_DOWN ? 2 : b0.stride;
-  const int Ho0 = (a.H - 1) / st0 + 1;
-  int lo = a.strips > 1 ? st * a.TH : 0, hi = a.strips > 1 ? (lo + a.TH < Ho0 ? lo + a.TH : Ho0) : Ho0;
+  const int Ho0 = (a.H - 1) / (b0.kind == EVAL_DOWN ? 2 : b0.stride) + 1;
+  B.row0 = -1;
   {
-    const int olo = b0.kind == EVAL_STEM ? lo : (lo > 0 ? lo - 1 : 0), ohi = b0.kind == EVAL_STEM ? hi : (hi < Ho0 ? hi + 1 : Ho0);
-    B.row0 = olo * st0 - 1;
-    const int rows = (ohi - 1) * st0 + 2 - B.row0;
+    const int rows = (Ho0 - 1) * (b0.kind == EVAL_DOWN ? 2 : b0.stride) + 3;
     if (b0.kind == EVAL_STEM) {
       load_rows_stem<T>(B.o, img, B.row0, rows, a.H, a.W, a.C);
     } else {
       load_rows<T>(B.x, img, B.row0, rows, a.H, a.W, a.C, pix_bytes<T, GAP>(a.C));
-      if (b0.kind == EVAL_IDENTITY) zero<T>(B.o, (hi - lo + 2) * row_bytes(a.W, pix_bytes<T, GAP>(a.C)));
+      if (b0.kind == EVAL_IDENTITY) zero<T>(B.o, (a.H + 2) * row_bytes(a.W, pix_bytes<T, GAP>(a.C)));
     }
   }
   // scale and shift of every batch norm of the launch, a wave per layer and four layers at a time
@@ -667,9 +685,8 @@ __global__ __launch_bounds__(NT) void eval_blocks_kernel(Args a) {
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int Wo = (a.W - 1) / b0.stride + 1, srow0 = B.row0;
     constexpr int PIX = pix_bytes<T, GAP>(16);
-    B.row0 = lo - 1;
     const int RBo = row_bytes(Wo, PIX), RBi = row_bytes(a.W, K1::PIX);
-    zero<T>(B.x, (hi - lo + 2) * RBo);
+    zero<T>(B.x, (Ho0 + 2) * RBo);
     typename K1::Wts w;
     __syncthreads();
     K1::load(a.convs[0], tab, w, wave, lane);
@@ -682,12 +699,12 @@ __global__ __launch_bounds__(NT) void eval_blocks_kernel(Args a) {
       if (ok) store_relu<T>(B.x + (row - B.row0) * RBo + (col + 1) * PIX + (lane >> 4) * 4 * (int)sizeof(T), v);
     };
     if (b0.stride == 1) {
-      K1::pass(B.o, srow0, RBi, lo, hi, Wo, ka, w, red, flip, wave, lane, put);
+      K1::pass(B.o, srow0, RBi, 0, Ho0, Wo, ka, w, red, flip, wave, lane, put);
     } else {
       typename K2::Wts v2;
 #pragma unroll
       for (int k = 0; k < K2::KPW; ++k) v2.w[0][k] = w.w[0][k];
-      K2::pass(B.o, srow0, RBi, lo, hi, Wo, ka, v2, red, flip, wave, lane, put);
+      K2::pass(B.o, srow0, RBi, 0, Ho0, Wo, ka, v2, red, flip, wave, lane, put);
     }
     B.H = Ho0; B.W = Wo; C = 16;
     __syncthreads();
@@ -695,46 +712,151 @@ __global__ __launch_bounds__(NT) void eval_blocks_kernel(Args a) {
     if (bi < a.nb) zero<T>(B.o, (B.H + 2) * row_bytes(B.W, PIX));   // (the input image was there)
   }
   __syncthreads();
+  auto none = [] {};
+  auto in_lds = [](float (&v)[4], int, int, int, int p, bool ok) __attribute__((always_inline)) { if (ok) store_relu<T>(p, v); };
   while (bi < a.nb) {
-    const int kind = a.blocks[bi].kind;
-    if (bi > 0) { lo = 0; hi = kind == EVAL_DOWN ? (B.H - 1) / 2 + 1 : B.H; }
-    if (kind == EVAL_IDENTITY) {
+    const EvalConvDesc* cv = a.convs + (a.blocks[bi].conv0 - a.blocks[0].conv0);
+    if (a.blocks[bi].kind == EVAL_IDENTITY) {
       int cnt = 1;
       while (bi + cnt < a.nb && a.blocks[bi + cnt].kind == EVAL_IDENTITY) ++cnt;
       const int npx = B.H * B.W;
-      const EvalConvDesc* cv0 = a.convs + (a.blocks[bi].conv0 - a.blocks[0].conv0);
-      const bool whole = a.strips == 1 && WHOLE, square = sizeof(T) == 2 && B.W == 512 / C && B.H == B.W;
+      const bool square = B.W == 512 / C && B.H == B.W;
       if (C == 16) {
-        if (whole && square) identity_square<GAP, 16>(cv0, tab, cnt, B, red, flip);
-        else if (whole && npx <= 1024) identity_images<T, GAP, 16, WHOLE ? 2 : 1>(cv0, tab, cnt, B, red, (int)a.dump_off, flip);
-        else identity_run<T, GAP, 16>(cv0, tab, cnt, B, lo, hi, red, flip);
+        if (square) identity_square<GAP, 16>(cv, tab, cnt, B, red, flip);
+        else if (npx <= 1024) identity_images<T, GAP, 16, 2>(cv, tab, cnt, B, red, (int)a.dump_off, flip);
+        else identity_run<T, GAP, 16>(cv, tab, cnt, B, 0, B.H, red, flip, none, in_lds);
       } else if (C == 32) {
-        if (whole && square) identity_square<GAP, 32>(cv0, tab, cnt, B, red, flip);
-        else if (whole && npx <= 256) identity_images<T, GAP, 32, 1>(cv0, tab, cnt, B, red, (int)a.dump_off, flip);
-        else identity_run<T, GAP, 32>(cv0, tab, cnt, B, lo, hi, red, flip);
+        if (square) identity_square<GAP, 32>(cv, tab, cnt, B, red, flip);
+        else if (npx <= 256) identity_images<T, GAP, 32, 1>(cv, tab, cnt, B, red, (int)a.dump_off, flip);
+        else identity_run<T, GAP, 32>(cv, tab, cnt, B, 0, B.H, red, flip, none, in_lds);
       } else {
-        if (whole && square) identity_square<GAP, 64>(cv0, tab, cnt, B, red, flip);
-        else if (whole && npx <= 64) identity_images<T, GAP, 64, 1>(cv0, tab, cnt, B, red, (int)a.dump_off, flip);
-        else identity_run<T, GAP, 64>(cv0, tab, cnt, B, lo, hi, red, flip);
+        if (square) identity_square<GAP, 64>(cv, tab, cnt, B, red, flip);
+        else if (npx <= 64) identity_images<T, GAP, 64, 1>(cv, tab, cnt, B, red, (int)a.dump_off, flip);
+        else identity_run<T, GAP, 64>(cv, tab, cnt, B, 0, B.H, red, flip, none, in_lds);
       }
+      __syncthreads();
       bi += cnt;
     } else {
       const int Ho = (B.H - 1) / 2 + 1, Wo = (B.W - 1) / 2 + 1;
-      const EvalConvDesc* cv = a.convs + (a.blocks[bi].conv0 - a.blocks[0].conv0);
-      if (C == 16) down_block<T, GAP, 16>(cv, tab, B, lo, hi, Ho, Wo, red, flip);
-      else down_block<T, GAP, 32>(cv, tab, B, lo, hi, Ho, Wo, red, flip);
+      zero<T>(B.y, (Ho + 2) * row_bytes(Wo, pix_bytes<T, GAP>(2 * C)));
+      if (C == 16) down_block<T, GAP, 16>(cv, tab, B, 0, Ho, Ho, Wo, red, flip, none, in_lds);
+      else down_block<T, GAP, 32>(cv, tab, B, 0, Ho, Ho, Wo, red, flip, none, in_lds);
+      __syncthreads();
+      const int t = B.x; B.x = B.y; B.y = t;
+      B.H = Ho; B.W = Wo;
       C *= 2;
       ++bi;
     }
   }
-  // the output rows of this workgroup
+  // the image's output
   constexpr int V = Store<T>::VEC;
-  const int ch = C / V, pix = pix_bytes<T, GAP>(C), RB = row_bytes(B.W, pix), per_row = B.W * ch, total = (hi - lo) * per_row;
-  T* out = reinterpret_cast<T*>(a.out) + ((size_t)n * B.H + lo) * B.W * C;
+  const int ch = C / V, pix = pix_bytes<T, GAP>(C), RB = row_bytes(B.W, pix), per_row = B.W * ch, total = B.H * per_row;
+  T* out = reinterpret_cast<T*>(a.out) + (size_t)n * B.H * B.W * C;
   for (int i = tid; i < total; i += NT) {
     const int r = i / per_row, e = i - r * per_row, px = e / ch, k = e - px * ch;
     *reinterpret_cast<uint4*>(out + (size_t)i * V) =
-        *reinterpret_cast<const uint4*>(lds() + B.x + (lo + r - B.row0) * RB + (px + 1) * pix + k * 16);
+        *reinterpret_cast<const uint4*>(lds() + B.x + (r + 1) * RB + (px + 1) * pix + k * 16);
+  }
+}
+
+// One block in strips. A workgroup runs 3-10 us, most of it waiting for memory, so everything it reads is requested before anything is
+// waited for: batch-norm vectors, the first rows, the weights of both layers. KIND and C (input channels; stem: none) at
+// compile time: the code of one kind of block is a tenth of that of all of them.
+template <typename T, int GAP, int KIND, int C>
+__global__ __launch_bounds__(NT) void eval_strip_kernel(StripArgs a) {
+  constexpr int V = Store<T>::VEC, NCONV = KIND == EVAL_STEM ? 1 : KIND == EVAL_IDENTITY ? 2 : 3, CO = KIND == EVAL_STEM ? 16 : KIND == EVAL_IDENTITY ? C : 2 * C;
+  const int n = blockIdx.x / a.strips, st = blockIdx.x - n * a.strips;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int red = (int)a.red_off;
+  int flip = 0;
+  Bufs B;
+  B.x = 0; B.o = (int)a.off1; B.y = (int)a.off2;
+  B.H = a.H; B.W = a.W;
+  const T* img = reinterpret_cast<const T*>(a.in) + (size_t)n * a.H * a.W * a.C;
+  // output rows of this workgroup, and the input rows they need
+  const int s0 = KIND == EVAL_DOWN ? 2 : KIND == EVAL_STEM ? a.stride : 1;
+  const int Ho = (a.H - 1) / s0 + 1, Wo = (a.W - 1) / s0 + 1;
+  const int lo = st * a.TH, hi = lo + a.TH < Ho ? lo + a.TH : Ho;
+  const int olo = KIND == EVAL_STEM ? lo : (lo > 0 ? lo - 1 : 0), ohi = KIND == EVAL_STEM ? hi : (hi < Ho ? hi + 1 : Ho);
+  B.row0 = olo * s0 - 1;
+  const int rows = (ohi - 1) * s0 + 2 - B.row0;
+  // ---- batch norms: a wave per convolution
+  float g = 0.f, be = 0.f, rm = 0.f, rv = 0.f;
+  const EvalConvDesc& mine = a.conv[wave < NCONV ? wave : 0];
+  const int mc = lane < mine.cout ? lane : 0;
+  if (wave < NCONV) { g = load_f(mine.gamma + mc); be = load_f(mine.beta + mc); rm = load_f(mine.rmean + mc); rv = load_f(mine.rvar + mc); }
+  // ---- input rows, zero border and padding between pixels included: 16-byte chunks of LDS, U of a thread at a time
+  constexpr int U = 4;
+  uint4 q[U];
+  constexpr int PIXI = KIND == EVAL_STEM ? 16 : pix_bytes<T, GAP>(C);
+  const int per_row = row_bytes(a.W, PIXI) / 16, total = rows * per_row;
+  const wide_rsrc_t ri = wide_rsrc(img, (size_t)a.H * a.W * a.C * sizeof(T));
+  auto request = [&](int i0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u * NT, r = i / per_row, e = i - r * per_row, h = B.row0 + r;
+      const int w = e / (PIXI / 16) - 1, k = e % (PIXI / 16);
+      const bool in = i < total && h >= 0 && h < a.H && w >= 0 && w < a.W;
+      if (KIND == EVAL_STEM) {        // up to V channels of a pixel
+        float f[V];
+#pragma unroll
+        for (int c = 0; c < V; ++c) f[c] = in && c < a.C ? Store<T>::load1(img + ((size_t)h * a.W + w) * a.C + c) : 0.f;
+        if (sizeof(T) == 4) q[u] = make_uint4(__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3]));
+        else q[u] = make_uint4(Store<bf16_t>::pack2(f[0], f[1]), Store<bf16_t>::pack2(f[2], f[3]), 0u, 0u);
+      } else {
+        q[u] = wide_load(ri, in && k < C / V ? (unsigned)((h * a.W + w) * C + k * V) * (unsigned)sizeof(T) : NOWHERE, 0);
+      }
+    }
+  };
+  const int dst = KIND == EVAL_STEM ? B.o : B.x;
+  if (KIND != EVAL_STEM) request(tid);
+  const int tab = (int)a.tab_off - 4 * a.conv[0].toff;
+  auto pre = [&]() __attribute__((always_inline)) {
+    if (KIND == EVAL_IDENTITY) zero<T>(B.o, (hi - lo + 2) * row_bytes(a.W, PIXI));
+    if (wave < NCONV && lane < mine.cout) {
+      float* t = reinterpret_cast<float*>(lds() + tab) + mine.toff;
+      const float sc = g / sqrtf(rv + mine.eps);
+      t[lane] = sc; t[mine.cout + lane] = be - rm * sc;
+    }
+    for (int i0 = tid; i0 < total; i0 += U * NT) {
+      if (KIND == EVAL_STEM || i0 != tid) request(i0);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (i0 + u * NT < total) *reinterpret_cast<uint4*>(lds() + dst + (i0 + u * NT) * 16) = q[u];
+    }
+  };
+  T* out = reinterpret_cast<T*>(a.out) + (size_t)n * Ho * Wo * CO;
+  auto last = [&](float (&v)[4], int c, int row, int col, int, bool ok) __attribute__((always_inline)) {
+    if (ok) Store<T>::store4(out + ((size_t)row * Wo + col) * CO + c, fmaxf(v[0], 0.f), fmaxf(v[1], 0.f), fmaxf(v[2], 0.f), fmaxf(v[3], 0.f));
+  };
+  if constexpr (KIND == EVAL_IDENTITY) {
+    identity_run<T, GAP, C>(a.conv, tab, 1, B, lo, hi, red, flip, pre, last);
+  } else if constexpr (KIND == EVAL_DOWN) {
+    down_block<T, GAP, C>(a.conv, tab, B, lo, hi, Ho, Wo, red, flip, pre, last);
+  } else {
+    typedef Conv<T, GAP, Mma<T>::KV, 16, 3, 1, 1, 1, 2> K1;
+    typedef Conv<T, GAP, Mma<T>::KV, 16, 3, 2, 1, 1, 2> K2;
+    typename K1::Wts w;
+    K1::load_weights(a.conv[0], w, wave, lane);
+    const int RBi = row_bytes(a.W, K1::PIX);
+    int ka[K1::KPW];
+    K1::addresses(ka, wave, lane, RBi);
+    pre();
+    __syncthreads();
+    K1::load_affine(a.conv[0], tab, w, wave, lane);
+    auto put = [&](const f32x4_t& acc, int b, int row, int col, bool ok) __attribute__((always_inline)) {
+      float v[4];
+      affine<T>(acc, w.sc[b], w.sh[b], v);
+      last(v, (lane >> 4) * 4, row, col, 0, ok);
+    };
+    if (a.stride == 1) {
+      K1::pass(B.o, B.row0, RBi, lo, hi, Wo, ka, w, red, flip, wave, lane, put);
+    } else {
+      typename K2::Wts v2;
+#pragma unroll
+      for (int k = 0; k < K2::KPW; ++k) v2.w[0][k] = w.w[0][k];
+      K2::pass(B.o, B.row0, RBi, lo, hi, Wo, ka, v2, red, flip, wave, lane, put);
+    }
   }
 }
 
@@ -880,23 +1002,53 @@ bool eval_plan(const EvalBlockShape* b, int nb, int N, int H, int W, int dtype, 
   return out->whole.count || strips_t < 1e30;
 }
 
-hipError_t eval_blocks_launch(const EvalBlockDesc* dev_blocks, const EvalConvDesc* dev_convs, const EvalLaunch& l, const void* in, void* out, int N, int C,
-                              int dtype, hipStream_t s) {
-  if (!dev_blocks || !dev_convs || l.nconv < 1 || N < 1 || l.count < 1 || l.lds > ev::LDS_MAX || (l.strips > 1 && l.count != 1)) return hipErrorInvalidValue;
+namespace ev {
+template <typename T, int GAP, int KIND, int C>
+static hipError_t strip_run(const StripArgs& a, unsigned grid, size_t lds, hipStream_t s) {
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&eval_strip_kernel<T, GAP, KIND, C>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX);
+  if (attr != hipSuccess) return attr;
+  DDG_LAUNCH((eval_strip_kernel<T, GAP, KIND, C>), dim3(grid), dim3(NT), lds, s, a);
+  return hipGetLastError();
+}
+template <typename T, int GAP>
+static hipError_t strip_launch(int kind, const StripArgs& a, unsigned grid, size_t lds, hipStream_t s) {
+  if (kind == EVAL_STEM) return strip_run<T, GAP, EVAL_STEM, 0>(a, grid, lds, s);
+  if (kind == EVAL_DOWN) return a.C == 16 ? strip_run<T, GAP, EVAL_DOWN, 16>(a, grid, lds, s) : strip_run<T, GAP, EVAL_DOWN, 32>(a, grid, lds, s);
+  return a.C == 16 ? strip_run<T, GAP, EVAL_IDENTITY, 16>(a, grid, lds, s) : a.C == 32 ? strip_run<T, GAP, EVAL_IDENTITY, 32>(a, grid, lds, s)
+                                                                                       : strip_run<T, GAP, EVAL_IDENTITY, 64>(a, grid, lds, s);
+}
+}
+
+hipError_t eval_blocks_launch(const EvalTables& t, const EvalLaunch& l, const void* in, void* out, int N, int C, int dtype, hipStream_t s) {
+  if (!t.dev_blocks || !t.dev_convs || !t.blocks || !t.convs || l.nconv < 1 || N < 1 || l.count < 1 || l.lds > ev::LDS_MAX || (l.strips > 1 && l.count != 1))
+    return hipErrorInvalidValue;
+  if (l.strips > 1 || dtype == F32) {      // (fp32: always strips, if only one)
+    const EvalBlockDesc& b = t.blocks[l.first];
+    if (l.count != 1 || l.nconv > 3 || !eval_block_ok(b.kind, C)) return hipErrorInvalidValue;
+    if ((size_t)l.H * l.W * C * dtype_size(dtype) >= ((size_t)1 << 31)) return hipErrorInvalidValue;   // 32-bit byte offsets inside an image
+    ev::StripArgs a{};
+    for (int i = 0; i < l.nconv; ++i) a.conv[i] = t.convs[l.conv0 + i];
+    a.in = in; a.out = out; a.H = l.H; a.W = l.W; a.C = C; a.stride = b.stride; a.TH = l.TH; a.strips = l.strips;
+    a.off1 = l.off1; a.off2 = l.off2; a.red_off = l.red_off; a.tab_off = l.tab_off;
+    const unsigned grid = (unsigned)(N * l.strips);
+    return dtype == F32 ? ev::strip_launch<float, 16>(b.kind, a, grid, l.lds, s) : l.gap == 16 ? ev::strip_launch<bf16_t, 16>(b.kind, a, grid, l.lds, s)
+                                                                                               : ev::strip_launch<bf16_t, 32>(b.kind, a, grid, l.lds, s);
+  }
   ev::Args a{};
-  a.blocks = dev_blocks + l.first; a.nb = l.count; a.in = in; a.out = out; a.N = N; a.H = l.H; a.W = l.W; a.C = C;
-  a.TH = l.TH; a.strips = l.strips; a.off1 = l.off1; a.off2 = l.off2; a.red_off = l.red_off;
-  a.convs = dev_convs + l.conv0; a.nconv = l.nconv; a.tab_off = l.tab_off; a.dump_off = l.dump_off;
+  a.blocks = t.dev_blocks + l.first; a.nb = l.count; a.in = in; a.out = out; a.N = N; a.H = l.H; a.W = l.W; a.C = C;
+  a.off1 = l.off1; a.off2 = l.off2; a.red_off = l.red_off;
+  a.convs = t.dev_convs + l.conv0; a.nconv = l.nconv; a.tab_off = l.tab_off; a.dump_off = l.dump_off;
   typedef void (*Kernel)(ev::Args);
-  static const Kernel kernels[3] = {ev::eval_blocks_kernel<float, false, 16>, ev::eval_blocks_kernel<bf16_t, true, 16>, ev::eval_blocks_kernel<bf16_t, true, 32>};
-  const int which = dtype != BF16 ? 0 : l.gap == 16 ? 1 : 2;
-  static bool attr_set[3] = {false, false, false};
+  static const Kernel kernels[2] = {ev::eval_blocks_kernel<bf16_t, 16>, ev::eval_blocks_kernel<bf16_t, 32>};
+  const int which = l.gap == 16 ? 0 : 1;
+  static bool attr_set[2] = {false, false};
   if (!attr_set[which]) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernels[which]), hipFuncAttributeMaxDynamicSharedMemorySize, (int)ev::LDS_MAX);
     if (e != hipSuccess) return e;
     attr_set[which] = true;
   }
-  DDG_LAUNCH(kernels[which], dim3((unsigned)(N * l.strips)), dim3(ev::NT), l.lds, s, a);
+  DDG_LAUNCH(kernels[which], dim3((unsigned)N), dim3(ev::NT), l.lds, s, a);
   return hipGetLastError();
 }
 
