@@ -332,6 +332,12 @@ struct RunDesc {
 hipError_t forward_tail_launch(const void* src, void* dst, size_t bytes, const RunDesc* dev_descs, int n, int max_c, float rho, hipStream_t s);
 hipError_t eval_vectors_launch(const RunDesc* dev_descs, int n, int max_c, hipStream_t s);
 
+// First layer of a network (kernels_stem.hip); conv_launch and wgrad_launch use them where they can.
+bool stem_conv_ok(const ConvArgs& a);
+hipError_t stem_conv_launch(const ConvArgs& a, hipStream_t s);
+bool stem_wgrad_ok(const WgradArgs& a);
+hipError_t stem_wgrad_launch(const WgradArgs& a, hipStream_t s);
+
 // Evaluation forward of stem / basic blocks with 16, 32 or 64 channels, many layers per launch
 // (kernels_eval.hip). A module's convolutions lie in a device table in parameter order: the packed
 // forward operand and the batch norm whose running estimates the pass normalises with; toff: where

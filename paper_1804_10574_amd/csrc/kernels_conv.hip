@@ -481,6 +481,7 @@ hipError_t conv_launch(const ConvArgs& a, hipStream_t s, const ConvArgs* other) 
   }
   if (a.dtype == BF16 ? conv_dgrad_s2_launch<bf16_t>(a, s) : conv_dgrad_s2_launch<float>(a, s)) return hipGetLastError();
   if (a.proj_in) return hipErrorInvalidValue;   // (the caller asks conv_dgrad_s2_ok)
+  if (stem_conv_ok(a)) return stem_conv_launch(a, s);
   return a.dtype == BF16 ? conv_dispatch<bf16_t>(a, nullptr, s) : conv_dispatch<float>(a, nullptr, s);
 }
 

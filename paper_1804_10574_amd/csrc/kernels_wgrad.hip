@@ -434,6 +434,7 @@ hipError_t wgrad_launch(const WgradArgs& a, hipStream_t s) {
     else DDG_LAUNCH(wgrad_mfma_vec_kernel<float>, grid, block, WGV_LDS, s, a);
     return hipGetLastError();
   }
+  if (stem_wgrad_ok(a)) return stem_wgrad_launch(a, s);
   if (a.JB <= 3) {
     if (a.dtype == BF16) DDG_LAUNCH((wgrad_mfma_kernel<bf16_t, 3>), grid, block, 0, s, a);
     else DDG_LAUNCH((wgrad_mfma_kernel<float, 3>), grid, block, 0, s, a);
