@@ -66,9 +66,28 @@ struct OrderModel {
   }
 };
 
+// Which waits of a real run are implied by earlier ones. A wait for another stream's event costs the host 8-15 us (and the stream about
+// as much) whether or not there is anything left to wait for, and about half of those that a step asks for are: a stream that waited for an
+// event comes after all that the recording stream had done or waited for by then. Same vector clocks as in the model above, which sees every
+// wait that is asked for. ResNet-20, two modules, batch 37, 16 iterations: 4.40 -> 4.23 ms, ResNet-8, five modules, fp32: 5.83 -> 5.58, ResNet-56, three modules, batch 50: 6.80 -> 6.71.
+struct StreamClocks {
+  std::vector<std::vector<long>> clk;           // [stream][stream]
+  std::vector<std::vector<long>> ev;            // [event]: clock at its last record (empty: never recorded)
+  void init(int nstreams, int nevents) { clk.assign(nstreams, std::vector<long>(nstreams, 0)); ev.assign(nevents, {}); }
+  void ran(int s) { ++clk[s][s]; }              // something was enqueued
+  void record(int e, int s) { ev[e] = clk[s]; }
+  bool waits(int s, int e) {                    // must stream s wait for e? (it then has)
+    bool behind = false;
+    for (size_t i = 0; i < ev[e].size(); ++i) if (ev[e][i] > clk[s][i]) { clk[s][i] = ev[e][i]; behind = true; }
+    return behind;
+  }
+};
+
 struct ddg_pipeline {
   int K = 0;
   OrderModel order;
+  StreamClocks clocks;
+  bool whole_at[2] = {false, false};    // the last module's iteration of that parity was one graph: fwd_done stands for bwd_done too
   bool check_order = false;
   std::vector<int> sid_f, sid_b;        // logical stream numbers of module k's forward / backward stream
   bool stale = false;
@@ -172,6 +191,7 @@ ddg_status ddg_pipeline_create(const ddg_module_desc* descs, int K, void* const*
   p->sid_f.assign(K + 1, 0);
   p->sid_b.assign(K + 1, 0);
   p->order.init(2 * K + 1);
+  p->clocks.init(2 * K + 1, 4 * (K + 1));
   p->stale = descs[0].stale_jacobian != 0;
   {
     const char* env = getenv("DDG_CHECK_ORDER");
@@ -335,10 +355,11 @@ ddg_status ddg_pipeline_step(ddg_pipeline* p, const void* x, const int32_t* labe
   auto ev_b = [&](int sl, int k) { return 2 * (K + 1) + sl * (K + 1) + k; };
   auto wait_f = [&](int sid, hipStream_t s, int sl, int k) -> hipError_t {
     if (model) om.wait(sid, ev_f(sl, k));
-    return p->dry ? hipSuccess : hipStreamWaitEvent(s, p->fwd_done[sl][k], 0); };
+    return p->dry || !p->clocks.waits(sid, ev_f(sl, k)) ? hipSuccess : hipStreamWaitEvent(s, p->fwd_done[sl][k], 0); };
   auto wait_b = [&](int sid, hipStream_t s, int sl, int k) -> hipError_t {
     if (model) om.wait(sid, ev_b(sl, k));
-    return p->dry ? hipSuccess : hipStreamWaitEvent(s, p->bwd_done[sl][k], 0); };
+    const bool f = k == K && p->whole_at[sl];
+    return p->dry || !p->clocks.waits(sid, f ? ev_f(sl, k) : ev_b(sl, k)) ? hipSuccess : hipStreamWaitEvent(s, f ? p->fwd_done[sl][k] : p->bwd_done[sl][k], 0); };
   auto nm = [](const char* base, int a, long b = -1) {
     std::string r = std::string(base) + std::to_string(a);
     if (b >= 0) r += "/" + std::to_string(b);
@@ -347,6 +368,7 @@ ddg_status ddg_pipeline_step(ddg_pipeline* p, const void* x, const int32_t* labe
     // stage the caller's tensors at stable addresses; the step size lives in device memory
     DDG_P(ddg::copy_launch(x, p->xin, p->x_bytes, p->fstreams[1]));
     DDG_P(ddg::copy_launch(labels, p->labels_dev, p->batch * sizeof(int32_t), p->streams[K]));
+    p->clocks.ran(p->sid_f[1]); p->clocks.ran(p->sid_b[K]);
     if (lr != p->lr_host) {
       // every module's update of the previous iteration must have read the old value
       for (int k = 1; k <= K; ++k) DDG_P(hipStreamSynchronize(p->streams[k]));
@@ -424,8 +446,9 @@ ddg_status ddg_pipeline_step(ddg_pipeline* p, const void* x, const int32_t* labe
     // recorded after the update: module K-1's forward(t+2), which waits for it, comes after its own
     // update(t+1) and so after the backward pass of module K that wrote the mailbox during t.)
     const bool whole = steady && k == K && !split;
-    if (whole && k > 1 && t > 0) DDG_P(wait_b(sf, fs, prev, k - 1));
     if (k > 1) DDG_P(wait_f(sf, fs, cur, k - 1));
+    if (whole && k > 1 && t > 0) DDG_P(wait_b(sf, fs, prev, k - 1));
+    if (k == K) p->whole_at[cur] = whole && !p->dry;
     // this iteration's h[k] buffer was last read by module k+1's forward two iterations ago
     // (the event of this parity still carries that record: module k+1 re-records it later)
     if (k < K && t > 1) DDG_P(wait_f(sf, fs, cur, k + 1));
@@ -455,7 +478,10 @@ ddg_status ddg_pipeline_step(ddg_pipeline* p, const void* x, const int32_t* labe
       return r; });
     if (st != DDG_OK) return st;
     if (model) om.record(ev_f(cur, k), sf);
-    if (!p->dry) DDG_P(hipEventRecord(p->fwd_done[cur][k], fs));
+    if (!p->dry) {
+      p->clocks.ran(sf); p->clocks.record(ev_f(cur, k), sf);
+      DDG_P(hipEventRecord(p->fwd_done[cur][k], fs));
+    }
   }
   // backward + update: the K modules are independent within one iteration
   for (int k = 1; k <= K; ++k) {
@@ -490,7 +516,10 @@ ddg_status ddg_pipeline_step(ddg_pipeline* p, const void* x, const int32_t* labe
       if (k == K && loss_out && s >= 0) DDG_P(ddg::copy_launch(p->loss_dev, loss_out, sizeof(float), bs));
     }
     if (model) om.record(ev_b(cur, k), sb);
-    if (!p->dry) DDG_P(hipEventRecord(p->bwd_done[cur][k], bs));
+    if (!p->dry) {
+      p->clocks.ran(sb);
+      if (!whole) { p->clocks.record(ev_b(cur, k), sb); DDG_P(hipEventRecord(p->bwd_done[cur][k], bs)); }
+    }
   }
 #undef DDG_P
   p->t = t + 1;
