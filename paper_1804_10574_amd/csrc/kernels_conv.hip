@@ -33,8 +33,14 @@ __device__ __forceinline__ void keep_frag(float4& f) { asm volatile("" : "+v"(f.
 // whatever it does, and these are 5-7 us.
 struct ConvPair { ConvArgs c[2]; };
 
+// k-steps whose loads are requested together. The small tiles are those of launches with few waves (conv_plan): such a wave has its SIMD
+// nearly to itself and waited for every k-step's loads. 16 -> 16 channels, fp32, 2 x 256 pixels: 6.3 -> 4.3 us; ResNet-20 on 24x24 images, fp32, batch
+// 64, 16 iterations 10.9 -> 9.5 ms, on 28x28, bf16, batch 8 / 64 8.5 / 9.8 -> 7.1 / 8.6. Launches with other waves to run would lose their places.
+template <typename T, int MB, int NB, bool VEC>
+constexpr int conv_batch() { return !VEC ? 1 : Mma<T>::KV == 8 ? (MB * NB <= 2 ? 5 : 1) : (MB * NB == 1 ? 9 : 1); }
+
 // bx of gx, by: this workgroup's index among those that walk over the pixels, its group of channel blocks.
-template <typename T, int MB, int NB, bool DGRAD, bool VEC>
+template <typename T, int MB, int NB, bool DGRAD, bool VEC, int KB = conv_batch<T, MB, NB, VEC>()>
 __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, bool second, int bx, int by, int gx) {
   using M_ = Mma<T>;
   using S_ = Store<T>;
@@ -83,19 +89,17 @@ __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, bool second, i
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) acc[i][nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-    for (int ks = 0; ks < a.ksteps; ++ks) {
+    // what k-step ks multiplies; a padded or masked position reads the tensor's first elements instead (dropped below)
+    auto request = [&](int ks, typename M_::frag_t (&wf)[NB], typename M_::frag_t (&ld)[MB], bool (&okv)[MB]) __attribute__((always_inline)) {
       const int kidx = (ks * 4 + lg) * KV;
       const int tap = kidx >> a.log2cp;
       const int c0 = kidx & cpmask;
       const int r = (a.R == 3) ? tap / 3 : 0;
       const int s = (a.R == 3) ? tap - r * 3 : tap;
       const bool tap_ok = (tap < a.ntaps) && (c0 < a.IC);
-      typename M_::frag_t wf[NB];
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb)
         wf[nb] = M_::load(wp + ((size_t)(ks * OCB + cb0 + nb) * 64 + lane) * KV);
-      typename M_::frag_t ld[MB];
-      bool okv[MB];
 #pragma unroll
       for (int i = 0; i < MB; ++i) {
         int ih, iw;
@@ -111,7 +115,6 @@ __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, bool second, i
         }
         okv[i] = ok;
         if (VEC) {
-          // a padded or masked position reads the tensor's first elements instead (dropped below)
           const unsigned off = ok ? (unsigned)((pn[i] * a.IH + ih) * a.IW + iw) * (unsigned)a.IC + (unsigned)c0 : 0u;   // (32 bits: the host checks)
           ld[i] = M_::load(in + off);
         } else {
@@ -131,15 +134,26 @@ __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, bool second, i
           }
         }
       }
+    };
+    // KB k-steps are requested together (past the last one: that one again, not multiplied)
+    for (int k0 = 0; k0 < a.ksteps; k0 += KB) {
+      typename M_::frag_t wf[KB][NB], ld[KB][MB];
+      bool okv[KB][MB];
 #pragma unroll
-      for (int i = 0; i < MB; ++i) {
-        typename M_::frag_t af = ld[i];
-        if (VEC) {
-          keep_frag(af);
-          if (!okv[i]) af = M_::zero();
+      for (int k = 0; k < KB; ++k) request(KB == 1 || k0 + k < a.ksteps ? k0 + k : a.ksteps - 1, wf[k], ld[k], okv[k]);
+#pragma unroll
+      for (int k = 0; k < KB; ++k) {
+        if (KB > 1 && k0 + k >= a.ksteps) break;
+#pragma unroll
+        for (int i = 0; i < MB; ++i) {
+          typename M_::frag_t af = ld[k][i];
+          if (VEC) {
+            keep_frag(af);
+            if (!okv[k][i]) af = M_::zero();
+          }
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) acc[i][nb] = M_::mma(wf[k][nb], af, acc[i][nb]);
         }
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[i][nb] = M_::mma(wf[nb], af, acc[i][nb]);
       }
     }
 
@@ -196,10 +210,10 @@ __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, bool second, i
   }
 }
 
-template <typename T, int MB, int NB, bool DGRAD, bool VEC>
+template <typename T, int MB, int NB, bool DGRAD, bool VEC, int KB = conv_batch<T, MB, NB, VEC>()>
 __global__ __launch_bounds__(256) void conv_mfma_kernel(ConvPair ab, int sets) {
   const int conv = (int)blockIdx.z >= sets ? 1 : 0;
-  conv_mfma_body<T, MB, NB, DGRAD, VEC>(ab.c[conv], (int)blockIdx.z != conv * sets, blockIdx.x, blockIdx.y, gridDim.x);
+  conv_mfma_body<T, MB, NB, DGRAD, VEC, KB>(ab.c[conv], (int)blockIdx.z != conv * sets, blockIdx.x, blockIdx.y, gridDim.x);
 }
 
 // Weight gradient (vector gathers) and input gradient of a layer in one launch: both need its dz and nothing of each
@@ -426,11 +440,16 @@ void conv_plan(ConvArgs& a) {
   if (ocb % 4 == 0) { a.nb = 4; a.mb = 2; }
   else if (ocb % 2 == 0) { a.nb = 2; a.mb = 2; }
   else { a.nb = 1; a.mb = 4; }
-  if (a.dtype != BF16) {
+  auto waves = [&](int mb, int nb) { return (long)((a.M + 16 * mb - 1) / (16 * mb)) * (ocb / nb); };
+  if (a.dtype == BF16) {
+    // a launch of few waves is over when its longest one is: smaller tiles (32 -> 64 channels, 2368 pixels: 74 waves of 32 pixels x 64 channels
+    // and its projection took 9.0 us, 592 of 16 x 16 6.1)
+    if (waves(a.mb, a.nb) < 512) { a.nb = 1; a.mb = waves(2, 1) < 512 ? 1 : 2; }
+  } else {
     // fp32 matrix instructions are 16 times slower per flop than bf16 ones: a wave's tile is
     // what bounds the launch, so tiles shrink until there are about two per SIMD
     a.nb = 1; a.mb = 4;
-    while (a.mb > 1 && (long)((a.M + 16 * a.mb - 1) / (16 * a.mb)) * ocb < 2048) a.mb /= 2;
+    while (a.mb > 1 && waves(a.mb, 1) < 2048) a.mb /= 2;
   }
   const int gy = ocb / a.nb;
   const int tiles = (a.M + 16 * a.mb - 1) / (16 * a.mb);
@@ -447,6 +466,15 @@ static hipError_t conv_dispatch(const ConvArgs& a, const ConvArgs* other, hipStr
   dim3 grid(a.grid_x, (a.OC / 16) / a.nb, other ? 2 * sets : sets), block(256);
   const ConvPair ab{{a, other ? *other : a}};
   const bool vec = a.IC % Mma<T>::KV == 0;
+  if constexpr (Mma<T>::KV == 4) {
+    // a stage's first convolutions beside other modules: their waves hold four times the registers for what they gain (ResNet-20, two modules, batch 128:
+    // 4096 waves, 12.40 ms per 16 iterations instead of 12.31; ResNet-8, five modules, 8192, 5.63 instead of 5.56)
+    const long waves = (long)a.grid_x * 4 * grid.y * grid.z;
+    if (a.mb == 1 && vec && !a.dgrad && a.stride == 2 && waves > 2048) {
+      DDG_LAUNCH((conv_mfma_kernel<T, 1, 1, false, true, 1>), grid, block, 0, s, ab, sets);
+      return hipGetLastError();
+    }
+  }
 #define DDG_CONV_CASE(MB_, NB_)                                                                   \
   if (a.mb == MB_ && a.nb == NB_) {                                                               \
     if (vec) {                                                                                    \
@@ -504,9 +532,8 @@ static hipError_t bwd_generic_dispatch(const WgradArgs& w, const ConvArgs& a, hi
     DDG_LAUNCH((bwd_generic_kernel<T, MB_, NB_>), grid, dim3(256), WGV_LDS, s, w, a);             \
     return hipGetLastError();                                                                     \
   }
-  DDG_BWD_CASE(4, 1)
-  if constexpr (Mma<T>::KV == 4) { DDG_BWD_CASE(2, 1) DDG_BWD_CASE(1, 1) }
-  else { DDG_BWD_CASE(2, 2) DDG_BWD_CASE(2, 4) }
+  DDG_BWD_CASE(4, 1) DDG_BWD_CASE(2, 1) DDG_BWD_CASE(1, 1)
+  if constexpr (Mma<T>::KV == 8) { DDG_BWD_CASE(2, 2) DDG_BWD_CASE(2, 4) }
 #undef DDG_BWD_CASE
   return hipErrorInvalidValue;
 }

@@ -167,7 +167,7 @@ hipError_t stem_conv_launch(const ConvArgs& a, hipStream_t s) {
     return hipGetLastError();                                                     \
   }
   if (a.dtype == BF16) {
-    DDG_STEM_CASE(bf16_t, 4, 1) DDG_STEM_CASE(bf16_t, 2, 2) DDG_STEM_CASE(bf16_t, 2, 4)
+    DDG_STEM_CASE(bf16_t, 4, 1) DDG_STEM_CASE(bf16_t, 2, 1) DDG_STEM_CASE(bf16_t, 1, 1) DDG_STEM_CASE(bf16_t, 2, 2) DDG_STEM_CASE(bf16_t, 2, 4)
   } else {
     DDG_STEM_CASE(float, 4, 1) DDG_STEM_CASE(float, 2, 1) DDG_STEM_CASE(float, 1, 1)
   }

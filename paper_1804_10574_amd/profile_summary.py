@@ -78,7 +78,7 @@ def kind_of(kernel_name: str) -> str:
     m = re.match(r"(?:update_pack|update_tiles|reduce_update)_kernel<[\w:]+, (true|false)>", n)
     if m:   # <T, ADAM>: the optimizer step and the repacking (and the sums of the weight gradients)
         return "adam" if m.group(1) == "true" else "sgd"
-    table = [("conv_dgrad_s2_kernel", "conv_dgrad.generic"), ("bwd_generic_kernel", "conv_dgrad.generic"), ("bn_apply_wide_kernel", "bn_apply"),
+    table = [("stem_conv_kernel", "conv_fprop.generic"), ("stem_wgrad_kernel", "conv_wgrad.generic"), ("conv_dgrad_s2_kernel", "conv_dgrad.generic"), ("bwd_generic_kernel", "conv_dgrad.generic"), ("bn_apply_wide_kernel", "bn_apply"),
              ("bn_bwd_apply_wide_kernel", "bn_bwd_apply"), ("wgrad_mfma_kernel", "conv_wgrad.generic"), ("wgrad_mfma_vec_kernel", "conv_wgrad.generic"), ("wgrad_reduce", "wgrad_reduce"),
              ("bn_bwd_apply_kernel", "bn_bwd_apply"), ("bn_bwd_apply_chunk_kernel", "bn_bwd_apply"), ("bn_bwd_reduce_kernel", "bn_bwd_reduce"),
              ("bn_bwd_finalize", "bn_bwd_finalize"), ("bn_apply_kernel", "bn_apply"),
