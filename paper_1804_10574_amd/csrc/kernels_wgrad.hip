@@ -11,6 +11,7 @@
 #include "ddg_wgrad_vec.h"
 #include "ddg_update.h"
 #include <cstdlib>
+#include <type_traits>
 
 namespace ddg {
 
@@ -345,18 +346,25 @@ __global__ __launch_bounds__(256) void reduce_update_kernel(const WredDesc* __re
   const int cl = tid & 63, rc = tid >> 6;
   const int col = blockIdx.x * 64 + cl;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (col < total4) {
+  // rows of a class, 8 or 16 in flight: with 128 rows two trips instead of four (ResNet-20, fp32, batch 128, 16 iterations 12.24 -> 12.14 ms); with 37
+  // rows the longer trip is 1 % of ResNet-20 at batch 37 slower than two short ones
+  auto add = [&](auto in_flight) __attribute__((always_inline)) {
+    constexpr int U = decltype(in_flight)::value;
     const float4* __restrict__ p = reinterpret_cast<const float4*>(d.partial) + col;
-    for (int r0 = rc; r0 < d.rows; r0 += 32) {
-      float4 v[8];
+    for (int r0 = rc; r0 < d.rows; r0 += 4 * U) {
+      float4 v[U];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
+      for (int q = 0; q < U; ++q) {
         const int r = r0 + 4 * q;
         v[q] = r < d.rows ? p[(size_t)r * total4] : make_float4(0.f, 0.f, 0.f, 0.f);
       }
 #pragma unroll
-      for (int q = 0; q < 8; ++q) { s.x += v[q].x; s.y += v[q].y; s.z += v[q].z; s.w += v[q].w; }
+      for (int q = 0; q < U; ++q) { s.x += v[q].x; s.y += v[q].y; s.z += v[q].z; s.w += v[q].w; }
     }
+  };
+  if (col < total4) {
+    if (d.rows > 64) add(std::integral_constant<int, 16>{});
+    else add(std::integral_constant<int, 8>{});
   }
   red[rc * 64 + cl] = s;
   __syncthreads();
