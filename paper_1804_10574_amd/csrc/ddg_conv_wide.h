@@ -25,8 +25,61 @@ struct ConvWideArgs {
   const bf16_t* bz; const float* bmean; const float* binvstd;
   // optional second minibatch (blockIdx.z = 1; forward only): same weights, its own tensors
   const bf16_t* in_b; bf16_t* out_b; float* stat_partial_b; const float* scale_b; const float* shift_b;
+  // optional, in place of scale and shift (halo and point kernels): the statistics rows they derive from, of either minibatch
+  BnRows rows, rows_b;
   int M, H, W, HW, IC, OC, R;
 };
+
+// Scale and shift of C input channels from the producer's statistics rows, by a workgroup of NT threads, into LDS (tab: C scales, then C shifts):
+// a launch of its own for it is 4.5 us of latency in the chain between two convolutions. Every workgroup adds the same rows in the same
+// order (fp64), one of each minibatch stores the vectors. A thread owns one 16-byte column group and every S-th row, U of them in flight.
+template <int NT> struct WideRows {
+  static constexpr int U = 14;
+  float4 v[U];
+  wide_rsrc_t res;
+  unsigned at, step;
+  __device__ __forceinline__ void request(const BnRows& r, int C) {
+    const int cols4 = C >> 1;
+    res = wide_rsrc(r.partial, (size_t)r.rows * C * 8);     // (rows past the last: zeros)
+    at = threadIdx.x * 16; step = NT / cols4 * cols4 * 16;
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = __builtin_bit_cast(float4, wide_load(res, at, u * step));
+  }
+  // part: NT * 32 bytes of LDS. Ends with a barrier.
+  __device__ __forceinline__ void finish(const BnRows& r, int C, float* tab, double* part, bool write) {
+    const int cols4 = C >> 1, S = NT / cols4, tid = threadIdx.x;
+    double t[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int left = r.rows - S * U;; left -= S * U) {
+      at += U * step;
+      if (left > 0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          t[0] += (double)v[u].x; t[1] += (double)v[u].y; t[2] += (double)v[u].z; t[3] += (double)v[u].w;
+          v[u] = __builtin_bit_cast(float4, wide_load(res, at, u * step));
+        }
+      } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u) { t[0] += (double)v[u].x; t[1] += (double)v[u].y; t[2] += (double)v[u].z; t[3] += (double)v[u].w; }
+        break;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) part[tid * 4 + j] = t[j];
+    __syncthreads();
+    for (int c = tid; c < C; c += NT) {
+      double t1 = 0.0, t2 = 0.0;
+      for (int q = 0; q < S; ++q) { t1 += part[q * 2 * C + c]; t2 += part[q * 2 * C + C + c]; }
+      const double mu = t1 * r.inv_count;
+      double var = t2 * r.inv_count - mu * mu;
+      if (var < 0.0) var = 0.0;
+      const float is = (float)rsqrt(var + (double)r.eps), sc = r.gamma[c] * is, sh = r.beta[c] - (float)mu * sc;
+      tab[c] = sc; tab[C + c] = sh;
+      if (write) { r.mean[c] = (float)mu; r.invstd[c] = is; r.scale[c] = sc; r.shift[c] = sh; }
+    }
+    __syncthreads();
+  }
+};
+constexpr int WIDE_ROWS_CMAX = 512;
 
 // relu(v*sc + sh) of eight bf16 values, rounded back to bf16
 __device__ __forceinline__ uint4 wide_act(uint4 v, const float* sc, const float* sh) {

@@ -247,6 +247,11 @@ hipError_t conv_wide_launch(const void* in, const void* wpack, void* out, float*
                             const void* add_mask, int N, int H, int W, int IC, int OC, int R, hipStream_t s,
                             const float* scale = nullptr, const float* shift = nullptr,
                             const ConvWideSecond* second = nullptr, const ConvStat* below = nullptr);
+// A forward launch that derives the on-load batch norm's scale and shift from the producer's statistics rows (of one or two
+// minibatches, `second` given) and stores the vectors they describe.
+hipError_t conv_wide_rows_launch(const void* in, const void* wpack, void* out, float* stat_partial, int N, int H, int W, int IC, int OC,
+                                 int R, hipStream_t s, const BnRows* rows, const ConvWideSecond* second = nullptr);
+bool conv_wide_takes_rows(int IC, int W, int R, int rows);   // may it?
 
 // A 1x1 layer (IC a multiple of 256, OC = 128 or 256) whose input is y = relu(bn(z) + res): formed from z's statistics
 // rows (of as many sums as conv_form_ok allows) and stored to y. f1, out_b, stat_partial_b (optional): the second minibatch. Statistics rows: conv_wide_rows_max().

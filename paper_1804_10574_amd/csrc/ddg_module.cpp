@@ -88,6 +88,7 @@ struct Unit {  // convolution + batch normalisation
   size_t wide_dz = 0;                    // its dz lies there in the module's wide_dz buffer until the launch that reads it
   bool wide_launch = false;              // that launch is due once this layer has joined
   bool small_c() const { return cout == 16 || cout == 32 || cout == 64; }
+  bool fin_in_conv = false;    // more channels, few rows: the convolution that applies the batch norm while loading finalises the statistics
   bool fin_in_apply = false;   // more channels, few rows: the normalise-add-ReLU kernel finalises the statistics
   int tiled_instance() const { return cin == 16 ? 1 : cin == 32 ? 2 : 3; }   // offset of a tiled kernel's profile kind
   size_t out_elems() const { return (size_t)N * P * Q * cout; }
@@ -474,6 +475,7 @@ ddg_status build_plan(ddg_module* m) {
       const bool on_load = cons.tiled_grid > 0 || (cons.wide_f && cons.wide_splits > 0 && !b.u[ui].small_c());
       if (!on_load) DDG_OKAY(dev_alloc(m, &a, m->groups * b.u[ui].out_elems() * m->esz));
       b.act.push_back(a);
+      b.u[ui].fin_in_conv = !a && cons.wide_f && !b.u[ui].small_c() && conv_wide_takes_rows(cons.cin, cons.W, cons.R, b.u[ui].fcap);
     }
     // units whose batch norm an elementwise kernel applies: the block's last, its projection, and those
     // with a materialised activation; the two that meet in one kernel go the same way
@@ -688,7 +690,7 @@ ConvArgs forward_args(ddg_module* m, Unit& u, const void* in, int g) {
 // The launch that finalises the statistics of a unit none of whose consumers does (evaluation normalises with the
 // running estimates).
 ddg_status finalize_forward(ddg_module* m, Unit& u, int g) {
-  if (u.small_c() || u.fin_in_apply || m->eval_mode) return DDG_OK;
+  if (u.small_c() || u.fin_in_apply || u.fin_in_conv || m->eval_mode) return DDG_OK;
   const int vo = g * u.vec_stride();
   Launch L(m, PK_BN_FINALIZE);
   DDG_TRY(bn_finalize_launch(u.fstat + (size_t)g * u.fcap * 2 * u.cout, u.frows, u.cout, m->theta + u.og, m->theta + u.ob,
@@ -699,7 +701,7 @@ ddg_status finalize_forward(ddg_module* m, Unit& u, int g) {
 
 // The same for both groups of a paired forward pass.
 ddg_status finalize_forward_two(ddg_module* m, Unit& u) {
-  if (u.small_c() || u.fin_in_apply) return DDG_OK;
+  if (u.small_c() || u.fin_in_apply || u.fin_in_conv) return DDG_OK;
   Launch L(m, PK_BN_FINALIZE);
   DDG_TRY(bn_finalize_launch(u.fstat, u.frows, u.cout, m->theta + u.og, m->theta + u.ob,
                              (float)((size_t)u.N * u.P * u.Q), m->d.bn_eps, u.mean, u.invstd, u.scale, u.shift, m->stream,
@@ -741,11 +743,17 @@ ddg_status unit_forward(ddg_module* m, Unit& u, const void* in, Unit* src, const
     if (src && !u.wide_f) return fail(DDG_ERR_STATE, "internal: generic conv needs a materialised input");
     if (u.wide_f) {
       u.frows = conv_wide_rows(u.N * u.P * u.Q, u.W, u.cin, u.cout, u.R, 1);
-      const int svo = src ? g * src->vec_stride() : 0;   // (a wide producer's vectors are final: it ran its finalise launch)
+      // (a wide producer's vectors are final, it ran its finalise launch, or derive from its rows here)
+      const int svo = src ? g * src->vec_stride() : 0;
+      const bool from_rows = src && src->fin_in_conv && !m->eval_mode;
+      const BnRows ir = from_rows ? fwd_rows(m, *src, g) : BnRows{};
       Launch L(m, PK_CONV_FPROP_WIDE, (u.in_elems() + u.out_elems()) * (double)m->esz + wbytes(m, u), conv_flops(u));
-      DDG_TRY(conv_wide_launch(in, u.wpack_f, z, fstat, nullptr, nullptr, u.N, u.H, u.W, u.cin, u.cout, u.R, m->stream,
-                               !src ? nullptr : (m->eval_mode ? src->escale : src->scale + svo),
-                               !src ? nullptr : (m->eval_mode ? src->eshift : src->shift + svo)));
+      if (from_rows)
+        DDG_TRY(conv_wide_rows_launch(in, u.wpack_f, z, fstat, u.N, u.H, u.W, u.cin, u.cout, u.R, m->stream, &ir));
+      else
+        DDG_TRY(conv_wide_launch(in, u.wpack_f, z, fstat, nullptr, nullptr, u.N, u.H, u.W, u.cin, u.cout, u.R, m->stream,
+                                 !src ? nullptr : (m->eval_mode ? src->escale : src->scale + svo),
+                                 !src ? nullptr : (m->eval_mode ? src->eshift : src->shift + svo)));
     } else {
       const ConvArgs a = forward_args(m, u, in, g);
       ConvArgs q{};
@@ -839,10 +847,18 @@ ddg_status unit_forward_two(ddg_module* m, Unit& u, const void* in0, const void*
   if (u.wide_f) {
     u.frows = conv_wide_rows(u.N * u.P * u.Q, u.W, u.cin, u.cout, u.R, 2);
     const int sv = src ? src->vec_stride() : 0;
-    ConvWideSecond sec{in1, z1, fstat1, src ? src->scale + sv : nullptr, src ? src->shift + sv : nullptr};
+    const bool from_rows = src && src->fin_in_conv;
+    const float* sc = src && !from_rows ? src->scale : nullptr;
+    const float* sh = src && !from_rows ? src->shift : nullptr;
+    const ConvWideSecond sec{in1, z1, fstat1, sc ? sc + sv : nullptr, sh ? sh + sv : nullptr};
     Launch L(m, PK_CONV_FPROP_WIDE, bytes, 2.0 * conv_flops(u));
-    DDG_TRY(conv_wide_launch(in0, u.wpack_f, u.z, u.fstat, nullptr, nullptr, u.N, u.H, u.W, u.cin, u.cout, u.R, m->stream,
-                             src ? src->scale : nullptr, src ? src->shift : nullptr, &sec));
+    if (from_rows) {
+      const BnRows ir[2] = {fwd_rows(m, *src, 0), fwd_rows(m, *src, 1)};
+      DDG_TRY(conv_wide_rows_launch(in0, u.wpack_f, u.z, u.fstat, u.N, u.H, u.W, u.cin, u.cout, u.R, m->stream, ir, &sec));
+    } else {
+      DDG_TRY(conv_wide_launch(in0, u.wpack_f, u.z, u.fstat, nullptr, nullptr, u.N, u.H, u.W, u.cin, u.cout, u.R, m->stream,
+                               sc, sh, &sec));
+    }
   } else {
     auto two = [&](Unit& q) {
       ConvArgs a = forward_args(m, q, in0, 0);

@@ -92,11 +92,15 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
   // everything slice 0 needs is requested at once (its scale and shift directly, the table in LDS serves the
   // later slices); index arithmetic while that is in flight
+  const bool from_rows = XFORM && a.rows.partial != nullptr;
+  const BnRows rows = second ? a.rows_b : a.rows;
+  WideRows<512> sums;
+  if (XFORM && from_rows) sums.request(rows, a.IC);
   uint4 first[NU];
 #pragma unroll
   for (int q = 0; q < NU; ++q) first[q] = wide_load(rin, row_off(q), 0);
   float sc0[8], sh0[8];
-  if (XFORM) {
+  if (XFORM && !from_rows) {
 #pragma unroll
     for (int e = 0; e < 8; e += 4) {
       *reinterpret_cast<float4*>(&sc0[e]) = *reinterpret_cast<const float4*>(g_scale + pc * 8 + e);
@@ -125,6 +129,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
   const int kofs = kg * KPW * 32 + half * 16;      // byte offset of the wave's first k-step in a row
 
+  if (XFORM && from_rows) {
+    sums.finish(rows, a.IC, tab, reinterpret_cast<double*>(smem + PITCH + BUF), blockIdx.x == 0 && blockIdx.y == 0);   // (the other buffer is free)
+#pragma unroll
+    for (int e = 0; e < 8; e += 4) {
+      *reinterpret_cast<float4*>(&sc0[e]) = *reinterpret_cast<const float4*>(&tab[pc * 8 + e]);
+      *reinterpret_cast<float4*>(&sh0[e]) = *reinterpret_cast<const float4*>(&tab[a.IC + pc * 8 + e]);
+    }
+  }
 #pragma unroll
   for (int q = 0; q < NU; ++q)
     *reinterpret_cast<uint4*>(smem + sdst + q * 32 * PITCH) = XFORM ? wide_act(first[q], sc0, sh0) : first[q];

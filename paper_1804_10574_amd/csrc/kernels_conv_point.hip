@@ -31,7 +31,8 @@
 // staging 0.5: the parts add, two waves a SIMD hide little of each other. The input gradient waits for the three
 // tensors of its epilogue (8 us without them). Tried: two tiles in flight (the same), one wave of each SIMD finishing
 // before it multiplies (18.1), matrix and vector instructions interleaved by hand (17.8), the activation
-// stored by a launch of its own (15.9 and a 6.6 us launch instead of the 4.7 us finalise).
+// stored by a launch of its own (15.9 and a 6.6 us launch). Since then the forward launch also adds the statistics rows of its
+// input (WideRows): 1.6 us more, for a finalise launch of 4.5 before it.
 #include "ddg_conv_wide.h"
 
 namespace ddg {
@@ -42,6 +43,7 @@ constexpr int pitch(int K) { return K * 2 + 16; }              // bytes per stag
 constexpr int opitch(int stats) { return stats == 1 ? 128 * 2 + 16 : 128 * 4 + 16; }   // bytes per pixel of a finished tile: as stored, or fp32 where something is added to it
 constexpr int RED = 32 * 128 * 4;                              // where sums of the 32 pixel classes meet
 constexpr int lds_bytes(int K, int stats) { return 2 * BM * (pitch(K) + opitch(stats)) + (stats ? RED : 0); }
+static_assert(512 * 32 + 2 * 256 * 4 <= 2 * BM * opitch(1), "sums and table of the on-load batch norm");
 constexpr int CHAIN = 8;                                       // tiles whose values a thread adds in fp32 (a power of two)
 }
 
@@ -82,10 +84,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int q = 0; q < NU; ++q) st.u[q] = wide_load(rin, left > 0 && mrow + q * RPP < a.M ? src + q * RPP * (K * 2) : NOWHERE, 0);
     src += BM * K * 2; mrow += BM; --left;
   };
+  const bool from_rows = XFORM && a.rows.partial != nullptr;
+  const BnRows rows = second ? a.rows_b : a.rows;
+  WideRows<512> sums;
+  if (XFORM && from_rows) sums.request(rows, K);
   Tile sa;
   issue(sa);
   float sc[8], sh[8];
-  if (XFORM) {
+  if (XFORM && !from_rows) {
 #pragma unroll
     for (int e = 0; e < 8; e += 4) {
       *reinterpret_cast<float4*>(&sc[e]) = *reinterpret_cast<const float4*>(g_scale + pc * 8 + e);
@@ -99,6 +105,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const unsigned kstep = (a.OC >> 4) * 1024;
 #pragma unroll
     for (int s = 0; s < KS; ++s) w[s] = __builtin_bit_cast(bf16x8_t, wide_load(rw, wl, (s >> 1) * kstep + (s & 1) * 512));
+  }
+  if (XFORM && from_rows) {          // (where the finished tiles go later)
+    unsigned char* lds = smem + 2 * BUF;
+    float* tab = reinterpret_cast<float*>(lds + 512 * 32);
+    sums.finish(rows, K, tab, reinterpret_cast<double*>(lds), grp == 0 && c0 == 0);
+#pragma unroll
+    for (int e = 0; e < 8; e += 4) {
+      *reinterpret_cast<float4*>(&sc[e]) = *reinterpret_cast<const float4*>(&tab[pc * 8 + e]);
+      *reinterpret_cast<float4*>(&sh[e]) = *reinterpret_cast<const float4*>(&tab[K + pc * 8 + e]);
+    }
   }
   auto stash = [&](const Tile& st, int buf) __attribute__((always_inline)) {
     unsigned char* P = smem + buf * BUF + prow * PITCH + pc * 16;

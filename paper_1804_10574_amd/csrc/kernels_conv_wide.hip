@@ -376,9 +376,16 @@ int conv_wide_sums(int M, int W, int IC, int OC, int R, int sets) {
   return conv_point_ok(IC, R) ? conv_point_groups(M, OC, sets) : conv_wide_rows(M, W, IC, OC, R, sets);
 }
 
-hipError_t conv_wide_launch(const void* in, const void* wpack, void* out, float* stat_partial, const void* add_g,
+// The halo and point kernels add up to so many rows themselves. A launch for it takes 4.5 us and a place in the chain; in a workgroup
+// 98 rows of 256 channels (200 KB that all workgroups read, at what an XCD's L2 gives) take 2.6 us and 49 rows 1.6. 23 bottleneck blocks, batch 32,
+// 12 steps: 51.74 -> 51.29 ms; 6 blocks, batch 13: 10.18 -> 10.01. The line is where the launch, whose 32 workgroups share the rows, would be as fast.
+bool conv_wide_takes_rows(int IC, int W, int R, int rows) {
+  return (conv_point_ok(IC, R) || (conv_halo_ok(IC, W, R) && (IC & (IC - 1)) == 0 && IC <= WIDE_ROWS_CMAX)) && rows * IC <= 32768;
+}
+
+static hipError_t conv_wide_any(const void* in, const void* wpack, void* out, float* stat_partial, const void* add_g,
                             const void* add_mask, int N, int H, int W, int IC, int OC, int R, hipStream_t s,
-                            const float* scale, const float* shift, const ConvWideSecond* second, const ConvStat* below) {
+                            const float* scale, const float* shift, const ConvWideSecond* second, const ConvStat* below, const BnRows* rows) {
   if (!conv_wide_ok(IC, OC, R, 1, BF16)) return hipErrorInvalidValue;
   const size_t M = (size_t)N * H * W;
   if (M * (size_t)(IC > OC ? IC : OC) >= ((size_t)1 << 31)) return hipErrorInvalidValue;   // 32-bit element offsets inside
@@ -391,16 +398,21 @@ hipError_t conv_wide_launch(const void* in, const void* wpack, void* out, float*
     a.in_b = (const bf16_t*)second->in; a.out_b = (bf16_t*)second->out; a.stat_partial_b = second->stat_partial;
     a.scale_b = second->scale; a.shift_b = second->shift;
   }
+  if (rows) {
+    if (scale || !conv_wide_takes_rows(IC, W, R, rows[0].rows) || !rows[0].partial || (second && (!rows[1].partial || rows[1].rows != rows[0].rows))) return hipErrorInvalidValue;
+    a.rows = rows[0];
+    if (second) a.rows_b = rows[1];
+  }
   int stats = stat_partial ? 1 : 0;
   if (below) {   // the BN-backward sums of the layer below, from the gradient this launch produces
-    if (below->mode != 2 || stat_partial || second || scale || !below->partial || !below->z || !below->zmean || !below->zinvstd)
+    if (below->mode != 2 || stat_partial || second || scale || rows || !below->partial || !below->z || !below->zmean || !below->zinvstd)
       return hipErrorInvalidValue;
     a.stat_partial = below->partial; a.bmask = (const bf16_t*)below->mask; a.bmscale = below->mscale; a.bmshift = below->mshift;
     a.bz = (const bf16_t*)below->z; a.bmean = below->zmean; a.binvstd = below->zinvstd;
     stats = 2;
   }
   a.M = (int)M; a.H = H; a.W = W; a.HW = H * W; a.IC = IC; a.OC = OC; a.R = R;
-  const bool xf = scale != nullptr;
+  const bool xf = scale != nullptr || rows;
   if (xf && (add_g || IC > 2048)) return hipErrorInvalidValue;   // forward only; the table lives in LDS
   if (conv_halo_ok(IC, W, R)) return conv_halo_launch(a, second ? 2 : 1, stats, xf, s);
   if (conv_point_ok(IC, R)) return conv_point_launch(a, second ? 2 : 1, stats, xf, s);
@@ -410,6 +422,18 @@ hipError_t conv_wide_launch(const void* in, const void* wpack, void* out, float*
   if (R == 3)
     return long_chunk ? conv_wide_dispatch<128, 3>(a, grid, stats, xf, IC, s) : conv_wide_dispatch<64, 3>(a, grid, stats, xf, IC, s);
   return long_chunk ? conv_wide_dispatch<128, 1>(a, grid, stats, xf, IC, s) : conv_wide_dispatch<64, 1>(a, grid, stats, xf, IC, s);
+}
+
+hipError_t conv_wide_launch(const void* in, const void* wpack, void* out, float* stat_partial, const void* add_g,
+                            const void* add_mask, int N, int H, int W, int IC, int OC, int R, hipStream_t s,
+                            const float* scale, const float* shift, const ConvWideSecond* second, const ConvStat* below) {
+  return conv_wide_any(in, wpack, out, stat_partial, add_g, add_mask, N, H, W, IC, OC, R, s, scale, shift, second, below, nullptr);
+}
+
+hipError_t conv_wide_rows_launch(const void* in, const void* wpack, void* out, float* stat_partial, int N, int H, int W, int IC, int OC,
+                                 int R, hipStream_t s, const BnRows* rows, const ConvWideSecond* second) {
+  if (!rows) return hipErrorInvalidValue;
+  return conv_wide_any(in, wpack, out, stat_partial, nullptr, nullptr, N, H, W, IC, OC, R, s, nullptr, nullptr, second, nullptr, rows);
 }
 
 }  // namespace ddg
