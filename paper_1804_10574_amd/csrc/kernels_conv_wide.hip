@@ -378,7 +378,8 @@ int conv_wide_sums(int M, int W, int IC, int OC, int R, int sets) {
 
 // The halo and point kernels add up to so many rows themselves. A launch for it takes 4.5 us and a place in the chain; in a workgroup
 // 98 rows of 256 channels (200 KB that all workgroups read, at what an XCD's L2 gives) take 2.6 us and 49 rows 1.6. 23 bottleneck blocks, batch 32,
-// 12 steps: 51.74 -> 51.29 ms; 6 blocks, batch 13: 10.18 -> 10.01. The line is where the launch, whose 32 workgroups share the rows, would be as fast.
+// 12 steps: 51.74 -> 51.29 ms; 6 blocks, batch 13: 10.18 -> 10.01, batch 25
+// (77 rows) 12.73 -> 12.61, batch 41 (126 rows, just inside the line) 16.67 -> 16.68: there the launch, whose 32 workgroups share the rows, is as fast.
 bool conv_wide_takes_rows(int IC, int W, int R, int rows) {
   return (conv_point_ok(IC, R) || (conv_halo_ok(IC, W, R) && (IC & (IC - 1)) == 0 && IC <= WIDE_ROWS_CMAX)) && rows * IC <= 32768;
 }

@@ -8,7 +8,7 @@
 // LDS time in bf16, against 10-13 us for the per-layer launch of a whole minibatch of 256 and 6-7
 // us for the smallest one (the launch, its weights and its halo loads are then all there is).
 // Measured, whole call: ResNet-110, batch 256, bf16 1394 -> 214 us (1.4-1.7 us per layer); the 32-channel group of
-// ResNet-56, batch 100, bf16 134 -> 29 us; ResNet-20, one image, fp32 227 -> 116 us.
+// ResNet-56, batch 100, bf16 134 -> 29 us; ResNet-20, one image, fp32 227 -> 103 us.
 //
 // Two ways of cutting the work, chosen by eval_plan() below:
 //   whole images: all blocks of a module in one launch, one image per workgroup (bf16);
