@@ -327,6 +327,29 @@ def test_events_order_every_tensor_the_streams_share(K, mode):
     p.close()
 
 
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("mode", ["streams", "forward_streams", "stale_jacobian"])
+@pytest.mark.parametrize("toggle", [0, 5])
+def test_waits_that_are_left_out_order_nothing(K, mode, toggle):
+    """A wait that earlier ones imply is not issued. The model, shown only those that are issued, finds no hazard, also where
+    graphs (the last module's whole iteration in one) come and go; and fewer are issued than asked for."""
+    lib = _order_hooks()
+    lib.ddg_internal_pipeline_model_issued.restype = None
+    lib.ddg_internal_pipeline_model_issued.argtypes = [__import__("ctypes").c_void_p]
+    fake, waits = 4096, {}
+    for issued in (False, True):
+        p = _dry_pipeline(K, mode == "forward_streams", stale=(mode == "stale_jacobian"))
+        if issued:
+            lib.ddg_internal_pipeline_model_issued(p._h)
+        for t in range(6 * K + 12):
+            if toggle and t % toggle == 0:
+                p.set_graphs(t // toggle % 2 == 0)
+            p.step(fake, fake, 0.01)
+        waits[issued] = lib.ddg_internal_pipeline_waits(p._h)
+        p.close()
+    assert waits[True] < waits[False] or K == 1
+
+
 @pytest.mark.parametrize("own_forward_streams", [False, True])
 def test_a_missing_wait_is_found(own_forward_streams):
     """Leaving out any single wait of a K = 3 schedule, in the model only: the model must report
