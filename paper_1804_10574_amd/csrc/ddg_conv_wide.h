@@ -79,7 +79,7 @@ template <int NT> struct WideRows {
     __syncthreads();
   }
 };
-constexpr int WIDE_ROWS_CMAX = 512;
+constexpr int WIDE_ROWS_CMAX = 256;
 
 // relu(v*sc + sh) of eight bf16 values, rounded back to bf16
 __device__ __forceinline__ uint4 wide_act(uint4 v, const float* sc, const float* sh) {

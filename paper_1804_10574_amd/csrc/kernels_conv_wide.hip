@@ -380,6 +380,8 @@ int conv_wide_sums(int M, int W, int IC, int OC, int R, int sets) {
 // 98 rows of 256 channels (200 KB that all workgroups read, at what an XCD's L2 gives) take 2.6 us and 49 rows 1.6. 23 bottleneck blocks, batch 32,
 // 12 steps: 51.74 -> 51.29 ms; 6 blocks, batch 13: 10.18 -> 10.01, batch 25
 // (77 rows) 12.73 -> 12.61, batch 41 (126 rows, just inside the line) 16.67 -> 16.68: there the launch, whose 32 workgroups share the rows, is as fast.
+// 128 channels at 28x28, batch 4 / 9 / 20 (245 rows): 6.86 -> 6.75, 8.75 -> 8.62, 12.37 -> 12.27. 512 channels at 7x7 keep the launch: no faster
+// without (batch 20 / 64: 16.16 -> 16.23, 24.5 -> 24.6), twice as many workgroups reading rows twice as long.
 bool conv_wide_takes_rows(int IC, int W, int R, int rows) {
   return (conv_point_ok(IC, R) || (conv_halo_ok(IC, W, R) && (IC & (IC - 1)) == 0 && IC <= WIDE_ROWS_CMAX)) && rows * IC <= 32768;
 }

@@ -18,7 +18,7 @@ class Rows(C.Structure):       # BnRows
 
 # 512 threads share rows of K channels: 1024/K rows at a time, 14 times
 @pytest.mark.parametrize("K,R,rows", [(128, 1, 1), (128, 1, 112), (128, 1, 113), (128, 1, 256), (256, 1, 3), (256, 1, 56), (256, 1, 57), (256, 1, 128),
-                                      (128, 3, 5), (256, 3, 55), (256, 3, 98), (512, 3, 28), (512, 3, 29), (512, 3, 64)])
+                                      (128, 3, 5), (256, 3, 55), (256, 3, 98), (256, 3, 128), (128, 3, 256)])
 @pytest.mark.parametrize("sets", [1, 2])
 def test_from_rows(K, R, rows, sets):
     import torch
@@ -30,6 +30,7 @@ def test_from_rows(K, R, rows, sets):
     M = N * hw * hw
     assert lib._ZN3ddg20conv_wide_takes_rowsEiiii(K, hw, R, rows) & 0xff == 1
     assert lib._ZN3ddg20conv_wide_takes_rowsEiiii(K, hw, R, 32768 // K + 1) & 0xff == 0
+    assert lib._ZN3ddg20conv_wide_takes_rowsEiiii(512, hw, 3, 1) & 0xff == 0          # (keeps its finalise launch)
     gen = torch.Generator(device="cuda"); gen.manual_seed(K + rows)
     f = dict(device="cuda", generator=gen)
     w = (torch.randn(R * R * K * OC, **f) * (R * R * K) ** -0.5).bfloat16()     # (some order of some weights)
