@@ -40,10 +40,12 @@ template <int NT> struct WideRows {
   unsigned at, step;
   __device__ __forceinline__ void request(const BnRows& r, int C) {
     const int cols4 = C >> 1;
-    res = wide_rsrc(r.partial, (size_t)r.rows * C * 8);     // (rows past the last: zeros)
+    // rows past the last: zeros. Their distance is in the lane's offset, which is checked against the resource's size; what the check does with the
+    // uniform offset is not documented, and with few rows that alone passed the end.
+    res = wide_rsrc(r.partial, (size_t)r.rows * C * 8);
     at = threadIdx.x * 16; step = NT / cols4 * cols4 * 16;
 #pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = __builtin_bit_cast(float4, wide_load(res, at, u * step));
+    for (int u = 0; u < U; ++u) v[u] = __builtin_bit_cast(float4, wide_load(res, at + u * step, 0));
   }
   // part: NT * 32 bytes of LDS. Ends with a barrier.
   __device__ __forceinline__ void finish(const BnRows& r, int C, float* tab, double* part, bool write) {
@@ -55,7 +57,7 @@ template <int NT> struct WideRows {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           t[0] += (double)v[u].x; t[1] += (double)v[u].y; t[2] += (double)v[u].z; t[3] += (double)v[u].w;
-          v[u] = __builtin_bit_cast(float4, wide_load(res, at, u * step));
+          v[u] = __builtin_bit_cast(float4, wide_load(res, at + u * step, 0));
         }
       } else {
 #pragma unroll

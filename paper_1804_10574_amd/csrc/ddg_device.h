@@ -114,7 +114,8 @@ __device__ __forceinline__ float row_sum16(float v) {
 // 16-byte loads with a uniform base, a 32-bit lane offset and a uniform offset (bytes): one address
 // register whatever is loaded, and none of them conditional: a lane that has nothing to load gives an offset past the end (NOWHERE) and gets
 // zeros, a store there is dropped. (A conditional load is a branch, and where branches meet the compiler waits for all loads in
-// flight.) Tensors, or what a resource covers of one, stay below 4 GiB.
+// flight.) Only the lane's offset is sure to be checked: what may lie past the end goes there, the uniform offset stays inside.
+// Tensors, or what a resource covers of one, stay below 4 GiB.
 typedef __amdgpu_buffer_rsrc_t wide_rsrc_t;
 __device__ __forceinline__ wide_rsrc_t wide_rsrc(const void* p, size_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)(unsigned)bytes, 0x00027000);
