@@ -107,12 +107,8 @@ int wgrad_tiled_rows(int N, int H, int W, int Cin, int Cout, int R, int stride, 
     const int v = atoi(e);
     if (v >= 8 && v <= 256) want = v;
   }
-  // As many tiles each (a workgroup less would lengthen the longest one's walk), and two at least, of 64 channels three: every
-  // partial tile is written here and read again by the reduction, whose share grows as the minibatch shrinks.
-  // ResNet-56, 16 iterations of batch 16 / 24 / 50: 6.07 / 6.29 / 6.96 -> 5.92 / 6.11 / 6.80 ms; four tiles of 64 channels and three of 32 are
-  // better still there, and 1-4 % worse where a chain of launches has the chip nearly to itself (ResNet-20, two modules).
-  const int least = Cin == 64 ? 3 : 2, even = (tiles + want - 1) / want, each = even > least ? even : least;
-  return (tiles + each - 1) / each;
+  if (want > tiles) want = tiles;
+  return want;
 }
 
 hipError_t wgrad_tiled_launch(const void* x, const float* scale, const float* shift, const void* dz,
