@@ -35,7 +35,7 @@ struct ConvPair { ConvArgs c[2]; };
 
 // k-steps whose loads are requested together. The small tiles are those of launches with few waves (conv_plan): such a wave has its SIMD
 // nearly to itself and waited for every k-step's loads. 16 -> 16 channels, fp32, 2 x 256 pixels: 6.3 -> 4.3 us; ResNet-20 on 24x24 images, fp32, batch
-// 64, 16 iterations 10.9 -> 9.5 ms, on 28x28, bf16, batch 8 / 64 8.5 / 9.8 -> 7.1 / 8.6. Launches with other waves to run would lose their places.
+// 64, 16 iterations 10.9 -> 9.5 ms; bf16: conv_plan. Launches with other waves to run would lose their places.
 template <typename T, int MB, int NB, bool VEC>
 constexpr int conv_batch() { return !VEC ? 1 : Mma<T>::KV == 8 ? (MB * NB <= 2 ? 5 : 1) : (MB * NB == 1 ? 9 : 1); }
 
@@ -442,9 +442,13 @@ void conv_plan(ConvArgs& a) {
   else { a.nb = 1; a.mb = 4; }
   auto waves = [&](int mb, int nb) { return (long)((a.M + 16 * mb - 1) / (16 * mb)) * (ocb / nb); };
   if (a.dtype == BF16) {
-    // a launch of few waves is over when its longest one is: smaller tiles (32 -> 64 channels, 2368 pixels: 74 waves of 32 pixels x 64 channels
-    // and its projection took 9.0 us, 592 of 16 x 16 6.1)
-    if (waves(a.mb, a.nb) < 512) { a.nb = 1; a.mb = waves(2, 1) < 512 ? 1 : 2; }
+    // a launch of few waves is over when its longest one is: smaller tiles. Forward, fewer channels only: a tile's pixels are those whose statistics a
+    // thread adds in fp32, and fewer of them would be another order of sums. ResNet-20, bf16, 16 iterations with wide tiles everywhere, so, and with
+    // fewer pixels forward as well: 28x28 images, batch 8 8.84 / 7.50 / 7.22 ms, batch 64 9.77 / 8.79 / 8.64; 32x32, batch 37 4.21 / 4.16 / 4.12.
+    if (waves(a.mb, a.nb) < 512) {
+      a.nb = 1;
+      if (a.dgrad) a.mb = waves(2, 1) < 512 ? 1 : 2;
+    }
   } else {
     // fp32 matrix instructions are 16 times slower per flop than bf16 ones: a wave's tile is
     // what bounds the launch, so tiles shrink until there are about two per SIMD
