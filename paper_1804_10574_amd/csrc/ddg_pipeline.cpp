@@ -29,12 +29,10 @@ struct OrderModel {
   std::map<int, std::vector<long>> ev;          // event id -> clock at its last record
   std::map<std::string, Buf> bufs;
   std::string msg;                              // first hazard found
-  long waits = 0, drop = -1;                    // test hook: the wait with this running number is ignored
   void init(int nstreams) { clk.assign(nstreams, std::vector<long>(nstreams, 0)); }
   bool before(const Acc& a, int s) const { return a.s < 0 || clk[s][a.s] >= a.v; }
   void record(int eid, int s) { ev[eid] = clk[s]; }
   void wait(int s, int eid) {
-    if (waits++ == drop) return;
     auto it = ev.find(eid);
     if (it == ev.end()) return;                 // never recorded: the wait returns at once
     for (size_t i = 0; i < clk[s].size(); ++i) if (it->second[i] > clk[s][i]) clk[s][i] = it->second[i];
@@ -68,19 +66,19 @@ struct OrderModel {
 
 // Which waits of a real run are implied by earlier ones. A wait for another stream's event costs the host 8-15 us (and the stream about
 // as much) whether or not there is anything left to wait for, and about half of those that a step asks for are: a stream that waited for an
-// event comes after all that the recording stream had done or waited for by then. Same vector clocks as in the model above, which sees every
-// wait that is asked for (or, for a test, only the others: no hazard either). ResNet-20, two modules, batch 37, 16 iterations: 4.40 -> 4.23 ms, ResNet-8, five modules, fp32: 5.83 -> 5.58, ResNet-56, three modules, batch 50: 6.80 -> 6.71.
+// event comes after all that the recording stream had done or waited for by then. Same vector clocks as in the model above, which checks the
+// outcome: it sees only the waits that are issued, for the events that are recorded. ResNet-20, two modules, batch 37, 16 iterations: 4.40 -> 4.23 ms, ResNet-8, five modules, fp32: 5.83 -> 5.58, ResNet-56, three modules, batch 50: 6.80 -> 6.71.
 struct StreamClocks {
   std::vector<std::vector<long>> clk;           // [stream][stream]
   std::vector<std::vector<long>> ev;            // [event]: clock at its last record (empty: never recorded)
   void init(int nstreams, int nevents) { clk.assign(nstreams, std::vector<long>(nstreams, 0)); ev.assign(nevents, {}); }
   void ran(int s) { ++clk[s][s]; }              // something was enqueued
   void record(int e, int s) { ev[e] = clk[s]; }
-  bool waits(int s, int e) {                    // must stream s wait for e? (it then has)
-    bool behind = false;
-    for (size_t i = 0; i < ev[e].size(); ++i) if (ev[e][i] > clk[s][i]) { clk[s][i] = ev[e][i]; behind = true; }
-    return behind;
+  bool behind(int s, int e) const {             // must stream s wait for e?
+    for (size_t i = 0; i < ev[e].size(); ++i) if (ev[e][i] > clk[s][i]) return true;
+    return false;
   }
+  void waited(int s, int e) { for (size_t i = 0; i < ev[e].size(); ++i) if (ev[e][i] > clk[s][i]) clk[s][i] = ev[e][i]; }
 };
 
 struct ddg_pipeline {
@@ -88,7 +86,8 @@ struct ddg_pipeline {
   OrderModel order;
   StreamClocks clocks;
   bool whole_at[2] = {false, false};    // the last module's iteration of that parity was one graph: fwd_done stands for bwd_done too
-  bool check_order = false, model_issued = false;   // model_issued (test hook): the model sees only the waits that are issued
+  bool check_order = false;
+  long asked = 0, issued = 0, drop = -1;   // waits so far; drop (test hook of dry runs): the issued wait with this running number is left out all the same
   std::vector<int> sid_f, sid_b;        // logical stream numbers of module k's forward / backward stream
   bool stale = false;
   std::vector<ddg_module*> mods;
@@ -347,19 +346,35 @@ ddg_status ddg_pipeline_step(ddg_pipeline* p, const void* x, const int32_t* labe
   if (use_graph) for (int k = 1; k <= K; ++k) if (ddg_internal_profiling(p->mods[k])) use_graph = false;
   const bool steady = use_graph || (p->dry && p->graphs && t >= K);   // (a dry run models the order of the graphs)
 #define DDG_P(expr) do { if ((expr) != hipSuccess) return DDG_ERR_DEVICE; } while (0)
-  // Every wait and record goes through these two, so that the ordering model sees exactly the
-  // dependencies the streams get. Event numbers: fwd_done[sl][k] = sl*(K+1)+k, bwd_done after them.
+  // Every wait and record goes through these, so that the ordering model sees exactly the dependencies the streams
+  // get (a call that failed gave none). Event numbers: fwd_done[sl][k] = sl*(K+1)+k, bwd_done after them.
   OrderModel& om = p->order;
   const bool model = p->check_order;
   auto ev_f = [&](int sl, int k) { return sl * (K + 1) + k; };
   auto ev_b = [&](int sl, int k) { return 2 * (K + 1) + sl * (K + 1) + k; };
-  auto wait = [&](int sid, hipStream_t s, int sl, int k, bool f, int asked) -> hipError_t {
+  auto wait = [&](int sid, hipStream_t s, int sl, int k, bool f) -> hipError_t {
     const int e = f ? ev_f(sl, k) : ev_b(sl, k);
-    const bool issued = p->clocks.waits(sid, e);
-    if (model && (issued || !p->model_issued)) om.wait(sid, p->model_issued ? e : asked);
-    return p->dry || !issued ? hipSuccess : hipStreamWaitEvent(s, f ? p->fwd_done[sl][k] : p->bwd_done[sl][k], 0); };
-  auto wait_f = [&](int sid, hipStream_t s, int sl, int k) { return wait(sid, s, sl, k, true, ev_f(sl, k)); };
-  auto wait_b = [&](int sid, hipStream_t s, int sl, int k) { return wait(sid, s, sl, k, k == K && p->whole_at[sl], ev_b(sl, k)); };
+    ++p->asked;
+    if (!p->clocks.behind(sid, e)) return hipSuccess;
+    const bool left_out = p->dry && p->issued == p->drop;
+    if (!p->dry) {
+      const hipError_t r = hipStreamWaitEvent(s, f ? p->fwd_done[sl][k] : p->bwd_done[sl][k], 0);
+      if (r != hipSuccess) return r;
+    }
+    ++p->issued;
+    p->clocks.waited(sid, e);
+    if (model && !left_out) om.wait(sid, e);
+    return hipSuccess; };
+  auto wait_f = [&](int sid, hipStream_t s, int sl, int k) { return wait(sid, s, sl, k, true); };
+  auto wait_b = [&](int sid, hipStream_t s, int sl, int k) { return wait(sid, s, sl, k, k == K && p->whole_at[sl]); };
+  auto record = [&](int sid, hipStream_t s, int e, std::vector<hipEvent_t>& evs, int k) -> hipError_t {
+    if (!p->dry) {
+      const hipError_t r = hipEventRecord(evs[k], s);
+      if (r != hipSuccess) return r;
+    }
+    p->clocks.record(e, sid);
+    if (model) om.record(e, sid);
+    return hipSuccess; };
   auto nm = [](const char* base, int a, long b = -1) {
     std::string r = std::string(base) + std::to_string(a);
     if (b >= 0) r += "/" + std::to_string(b);
@@ -477,9 +492,8 @@ ddg_status ddg_pipeline_step(ddg_pipeline* p, const void* x, const int32_t* labe
       if (r == DDG_OK && whole) r = call_backward_update(k);
       return r; });
     if (st != DDG_OK) return st;
-    if (model) om.record(ev_f(cur, k), sf);
-    p->clocks.ran(sf); p->clocks.record(ev_f(cur, k), sf);
-    if (!p->dry) DDG_P(hipEventRecord(p->fwd_done[cur][k], fs));
+    p->clocks.ran(sf);
+    DDG_P(record(sf, fs, ev_f(cur, k), p->fwd_done[cur], k));
   }
   // backward + update: the K modules are independent within one iteration
   for (int k = 1; k <= K; ++k) {
@@ -513,12 +527,8 @@ ddg_status ddg_pipeline_step(ddg_pipeline* p, const void* x, const int32_t* labe
     if (!p->dry) {
       if (k == K && loss_out && s >= 0) DDG_P(ddg::copy_launch(p->loss_dev, loss_out, sizeof(float), bs));
     }
-    if (model) om.record(ev_b(cur, k), sb);
     p->clocks.ran(sb);
-    if (!whole) {
-      p->clocks.record(ev_b(cur, k), sb);
-      if (!p->dry) DDG_P(hipEventRecord(p->bwd_done[cur][k], bs));
-    }
+    if (!whole) DDG_P(record(sb, bs, ev_b(cur, k), p->bwd_done[cur], k));   // (whole: fwd_done stands for it)
   }
 #undef DDG_P
   p->t = t + 1;
@@ -529,11 +539,11 @@ ddg_status ddg_pipeline_step(ddg_pipeline* p, const void* x, const int32_t* labe
   return DDG_OK;
 }
 
-// Test hooks of the ordering model (not part of the C boundary): the number of waits the model
-// has seen; from now on only those that are not implied by earlier ones; and the running number of a wait it is to ignore.
-long ddg_internal_pipeline_waits(const ddg_pipeline* p) { return p ? p->order.waits : -1; }
-void ddg_internal_pipeline_model_issued(ddg_pipeline* p) { if (p) p->model_issued = true; }
-void ddg_internal_pipeline_drop_wait(ddg_pipeline* p, long n) { if (p) p->order.drop = n; }
+// Test hooks of the ordering model (not part of the C boundary): the number of waits that were issued, and of those that were
+// asked for; and the running number of an issued wait that a dry run is to leave out as if an earlier one implied it.
+long ddg_internal_pipeline_waits(const ddg_pipeline* p) { return p ? p->issued : -1; }
+long ddg_internal_pipeline_waits_asked(const ddg_pipeline* p) { return p ? p->asked : -1; }
+void ddg_internal_pipeline_drop_wait(ddg_pipeline* p, long n) { if (p) p->drop = n; }
 // Calls of module j's backward stream that a stream has not waited for, directly or not, which waits for
 // module k's forward pass of the last step (its `fwd_done` event).
 long ddg_internal_pipeline_behind(const ddg_pipeline* p, int k, int j) {

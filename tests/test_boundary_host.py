@@ -295,6 +295,8 @@ def _order_hooks():
     lib = ddg.load_library()
     lib.ddg_internal_pipeline_waits.restype = C.c_long
     lib.ddg_internal_pipeline_waits.argtypes = [C.c_void_p]
+    lib.ddg_internal_pipeline_waits_asked.restype = C.c_long
+    lib.ddg_internal_pipeline_waits_asked.argtypes = [C.c_void_p]
     lib.ddg_internal_pipeline_drop_wait.restype = None
     lib.ddg_internal_pipeline_drop_wait.argtypes = [C.c_void_p, C.c_long]
     lib.ddg_internal_pipeline_behind.restype = C.c_long
@@ -331,44 +333,48 @@ def test_events_order_every_tensor_the_streams_share(K, mode):
 @pytest.mark.parametrize("mode", ["streams", "forward_streams", "stale_jacobian"])
 @pytest.mark.parametrize("toggle", [0, 5])
 def test_waits_that_are_left_out_order_nothing(K, mode, toggle):
-    """A wait that earlier ones imply is not issued. The model, shown only those that are issued, finds no hazard, also where
-    graphs (the last module's whole iteration in one) come and go; and fewer are issued than asked for."""
+    """A wait that earlier ones imply is not issued. The model, which sees only those that are issued, finds no hazard, also where graphs (the
+    last module's whole iteration in one) come and go and where the streams are waited for, an evaluation runs or the
+    iteration number is set between two steps; and fewer are issued than asked for."""
     lib = _order_hooks()
-    lib.ddg_internal_pipeline_model_issued.restype = None
-    lib.ddg_internal_pipeline_model_issued.argtypes = [__import__("ctypes").c_void_p]
-    fake, waits = 4096, {}
-    for issued in (False, True):
-        p = _dry_pipeline(K, mode == "forward_streams", stale=(mode == "stale_jacobian"))
-        if issued:
-            lib.ddg_internal_pipeline_model_issued(p._h)
-        for t in range(6 * K + 12):
-            if toggle and t % toggle == 0:
-                p.set_graphs(t // toggle % 2 == 0)
-            p.step(fake, fake, 0.01)
-        waits[issued] = lib.ddg_internal_pipeline_waits(p._h)
-        p.close()
-    assert waits[True] < waits[False] or K == 1
+    fake = 4096
+    p = _dry_pipeline(K, mode == "forward_streams", stale=(mode == "stale_jacobian"))
+    for i in range(6 * K + 12):
+        if toggle and i % toggle == 0:
+            p.set_graphs(i // toggle % 2 == 0)
+        if toggle and i % 7 == 3:
+            p.sync()
+        if toggle and i % 11 == 6 and mode != "stale_jacobian":      # (neither is there in that mode)
+            p.forward_eval(fake, fake)
+        if toggle and i == 4 * K + 3 and mode != "stale_jacobian":
+            p.set_time(p.time() + 1)              # the other parity of all buffers and events
+        p.step(fake, fake, 0.01)
+    issued, asked = lib.ddg_internal_pipeline_waits(p._h), lib.ddg_internal_pipeline_waits_asked(p._h)
+    p.close()
+    assert 0 < issued < asked or K == 1, (issued, asked)
 
 
-@pytest.mark.parametrize("own_forward_streams", [False, True])
-def test_a_missing_wait_is_found(own_forward_streams):
-    """Leaving out any single wait of a K = 3 schedule, in the model only: the model must report
-    a hazard for the waits that order two streams' accesses to a shared tensor, and name it."""
+@pytest.mark.parametrize("mode", ["streams", "forward_streams", "stale_jacobian"])
+def test_a_missing_wait_is_found(mode):
+    """Leaving out any single wait that a K = 3 schedule issues, as a mistake in what counts as implied would (later waits are left out or issued as
+    if the stream had waited): the model must report a hazard and name the tensor. With a forward stream per module a
+    quarter of them leave no access to a shared tensor unordered when they go."""
     lib = _order_hooks()
+    own_forward_streams, stale = mode == "forward_streams", mode == "stale_jacobian"
     K, steps = 3, 12
     fake = 4096
-    p = _dry_pipeline(K, own_forward_streams)
+    p = _dry_pipeline(K, own_forward_streams, stale)
     for t in range(steps):
         p.step(fake, fake, 0.01)
     total = lib.ddg_internal_pipeline_waits(p._h)
     p.close()
-    assert total > 4 * steps
+    assert total > 3 * steps
     found, kinds = 0, set()
     for n in range(total):
-        p = _dry_pipeline(K, own_forward_streams)
+        p = _dry_pipeline(K, own_forward_streams, stale)
         lib.ddg_internal_pipeline_drop_wait(p._h, n)
         try:
-            for t in range(steps):
+            for t in range(steps + 3):
                 p.step(fake, fake, 0.01)
         except ddg.DDGError as e:
             assert e.status == 3 and "hazard" in str(e), str(e)
@@ -377,8 +383,7 @@ def test_a_missing_wait_is_found(own_forward_streams):
             kinds.add(str(e).split(" hazard")[0].split(": ")[-1] + " " + tensor)
         p.close()
     print(found, "of", total, sorted(kinds))
-    # most waits are the only thing that orders their pair of accesses
-    assert found >= total // 2, (found, total)
+    assert found == total or own_forward_streams and found >= total * 3 // 4, (found, total)
     want = {"read-after-write h", "read-after-write mail", "write-after-read h"}
     if own_forward_streams:
         want |= {"read-after-write w", "write-after-read w", "write-after-read mail"}
