@@ -47,5 +47,29 @@ def pack(w, a, n):
     return out
 
 
-def conv(a):
-    assert lib()._ZN3ddg11conv_launchERKNS_8ConvArgsEP12ihipStream_tPS1_(C.byref(a), P(None), None) == 0
+def conv(a, other=None):
+    assert lib()._ZN3ddg11conv_launchERKNS_8ConvArgsEP12ihipStream_tPS1_(C.byref(a), P(None), C.byref(other) if other else None) == 0
+
+
+def wgrad_args(N, H, W, cin, cout, dtype):
+    """A planned weight gradient of a 3x3 convolution of stride 1."""
+    a = WgradArgs()
+    a.N, a.H, a.W, a.Cin, a.P, a.Q, a.Cout, a.R, a.stride, a.pad, a.M, a.dtype = N, H, W, cin, H, W, cout, 3, 1, 1, N * H * W, dtype
+    lib()._ZN3ddg10wgrad_planERNS_9WgradArgsE(C.byref(a))
+    return a
+
+
+def wgrad(a):
+    assert lib()._ZN3ddg12wgrad_launchERKNS_9WgradArgsEP12ihipStream_t(C.byref(a), P(None)) == 0
+
+
+class Dim3(C.Structure):
+    _fields_ = [(n, C.c_uint) for n in "xyz"]
+
+
+def launch(kernel, grid, threads, *args):
+    """One of the library's kernels, by its handle's name, on the default stream."""
+    run = lib().hipLaunchKernel
+    run.argtypes = [P, Dim3, Dim3, C.POINTER(P), C.c_size_t, P]
+    ptrs = (P * len(args))(*[C.cast(C.pointer(a), P) for a in args])
+    assert run(C.addressof(C.c_char.in_dll(lib(), kernel)), Dim3(*grid), Dim3(threads, 1, 1), ptrs, 0, None) == 0
