@@ -1,4 +1,6 @@
-// First layer of a network: 3x3, stride 1, at most 4 (weight gradient: 3 or 4) input channels.
+// First layer of a network: 3x3, stride 1, 1 to 4 input channels in bf16 and 1 to 3 in fp32 (four are a whole fragment of the generic kernel
+// there), rows up to 223 or 127 wide by the tile (stem_conv_ok); weight gradient: 3 channels (four have the kernel with vector gathers, fewer other columns), and as many
+// pixels a workgroup as 48 KB of LDS hold: 1.5 M in all at 16 output channels, 0.38 M at 64 (32 wide). Others run in the generic kernels.
 //
 // With so few channels a fragment of the implicit GEMM is one tap of one pixel, 6 or 12 bytes at an address of its own, and the generic kernels
 // spent their time on vector instructions: pixel indexes, bounds and element gathers for every tap of every pixel (61 and 111 a matrix
@@ -167,7 +169,7 @@ hipError_t stem_conv_launch(const ConvArgs& a, hipStream_t s) {
     return hipGetLastError();                                                     \
   }
   if (a.dtype == BF16) {
-    DDG_STEM_CASE(bf16_t, 4, 1) DDG_STEM_CASE(bf16_t, 2, 1) DDG_STEM_CASE(bf16_t, 1, 1) DDG_STEM_CASE(bf16_t, 2, 2) DDG_STEM_CASE(bf16_t, 2, 4)
+    DDG_STEM_CASE(bf16_t, 4, 1) DDG_STEM_CASE(bf16_t, 2, 1) DDG_STEM_CASE(bf16_t, 2, 2) DDG_STEM_CASE(bf16_t, 2, 4)
   } else {
     DDG_STEM_CASE(float, 4, 1) DDG_STEM_CASE(float, 2, 1) DDG_STEM_CASE(float, 1, 1)
   }

@@ -20,8 +20,8 @@ constexpr int WG_NJ = 9;  // column blocks (16 wide) per wave at most
 // NJ: column blocks per wave, 3 for the stem (3 channels padded to 4, 36 columns; with 9 two thirds of the
 // gathers and matrix instructions were padding). As in the kernel below nothing in the loop is conditional and
 // the loads of step st+3 are requested before step st is multiplied. Stem, 3 -> 16 channels, in a running
-// pipeline: bf16 batch 256 60 -> 25 us, fp32 batch 128 24 -> 13 us. (Stems whose pixels fit LDS run in
-// stem_wgrad_kernel since; rows too wide for it come here.)
+// pipeline: bf16 batch 256 60 -> 25 us, fp32 batch 128 24 -> 13 us. (Stems of 3 channels run in stem_wgrad_kernel since, where a
+// workgroup's pixels fit LDS; wide rows and more than 0.4 to 1.5 M pixels come here.)
 template <typename T, int NJ>
 __global__ __launch_bounds__(256) void wgrad_mfma_kernel(WgradArgs a) {
   using S_ = Store<T>;
