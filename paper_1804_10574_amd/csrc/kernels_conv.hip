@@ -35,7 +35,8 @@ struct ConvPair { ConvArgs c[2]; };
 
 // k-steps whose loads are requested together. The small tiles are those of launches with few waves (conv_plan): such a wave has its SIMD
 // nearly to itself and waited for every k-step's loads. 16 -> 16 channels, fp32, 2 x 256 pixels: 6.3 -> 4.3 us; ResNet-20 on 24x24 images, fp32, batch
-// 64, 16 iterations 10.9 -> 9.5 ms; bf16: conv_plan. Launches with other waves to run would lose their places.
+// 64, 16 iterations 10.9 -> 9.5 ms, 87 fp32 pipelines of two to five modules (20 to 32 wide, batch 16 to 256) 0.938 of the time with a step at a time; bf16:
+// conv_plan. Launches with other waves to run would lose their places.
 template <typename T, int MB, int NB, bool VEC>
 constexpr int conv_batch() { return !VEC ? 1 : Mma<T>::KV == 8 ? (MB * NB <= 2 ? 5 : 1) : (MB * NB == 1 ? 9 : 1); }
 
@@ -471,8 +472,11 @@ static hipError_t conv_dispatch(const ConvArgs& a, const ConvArgs* other, hipStr
   const ConvPair ab{{a, other ? *other : a}};
   const bool vec = a.IC % Mma<T>::KV == 0;
   if constexpr (Mma<T>::KV == 4) {
-    // a stage's first convolutions beside other modules: their waves hold four times the registers for what they gain (ResNet-20, two modules, batch 128:
-    // 4096 waves, 12.40 ms per 16 iterations instead of 12.31; ResNet-8, five modules, 8192, 5.63 instead of 5.56)
+    // A stage's first convolutions of many waves, a k-step at a time: with nine their waves hold 108 registers instead of 40 and what other modules run
+    // beside them waits. Networks of ResNet's kind at 32x32, 8 to 32 layers, two or three modules, batch 104 to 136, 77 pipelines: nine everywhere
+    // is 1 to 2 % slower than one everywhere in 15 of them, at batch 116 to 128 above all; with this line none is (the worst 0.8 %), and the means are equal. 372 pipelines
+    // in all, of one to five modules: 0.06 % shorter with the line, the 88 of one module 0.1 % longer. Stride 1 has no line: it would cost networks at 24x24 and 28x28 1 %
+    // in the mean and up to 5 (ResNet-56, batch 64).
     const long waves = (long)a.grid_x * 4 * grid.y * grid.z;
     if (a.mb == 1 && vec && !a.dgrad && a.stride == 2 && waves > 2048) {
       DDG_LAUNCH((conv_mfma_kernel<T, 1, 1, false, true, 1>), grid, block, 0, s, ab, sets);
