@@ -8,7 +8,7 @@
 // LDS time in bf16, against 10-13 us for the per-layer launch of a whole minibatch of 256 and 6-7
 // us for the smallest one (the launch, its weights and its halo loads are then all there is).
 // Measured, whole call: ResNet-110, batch 256, bf16 1394 -> 214 us (1.4-1.7 us per layer); the 32-channel group of
-// ResNet-56, batch 100, bf16 134 -> 29 us; ResNet-20, one image, fp32 227 -> 103 us.
+// ResNet-56, batch 100, bf16 134 -> 29 us; ResNet-20, one image, fp32 227 -> 100 us.
 //
 // Two ways of cutting the work, chosen by eval_plan() below:
 //   whole images: all blocks of a module in one launch, one image per workgroup (bf16);
@@ -17,8 +17,8 @@
 //           that one image has to be spread over several; bf16 modules whose buffers, each at its largest over the blocks,
 //           exceed LDS: large images, and deep networks in one module from 32x32 on (ResNet-110: its table of scales and shifts
 //           alone is 32 KB); and bf16 where a few large images would leave most compute units idle). Strips are no slower than
-//           the per-layer kernels either: ResNet-110 in one module, batch 37, 1.29x, batch 1 1.41x. As whole images
-//           ResNet-20 in one module takes 57 us at batch 256 and 54 at batch 1, 130 and 85 in strips.
+//           the per-layer kernels either: the blocks of ResNet-110 in one module, batch 37, 501 -> 339 us, batch 1 459 -> 323. As whole images
+//           those of ResNet-20 take 42 us at batch 256 and 38 at batch 1, 95 and 55 in strips (calls one after the other).
 //
 // Buffers: three LDS regions of NHWC pixels with a zero border (row and column -1 and H / W). An identity block reads x, writes
 // o = relu(bn1(conv1 x)), then adds relu(bn2(conv2 o) + x)
@@ -862,7 +862,8 @@ __global__ __launch_bounds__(NT) void eval_strip_kernel(StripArgs a) {
 
 }  // namespace ev
 
-// LDS of a launch over `kinds`/`chans` (nb blocks) on H x W images with TH output rows per workgroup.
+// LDS of a launch over `kinds`/`chans` (nb blocks) on H x W images with TH output rows per workgroup. (Strips store from the accumulators, so a
+// strip of a stem or of a block between stages does not use the region that is counted for its output.)
 static void eval_lds(const EvalBlockShape* b, int nb, int H, int W, int TH, int strips, int dtype, int gap, EvalLaunch* l) {
   const size_t esz = dtype_size(dtype);
   auto row = [&](int w, int c) -> size_t { return ev::row_bytes(w, ev::pix_bytes_of(c, (int)esz, gap)); };   // bytes of a row of w pixels
@@ -912,7 +913,10 @@ bool eval_block_ok(int kind, int c) {
 // Estimated time of a bf16 launch of N images, us: 2 for the launch, 0.15 per MB in and out, and per round over 256 compute units
 // (registers: one workgroup per unit) 2, 1 per layer, 0.04 per KB of a workgroup's rows in and out, and for every 16 pixels of a
 // layer what `per` says, in whole groups of a workgroup's waves. Fitted to 1752 measured evaluations (maps 8 to 64 wide, 1 to 256 images,
-// one to three blocks, both pitches, whole images and strips), which it meets within 9 % rms.
+// one to three blocks, both pitches, whole images and strips), when a strip's workgroup still fetched what it reads piece by piece. Whole images it meets within 10 % rms;
+// strips now take 21 % less than it says in the mean. Over 711 evaluations (the same range, stems, blocks between stages and ResNet-20 too) the cut that
+// it chooses takes 1.7 % longer than the best of the four in the mean, more than 10 % longer in 47: whole images in place of strips, the worst 3 blocks
+// of 16 channels, 40x40, 64 images, 29 us instead of 20.
 static double eval_cost(const EvalBlockShape* b, const EvalLaunch& l, int N) {
   const bool wide = l.gap == 32;
   double layers = 0.0, matrix = 0.0;
@@ -939,11 +943,12 @@ static double eval_cost(const EvalBlockShape* b, const EvalLaunch& l, int N) {
 // How a module's blocks are cut into launches: all blocks at once, whole images (bf16, if the buffers fit LDS), or one
 // block per launch in strips of the height that minimises
 //   rounds over 256 compute units x (2 us + the strip's matrix time, halo rows included)
-// (2 us: loads, barriers and epilogues of a block, measured on one image). bf16: in either of two pitches, whichever of the four
+// (2 us: loads, barriers and epilogues of a block; of 84 fp32 evaluations of one block, 7 to 48 wide, 1 to 256 images, two take more than 5 % longer than
+// the best height, of 84 in bf16 22, 3.4 % in the mean). bf16: in either of two pitches, whichever of the four
 // eval_cost() finds shortest. us a call, strips of 32 / 16 bytes between pixels, whole images of 32 / 16 (-: does not fit):
-//   3 blocks of 32 channels, 28x28, 256 images  82 / 61 / - / 39       3 blocks, 24x24, 256 images  54 / 49 / 36 / 31
-//   3 blocks of 64 channels, 14x14, 256 images  65 / 73 / 51 / 59      3 blocks, 14x14, 37 images  34 / 35 / 44 / 53
-//   1 block of 16 channels, 48x48: 8 images 7 in strips, 18 whole; 256 images 24, 24      3 blocks, 256 images 72, 46
+//   3 blocks of 32 channels, 28x28, 256 images  59 / 58 / - / 37       3 blocks, 24x24, 256 images  52 / 48 / 34 / 30
+//   3 blocks of 64 channels, 14x14, 256 images  59 / 70 / 45 / 56      3 blocks, 14x14, 37 images  30 / 31 / 41 / 52
+//   1 block of 16 channels, 48x48: 8 images 6 in strips, 19 whole; 256 images 23, 23      3 blocks, 256 images 69, 44
 bool eval_plan(const EvalBlockShape* b, int nb, int N, int H, int W, int dtype, EvalPlan* out) {
   for (int i = 0; i < nb; ++i)
     if (!eval_block_ok(b[i].kind, b[i].c) || (i > 0 && b[i].kind == EVAL_STEM)) return false;
